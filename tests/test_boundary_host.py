@@ -404,3 +404,27 @@ def test_mixed_launch_covers_every_tile_exactly_once(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True, env=env)
     assert r.returncode == 0, r.stdout + r.stderr
     assert r.stdout.startswith("ok ") and "runtime error" not in r.stderr
+
+
+def test_packed_parameter_block_equals_the_structure():
+    """The binding hands fa_fwd_ex the structure as packed bytes: the same bytes as the structure filled field by field,
+    and values that do not fit a field take the field-by-field way (ctypes' conversions) instead of raising."""
+    some = dict(dtype=1, q=0x1000, k=0x2010, v=0x3020, o=0x7fffffff4040, lse=None, seq_lens=0x5050, batch=3, heads=12, max_len=777,
+                head_dim=64, scale=0.1, window_left=63, window_right=-1, q_strides=(1 << 40, 64, 2304), k_strides=None,
+                v_strides=[8, 16, 64], o_strides=(0, 0, 0), stream=0x99, tuning=0x3337, key_bias=0x6002, key_bias_stride=1 << 33,
+                rope_cos=0x7010, rope_sin=None, rope_stride=32, scratch=0x8000, scratch_bytes=(1 << 63) + 5)
+    none = {**some, "lse": 0x44, "seq_lens": None, "key_bias": None, "rope_cos": None, "rope_sin": 0x10, "scratch": None, "stream": 0,
+            "q_strides": None, "scale": -3, "scratch_bytes": 0}
+    for kw in (some, none):
+        packed, filled = fa._pack_params(*kw.values()), fa._fill_params(*kw.values())
+        # compared field by field: the padding bytes between fields are not part of the contract
+        got = fa.FaParams.from_buffer_copy(packed)
+        assert len(packed) == ctypes.sizeof(fa.FaParams)
+        for name, _ in fa.FaParams._fields_:
+            x, y = getattr(got, name), getattr(filled, name)
+            assert (list(x) == list(y)) if name.endswith("_strides") else x == y, name
+    good = dict(dtype=0, q=16, k=16, v=16, o=16, batch=1, heads=1, max_len=64, scale=0.125, stream=0, check=False)
+    assert fa.fa_fwd_ex(**{**good, "max_len": 1 << 31}) == -2          # wraps to a negative length
+    assert fa.fa_fwd_ex(**{**good, "scale": 1e300}) == -4              # infinite as a float
+    with pytest.raises(TypeError):
+        fa.fa_fwd_ex(**{**good, "batch": 1.0})
