@@ -162,7 +162,7 @@ typedef struct fa_params {
      in fp32 and rounded to the 16-bit storage type before the score product, exactly as if the
      caller had rotated the tensors itself; v is not rotated.  Tables are shared by all batch
      elements and heads.  16-byte alignment; rope_stride in floats, 0 = head_dim/2, else a
-     multiple of 4 and >= head_dim/2.  The 32-row key-split shape and the 384 / 512-row and mixed
+     multiple of 4 and >= head_dim/2.  The shapes that split the keys and the 384 / 512-row and mixed
      shapes are not used with a rotation. */
   const float* rope_cos;
   const float* rope_sin;
@@ -184,10 +184,10 @@ typedef struct fa_params {
 #define FA_TUNE_BM_128 0x1u  /* 4 wavefronts x 32 query rows  */
 #define FA_TUNE_BM_256 0x2u  /* head_dim 64 and 32: 4 wavefronts x 64 query rows; head_dim 128 global
                                 layers: 8 wavefronts x 32 rows on one pair of K/V stages */
-#define FA_TUNE_BM_32 0x3u   /* 32 query rows, the 4 wavefronts split the keys (global layers of
+#define FA_TUNE_BM_32 0x3u   /* 32 query rows, eight wavefronts split the keys (global layers of
                                 head_dim 64 without a key bias; ignored otherwise).  The library
-                                picks it by itself when the call has at most 256 blocks of 32 query
-                                rows (one per compute unit) and max_len > 128. */
+                                picks this or another shape that splits the keys by itself when
+                                the call's query tiles number at most one per compute unit. */
 #define FA_TUNE_BM_384 0x4u  /* 12 wavefronts x 32 query rows sharing one K/V stage (global layers of
                                 head_dim 64 without a key bias; ignored otherwise) */
 #define FA_TUNE_BM_512 0x5u  /* 8 wavefronts x 64 query rows sharing one K/V stage (same restriction) */

@@ -118,6 +118,42 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
   return c256 <= c128 ? 256 : 128;
 }
 
+// Shape of the split kernel for a global layer, 16 * NQ + NK (NQ blocks of 32 query rows per workgroup, each shared by
+// NK wavefronts that split the keys), or 0 where the other kernels are faster.  Its workgroups have a compute unit to
+// themselves (head_dim 32: half or a quarter of one), so a shape is taken only where the call fits the 256 units in one
+// round - a second, thin round costs as much as the first - and the fewest rows per workgroup that do fit are the
+// fastest.  Measured, fp16, 12 x 64 / 8 x 128 / 24 x 32, against the 128-row kernel (us per call):
+//   head_dim 64   32 rows: 512 tokens 7.6 -> 6.2;  64 rows: 1024 13.6 -> 11.1, 1280 17.2 -> 11.8, 5 x 256 7.3 -> 6.6;
+//                 96 rows: 1400 18.9 -> 15.7, 2000 24.9 -> 20.3, but 3 x 450 9.7 -> 10.0 (short sequences do not repay
+//                 the merge of a 12-wavefront workgroup);  128 rows: 1900 of 2048 22.5 -> 21.3, 2304 27.5 -> 25.3, but
+//                 2 x 1024 15.1 -> 15.2, 4 x 400 9.2 -> 10.5.  (A round too many: 2 x 700 in 64 rows 18.2 against 12.0.)
+//                 At 64 tokens there is nothing to split: 5.3 -> 5.7.
+//                 With a key bias, whose pipelined kernel is slower, the lines lie lower: 3 x 450 11.5 -> 10.4,
+//                 3 x 600 13.9 -> 13.0, 4 x 400 10.8 -> 11.4.
+//   head_dim 128  32 rows: 512 13.6 -> 8.4;  64 rows: 2048 37 -> 24;  128 rows: 4 x 640 16.8 -> 15.5, 4096 75 -> 65, but
+//                 8 x 512 15.6 -> 15.8.  With a bias 16 x 256 13.5 -> 12.3.
+//   head_dim 32   32 rows (two workgroups per unit): 512 8.0 -> 6.8, 2 x 300 6.9 -> 6.3, 4 x 160 5.5 -> 5.8;  64 rows where
+//                 the 128-row kernel has its thin second round (257 - 384 tiles): 1400 21.3 -> 18.5, 2048 29.2 -> 25.5,
+//                 2 x 700 13.0 -> 12.9; beyond it 2400 33.0 -> 35.3.
+int choose_split(const fa_params& p) {
+  const int64_t bh = (int64_t)p.batch * p.heads;
+  auto tiles = [&](int rows) { return ((int64_t)p.max_len + rows - 1) / rows * bh; };
+  const bool bias = p.key_bias != nullptr;
+  if (p.max_len <= 64) return 0;
+  if (p.head_dim == 64) {
+    if (tiles(64) <= 256) return tiles(32) <= 256 && p.max_len > 128 ? 0x18 : 0x24;
+    if (tiles(96) <= 256 && p.max_len >= (bias ? 448 : 640)) return 0x34;
+    if (tiles(128) <= 256 && p.max_len >= (bias ? 512 : 1536)) return 0x42;
+  } else if (p.head_dim == 128) {
+    if (tiles(64) <= 256) return tiles(32) <= 256 ? 0x14 : 0x24;
+    if (tiles(128) <= 256 && p.max_len >= (bias ? 256 : 640)) return 0x42;
+  } else {
+    if (!bias && tiles(32) <= 512 && p.max_len >= 256) return 0x14;
+    if (tiles(64) <= 768 && (bias || (tiles(64) > 512 && p.max_len >= 640))) return 0x22;
+  }
+  return 0;
+}
+
 }  // namespace
 
 namespace {
@@ -247,19 +283,14 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
     if (t_bm == FA_TUNE_BM_128) bm = 128;
     if (t_bm == FA_TUNE_BM_256) bm = 256;
   }
-  // Key-split kernel (32 query rows per workgroup, the wavefronts split the keys): global
-  // layers of head_dim 64 without a bias whose 32-row blocks number at most one per compute
-  // unit (its workgroups use a whole unit's LDS, so a second round would cost more than the
-  // split gains).  Measured on MI355X against 128-row tiles: 1 x 12 heads x 512 and 1 x 4 x 512
-  // 7-15 % faster, 1 x 1 x 8192 38 % faster; 2 x 12 x 512 (two rounds) 32 % slower, 128 tokens
-  // no difference.  Its lanes address rows by 32-bit byte offsets from the (batch, head) slice.
-  {
-    const int64_t row_stride = a.ks[2] > a.vs[2] ? a.ks[2] : a.vs[2];
-    const bool eligible = p->head_dim == 64 && !windowed && !p->key_bias && !p->rope_cos && t_v != FA_TUNE_V_SCALAR &&
-                          (double)p->max_len * (double)row_stride * 2.0 < 4.0e9;
-    const int64_t blocks32 = (((int64_t)p->max_len + 31) / 32) * p->batch * p->heads;
-    if (eligible && (t_bm == FA_TUNE_BM_32 || (t_bm == FA_TUNE_BM_AUTO && blocks32 <= 256 && p->max_len > 128)))
-      bm = 32;
+  // Split kernel (a workgroup's wavefronts split the keys as well as the rows): global layers too small for the shapes
+  // above to give every SIMD two wavefronts.  Its key bias sits in LDS.
+  int split = 0;
+  if (!windowed && !p->rope_cos && t_v != FA_TUNE_V_SCALAR && !bias_on_masked_kernel &&
+      (!p->key_bias || p->max_len <= kSplitBiasKeys)) {
+    if (t_bm == FA_TUNE_BM_AUTO) split = choose_split(*p);
+    if (t_bm == FA_TUNE_BM_32 && p->head_dim == 64 && !p->key_bias) split = 0x18;
+    if (split) bm = 32 * (split >> 4);
   }
   const int tile_rows = bm == 0 ? 128 : bm;   // (the mixed launch sizes its own grid)
   const int64_t n_qtiles = ((int64_t)p->max_len + tile_rows - 1) / tile_rows;
@@ -292,6 +323,9 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   const int64_t per = ((int64_t)p->heads * n_qtiles + 7) / 8;
   if (8 * per * p->batch > 0x7FFFFFF0LL) return FA_ERR_BAD_SHAPE;
   a.xcd_per = (int32_t)per;
+  a.split = split;
+  // (a launch of at most two workgroups per unit has nothing else to hide the read of the sequence length behind)
+  a.late_n = total <= 512;
   a.mix_ids_a = bm == 0 ? fa_mix_ids((int)n_qtiles, p->heads) : 0;
   const int v_path = t_v == FA_TUNE_V_SCALAR ? 1 : 0;
 

@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+constexpr int kSplitBiasKeys = 4096;   // longest tensor the split kernel takes with a key bias (which it keeps in LDS)
+
 struct FaKernelArgs {
   const void* q;
   const void* k;
@@ -27,6 +29,8 @@ struct FaKernelArgs {
   int32_t total_tiles;  // batch * heads * n_qtiles
   int32_t map_xcd;  // nonzero: each XCD owns a contiguous eighth of every batch element's tiles
   int32_t xcd_per;  // ceil(heads * n_qtiles / 8)
+  int32_t split;    // split kernel: 16 * NQ + NK (blocks of 32 query rows x key splits per workgroup), 0 = another kernel
+  int32_t late_n;   // split kernel: loads are issued before the sequence length is looked at
   int32_t mix_ids_a; // mixed-shape kernel: workgroup ids reserved for 256-row workgroups (fa_mix_map.h)
 };
 
@@ -49,7 +53,7 @@ int fa_launch_rope_rotate(const FaRopeArgs& r, int is_bf16, void* stream);
 int fa_static_scratch(void** ptr);
 
 // Host-side launchers implemented in fa_kernels.hip.  Return hipError_t as int.
-// bm: query rows per workgroup: 32 (key-split kernel), 128, 256, 384 (12 wavefronts), 512 (8
+// bm: query rows per workgroup: 32 NQ (split kernel, a.split set), 128, 256, 384 (12 wavefronts), 512 (8
 // wavefronts), or 0 = 256-row and 128-row workgroups mixed (one sequence, a.mix_ids_a set); v_path: 0 = LDS
 // transpose reads, 1 = 16-bit reads.
 // win_kernel: 0 = library's choice among the window kernels, 1 = never the two-phase kernel, 2 = the

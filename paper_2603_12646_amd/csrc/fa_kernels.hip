@@ -43,10 +43,10 @@
 //       LDS (the paper's 63/64 window): everything is requested at once, then each
 //       wavefront runs the same pipeline over the blocks its queries can see.
 //   fa_fwd_window_kernel  wider or one-sided windows: ring of 32-key stages.
-//   fa_fwd_keysplit_kernel  global layers of head_dim 64 with so few query tiles that the
-//       other kernels would leave most of the chip idle (one 512-token sequence): a
-//       workgroup owns 32 query rows, its four wavefronts split the KEYS, and the four
-//       partial results are merged through LDS.
+//   fa_fwd_split_kernel  global layers with so few query tiles that the kernels above would leave
+//       SIMDs with one wavefront or none (a single request, a few short sequences): NQ query
+//       blocks per workgroup, each shared by NK wavefronts that split the KEYS and merge their
+//       partial results through LDS.
 //   fa_fwd_masked_kernel  general path (register staging, padded tiles, optional 16-bit V
 //       reads) for head_dim 32, 64, 128: the production path of head_dim 32 and of the local
 //       layers of head_dim 128, and at head_dim 64 an independent implementation for the tests.
@@ -696,12 +696,7 @@ __device__ __forceinline__ void epilogue(const FaKernelArgs& a, RowState<NQB, D>
 // kb0: first key of the current block; interior: every valid query of the wavefront sees all
 // 32 keys, so no mask work; otherwise [jlo, jhi] is the lane's visible key range.
 // alive: the lane's query row exists.
-// EDGE = false is the straight-line form for the common unit - interior block, every existing
-// row already has a reference - whose only branch is the rare overflow redo at the end, so
-// that the compiler can interleave the vector work with the matrix products of the same
-// wavefront (with the mask and adoption branches in between it cannot); the caller checks
-// both conditions.  EDGE = true handles everything.
-template <class T, bool EDGE, class Init>
+template <class T, class Init>
 __device__ __forceinline__ void resident_unit(RowState<1>& st, const typename T::v8 (&qreg)[1][4], floatx16& s_cur,
                                               floatx16& s_nxt, typename T::v8 (&p_prev)[2],
                                               typename T::v8 (&p_cur)[2], const uint16_t* k_next,
@@ -722,11 +717,11 @@ __device__ __forceinline__ void resident_unit(RowState<1>& st, const typename T:
   uint32_t pk[8];
   float blk;
   uint32_t vis = 0xFFFFu;
-  if (EDGE && !interior) vis = visible_bits(kb0, hh, jlo, jhi);
+  if (!interior) vis = visible_bits(kb0, hh, jlo, jhi);
   // Rows that have not seen a key yet (the wavefront's first block, and the odd row whose
   // window starts a block later) adopt this block's maximum as their reference.  Nothing
   // has been accumulated for such a row, so there is nothing to rescale.
-  if (EDGE && __any(alive && st.m_ref[0] == -INFINITY)) {
+  if (__any(alive && st.m_ref[0] == -INFINITY)) {
     float t0 = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, keep_or_neg_inf(s_cur[r], vis, r));
@@ -736,7 +731,7 @@ __device__ __forceinline__ void resident_unit(RowState<1>& st, const typename T:
       st.mc[0] = tmax == -INFINITY ? 0.f : tmax * c;
     }
   }
-  if (!EDGE || interior) prob_block<T, false>(s_cur, c, st.mc[0], vis, pk, blk);
+  if (interior) prob_block<T, false>(s_cur, c, st.mc[0], vis, pk, blk);
   else prob_block<T, true>(s_cur, c, st.mc[0], vis, pk, blk);
   // !(blk <= limit) also catches a NaN sum
   const bool trig = alive && !(blk <= kPLimit);
@@ -748,8 +743,7 @@ __device__ __forceinline__ void resident_unit(RowState<1>& st, const typename T:
     for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, keep_or_neg_inf(s_cur[r], vis, r));
     const float tmax = max_xor32(t0);
     rescale_rows(st, 0, row_trig, tmax, c);
-    if (EDGE) prob_block<T, true>(s_cur, c, st.mc[0], vis, pk, blk);
-    else prob_block<T, false>(s_cur, c, st.mc[0], vis, pk, blk);
+    prob_block<T, true>(s_cur, c, st.mc[0], vis, pk, blk);
   }
   st.lsum[0] += blk;
   p_cur[0] = as_v8<T>(make_uint4(pk[0], pk[1], pk[2], pk[3]));
@@ -1181,9 +1175,7 @@ __global__ __launch_bounds__(kThreads, 2) void fa_fwd_window_resident_kernel(con
       // blocks every valid query of the wavefront sees completely need no mask work
       const int kb0 = u * 32;
       const bool interior = kb0 + 32 <= n && kb0 >= qw_last - a.wl && kb0 + 31 <= qw0 + a.wr;
-      // (the straight-line form of the unit measured no faster here: two wavefronts per SIMD
-      // already overlap each other's matrix and vector work)
-      resident_unit<T, true>(st, qreg, s_cur, s_nxt, p_prev, p_cur, &lds_k[(un - b_lo) * kBlk],
+      resident_unit<T>(st, qreg, s_cur, s_nxt, p_prev, p_cur, &lds_k[(un - b_lo) * kBlk],
                              &lds_v[(up - b_lo) * kBlk], [&](floatx16& sv) { score_init(sv, un - b_lo); }, kb0,
                              interior, jlo, jhi, alive, c, lane);
     };
@@ -1478,34 +1470,160 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
 }
 
 // ======================================================================================
-// Key-split kernel: global layers with very few query tiles (a single short sequence).
-// With 128-row tiles one 512-token sequence of 12 heads is 48 workgroups on 256 compute
-// units, one wavefront per SIMD walking 16 key blocks one after the other.  Here a
-// workgroup owns ONE 32-row query block and its four wavefronts split the keys: wavefront w
-// takes the 32-key blocks w, w+4, w+8, ...  Nothing is shared between wavefronts until the
-// end, so each stages its own blocks in a private ring of kSplitRing LDS slots (direct
-// global->LDS loads, no barriers; up to 512 keys everything is requested at once).  The
-// four partial (reference, sum, accumulator) states are then merged through LDS with the
-// split/merge identity of the online softmax, and wavefront 0 runs the common epilogue.
+// Split kernel: global layers whose query tiles alone would leave SIMDs with one wavefront or
+// none (a single request, a few short sequences).  A workgroup is NQ x NK wavefronts: NQ query
+// blocks of 32 rows, each shared by NK wavefronts that split the KEYS: in step i wavefront
+// (qb, g) takes the 32-key block i NK + g, so the NK NQ wavefronts read one contiguous super
+// tile of 32 NK keys, staged once in LDS for all of them.
+//
+// What bounds such a call is latency, not a unit's throughput: a lone wavefront per SIMD pays
+// its LDS and memory round trips in full (one 2K-token request: 0.32 us per 32 x 32 unit at one
+// wavefront per SIMD, 0.20 at two or three).  Hence
+//   * everything is fetched by direct loads in an order the waits can count on (Q, K0, K1, then
+//     pairs (K of step t + 2, V of step t)), so the first product waits for Q and K0 only, and
+//     loads run P - 2 steps ahead of their use; a call with at most P steps requests everything
+//     up front;
+//   * the requests are issued before the sequence length is looked at (late_n), where the launch
+//     is so small that no other workgroup hides that read;
+//   * the ragged last block is a masked step like any other: nothing is staged a second time;
+//   * the NK partial (reference, sum, accumulator) states are merged through LDS with the
+//     split / merge identity of the online softmax, every wavefront finishing 1/NK of the output
+//     columns.
 // ======================================================================================
-constexpr int kSplitRing = 4;
+template <class T, int D, bool BIAS>
+struct SplitWave {
+  static constexpr int KS = D / 16, DB = D / 32;
+  RowState<1, D> st;
+  typename T::v8 q[KS];
+  uint32_t kfo[KS], vfo[DB];   // per-lane operand offsets (16-bit elements) into a swizzled 32-row block
 
-template <class T>
-__global__ __launch_bounds__(kThreads, 1) void fa_fwd_keysplit_kernel(const FaKernelArgs a) {
-  constexpr int BM = 32;
-  constexpr int kBlk = 32 * kD;  // elements per 32-key block
-  constexpr int kMergeVals = 35; // 32 accumulator values, reference, reference * c, sum share
-  __shared__ __attribute__((aligned(16))) uint16_t lds_k[kWaves * kSplitRing * kBlk];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_v[kWaves * kSplitRing * kBlk];
-  __shared__ float mbuf[(kWaves - 1) * kMergeVals * 64];  // [wavefront 1..3][value][lane]
-  static_assert(kSplitRing * kBlk >= kEpiPatch, "wavefront 0's V ring doubles as its epilogue patch");
+  __device__ __forceinline__ void init(int lane) {
+    init_state(st);
+    const int l32 = lane & 31, hh = lane >> 5, p16 = lane & 15, gg = (lane >> 4) & 1, row = 4 * hh + (p16 >> 2);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kfo[ks] = l32 * D + (((2 * ks + hh) ^ k_swz_d<D>(l32)) * 8);
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      vfo[db] = row * D + (((4 * db + 2 * gg + ((p16 & 3) >> 1)) ^ v_swz_d<D>(row)) * 8) + (p16 & 1) * 4;
+  }
+  __device__ __forceinline__ typename T::v8 k_frag(const uint16_t* kblk, int ks) const {
+    return as_v8<T>(*(const uint4*)&kblk[kfo[ks]]);
+  }
+  __device__ __forceinline__ typename T::v8 vt_frag(const uint16_t* vblk, int ks2, int db) const {
+    typedef __attribute__((address_space(3))) shortx4 lds_s4;
+    const shortx4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)&vblk[vfo[db] + ks2 * 16 * D]);
+    const shortx4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)&vblk[vfo[db] + (ks2 * 16 + 8) * D]);
+    shortx8 x;
+    x[0] = x0[0]; x[1] = x0[1]; x[2] = x0[2]; x[3] = x0[3];
+    x[4] = x1[0]; x[5] = x1[1]; x[6] = x1[2]; x[7] = x1[3];
+    return __builtin_bit_cast(typename T::v8, x);
+  }
+
+  // scores of a block on top of `s` (zero, or the block's bias)
+  __device__ __forceinline__ void scores(floatx16& s, const uint16_t* kblk, const float* bblk, int lane) {
+    const int hh = lane >> 5;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 b4 = BIAS ? *(const float4*)&bblk[8 * g + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
+      s[4 * g + 0] = b4.x; s[4 * g + 1] = b4.y; s[4 * g + 2] = b4.z; s[4 * g + 3] = b4.w;
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) s = T::mfma(k_frag(kblk, ks), q[ks], s);
+  }
+  __device__ __forceinline__ void accumulate(const typename T::v8 (&p)[2], const uint16_t* vblk) {
+#pragma unroll
+    for (int ks2 = 0; ks2 < 2; ++ks2)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        st.oacc[0][db] = T::mfma(vt_frag(vblk, ks2, db), p[ks2], st.oacc[0][db]);
+  }
+  // first reference of the rows: the maximum of the wavefront's first block
+  __device__ __forceinline__ void prime(const floatx16& s, uint32_t vis, float c) {
+    float t0 = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, keep_or_neg_inf(s[r], vis, r));
+    st.m_ref[0] = max_xor32(t0);
+    st.mc[0] = st.m_ref[0] == -INFINITY ? 0.f : st.m_ref[0] * c;
+  }
+  template <bool MASKED>
+  __device__ __forceinline__ void softmax(const floatx16& s, typename T::v8 (&p)[2], uint32_t vis, bool alive, float c) {
+    uint32_t pk[8];
+    float blk;
+    prob_block<T, MASKED>(s, c, st.mc[0], vis, pk, blk);
+    // !(blk <= limit) also catches a NaN sum; with a bias the first blocks can be excluded entirely
+    const bool trig = alive && (!(blk <= kPLimit) || (BIAS && st.m_ref[0] == -INFINITY));
+    if (__any(trig)) {
+      const bool row_trig = sum_xor32(trig ? 1.f : 0.f) > 0.f;   // a row refreshes on its own two lanes' evidence only
+      float t0 = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, MASKED ? keep_or_neg_inf(s[r], vis, r) : s[r]);
+      rescale_rows(st, 0, row_trig, max_xor32(t0), c);
+      prob_block<T, MASKED>(s, c, st.mc[0], vis, pk, blk);
+    }
+    st.lsum[0] += blk;
+    p[0] = as_v8<T>(make_uint4(pk[0], pk[1], pk[2], pk[3]));
+    p[1] = as_v8<T>(make_uint4(pk[4], pk[5], pk[6], pk[7]));
+  }
+  // The common step, straight-line but for the rare refresh: scores of the next block and P.V of the previous one on
+  // the matrix cores, this block's probabilities on the vector ALU.  (Fetching the operands out of LDS a step ahead
+  // measured no faster: 0.30 us per unit at one wavefront per SIMD, 0.245 at two, either way.)
+  __device__ __forceinline__ void step(const floatx16& s_cur, floatx16& s_nxt, const typename T::v8 (&p_prev)[2],
+                                       typename T::v8 (&p_cur)[2], const uint16_t* k_next, const uint16_t* v_prev,
+                                       const float* b_next, bool alive, float c, int lane) {
+    const int hh = lane >> 5;
+    typename T::v8 ka[KS], va[2 * DB];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) ka[ks] = k_frag(k_next, ks);
+#pragma unroll
+    for (int i = 0; i < 2 * DB; ++i) va[i] = vt_frag(v_prev, i / DB, i % DB);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 b4 = BIAS ? *(const float4*)&b_next[8 * g + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
+      s_nxt[4 * g + 0] = b4.x; s_nxt[4 * g + 1] = b4.y; s_nxt[4 * g + 2] = b4.z; s_nxt[4 * g + 3] = b4.w;
+    }
+    static_assert(KS == 2 * DB, "one score product alternates with one output product");
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      s_nxt = T::mfma(ka[i], q[i], s_nxt);
+      st.oacc[0][i % DB] = T::mfma(va[i], p_prev[i / DB], st.oacc[0][i % DB]);
+    }
+    softmax<false>(s_cur, p_cur, 0xFFFFu, alive, c);
+  }
+};
+
+// LDS of the split kernel in 16-bit elements: the Q tile, then P ring slots of [K super tile][V super tile]; after the
+// loop the same memory holds the partial results and the output patches.
+template <int D, int NQ, int NK, int P>
+struct SplitLds {
+  static constexpr int kBlk = 32 * D;
+  static constexpr int kQ = NQ * kBlk, kSlot = 2 * NK * kBlk;
+  static constexpr int kRing = kQ + P * kSlot;
+  static constexpr int kPart = NQ * (NK - 1) * 16 * (D / 32) * 64 * 2;   // other wavefronts' accumulator pieces
+  static constexpr int kState = NQ * NK * 2 * 64 * 2;                    // reference and row sum of every wavefront
+  static constexpr int kMerge = kPart + kState + NQ * epi_patch(D);
+  static constexpr int kElems = kRing > kMerge ? kRing : kMerge;
+};
+
+template <class T, int D, int NQ, int NK, int P, int WPS, bool BIAS>
+__global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const FaKernelArgs a) {
+  constexpr int NW = NQ * NK, THREADS = NW * 64, BM = 32 * NQ;
+  constexpr int KS = D / 16, DB = D / 32;
+  typedef SplitLds<D, NQ, NK, P> L;
+  constexpr int kBlk = L::kBlk;
+  constexpr int CH = D / 8, RPL = 64 / CH, LPB = 32 / RPL;   // 16-byte chunks per row, rows per load, loads per block
+  // a block's loads are dealt to NL of the NQ wavefronts that share it, LW each
+  constexpr int NL = NQ == 3 ? 2 : NQ, LW = LPB / NL;
+  static_assert(LPB % NL == 0 && P >= 2, "whole loads per wavefront");
+  __shared__ __attribute__((aligned(16))) uint16_t lds[L::kElems + (BIAS ? 2 * kSplitBiasKeys : 0)];
+  float* const lds_bias = (float*)(lds + L::kElems);
 
   TileCoord tc;
-  if (!locate_tile<BM, false>(a, tc)) return;  // tc.n still as loaded: see below
+  if (!locate_tile<BM, false>(a, tc)) return;   // tc.n still as loaded: see below
   const int N = a.max_len, q0 = tc.q0;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qb = wave % NQ, g = wave / NQ;
   const int l32 = lane & 31, hh = lane >> 5;
 
   const uint16_t* qp = (const uint16_t*)a.q + tc.b * a.qs[0] + tc.h * a.qs[1];
@@ -1514,188 +1632,301 @@ __global__ __launch_bounds__(kThreads, 1) void fa_fwd_keysplit_kernel(const FaKe
   uint16_t* op = (uint16_t*)a.o + tc.b * a.os[0] + tc.h * a.os[1];
   float* lsep = a.lse ? a.lse + ((int64_t)tc.b * a.heads + tc.h) * N : nullptr;
 
-  uint16_t* my_k = &lds_k[wave * kSplitRing * kBlk];
-  uint16_t* my_v = &lds_v[wave * kSplitRing * kBlk];
+  const bool late_n = a.late_n != 0;
+  if (!late_n) tc.n = tc.n < 0 ? 0 : (tc.n > N ? N : tc.n);
+  if (!late_n && q0 >= tc.n) {
+    zero_fill<BM, D, THREADS>(a, tc, op, lsep);
+    return;
+  }
 
-  // Block i of this wavefront is key block wave + 4 i and lives in ring slot i % kSplitRing.
-  // A block is 4 + 4 loads of 8 rows each (1 KB per load).  A lane's row is clamped to the
-  // last row of the tensor (rows >= n are masked or zeroed below), so its global offset is a
-  // per-lane 32-bit byte offset from the (batch, head) slice.
-  const int r8 = lane >> 3;
-  const uint32_t krow_b = 2u * (uint32_t)a.ks[2], vrow_b = 2u * (uint32_t)a.vs[2];
-  auto issue_block = [&](int i) {
-    const int j = wave + kWaves * i, slot = i % kSplitRing;
+  // A load moves RPL rows of a 32-row block (lane: row lane / CH, chunk position lane % CH).  A block whose rows
+  // all exist is addressed by a scalar base and a fixed per-lane offset; where rows would leave the tensor the
+  // lane's row is clamped to the last one (such rows are masked, zeroed or never read).
+  int row_of[LW];
+  uint32_t kchunk[LW], vchunk[LW], koff[LW], voff[LW];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int r = 8 * g + r8;  // row within the block
-      const int jg = 32 * j + r;
-      const uint32_t jc = (uint32_t)(jg < N ? jg : N - 1);
-      load16_to_lds(kp, jc * krow_b + 2u * (uint32_t)(((lane & 7) ^ k_swz(r)) * 8), &my_k[slot * kBlk + 8 * g * kD]);
-      load16_to_lds(vp, jc * vrow_b + 2u * (uint32_t)(((lane & 7) ^ v_swz(r)) * 8), &my_v[slot * kBlk + 8 * g * kD]);
+  for (int x = 0; x < LW; ++x) {
+    row_of[x] = (qb * LW + x) * RPL + lane / CH;
+    kchunk[x] = 2u * (uint32_t)(((lane % CH) ^ k_swz_d<D>(row_of[x])) * 8);
+    vchunk[x] = 2u * (uint32_t)(((lane % CH) ^ v_swz_d<D>(row_of[x])) * 8);
+    koff[x] = (uint32_t)row_of[x] * 2u * (uint32_t)a.ks[2] + kchunk[x];
+    voff[x] = (uint32_t)row_of[x] * 2u * (uint32_t)a.vs[2] + vchunk[x];
+  }
+  auto load_block = [&](const uint16_t* base, int64_t rs, const uint32_t (&off)[LW], const uint32_t (&chunk)[LW], int j,
+                        uint16_t* dst) {
+    if (NL < NQ && qb >= NL) return;
+    if (32 * j + 32 <= N) {
+      const uint16_t* gb = base + (int64_t)(32 * j) * rs;
+#pragma unroll
+      for (int x = 0; x < LW; ++x) load16_to_lds(gb, off[x], dst + (qb * LW + x) * RPL * D);
+    } else {
+      const int first = 32 * j < N ? 32 * j : N - 1;
+      const uint16_t* gb = base + (int64_t)first * rs;
+#pragma unroll
+      for (int x = 0; x < LW; ++x) {
+        const int r = row_of[x] < N - 1 - first ? row_of[x] : N - 1 - first;
+        load16_to_lds(gb, (uint32_t)r * 2u * (uint32_t)rs + chunk[x], dst + (qb * LW + x) * RPL * D);
+      }
     }
   };
-  // The first ring of blocks is requested from the tensor length alone, BEFORE the sequence
-  // length is looked at: reading it (device memory) then overlaps the loads instead of
-  // preceding them.  Blocks past the sequence end are fetched and never read.
-  const int nb_max = (N + 31) >> 5;
-  const int cnt_max = nb_max > wave ? (nb_max - wave + kWaves - 1) / kWaves : 0;
-  int issued = cnt_max < kSplitRing ? cnt_max : kSplitRing;  // blocks 0 .. issued-1 are requested
-#pragma unroll
-  for (int i = 0; i < kSplitRing; ++i)
-    if (i < issued) issue_block(i);
+  uint16_t* const ring = lds + L::kQ;
+  auto k_slot = [&](int i) { return ring + (i % P) * L::kSlot + g * kBlk; };
+  auto v_slot = [&](int i) { return ring + (i % P) * L::kSlot + (NK + g) * kBlk; };
+  auto load_k = [&](int i) { load_block(kp, a.ks[2], koff, kchunk, i * NK + g, k_slot(i)); };
+  auto load_v = [&](int i) { load_block(vp, a.vs[2], voff, vchunk, i * NK + g, v_slot(i)); };
+  auto load_pair = [&](int t, int steps) {   // K of step t + 2, V of step t
+    if (t + 2 < steps) load_k(t + 2);
+    load_v(t);
+  };
 
-  typename T::v8 qreg[1][4];
-  load_q<T, 1, 4, false>(a, qp, q0, lane, qreg);  // every wavefront holds the same 32 query rows
+  // Requests of the start, from the tensor length (late_n) or the sequence length.
+  const int steps_req = ((late_n ? N : tc.n) + 32 * NK - 1) / (32 * NK);
+  // Q: the block's loads are dealt to its NK wavefronts; swizzled like a K block
+#pragma unroll
+  for (int x = 0; x < (LPB + NK - 1) / NK; ++x) {
+    const int part = x * NK + g;
+    if (LPB % NK == 0 || part < LPB) {
+      const int r = part * RPL + lane / CH;
+      const int first = q0 + 32 * qb < N ? q0 + 32 * qb : N - 1;
+      const int rr = r < N - 1 - first ? r : N - 1 - first;
+      load16_to_lds(qp + (int64_t)first * a.qs[2],
+                    (uint32_t)rr * 2u * (uint32_t)a.qs[2] + 2u * (uint32_t)(((lane % CH) ^ k_swz_d<D>(r)) * 8),
+                    lds + qb * kBlk + part * RPL * D);
+    }
+  }
+  load_k(0);
+  if (steps_req > 1) load_k(1);
+  int pairs = steps_req <= P ? steps_req : P - 2;   // pairs requested so far
+  for (int t = 0; t < pairs; ++t) load_pair(t, steps_req);
+  if (BIAS) {
+    const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
+    for (int j = tid; j < ((N + 31) & ~31); j += THREADS) lds_bias[j] = T::to_float(bp[j < N ? j : N - 1]) * a.inv_abs_scale;
+  }
 
   // only now the sequence length
   const int n = tc.n < 0 ? 0 : (tc.n > N ? N : tc.n);
   tc.n = n;
   if (q0 >= n) {
     wait_direct_loads();  // the loads write this workgroup's LDS: they must land before it ends
-    zero_fill<BM>(a, tc, op, lsep);
+    zero_fill<BM, D, THREADS>(a, tc, op, lsep);
     return;
   }
   const int nb = (n + 31) >> 5;
-  const int cnt = nb > wave ? (nb - wave + kWaves - 1) / kWaves : 0;  // this wavefront's blocks; <= cnt_max
+  const int steps = (nb + NK - 1) / NK;                   // <= steps_req
+  const int nfs = n / (32 * NK);                          // steps whose super tile is full: steps or steps - 1
+  const bool wave_has_rows = q0 + 32 * qb < n;
+  const int ig = q0 + 32 * qb + l32;
+  const bool alive = ig < n;
+  const float c = a.c;
 
-  RowState<1> st;
-  init_state(st);
-  const bool alive = q0 + l32 < n;
-
-  // loads complete in order, 8 per block: block i has landed once at most 8 * (blocks
-  // requested after it) loads are outstanding
-  auto wait_for = [&](int i) {
-    const int younger = issued - 1 - i;
-    if (younger >= 3) wait_vmcnt<24>();
-    else if (younger == 2) wait_vmcnt<16>();
-    else if (younger == 1) wait_vmcnt<8>();
+  // Loads land in order.  Step i needs Q, K0, K1 and the pairs below i; of the pairs requested after them every
+  // one holds at least V's LW loads, and K's LW too while K of its step t + 2 exists.
+  auto wait_pairs_below = [&](int i) {
+    const int later = pairs - i;             // requested pairs that may still be under way
+    if (P > 2 && later == P - 2 && pairs + 1 < steps) wait_vmcnt<(P > 2 ? (P - 2) * 2 * LW : 0)>();
+    else if (later >= 3) wait_vmcnt<3 * LW>();
+    else if (later == 2) wait_vmcnt<2 * LW>();
+    else if (later == 1) wait_vmcnt<LW>();
     else wait_vmcnt<0>();
   };
-  // V rows at or beyond n are overwritten with zeros by the lanes that fetched them (0 *
-  // whatever is stored in the padding must be 0); the slot is this wavefront's own
-  auto scrub = [&](int i) {
-    const int kb0 = 32 * (wave + kWaves * i);
-    if (kb0 + 32 <= n) return;
-    uint16_t* vblk = &my_v[(i % kSplitRing) * kBlk];
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      if (kb0 + 8 * g + r8 >= n) *(uint4*)&vblk[(8 * g + r8) * kD + (lane & 7) * 8] = make_uint4(0, 0, 0, 0);
+  auto request_up_to = [&](int t) {
+    while (pairs < steps && pairs <= t) {
+      load_pair(pairs, steps);
+      ++pairs;
+    }
+  };
+  // every wavefront of the workgroup is past its reads of a ring slot (a wavefront that shares its blocks with nobody
+  // needs no barrier: its own reads are waited for)
+  auto slots_free = [&] {
+    if (NQ > 1) __syncthreads();
+    else __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
   };
 
-  if (cnt > 0) {
-    // the same software pipeline as the resident window kernel, over this wavefront's blocks
-    floatx16 sA, sB;
-    typename T::v8 pA[2], pB[2];
-    pA[0] = pA[1] = as_v8<T>(make_uint4(0, 0, 0, 0));
-    auto zero_scores = [](floatx16& sv) {
+  SplitWave<T, D, BIAS> w;
+  w.init(lane);
+  floatx16 sA, sB;
+  typename T::v8 pA[2], pB[2];
+  pA[0] = pA[1] = pB[0] = pB[1] = as_v8<T>(make_uint4(0, 0, 0, 0));
+  // V rows at or beyond n are overwritten with zeros by the lanes that fetched them, once the partial super tile has
+  // landed: 0 * whatever is stored in the padding must be 0
+  auto scrub = [&](int i) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sv[r] = 0.f;
-    };
-    wait_for(0);
+    for (int x = 0; x < LW; ++x)
+      if ((NL == NQ || qb < NL) && 32 * (i * NK + g) + row_of[x] >= n)
+        *(uint4*)&v_slot(i)[row_of[x] * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
+  };
+  if (nfs == 0) {
+    request_up_to(0);   // (two slots and a tensor longer than this sequence: V0 has not been requested yet)
+    wait_vmcnt<0>();
     scrub(0);
-    zero_scores(sA);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) sA = T::mfma(load_k_frag_swz<T>(my_k, l32, hh, ks), qreg[0][ks], sA);
-    // A global layer shows every existing row at least one key of the wavefront's first block:
-    // the rows take its maximum as their reference here, once, so that every full block can
-    // run the straight-line unit (nothing is accumulated yet, so there is nothing to rescale).
-    {
-      const int kb0 = 32 * wave;
-      const uint32_t vis = kb0 + 32 <= n ? 0xFFFFu : visible_bits(kb0, hh, 0, n - 1);
-      float t0 = -INFINITY;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, keep_or_neg_inf(sA[r], vis, r));
-      const float tmax = max_xor32(t0);
-      st.m_ref[0] = tmax;
-      st.mc[0] = tmax == -INFINITY ? 0.f : tmax * a.c;
-    }
-
-    // Unit i: probabilities of block i; scores of block i+1; P.V of block i-1.  At the two
-    // ends the neighbour is clamped: its product is unused (scores) or multiplied by zero
-    // probabilities (P.V).
-    auto unit = [&](floatx16& s_cur, floatx16& s_nxt, typename T::v8 (&p_prev)[2], typename T::v8 (&p_cur)[2], int i) {
-      const int in = i + 1 < cnt ? i + 1 : cnt - 1;
-      const int ip = i > 0 ? i - 1 : 0;
-      if (i + 1 < cnt) {
-        wait_for(i + 1);
-        scrub(i + 1);
-      }
-      const int kb0 = 32 * (wave + kWaves * i);
-      if (kb0 + 32 <= n)
-        resident_unit<T, false>(st, qreg, s_cur, s_nxt, p_prev, p_cur, &my_k[(in % kSplitRing) * kBlk],
-                                &my_v[(ip % kSplitRing) * kBlk], zero_scores, kb0, true, 0, n - 1, alive, a.c, lane);
-      else
-        resident_unit<T, true>(st, qreg, s_cur, s_nxt, p_prev, p_cur, &my_k[(in % kSplitRing) * kBlk],
-                               &my_v[(ip % kSplitRing) * kBlk], zero_scores, kb0, kb0 + 32 <= n, 0, n - 1, alive, a.c,
-                               lane);
-      // block i-1 is consumed (its fragments are in registers): refill its slot.  Only
-      // sequences beyond kSplitRing blocks per wavefront (512 keys) get here.
-      if (i >= 1 && i - 1 + kSplitRing < cnt) {
-        issue_block(i - 1 + kSplitRing);
-        issued = i + kSplitRing;
-      }
-    };
-    auto drain = [&](typename T::v8 (&p_last)[2], int i) {
-      const uint16_t* vblk = &my_v[(i % kSplitRing) * kBlk];
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-        st.oacc[0][x & 1] = T::mfma(load_vt_frag_swz<T>(vblk, lane, x >> 1, x & 1), p_last[x >> 1], st.oacc[0][x & 1]);
-    };
-    int i = 0;
-    for (; i + 1 < cnt; i += 2) {
-      unit(sA, sB, pA, pB, i);
-      unit(sB, sA, pB, pA, i + 1);
-    }
-    if (i < cnt) {
-      unit(sA, sB, pA, pB, i);
-      drain(pB, i);
-    } else {
-      drain(pA, cnt - 1);
-    }
-  }
-  // blocks requested beyond this wavefront's share of [0, n) may still be landing in its ring
-  wait_direct_loads();
-
-  // ---- merge the four partial results (same lane <-> (row, column) mapping in every wavefront)
-  if (wave > 0) {
-    float* dst = mbuf + (wave - 1) * kMergeVals * 64 + lane;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dst[(16 * db + r) * 64] = st.oacc[0][db][r];
-    dst[32 * 64] = st.m_ref[0];
-    dst[33 * 64] = st.mc[0];
-    dst[34 * 64] = st.lsum[0];
+  } else if (NL < NQ && qb >= NL) {
+    wait_vmcnt<0>();       // a wavefront that moves no K or V: its part of Q is all it has under way
+  } else {
+    wait_pairs_below(0);
   }
   __syncthreads();
-  if (wave != 0) return;
-  {
-    float m_new = st.m_ref[0];
+  auto bias_of_block = [&](int i) { return &lds_bias[BIAS ? 32 * (i * NK + g) : 0]; };
 #pragma unroll
-    for (int w = 0; w < kWaves - 1; ++w) m_new = fmaxf(m_new, mbuf[w * kMergeVals * 64 + 32 * 64 + lane]);
-    const float mc_new = (m_new == -INFINITY) ? 0.f : m_new * a.c;
-    // a wavefront that saw no key has nothing accumulated: factor 0, kept away from exp2(+inf)
-    const float f0 = (st.m_ref[0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(st.mc[0] - mc_new);
-    st.lsum[0] *= f0;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) st.oacc[0][db][r] *= f0;
-#pragma unroll
-    for (int w = 0; w < kWaves - 1; ++w) {
-      const float* src = mbuf + w * kMergeVals * 64 + lane;
-      const float f = (src[32 * 64] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(src[33 * 64] - mc_new);
-      st.lsum[0] = __builtin_fmaf(f, src[34 * 64], st.lsum[0]);
-#pragma unroll
-      for (int db = 0; db < 2; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          st.oacc[0][db][r] = __builtin_fmaf(f, src[(16 * db + r) * 64], st.oacc[0][db][r]);
+  for (int ks = 0; ks < KS; ++ks) {
+    uint4 u = __builtin_bit_cast(uint4, w.k_frag(lds + qb * kBlk, ks));
+    if (a.negate_q) {
+      u.x ^= 0x80008000u; u.y ^= 0x80008000u; u.z ^= 0x80008000u; u.w ^= 0x80008000u;
     }
-    st.m_ref[0] = m_new;
-    st.mc[0] = mc_new;
+    w.q[ks] = as_v8<T>(u);
   }
-  epilogue<T, 1, kD>(a, st, op, lsep, q0, n, lane, lds_v);
+  w.scores(sA, k_slot(0), bias_of_block(0), lane);
+  w.prime(sA, nfs > 0 ? 0xFFFFu : visible_bits(32 * g, hh, 0, n - 1), c);
+
+  // Step 0 (if its super tile is full): probabilities of block 0, scores of block 1.
+  if (nfs > 0) {
+    if (steps > P) slots_free();   // K0's slot is refilled
+    request_up_to(P - 2);
+    if (wave_has_rows) {
+      const int in = steps > 1 ? 1 : 0;
+      w.scores(sB, k_slot(in), bias_of_block(in), lane);
+      w.template softmax<false>(sA, pA, 0xFFFFu, alive, c);
+    }
+  }
+  // Step i (a full super tile): probabilities of block i, scores of block i + 1, P.V of block i - 1.
+  int i = 1;
+  {
+    // The steady part, P steps per turn: ring slots are compile-time constants, the row bases of the requested blocks
+    // just advance, and the wait is one instruction (the pairs under way all hold K and V).  Step i requests pair
+    // i + P - 2, whose K of step i + P lies inside the full super tiles.
+    if (P == 4 && i + 2 * P - 1 < nfs && pairs == P - 1) {
+      const int64_t kstep = (int64_t)(32 * NK) * a.ks[2], vstep = (int64_t)(32 * NK) * a.vs[2];
+      const uint16_t* kg = kp + (int64_t)(32 * g) * a.ks[2] + (P + 1) * kstep;
+      const uint16_t* vg = vp + (int64_t)(32 * g) * a.vs[2] + (P - 1) * vstep;
+      uint16_t* const my_k = ring + g * kBlk;
+      uint16_t* const my_v = ring + (NK + g) * kBlk;
+      auto steady = [&](auto Jc, floatx16& s_cur, floatx16& s_nxt, typename T::v8 (&p_prev)[2], typename T::v8 (&p_cur)[2], int i) {
+        constexpr int J = decltype(Jc)::value;   // i % P
+        wait_vmcnt<(P > 2 ? (P - 2) * 2 * LW : 0)>();
+        slots_free();
+        if (NL == NQ || qb < NL) {
+#pragma unroll
+          for (int x = 0; x < LW; ++x) load16_to_lds(kg, koff[x], my_k + J * L::kSlot + (qb * LW + x) * RPL * D);
+#pragma unroll
+          for (int x = 0; x < LW; ++x) load16_to_lds(vg, voff[x], my_v + (J + P - 2) % P * L::kSlot + (qb * LW + x) * RPL * D);
+        }
+        kg += kstep;
+        vg += vstep;
+        if (wave_has_rows)
+          w.step(s_cur, s_nxt, p_prev, p_cur, my_k + (J + 1) % P * L::kSlot, my_v + (J + P - 1) % P * L::kSlot,
+                 bias_of_block(i + 1), alive, c, lane);
+      };
+      for (; i + 2 * P - 1 < nfs; i += P) {
+        steady(std::integral_constant<int, 1>{}, sB, sA, pA, pB, i);
+        steady(std::integral_constant<int, 2>{}, sA, sB, pB, pA, i + 1);
+        steady(std::integral_constant<int, 3>{}, sB, sA, pA, pB, i + 2);
+        steady(std::integral_constant<int, 0>{}, sA, sB, pB, pA, i + 3);
+      }
+      pairs = i + P - 2;
+    }
+  }
+  auto step = [&](floatx16& s_cur, floatx16& s_nxt, typename T::v8 (&p_prev)[2], typename T::v8 (&p_cur)[2], int i) {
+    wait_pairs_below(i);
+    slots_free();
+    request_up_to(i + P - 2);   // their slots were last read in step i - 1
+    const int in = i + 1 < steps ? i + 1 : i;   // (the last block's successor: its scores are not used)
+    if (wave_has_rows)
+      w.step(s_cur, s_nxt, p_prev, p_cur, k_slot(in), v_slot(i - 1), bias_of_block(in), alive, c, lane);
+  };
+  for (; i + 1 < nfs; i += 2) {
+    step(sB, sA, pA, pB, i);
+    step(sA, sB, pB, pA, i + 1);
+  }
+  if (i < nfs) {
+    step(sB, sA, pA, pB, i);
+    pA[0] = pB[0];
+    pA[1] = pB[1];
+  } else if (nfs > 0) {
+    sA = sB;
+  }
+  // Now sA holds the scores of the partial super tile (if there is one) and pA the last full block's probabilities.
+  if (nfs > 0 || steps > nfs) {
+    if (nfs > 0) {
+      if (steps > nfs && P == 2) {   // (with more slots the last pair has been requested by now)
+        slots_free();
+        request_up_to(nfs);
+      }
+      wait_vmcnt<0>();
+      if (steps > nfs) scrub(nfs);
+      if (NQ > 1) __syncthreads();
+      w.accumulate(pA, v_slot(nfs - 1));
+    }
+    if (steps > nfs) {
+      w.template softmax<true>(sA, pA, visible_bits(32 * (nfs * NK + g), hh, 0, n - 1), alive, c);
+      w.accumulate(pA, v_slot(nfs));
+    }
+  }
+  wait_direct_loads();   // requests beyond the sequence's last step may still be landing in the ring
+  __syncthreads();       // the ring becomes the merge memory
+
+  // ---- merge the NK partial results of each query block: the accumulator's groups of four registers (four output
+  // columns of a row; the same lane <-> (row, column) mapping in every wavefront) are dealt to the NK wavefronts,
+  // group x to wavefront x % NK, which finishes it
+  constexpr int G = 4 * DB;
+  float4* const part = (float4*)lds + (size_t)qb * (NK - 1) * G * 64 + lane;       // [group][contributor][lane]
+  float* const state = (float*)(lds + L::kPart) + (size_t)qb * NK * 2 * 64 + lane; // [wavefront][reference, sum][lane]
+  uint16_t* const patch = lds + L::kPart + L::kState + qb * epi_patch(D);
+  constexpr int kEpiStride = epi_stride(D);
+  state[(2 * g + 0) * 64] = w.st.m_ref[0];
+  state[(2 * g + 1) * 64] = w.st.lsum[0];
+#pragma unroll
+  for (int x = 0; x < G; ++x) {
+    if (x % NK != g) {   // (wavefront-uniform)
+      const int r = 4 * (x % 4);
+      part[(x * (NK - 1) + (g < x % NK ? g : g - 1)) * 64] =
+          make_float4(w.st.oacc[0][x / 4][r], w.st.oacc[0][x / 4][r + 1], w.st.oacc[0][x / 4][r + 2], w.st.oacc[0][x / 4][r + 3]);
+    }
+  }
+  __syncthreads();
+  float mk[NK], m_new = -INFINITY, fk[NK], ltot = 0.f;
+#pragma unroll
+  for (int x = 0; x < NK; ++x) {
+    mk[x] = state[(2 * x + 0) * 64];
+    m_new = fmaxf(m_new, mk[x]);
+  }
+  const float mc_new = m_new == -INFINITY ? 0.f : m_new * c;
+#pragma unroll
+  for (int x = 0; x < NK; ++x) {
+    // a wavefront that saw no key has nothing accumulated: factor 0, kept away from exp2(+inf)
+    fk[x] = mk[x] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk[x] * c - mc_new);
+    ltot = __builtin_fmaf(fk[x], state[(2 * x + 1) * 64], ltot);
+  }
+  ltot = sum_xor32(ltot);
+  const bool live = alive && ltot > 0.f;
+  const float inv = live ? 1.0f / ltot : 0.f;
+#pragma unroll
+  for (int x = 0; x < G; ++x) {
+    if (x % NK == g) {
+      const int r = 4 * (x % 4);
+      const float f = fk[x % NK];
+      float4 v = make_float4(w.st.oacc[0][x / 4][r] * f, w.st.oacc[0][x / 4][r + 1] * f, w.st.oacc[0][x / 4][r + 2] * f,
+                             w.st.oacc[0][x / 4][r + 3] * f);
+#pragma unroll
+      for (int y = 0; y < NK; ++y) {
+        if (y == x % NK) continue;
+        const float4 u = part[(x * (NK - 1) + (y < x % NK ? y : y - 1)) * 64];
+        v.x = __builtin_fmaf(fk[y], u.x, v.x);
+        v.y = __builtin_fmaf(fk[y], u.y, v.y);
+        v.z = __builtin_fmaf(fk[y], u.z, v.z);
+        v.w = __builtin_fmaf(fk[y], u.w, v.w);
+      }
+      // columns 32 (x / 4) + 8 (x % 4) + 4 hh .. + 3 of the lane's row
+      *(uint2*)&patch[l32 * kEpiStride + 8 * x + 4 * hh] =
+          live ? make_uint2(T::pack2(v.x * inv, v.y * inv), T::pack2(v.z * inv, v.w * inv)) : make_uint2(0, 0);
+    }
+  }
+  __syncthreads();
+  for (int pass = g; pass < 32 / RPL; pass += NK) {
+    const int r = pass * RPL + lane / CH;
+    const int row = q0 + 32 * qb + r;
+    const uint4 v = *(const uint4*)&patch[r * kEpiStride + (lane % CH) * 8];
+    if (row < N) *(uint4*)(op + row * a.os[2] + (lane % CH) * 8) = v;
+  }
+  if (lsep && g == 0 && hh == 0 && ig < N) lsep[ig] = live ? (mc_new + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
 }
 
 // ======================================================================================
@@ -2244,9 +2475,27 @@ __global__ __launch_bounds__(256) void fa_rope_rotate_kernel(const FaRopeArgs r)
 // address is looked up once per device and only that address is ever handed to a kernel.
 static __device__ __align__(256) unsigned char fa_static_scratch_array[FA_STATIC_SCRATCH_BYTES];
 
+typedef void (*Kernel)(const FaKernelArgs);
+// The split kernel's shapes: NQ query blocks x NK key splits, ring slots, wavefronts per SIMD asked for.  Slots fill
+// the LDS of a compute unit that such a workgroup has to itself (head_dim 32: a half or a quarter of it).
+template <class T, bool BIAS>
+Kernel split_kernel(int head_dim, int split) {
+  switch (head_dim * 256 + split) {
+    case 64 * 256 + 0x18: return fa_fwd_split_kernel<T, 64, 1, 8, 2, 2, BIAS>;
+    case 64 * 256 + 0x24: return fa_fwd_split_kernel<T, 64, 2, 4, 4, 2, BIAS>;
+    case 64 * 256 + 0x34: return fa_fwd_split_kernel<T, 64, 3, 4, BIAS ? 3 : 4, 3, BIAS>;
+    case 64 * 256 + 0x42: return fa_fwd_split_kernel<T, 64, 4, 2, 4, 2, BIAS>;
+    case 128 * 256 + 0x14: return fa_fwd_split_kernel<T, 128, 1, 4, 2, 1, BIAS>;
+    case 128 * 256 + 0x24: return fa_fwd_split_kernel<T, 128, 2, 4, 2, 2, BIAS>;
+    case 128 * 256 + 0x42: return fa_fwd_split_kernel<T, 128, 4, 2, BIAS ? 2 : 4, 2, BIAS>;
+    case 32 * 256 + 0x14: return fa_fwd_split_kernel<T, 32, 1, 4, 4, BIAS ? 1 : 2, BIAS>;
+    case 32 * 256 + 0x22: return fa_fwd_split_kernel<T, 32, 2, 2, 4, 3, BIAS>;
+    default: return nullptr;
+  }
+}
+
 template <class T>
 int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stream) {
-  typedef void (*Kernel)(const FaKernelArgs);
   unsigned grid = (unsigned)a.total_tiles;
   if (a.map_xcd) grid = 8u * (unsigned)a.xcd_per * (unsigned)a.batch;
   if (bm == 0) grid = a.mix_ids_a + kMixIdsB;
@@ -2268,6 +2517,12 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
   // against 7.8 us, 4K equal, 8K 17.3 against 14.9 us, 32K 43 against 37 us); it exists for
   // head_dim 64 only.
   const bool latency_bound = a.head_dim == kD && a.total_tiles <= 384;
+  if (a.split) {
+    // (the host has checked that this shape exists for the head size)
+    kern = a.key_bias ? split_kernel<T, true>(a.head_dim, a.split) : split_kernel<T, false>(a.head_dim, a.split);
+    threads = 64u * (unsigned)((a.split >> 4) * (a.split & 15));
+    if (!kern) return (int)hipErrorInvalidValue;
+  } else
   if (!a.key_bias && !global && v_path == 0 && bm == 128 && slice_fits_32bit && win_blocks <= kResBlocks &&
       wave_blocks <= kTwoPhaseBlocks && win_kernel != 1 && !(latency_bound && !rope && win_kernel != 2)) {
     // local layer with a narrow two-sided window (the paper's 63/64), any head_dim
@@ -2306,9 +2561,6 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     // kernel covers every mask; bm is 128 here
     if (a.head_dim == 32) kern = v_path == 0 ? fa_fwd_masked_kernel<T, 32, 1, true> : fa_fwd_masked_kernel<T, 32, 1, false>;
     else kern = v_path == 0 ? fa_fwd_masked_kernel<T, 128, 1, true> : fa_fwd_masked_kernel<T, 128, 1, false>;
-  } else if (bm == 32) {
-    // the host asks for 32-row tiles only for global layers of head_dim 64 without a bias
-    kern = fa_fwd_keysplit_kernel<T>;
   } else if (global && v_path == 0) {
     if (bm == 0) {
       kern = fa_fwd_global_mixed_kernel<T>;

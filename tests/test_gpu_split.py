@@ -1,0 +1,81 @@
+"""GPU parity of the split kernel (a workgroup's wavefronts split the keys as well as the rows) in every shape the
+library picks by itself, at the edges of its steps: a step is 32 NK keys, so lengths around its multiples, shorter than
+one step, one key and none; the ring is refilled where a sequence has more steps than slots.  Against the fp64 oracle
+with the bounds of the other parity tests."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_12646_amd as fa
+from oracle.attention_oracle import attention_oracle
+from workloads import draw, round_to_storage
+
+from tests.gpu_util import FA_DT, check_against, poison, run_ex, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# (head_dim, heads, max_len, lengths, key bias): NQ x NK chosen by the tile counts
+CASES = {
+    "d64_1x8_resident": (64, 2, 500, [500, 256, 255, 0], False),
+    "d64_1x8_streaming": (64, 1, 1300, [1300, 1024, 513, 31], False),
+    "d64_2x4": (64, 30, 200, [200, 128], False),
+    "d64_2x4_long": (64, 12, 1270, [1267], False),
+    "d64_3x4": (64, 15, 700, [700, 641], False),
+    "d64_3x4_other": (64, 30, 690, [97], False),
+    "d64_4x2": (64, 19, 1601, [1537], False),
+    "d128_1x4": (128, 2, 300, [300, 129, 128, 1], False),
+    "d128_2x4": (128, 30, 200, [200, 63], False),
+    "d128_4x2": (128, 15, 700, [700, 577], False),
+    "d32_1x4": (32, 20, 300, [300, 161], False),
+    "d32_2x2": (32, 25, 700, [700, 64], False),
+    "d64_1x8_bias": (64, 2, 500, [500, 256, 255, 1], True),
+    "d64_2x4_bias": (64, 30, 200, [200, 128], True),
+    "d64_3x4_bias": (64, 15, 700, [700, 641], True),
+    "d64_4x2_bias": (64, 24, 600, [600, 513], True),
+    "d128_1x4_bias": (128, 2, 300, [300, 129, 128, 1], True),
+    "d128_4x2_bias": (128, 15, 700, [700, 577], True),
+    "d32_2x2_bias": (32, 12, 300, [300, 161], True),
+}
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_split_kernel_shapes(name, dtype):
+    D, H, N, lens, biased = CASES[name]
+    B = len(lens)
+    rng = np.random.default_rng(N + D)
+    _, q, k, v = draw(7000 + N, B, H, N, D, dtype)
+    bias = None
+    if biased:
+        # ordinary values, holes, and in the first element a whole first step excluded (its rows see no key until later)
+        bias = round_to_storage(rng.standard_normal((B, N)).astype(np.float32), dtype)
+        bias[rng.random((B, N)) < 0.2] = -np.inf
+        bias[0, :260] = -np.inf
+    scale = -(D ** -0.5) if biased else D ** -0.5
+    o_ref, lse_ref = attention_oracle(q, k, v, lens, scale, key_bias=bias)
+    for b, n in enumerate(lens):   # nothing stored in the padding may show
+        for x in (q, k, v):
+            x[b, :, n:] = np.nan
+    o, lse = run_ex(q, k, v, lens, dtype, scale, key_bias=bias)
+    check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=name)
+    o2, lse2 = run_ex(q, k, v, lens, dtype, scale, key_bias=bias, tuning=fa.FA_TUNE_MAP_LINEAR)
+    assert np.array_equal(o, o2) and np.array_equal(lse, lse2)
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_split_kernel_packed_qkv(D):
+    """Read from one [batch, len, 3, heads, dim] buffer, written as [batch, len, heads, dim]: the same bits as dense."""
+    B, H, N = 2, 12, 333
+    lens = [333, 100]
+    _, q, k, v = draw(91, B, H, N, D, "bf16")
+    o, lse = run_ex(q, k, v, lens, "bf16", D ** -0.5)
+    packed = torch.stack([to_dev(np.ascontiguousarray(x.transpose(0, 2, 1, 3)), "bf16") for x in (q, k, v)], dim=2)
+    st = (N * 3 * H * D, D, 3 * H * D)
+    o2 = poison((B, N, H, D), "bf16")
+    lse2 = torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    fa.fa_fwd_ex(dtype=FA_DT["bf16"], q=packed[:, :, 0], k=packed[:, :, 1], v=packed[:, :, 2], o=o2, lse=lse2,
+                 seq_lens=torch.tensor(lens, dtype=torch.int32, device="cuda"), batch=B, heads=H, max_len=N, head_dim=D,
+                 scale=D ** -0.5, q_strides=st, k_strides=st, v_strides=st, o_strides=(N * H * D, D, H * D))
+    torch.cuda.synchronize()
+    assert np.array_equal(o2.double().cpu().numpy().transpose(0, 2, 1, 3), o)
+    assert np.array_equal(lse2.double().cpu().numpy(), lse)

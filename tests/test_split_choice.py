@@ -1,0 +1,83 @@
+"""The host's choice of a split-kernel shape, walked on the CPU with stub launchers: a shape is one the kernels exist in,
+its grid matches its rows per workgroup and fits the 256 compute units in one round, and calls that the kernel does not
+cover (windows, a rotation in the call, a long key bias, forced shapes) never get one."""
+import pathlib
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = pathlib.Path(__file__).resolve().parent.parent
+
+DRIVER = r"""
+#include <cstdio>
+#include <cstring>
+#include <initializer_list>
+#include "fa.h"
+#include "fa_args.h"
+static FaKernelArgs last;
+static int last_bm;
+int fa_launch_f16(const FaKernelArgs& a, int bm, int, int, void*) { last = a; last_bm = bm; return 0; }
+int fa_launch_bf16(const FaKernelArgs& a, int bm, int, int, void*) { last = a; last_bm = bm; return 0; }
+int fa_launch_rope_rotate(const FaRopeArgs&, int, void*) { return 0; }
+int fa_static_scratch(void**) { return 0; }
+#define EXPECT(cond) do { if (!(cond)) { printf("FAILED line %d: %s (d %d b %d h %d n %d bias %d split %x bm %d)\n", __LINE__, #cond, \
+  p.head_dim, p.batch, p.heads, p.max_len, p.key_bias != nullptr, last.split, last_bm); return 1; } } while (0)
+int main() {
+  alignas(16) static char buf[64];
+  alignas(16) static float table[64];
+  fa_params p;
+  std::memset(&p, 0, sizeof p);
+  p.struct_size = sizeof p;
+  p.q = p.k = p.v = p.o = buf;
+  p.scale = 0.125f;
+  long taken = 0, calls = 0;
+  for (int d : {32, 64, 128})
+    for (int b : {1, 2, 3, 5, 8, 32})
+      for (int h : {1, 4, 8, 12, 24, 86})
+        for (int n = 1; n < 5000; n += 1 + n / 7)
+          for (int biased = 0; biased < 2; ++biased) {
+            p.head_dim = d; p.batch = b; p.heads = h; p.max_len = n;
+            p.key_bias = biased ? buf : nullptr;
+            p.rope_cos = p.rope_sin = nullptr; p.tuning = 0; p.scale = 0.125f;
+            p.window_left = p.window_right = -1;
+            EXPECT(fa_fwd_ex(&p) == 0);
+            ++calls;
+            if (last.split) {
+              ++taken;
+              const int nq = last.split >> 4, s = last.split;
+              EXPECT(d == 64 ? (s == 0x18 || s == 0x24 || s == 0x34 || s == 0x42)
+                             : (d == 128 ? (s == 0x14 || s == 0x24 || s == 0x42) : (s == 0x14 || s == 0x22)));
+              EXPECT(last_bm == 32 * nq && last.n_qtiles == (n + 32 * nq - 1) / (32 * nq));
+              EXPECT(last.total_tiles == last.n_qtiles * b * h && last.total_tiles <= (d == 32 ? 768 : 256));
+              EXPECT(!biased || n <= kSplitBiasKeys);
+            }
+            p.window_left = 63; p.window_right = 64;
+            EXPECT(fa_fwd_ex(&p) == 0 && last.split == 0);
+            p.window_left = p.window_right = -1; p.rope_cos = p.rope_sin = table;
+            EXPECT(fa_fwd_ex(&p) == 0 && last.split == 0);
+            p.rope_cos = p.rope_sin = nullptr; p.tuning = FA_TUNE_BM_128;
+            EXPECT(fa_fwd_ex(&p) == 0 && last.split == 0);
+            p.tuning = FA_TUNE_V_SCALAR;
+            EXPECT(fa_fwd_ex(&p) == 0 && last.split == 0);
+            p.tuning = 0; p.scale = 0.0f;
+            EXPECT(fa_fwd_ex(&p) == 0 && (!biased || last.split == 0));
+          }
+  p.scale = 0.125f; p.key_bias = buf; p.batch = 1; p.heads = 1; p.head_dim = 64;
+  p.max_len = kSplitBiasKeys; EXPECT(fa_fwd_ex(&p) == 0 && last.split != 0);
+  p.max_len = kSplitBiasKeys + 1; EXPECT(fa_fwd_ex(&p) == 0 && last.split == 0);
+  printf("ok %ld of %ld\n", taken, calls);
+  return 0;
+}
+"""
+
+
+def test_split_shapes_chosen_by_the_host(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    src, exe, csrc = tmp_path / "driver.cpp", tmp_path / "driver", ROOT / "paper_2603_12646_amd" / "csrc"
+    src.write_text(DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", str(ROOT / "include"),
+                    "-I", str(csrc), str(src), str(csrc / "fa_api.cpp"), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
