@@ -1223,13 +1223,22 @@ __global__ __launch_bounds__(kThreads, 2) void fa_fwd_window_resident_kernel(con
 // ======================================================================================
 constexpr int kTwoPhaseBlocks = 5;
 
-template <class T, int D>
+// OPT: a rotation (kTwoPhaseRope) or a key bias (kTwoPhaseBias) is a compile-time variant.
+//   Rotation: the K blocks are rotated in place in LDS, once for the four wavefronts.  What that costs is the angle
+//   tables: 256 bytes per K row, as much as its K and V, so a thread requests its rows' entries right behind the K
+//   loads and holds them in registers (the score accumulators are not live yet) until K has landed.
+//   Bias: each key's bias divided by |scale| is the C operand of its block's first score product.
+enum { kTwoPhasePlain = 0, kTwoPhaseRope = 1, kTwoPhaseBias = 2 };
+
+template <class T, int D, int OPT = kTwoPhasePlain>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twophase_kernel(const FaKernelArgs a) {
+  constexpr bool ROPE = OPT == kTwoPhaseRope, BIAS = OPT == kTwoPhaseBias;
   constexpr int BM = kWaves * 32;
   constexpr int KS = D / 16, DB = D / 32;
   constexpr int kBlk = 32 * D;  // elements per block
   static_assert(kResBlocks * kBlk >= kWaves * epi_patch(D), "the region doubles as the epilogue patches");
   __shared__ __attribute__((aligned(16))) uint16_t lds[kResBlocks * kBlk];
+  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? kResBlocks * 32 : 4];
 
   TileCoord tc;
   if (!locate_tile<BM, false>(a, tc)) return;  // tc.n still as loaded: see below
@@ -1312,9 +1321,38 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
   };
   request_blocks(kp, a.ks[2], true);
 
+  // ROPE: item x of a thread is chunk pair tid % HALF of region row tid / HALF + x * RSTEP (its key clamped into the
+  // tensor: rows outside it are never used unmasked)
+  constexpr int HALF = D / 16, RSTEP = kThreads / HALF;
+  constexpr int kItems = kResBlocks * 32 / RSTEP;              // D = 32, 64, 128: 2, 4, 8
+  constexpr int kHeld = ROPE && D != 128 ? kItems : 0;          // items whose table entries are held (32, 64 registers)
+  const int rope_r = tid / HALF, rope_c = tid % HALF;
+  auto table_row = [&](int x) {
+    int key = b_lo * 32 + rope_r + x * RSTEP;
+    key = key < N ? key : N - 1;
+    return (int64_t)key * a.rope_stride + 8 * rope_c;
+  };
+  float4 held[kHeld > 0 ? kHeld : 1][4];
+  if (ROPE) {
+#pragma unroll
+    for (int x = 0; x < kHeld; ++x) {
+      const float4* cs = (const float4*)(a.rope_cos + table_row(x));
+      const float4* sn = (const float4*)(a.rope_sin + table_row(x));
+      held[x][0] = cs[0];
+      held[x][1] = cs[1];
+      held[x][2] = sn[0];
+      held[x][3] = sn[1];
+    }
+  }
+  if (BIAS) {   // one value per thread: key b_lo*32 + tid (256 keys, 256 threads)
+    const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
+    const int jg = b_lo * 32 + tid;
+    lds_bias[tid] = T::to_float(bp[jg < N ? jg : N - 1]) * a.inv_abs_scale;
+  }
+
   const int qw0 = q0 + wave * 32;
   typename T::v8 qreg[1][KS];
-  load_q<T, 1>(a, qp, qw0, lane, qreg);
+  load_q<T, 1, KS, ROPE>(a, qp, qw0, lane, qreg);
 
   // only now the sequence length
   const int n = tc.n < 0 ? 0 : (tc.n > N ? N : tc.n);
@@ -1345,17 +1383,44 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
   // ---- phase 1: scores of every visible block
   wait_direct_loads();
   __syncthreads();
-  if (a.rope_cos) {
-    // rotary embedding: the K blocks are rotated in place, once for the four wavefronts
-    rope_rows_in_lds<T, D, true>(a, lds, D, (b_hi - b_lo) * 32, b_lo * 32, tid, kThreads);
+  if (ROPE) {
+#pragma unroll
+    for (int x = 0; x < kItems; ++x) {
+      const int r = rope_r + x * RSTEP;
+      if (r < (b_hi - b_lo) * 32) {
+        float4 tb[4];
+        if (x < kHeld) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) tb[e] = held[x < kHeld ? x : 0][e];
+        } else {
+          const float4* cs = (const float4*)(a.rope_cos + table_row(x));
+          const float4* sn = (const float4*)(a.rope_sin + table_row(x));
+          tb[0] = cs[0]; tb[1] = cs[1]; tb[2] = sn[0]; tb[3] = sn[1];
+        }
+        uint4* plo = (uint4*)&lds[r * D + ((rope_c ^ k_swz_d<D>(r & 31)) * 8)];
+        uint4* phi = (uint4*)&lds[r * D + (((rope_c + HALF) ^ k_swz_d<D>(r & 31)) * 8)];
+        uint4 lo4 = *plo, hi4 = *phi;
+        rotate8<T>(lo4, hi4, (const float*)&tb[0], (const float*)&tb[2]);
+        *plo = lo4;
+        *phi = hi4;
+      }
+    }
     __syncthreads();
   }
   floatx16 sc[kTwoPhaseBlocks];   // sc[i] is set and used for i < cnt only
 #pragma unroll
   for (int i = 0; i < kTwoPhaseBlocks; ++i) {
     if (i < cnt) {
+      if (BIAS) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sc[i][r] = 0.f;
+        for (int g = 0; g < 4; ++g) {
+          const float4 b4 = *(const float4*)&lds_bias[(fb + i - b_lo) * 32 + 8 * g + 4 * hh];
+          sc[i][4 * g + 0] = b4.x; sc[i][4 * g + 1] = b4.y; sc[i][4 * g + 2] = b4.z; sc[i][4 * g + 3] = b4.w;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[i][r] = 0.f;
+      }
       const uint16_t* kblk = &lds[(fb + i - b_lo) * kBlk];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) sc[i] = T::mfma(load_k_frag_swz_d<T, D>(kblk, l32, hh, ks), qreg[0][ks], sc[i]);
@@ -2476,6 +2541,12 @@ __global__ __launch_bounds__(256) void fa_rope_rotate_kernel(const FaRopeArgs r)
 static __device__ __align__(256) unsigned char fa_static_scratch_array[FA_STATIC_SCRATCH_BYTES];
 
 typedef void (*Kernel)(const FaKernelArgs);
+template <class T, int OPT>
+Kernel twophase_kernel(int head_dim) {
+  return head_dim == 32 ? fa_fwd_window_twophase_kernel<T, 32, OPT>
+                        : (head_dim == 64 ? fa_fwd_window_twophase_kernel<T, 64, OPT> : fa_fwd_window_twophase_kernel<T, 128, OPT>);
+}
+
 // The split kernel's shapes: NQ query blocks x NK key splits, ring slots, wavefronts per SIMD asked for.  Slots fill
 // the LDS of a compute unit that such a workgroup has to itself (head_dim 32: a half or a quarter of it).
 template <class T, bool BIAS>
@@ -2523,11 +2594,12 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     threads = 64u * (unsigned)((a.split >> 4) * (a.split & 15));
     if (!kern) return (int)hipErrorInvalidValue;
   } else
-  if (!a.key_bias && !global && v_path == 0 && bm == 128 && slice_fits_32bit && win_blocks <= kResBlocks &&
-      wave_blocks <= kTwoPhaseBlocks && win_kernel != 1 && !(latency_bound && !rope && win_kernel != 2)) {
+  if (!(a.key_bias && (rope || !(a.c > 0.f))) && !global && v_path == 0 && bm == 128 && slice_fits_32bit &&
+      win_blocks <= kResBlocks && wave_blocks <= kTwoPhaseBlocks && win_kernel != 1 &&
+      !(latency_bound && !rope && win_kernel != 2)) {
     // local layer with a narrow two-sided window (the paper's 63/64), any head_dim
-    kern = a.head_dim == 32 ? fa_fwd_window_twophase_kernel<T, 32>
-                            : (a.head_dim == 64 ? fa_fwd_window_twophase_kernel<T, 64> : fa_fwd_window_twophase_kernel<T, 128>);
+    kern = rope ? twophase_kernel<T, kTwoPhaseRope>(a.head_dim)
+                : (a.key_bias ? twophase_kernel<T, kTwoPhaseBias>(a.head_dim) : twophase_kernel<T, kTwoPhasePlain>(a.head_dim));
   } else if (a.key_bias && !rope && !global && v_path == 0 && a.c > 0.f && a.head_dim == kD && bm == 128 && slice_fits_32bit &&
       win_blocks <= kResBlocks) {
     // additive key bias on a local layer whose key range stays resident in LDS

@@ -1,0 +1,62 @@
+"""GPU parity of the local layers' two-phase kernel with an additive key bias and with a rotation (compile-time variants),
+at every head size: tile edges, the merged end blocks, keys excluded for whole windows, negative scale, packed inputs,
+and sequence lengths that end inside and at the edges of 32-key blocks.  Against the fp64 oracles with the bounds of the
+other parity tests."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_12646_amd as fa
+from oracle.attention_oracle import attention_oracle
+from workloads import draw, round_to_storage
+
+from tests.gpu_util import FA_DT, check_against, poison, run_ex, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("left,right", [(63, 64), (0, 0), (10, 64), (64, 3)])
+def test_two_phase_kernel_with_key_bias(D, dtype, left, right):
+    lens = [421, 320, 97, 1]
+    B, H, N = len(lens), 2, 421
+    rng = np.random.default_rng(D + left)
+    _, q, k, v = draw(4000 + D, B, H, N, D, dtype)
+    bias = round_to_storage(rng.standard_normal((B, N)).astype(np.float32), dtype)
+    bias[rng.random((B, N)) < 0.2] = -np.inf
+    bias[0, 100:300] = -np.inf                      # rows around 200 see no key at all
+    # the paper's padding value on every second key: beside ordinary keys their probabilities are 0.  (On whole windows it
+    # would compare what fp32 cannot hold: a score near -65504 has a spacing of 2^-8, so any fp32 sum of score and bias is up
+    # to 2^-9 off and its probability 0.2 %, more than this test's 2e-3 on values up to 4.)
+    bias[1, 200::2] = round_to_storage(np.full((1,), -65504.0, dtype=np.float32), dtype)[0]
+    bias[1, 201::2] = 0.0
+    scale = -(D ** -0.5)
+    o_ref, lse_ref = attention_oracle(q, k, v, lens, scale, left, right, key_bias=bias)
+    for b, n in enumerate(lens):
+        for x in (q, k, v):
+            x[b, :, n:] = np.nan
+    o, lse = run_ex(q, k, v, lens, dtype, scale, left, right, tuning=fa.FA_TUNE_WIN_TWO_PHASE, key_bias=bias)
+    check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"two-phase bias D{D} {left}/{right}")
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_two_phase_kernel_with_key_bias_packed_and_many_tiles(D):
+    """The library's own choice on a call of more than 384 tiles, read from a packed QKV buffer: the bits of the dense call."""
+    B, H, N = 3, 12, 1409
+    lens = [1409, 700, 1280]
+    _, q, k, v = draw(4100, B, H, N, D, "bf16")
+    bias = round_to_storage(np.random.default_rng(2).standard_normal((B, N)).astype(np.float32), "bf16")
+    o, lse = run_ex(q, k, v, lens, "bf16", D ** -0.5, 63, 64, key_bias=bias)
+    sel = [0, 5, 11]
+    o_ref, lse_ref = attention_oracle(q[:, sel], k[:, sel], v[:, sel], lens, D ** -0.5, 63, 64, key_bias=bias)
+    check_against(o[:, sel], lse[:, sel], o_ref, lse_ref, lens, "bf16", relative=True, label=f"bias many tiles D{D}")
+    packed = torch.stack([to_dev(np.ascontiguousarray(x.transpose(0, 2, 1, 3)), "bf16") for x in (q, k, v)], dim=2)
+    st = (N * 3 * H * D, D, 3 * H * D)
+    o2 = poison((B, N, H, D), "bf16")
+    fa.fa_fwd_ex(dtype=FA_DT["bf16"], q=packed[:, :, 0], k=packed[:, :, 1], v=packed[:, :, 2], o=o2,
+                 seq_lens=torch.tensor(lens, dtype=torch.int32, device="cuda"), batch=B, heads=H, max_len=N, head_dim=D,
+                 scale=D ** -0.5, window_left=63, window_right=64, q_strides=st, k_strides=st, v_strides=st,
+                 o_strides=(N * H * D, D, H * D), key_bias=to_dev(bias, "bf16"))
+    torch.cuda.synchronize()
+    assert np.array_equal(o2.double().cpu().numpy().transpose(0, 2, 1, 3), o)
