@@ -510,9 +510,22 @@ __device__ __forceinline__ bool locate_tile(const FaKernelArgs& a, TileCoord& tc
     const int per = a.xcd_per;                // ceil(heads * n_qtiles / 8)
     tc.b = j / per;
     const int t = x * per + (j - tc.b * per);
-    if (tc.b >= a.batch || t >= a.heads * a.n_qtiles) return false;
-    tc.h = t / a.n_qtiles;
-    tc.qt = t - tc.h * a.n_qtiles;
+    if (tc.b >= a.batch || (!a.heads_first && t >= a.heads * a.n_qtiles)) return false;
+    if (a.heads_first) {
+      // all heads of a query tile in a row: the angle tables, or the lines that narrow heads share, are read once per XCD
+      int n = a.max_len;
+      if (a.seq_lens) {
+        n = a.seq_lens[tc.b];
+        n = n < 0 ? 0 : (n > a.max_len ? a.max_len : n);
+      }
+      const int u = fa_heads_first_tile(x, j - tc.b * per, per, (n + BM - 1) / BM * a.heads, a.heads * a.n_qtiles);
+      if (u < 0) return false;
+      tc.qt = u / a.heads;
+      tc.h = u - tc.qt * a.heads;
+    } else {
+      tc.h = t / a.n_qtiles;
+      tc.qt = t - tc.h * a.n_qtiles;
+    }
   } else {
     const int tile = blockIdx.x;
     if (tile >= a.total_tiles) return false;

@@ -119,3 +119,16 @@ inline int fa_mix_ids(int max_tiles, int H) {
   }
   return 8 * ((a_max + 7) / 8);
 }
+
+// Heads-first order of one batch element's tiles (number = query tile * heads + head): the workgroup that is number jb of
+// the `per` ids that XCD x has for this element.  The `live` tiles below the sequence length come first and are cut into
+// eighths by themselves - cut together with the padding, the XCDs with the late positions would hold padding only - and
+// the padding tiles go to the ids that are left, in XCD order.  -1: no tile for this id.
+FA_HD inline int fa_heads_first_tile(int x, int jb, int per, int live, int total) {
+  const int per_live = (live + 7) >> 3;
+  const int before = x * per_live < live ? x * per_live : live;            // live tiles of the XCDs before this one
+  const int mine = live - before < per_live ? live - before : per_live;    // and its own
+  if (jb < mine) return before + jb;
+  const int u = live + (x * per - before) + (jb - mine);
+  return u < total ? u : -1;
+}

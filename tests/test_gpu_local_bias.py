@@ -60,3 +60,30 @@ def test_two_phase_kernel_with_key_bias_packed_and_many_tiles(D):
                  o_strides=(N * H * D, D, H * D), key_bias=to_dev(bias, "bf16"))
     torch.cuda.synchronize()
     assert np.array_equal(o2.double().cpu().numpy().transpose(0, 2, 1, 3), o)
+
+
+@pytest.mark.parametrize("D,rope,N,lens", [(64, True, 6200, [6200, 1000]), (128, True, 6200, [0, 6150]), (32, True, 6200, None),
+                                           (32, False, 2100, [2100, 129]), (32, True, 2100, [1, 2000])])
+def test_heads_first_order_gives_the_bits_of_the_linear_order(D, rope, N, lens):
+    """Calls that hand out the heads of a query tile in a row (a rotation on a long local layer; heads of 32 side by side):
+    the same bits as with workgroup ids taken as tile numbers, every padded row zero."""
+    B, H = 2, 3
+    g = torch.Generator(device="cuda").manual_seed(N + D)
+    qkv = torch.randn((B, N, 3, H, D), generator=g, device="cuda").bfloat16()
+    ang = torch.arange(N, device="cuda", dtype=torch.float32)[:, None] * 10000.0 ** (-2.0 * torch.arange(D // 2, device="cuda") / D)
+    cos, sin = (ang.cos().contiguous(), ang.sin().contiguous()) if rope else (None, None)
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    st = (N * 3 * H * D, D, 3 * H * D)
+    got = []
+    for tuning in (0, fa.FA_TUNE_MAP_LINEAR):
+        o = poison((B, N, H, D), "bf16")
+        lse = torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda")
+        fa.fa_fwd_ex(dtype=FA_DT["bf16"], q=qkv[:, :, 0], k=qkv[:, :, 1], v=qkv[:, :, 2], o=o, lse=lse, seq_lens=sl, batch=B,
+                     heads=H, max_len=N, head_dim=D, scale=D ** -0.5, window_left=63, window_right=64, q_strides=st,
+                     k_strides=st, v_strides=st, o_strides=(N * H * D, D, H * D), rope_cos=cos, rope_sin=sin,
+                     tuning=tuning | fa.FA_TUNE_WIN_TWO_PHASE)
+        torch.cuda.synchronize()
+        got.append((o, lse))
+    assert not torch.isnan(got[0][0]).any() and torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    for b, n in enumerate(lens or []):
+        assert (got[0][0][b, n:] == 0).all() and torch.isneginf(got[0][1][b, :, n:]).all()

@@ -81,3 +81,47 @@ def test_split_shapes_chosen_by_the_host(tmp_path):
                     "-I", str(csrc), str(src), str(csrc / "fa_api.cpp"), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
+
+
+HEADS_FIRST_DRIVER = r"""
+#include <cstdio>
+#include <vector>
+#include "fa_mix_map.h"
+int main() {
+  long walks = 0;
+  for (int heads : {1, 3, 12, 24, 31})
+    for (int tiles = 1; tiles < 60; ++tiles)
+      for (int live_tiles = 0; live_tiles <= tiles; live_tiles += 1 + tiles / 9) {
+        const int total = heads * tiles, live = heads * live_tiles, per = (total + 7) / 8;
+        std::vector<int> seen(total, 0);
+        for (int x = 0; x < 8; ++x) {
+          int mine = 0;
+          for (int jb = 0; jb < per; ++jb) {
+            const int u = fa_heads_first_tile(x, jb, per, live, total);
+            if (u < -1 || u >= total) { printf("FAILED range %d\n", u); return 1; }
+            if (u >= 0) ++seen[u];
+            mine += u >= 0 && u < live;
+          }
+          if (mine > (live + 7) / 8) { printf("FAILED share %d of %d\n", mine, live); return 1; }
+        }
+        for (int u = 0; u < total; ++u)
+          if (seen[u] != 1) { printf("FAILED heads %d tiles %d live %d: tile %d seen %d times\n", heads, tiles, live_tiles, u, seen[u]); return 1; }
+        ++walks;
+      }
+  printf("ok %ld\n", walks);
+  return 0;
+}
+"""
+
+
+def test_heads_first_order_hands_out_every_tile_once(tmp_path):
+    """Every workgroup id of the heads-first order walked on the CPU: each tile once, and no XCD more than its eighth of
+    the tiles below the sequence length."""
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
+    src.write_text(HEADS_FIRST_DRIVER.replace("#include <vector>", "#include <initializer_list>\n#include <vector>"))
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-I",
+                    str(ROOT / "paper_2603_12646_amd" / "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
