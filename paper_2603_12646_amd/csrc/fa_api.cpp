@@ -122,11 +122,16 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
 // NK wavefronts that split the keys), or 0 where the other kernels are faster.  Its workgroups have a compute unit to
 // themselves (head_dim 32: half or a quarter of one), so a shape is taken only where the call fits the 256 units in one
 // round - a second, thin round costs as much as the first - and the fewest rows per workgroup that do fit are the
-// fastest.  Measured, fp16, 12 x 64 / 8 x 128 / 24 x 32, against the 128-row kernel (us per call):
+// fastest; behind these head_dim 64 has a shape of which three fit a unit.  Measured, fp16, 12 x 64 / 8 x 128 / 24 x 32,
+// against the 128-row kernel (us per call):
 //   head_dim 64   32 rows: 512 tokens 7.6 -> 6.2;  64 rows: 1024 13.6 -> 11.1, 1280 17.2 -> 11.8, 5 x 256 7.3 -> 6.6;
 //                 96 rows: 1400 18.9 -> 15.7, 2000 24.9 -> 20.3, but 3 x 450 9.7 -> 10.0 (short sequences do not repay
-//                 the merge of a 12-wavefront workgroup);  128 rows: 1900 of 2048 22.5 -> 21.3, 2304 27.5 -> 25.3, but
-//                 2 x 1024 15.1 -> 15.2, 4 x 400 9.2 -> 10.5.  (A round too many: 2 x 700 in 64 rows 18.2 against 12.0.)
+//                 the merge of a 12-wavefront workgroup);  128 rows: 1900 of 2048 22.5 -> 21.3, but 2 x 1024 15.1 -> 15.2,
+//                 4 x 400 9.2 -> 10.5.  (A round too many: 2 x 700 in 64 rows 18.2 against 12.0.)
+//                 64 rows on four wavefronts, three workgroups per unit: up to 768 of them; in particular where the
+//                 128-row kernel has one to one and a half workgroups per unit: 2500 30.1 -> 27.0, 2 x 1300 24.1 -> 17.2,
+//                 3072 50.3 -> 44.7, 4096 64.4 -> 62.2, 4 x 900 19.8 -> 18.7, 8 x 500 13.6 -> 13.1, but 6 x 450
+//                 13.0 -> 13.3, 5 x 400 9.3 -> 10.5; 2 x 1024 15.0 -> 13.8, 3 x 700 12.3 -> 12.1, but 3 x 600 10.7 -> 11.1.
 //                 At 64 tokens there is nothing to split: 5.3 -> 5.7.
 //                 With a key bias, whose pipelined kernel is slower, the lines lie lower: 3 x 450 11.5 -> 10.4,
 //                 3 x 600 13.9 -> 13.0, 4 x 400 10.8 -> 11.4.
@@ -143,7 +148,9 @@ int choose_split(const fa_params& p) {
   if (p.head_dim == 64) {
     if (tiles(64) <= 256) return tiles(32) <= 256 && p.max_len > 128 ? 0x18 : 0x24;
     if (tiles(96) <= 256 && p.max_len >= (bias ? 448 : 640)) return 0x34;
-    if (tiles(128) <= 256 && p.max_len >= (bias ? 512 : 1536)) return 0x42;
+    if (bias) return tiles(128) <= 256 && p.max_len >= 512 ? 0x42 : 0;
+    if (tiles(128) <= 192 && p.max_len >= 1536) return 0x42;
+    if (tiles(64) <= 768 && p.max_len >= (tiles(128) <= 256 ? 704 : 480)) return 0x22;
   } else if (p.head_dim == 128) {
     if (tiles(64) <= 256) return tiles(32) <= 256 ? 0x14 : 0x24;
     if (tiles(128) <= 256 && p.max_len >= (bias ? 256 : 640)) return 0x42;

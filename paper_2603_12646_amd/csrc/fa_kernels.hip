@@ -1871,7 +1871,7 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
     // The steady part, P steps per turn: ring slots are compile-time constants, the row bases of the requested blocks
     // just advance, and the wait is one instruction (the pairs under way all hold K and V).  Step i requests pair
     // i + P - 2, whose K of step i + P lies inside the full super tiles.
-    if (P == 4 && i + 2 * P - 1 < nfs && pairs == P - 1) {
+    if ((P == 2 || P == 4) && i + 2 * P - 1 < nfs && pairs == P - 1) {
       const int64_t kstep = (int64_t)(32 * NK) * a.ks[2], vstep = (int64_t)(32 * NK) * a.vs[2];
       const uint16_t* kg = kp + (int64_t)(32 * g) * a.ks[2] + (P + 1) * kstep;
       const uint16_t* vg = vp + (int64_t)(32 * g) * a.vs[2] + (P - 1) * vstep;
@@ -1895,9 +1895,11 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
       };
       for (; i + 2 * P - 1 < nfs; i += P) {
         steady(std::integral_constant<int, 1>{}, sB, sA, pA, pB, i);
-        steady(std::integral_constant<int, 2>{}, sA, sB, pB, pA, i + 1);
-        steady(std::integral_constant<int, 3>{}, sB, sA, pA, pB, i + 2);
-        steady(std::integral_constant<int, 0>{}, sA, sB, pB, pA, i + 3);
+        steady(std::integral_constant<int, 2 % P>{}, sA, sB, pB, pA, i + 1);
+        if (P == 4) {
+          steady(std::integral_constant<int, 3 % P>{}, sB, sA, pA, pB, i + 2);
+          steady(std::integral_constant<int, 0>{}, sA, sB, pB, pA, i + 3);
+        }
       }
       pairs = i + P - 2;
     }
@@ -2569,6 +2571,8 @@ Kernel split_kernel(int head_dim, int split) {
     case 64 * 256 + 0x24: return fa_fwd_split_kernel<T, 64, 2, 4, 4, 2, BIAS>;
     case 64 * 256 + 0x34: return fa_fwd_split_kernel<T, 64, 3, 4, BIAS ? 3 : 4, 3, BIAS>;
     case 64 * 256 + 0x42: return fa_fwd_split_kernel<T, 64, 4, 2, 4, 2, BIAS>;
+    // (three workgroups per unit; without a key bias only: with one its LDS would allow two)
+    case 64 * 256 + 0x22: return BIAS ? nullptr : (Kernel)fa_fwd_split_kernel<T, 64, 2, 2, 2, 3, false>;
     case 128 * 256 + 0x14: return fa_fwd_split_kernel<T, 128, 1, 4, 2, 1, BIAS>;
     case 128 * 256 + 0x24: return fa_fwd_split_kernel<T, 128, 2, 4, 2, 2, BIAS>;
     case 128 * 256 + 0x42: return fa_fwd_split_kernel<T, 128, 4, 2, BIAS ? 2 : 4, 2, BIAS>;

@@ -23,6 +23,8 @@ CASES = {
     "d64_3x4": (64, 15, 700, [700, 641], False),
     "d64_3x4_other": (64, 30, 690, [97], False),
     "d64_4x2": (64, 19, 1601, [1537], False),
+    "d64_2x2": (64, 35, 500, [500, 333], False),
+    "d64_2x2_streaming": (64, 12, 2210, [2177], False),
     "d128_1x4": (128, 2, 300, [300, 129, 128, 1], False),
     "d128_2x4": (128, 30, 200, [200, 63], False),
     "d128_4x2": (128, 15, 700, [700, 577], False),

@@ -46,10 +46,10 @@ int main() {
             if (last.split) {
               ++taken;
               const int nq = last.split >> 4, s = last.split;
-              EXPECT(d == 64 ? (s == 0x18 || s == 0x24 || s == 0x34 || s == 0x42)
+              EXPECT(d == 64 ? (s == 0x18 || s == 0x24 || s == 0x34 || s == 0x42 || (s == 0x22 && !biased))
                              : (d == 128 ? (s == 0x14 || s == 0x24 || s == 0x42) : (s == 0x14 || s == 0x22)));
               EXPECT(last_bm == 32 * nq && last.n_qtiles == (n + 32 * nq - 1) / (32 * nq));
-              EXPECT(last.total_tiles == last.n_qtiles * b * h && last.total_tiles <= (d == 32 ? 768 : 256));
+              EXPECT(last.total_tiles == last.n_qtiles * b * h && last.total_tiles <= (d == 32 || s == 0x22 ? 768 : 256));
               EXPECT(!biased || n <= kSplitBiasKeys);
             }
             p.window_left = 63; p.window_right = 64;
