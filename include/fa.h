@@ -146,10 +146,10 @@ typedef struct fa_params {
      key_bias[b, j] is added to scale * q_i.k_j for every head and query (it is not
      multiplied by scale); -infinity excludes key j, so any key mask can be expressed,
      and the paper's -65504 on padded keys works as written.  It applies on top of
-     seq_lens and the window.  2-byte alignment.  Global layers of head_dim 64 / 128
-     and the resident local-layer kernel keep their pipelines (the bias enters through
-     the score product's accumulator input); wider or one-sided windows, head_dim 32
-     and scale == 0 take the general (masked) kernel. */
+     seq_lens and the window.  2-byte alignment.  Global layers and
+     narrow two-sided windows (the local layers' 63 / 64) keep their pipelines (the bias enters through
+     the score product's accumulator input); wider or one-sided windows and scale == 0 take the
+     general (masked) kernel. */
   const void* key_bias;
   int64_t key_bias_stride; /* elements between batch rows; 0 = max_len; >= max_len */
   /* Rotary position embedding of q and k inside the call (the paper's classifier uses rotary

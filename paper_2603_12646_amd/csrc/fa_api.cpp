@@ -282,7 +282,7 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
     bm = shape_cost(w256, 1, 8, 1.0) < shape_cost(w128, 2, 4, 1.03) ? 256 : 128;
     if (t_bm == FA_TUNE_BM_128) bm = 128;
     if (t_bm == FA_TUNE_BM_256) bm = 256;
-  } else if (p->head_dim == 32 && !windowed && !p->key_bias && t_v != FA_TUNE_V_SCALAR) {
+  } else if (p->head_dim == 32 && !windowed && !bias_on_masked_kernel && t_v != FA_TUNE_V_SCALAR) {
     // head_dim 32 global layers: the pipelined kernel in its 128- and 256-row shapes, chosen by
     // the same fill model (it matches a sweep of 1K-32K tokens x 8-24 heads to within 1 %)
     bm = choose_bm(*p, false);

@@ -47,9 +47,12 @@
 //       SIMDs with one wavefront or none (a single request, a few short sequences): NQ query
 //       blocks per workgroup, each shared by NK wavefronts that split the KEYS and merge their
 //       partial results through LDS.
+//   fa_fwd_window_twophase_kernel  local layers with a narrow two-sided window: K, then V, through one
+//       LDS region; also with a key bias or a rotation.
 //   fa_fwd_masked_kernel  general path (register staging, padded tiles, optional 16-bit V
-//       reads) for head_dim 32, 64, 128: the production path of head_dim 32 and of the local
-//       layers of head_dim 128, and at head_dim 64 an independent implementation for the tests.
+//       reads) for head_dim 32, 64, 128: the production path of wide or one-sided windows of
+//       head_dim 32 / 128 and of a key bias outside the pipelined cases; at head_dim 64 also an
+//       independent implementation for the tests.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -2621,9 +2624,10 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
       win_blocks <= kResBlocks) {
     // additive key bias on a local layer whose key range stays resident in LDS
     kern = fa_fwd_window_resident_kernel<T, true>;
-  } else if (a.key_bias && !rope && global && v_path == 0 && a.c > 0.f && (a.head_dim == 64 || a.head_dim == 128)) {
+  } else if (a.key_bias && !rope && global && v_path == 0 && a.c > 0.f) {
     // additive key bias on a global layer: the pipelined kernel with the bias as MFMA C operand
-    if (a.head_dim == 128) kern = fa_fwd_global_kernel<T, 128, 1, 4, true>;
+    if (a.head_dim == 32) kern = bm == 256 ? fa_fwd_global_kernel<T, 32, 2, 4, true> : fa_fwd_global_kernel<T, 32, 1, 4, true>;
+    else if (a.head_dim == 128) kern = fa_fwd_global_kernel<T, 128, 1, 4, true>;
     else if (bm == 256) kern = fa_fwd_global_kernel<T, 64, 2, 4, true>;
     else kern = fa_fwd_global_kernel<T, 64, 1, 4, true>;
   } else if (a.key_bias) {

@@ -81,3 +81,22 @@ def test_split_kernel_packed_qkv(D):
     torch.cuda.synchronize()
     assert np.array_equal(o2.double().cpu().numpy().transpose(0, 2, 1, 3), o)
     assert np.array_equal(lse2.double().cpu().numpy(), lse)
+
+
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("N", [1, 33, 64, 65, 129, 640])
+def test_key_bias_pipelined_kernel_head_dim_32(N, dtype, tuning):
+    """The pipelined global kernel with a key bias at head_dim 32, in both tile shapes, on lengths around its 64-key tiles."""
+    B, H, D = 2, 3, 32
+    lens = [N, max(1, N - 40)]
+    rng = np.random.default_rng(N)
+    _, q, k, v = draw(8000 + N, B, H, N, D, dtype)
+    bias = round_to_storage(rng.standard_normal((B, N)).astype(np.float32), dtype)
+    bias[0, : N // 3] = -np.inf
+    o_ref, lse_ref = attention_oracle(q, k, v, lens, 0.2, key_bias=bias)
+    for b, n in enumerate(lens):
+        for x in (q, k, v):
+            x[b, :, n:] = np.nan
+    o, lse = run_ex(q, k, v, lens, dtype, 0.2, key_bias=bias, tuning=tuning)
+    check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"bias d32 {N}")
