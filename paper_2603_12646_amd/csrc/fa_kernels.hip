@@ -502,7 +502,9 @@ struct TileCoord {
 
 // CLAMP = false leaves tc.n as loaded (the caller clamps it into [0, max_len] when it first
 // needs it, so that the wait for the load can come after other work).
-template <int BM, bool CLAMP = true>
+// HEADS_FIRST: the kernel also knows the heads-first order (a.heads_first); the others keep the query tiles of one head in
+// a row, which is an order of the same tiles.
+template <int BM, bool CLAMP = true, bool HEADS_FIRST = false>
 __device__ __forceinline__ bool locate_tile(const FaKernelArgs& a, TileCoord& tc) {
   if (a.map_xcd) {
     // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  Tiles of
@@ -513,8 +515,9 @@ __device__ __forceinline__ bool locate_tile(const FaKernelArgs& a, TileCoord& tc
     const int per = a.xcd_per;                // ceil(heads * n_qtiles / 8)
     tc.b = j / per;
     const int t = x * per + (j - tc.b * per);
-    if (tc.b >= a.batch || (!a.heads_first && t >= a.heads * a.n_qtiles)) return false;
-    if (a.heads_first) {
+    const bool heads_first = HEADS_FIRST && a.heads_first;
+    if (tc.b >= a.batch || (!heads_first && t >= a.heads * a.n_qtiles)) return false;
+    if (heads_first) {
       // all heads of a query tile in a row: the angle tables, or the lines that narrow heads share, are read once per XCD
       int n = a.max_len;
       if (a.seq_lens) {
@@ -1257,7 +1260,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
   __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? kResBlocks * 32 : 4];
 
   TileCoord tc;
-  if (!locate_tile<BM, false>(a, tc)) return;  // tc.n still as loaded: see below
+  if (!locate_tile<BM, false, ROPE || D == 32>(a, tc)) return;  // tc.n still as loaded: see below
   const int N = a.max_len, q0 = tc.q0;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
