@@ -258,9 +258,11 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
     }
   }
 
-  // a key bias runs 128-row kernels only unless it can ride on the pipelined global kernel
+  // a key bias runs 128-row kernels only unless it can ride on the pipelined global kernel, which has no variant that
+  // also rotates (a rotation done ahead of the call is gone from p by now)
   const bool windowed = p->window_left >= 0 || p->window_right >= 0;
-  const bool bias_on_masked_kernel = p->key_bias && (windowed || p->scale == 0.0f || (p->tuning & 0xF0u) == FA_TUNE_V_SCALAR);
+  const bool bias_on_masked_kernel =
+      p->key_bias && (windowed || p->rope_cos || p->scale == 0.0f || (p->tuning & 0xF0u) == FA_TUNE_V_SCALAR);
   int bm = 128;
   if (p->head_dim == 64 && !bias_on_masked_kernel) {
     // 384 (12 wavefronts x 32 rows), 512 (8 wavefronts x 64 rows) and the mixed launch exist for

@@ -2606,6 +2606,7 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
   const int wave_blocks = (a.wl >= 0 && a.wr >= 0) ? (31 + a.wr) / 32 + (a.wl + 31) / 32 + 1 : 1 << 30;
   Kernel kern = nullptr;
   unsigned threads = kThreads;
+  int rows = 128;   // query rows per workgroup of the kernel chosen below: what the grid has to be made for
   // rotary embedding is applied by the two-phase window kernel, the pipelined global kernel
   // (four-wavefront shapes) and the masked kernel
   const bool rope = a.rope_cos != nullptr;
@@ -2619,6 +2620,7 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     // (the host has checked that this shape exists for the head size)
     kern = a.key_bias ? split_kernel<T, true>(a.head_dim, a.split) : split_kernel<T, false>(a.head_dim, a.split);
     threads = 64u * (unsigned)((a.split >> 4) * (a.split & 15));
+    rows = 32 * (a.split >> 4);
     if (!kern) return (int)hipErrorInvalidValue;
   } else
   if (!(a.key_bias && (rope || !(a.c > 0.f))) && !global && v_path == 0 && bm == 128 && slice_fits_32bit &&
@@ -2633,9 +2635,10 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     kern = fa_fwd_window_resident_kernel<T, true>;
   } else if (a.key_bias && !rope && global && v_path == 0 && a.c > 0.f) {
     // additive key bias on a global layer: the pipelined kernel with the bias as MFMA C operand
-    if (a.head_dim == 32) kern = bm == 256 ? fa_fwd_global_kernel<T, 32, 2, 4, true> : fa_fwd_global_kernel<T, 32, 1, 4, true>;
+    if (bm == 256 && a.head_dim != 128) rows = 256;
+    if (a.head_dim == 32) kern = rows == 256 ? fa_fwd_global_kernel<T, 32, 2, 4, true> : fa_fwd_global_kernel<T, 32, 1, 4, true>;
     else if (a.head_dim == 128) kern = fa_fwd_global_kernel<T, 128, 1, 4, true>;
-    else if (bm == 256) kern = fa_fwd_global_kernel<T, 64, 2, 4, true>;
+    else if (rows == 256) kern = fa_fwd_global_kernel<T, 64, 2, 4, true>;
     else kern = fa_fwd_global_kernel<T, 64, 1, 4, true>;
   } else if (a.key_bias) {
     // additive key bias otherwise: the masked kernel, 128-row tiles, any head_dim and window
@@ -2644,24 +2647,28 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     else kern = fa_fwd_masked_kernel<T, 128, 1, true, true>;
   } else if (rope && global && v_path == 0) {
     // rotation on a global layer: the pipelined kernel's four-wavefront shapes
+    if (bm == 256 && a.head_dim != 128) rows = 256;
     if (a.head_dim == 128) kern = fa_fwd_global_kernel<T, 128, 1, 4, false, true>;
-    else if (a.head_dim == 32) kern = bm == 256 ? fa_fwd_global_kernel<T, 32, 2, 4, false, true> : fa_fwd_global_kernel<T, 32, 1, 4, false, true>;
-    else kern = bm == 256 ? fa_fwd_global_kernel<T, 64, 2, 4, false, true> : fa_fwd_global_kernel<T, 64, 1, 4, false, true>;
+    else if (a.head_dim == 32) kern = rows == 256 ? fa_fwd_global_kernel<T, 32, 2, 4, false, true> : fa_fwd_global_kernel<T, 32, 1, 4, false, true>;
+    else kern = rows == 256 ? fa_fwd_global_kernel<T, 64, 2, 4, false, true> : fa_fwd_global_kernel<T, 64, 1, 4, false, true>;
   } else if (a.head_dim == 128 && global && v_path == 0) {
     if (bm == 256) {
       kern = fa_fwd_global_kernel<T, 128, 1, 8>;   // eight wavefronts on one pair of K/V stages
       threads = 512;
+      rows = 256;
     } else {
       kern = fa_fwd_global_kernel<T, 128, 1, 4>;
     }
   } else if (a.head_dim == 32 && global && v_path == 0) {
-    kern = bm == 256 ? fa_fwd_global_kernel<T, 32, 2, 4> : fa_fwd_global_kernel<T, 32, 1, 4>;
+    if (bm == 256) rows = 256;
+    kern = rows == 256 ? fa_fwd_global_kernel<T, 32, 2, 4> : fa_fwd_global_kernel<T, 32, 1, 4>;
   } else if (a.head_dim != kD) {
     // wide or one-sided windows of head_dim 32 / 128 (and the 16-bit V-read path): the masked
     // kernel covers every mask; bm is 128 here
     if (a.head_dim == 32) kern = v_path == 0 ? fa_fwd_masked_kernel<T, 32, 1, true> : fa_fwd_masked_kernel<T, 32, 1, false>;
     else kern = v_path == 0 ? fa_fwd_masked_kernel<T, 128, 1, true> : fa_fwd_masked_kernel<T, 128, 1, false>;
   } else if (global && v_path == 0) {
+    rows = bm;
     if (bm == 0) {
       kern = fa_fwd_global_mixed_kernel<T>;
     } else if (bm == 512) {
@@ -2674,14 +2681,17 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
       kern = fa_fwd_global_kernel<T, 64, 2, 4>;
     } else {
       kern = fa_fwd_global_kernel<T, 64, 1, 4>;
+      rows = 128;
     }
   } else if (!global && !rope && v_path == 0 && bm == 128 && slice_fits_32bit) {
     kern = win_blocks <= kResBlocks ? fa_fwd_window_resident_kernel<T> : fa_fwd_window_kernel<T>;
   } else if (bm == 256) {
+    rows = 256;
     kern = v_path == 0 ? fa_fwd_masked_kernel<T, 64, 2, true> : fa_fwd_masked_kernel<T, 64, 2, false>;
   } else {
     kern = v_path == 0 ? fa_fwd_masked_kernel<T, 64, 1, true> : fa_fwd_masked_kernel<T, 64, 1, false>;
   }
+  if (rows != bm) return (int)hipErrorInvalidValue;   // the grid is made of tiles of another size
   // hipLaunchKernel returns THIS launch's status; an error left by the caller's earlier HIP
   // work stays where it is (neither reported as ours nor cleared)
   FaKernelArgs args = a;

@@ -119,6 +119,21 @@ def test_rope_with_key_bias():
             check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"rope+bias {dtype} ({left},{right})")
 
 
+@pytest.mark.parametrize("D,H,N,tuning", [(32, 2, 700, fa.FA_TUNE_BM_256), (64, 2, 700, fa.FA_TUNE_BM_256), (128, 2, 700, fa.FA_TUNE_BM_256),
+                                          (32, 24, 2900, 0), (64, 24, 2900, 0)])
+def test_rope_with_key_bias_writes_every_row(D, H, N, tuning):
+    """Key bias and in-call rotation without scratch, where the size or the forced shape asks for 256-row tiles: the masked
+    kernel runs, in 128-row tiles, and no row of the poisoned outputs keeps what it held."""
+    _, q, k, v = draw(9450 + D, 1, H, N, D, "fp16")
+    bias = round_to_storage(np.random.default_rng(9450).standard_normal((1, N)).astype(np.float32), "fp16")
+    c32, s32, c64, s64 = tables(N, D)
+    o, lse = run_rope(q, k, v, None, "fp16", D ** -0.5, c32, s32, key_bias=bias, tuning=tuning)
+    assert not np.isnan(o).any() and not np.isnan(lse).any()
+    h = H - 1
+    o_ref, lse_ref = attention_oracle_rope(q[:, h:], k[:, h:], v[:, h:], c64, s64, "fp16", None, D ** -0.5, key_bias=bias)
+    check_against(o[:, h:], lse[:, h:], o_ref, lse_ref, None, "fp16", relative=True, label=f"rope+bias rows D{D}")
+
+
 @pytest.mark.parametrize("name", ["c3_8k", "c5b_32k_local", "c4_16k_x3"])
 def test_rope_named_workloads_sampled_rows(name):
     """Full-size launches of the 8K global, 32K local and 3 x 16K workloads with a rotation
