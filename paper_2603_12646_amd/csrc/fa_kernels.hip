@@ -1584,9 +1584,15 @@ struct SplitWave {
   RowState<1, D> st;
   typename T::v8 q[KS];
   uint32_t kfo[KS], vfo[DB];   // per-lane operand offsets (16-bit elements) into a swizzled 32-row block
+  // A block sum above this refreshes the row's reference: kPLimit, or -1 while the row has none (its blocks so far held
+  // no score above -infinity), so that the first block with a score always sets it.  A register in place of a constant:
+  // the test costs what it did without.
+  float sum_limit;
 
+  __device__ __forceinline__ void set_limit() { sum_limit = st.m_ref[0] == -INFINITY ? -1.f : kPLimit; }
   __device__ __forceinline__ void init(int lane) {
     init_state(st);
+    set_limit();
     const int l32 = lane & 31, hh = lane >> 5, p16 = lane & 15, gg = (lane >> 4) & 1, row = 4 * hh + (p16 >> 2);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) kfo[ks] = l32 * D + (((2 * ks + hh) ^ k_swz_d<D>(l32)) * 8);
@@ -1632,20 +1638,21 @@ struct SplitWave {
     for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, keep_or_neg_inf(s[r], vis, r));
     st.m_ref[0] = max_xor32(t0);
     st.mc[0] = st.m_ref[0] == -INFINITY ? 0.f : st.m_ref[0] * c;
+    set_limit();
   }
   template <bool MASKED>
   __device__ __forceinline__ void softmax(const floatx16& s, typename T::v8 (&p)[2], uint32_t vis, bool alive, float c) {
     uint32_t pk[8];
     float blk;
     prob_block<T, MASKED>(s, c, st.mc[0], vis, pk, blk);
-    // !(blk <= limit) also catches a NaN sum; with a bias the first blocks can be excluded entirely
-    const bool trig = alive && (!(blk <= kPLimit) || (BIAS && st.m_ref[0] == -INFINITY));
+    const bool trig = alive && !(blk <= sum_limit);   // (also catches a NaN sum)
     if (__any(trig)) {
       const bool row_trig = sum_xor32(trig ? 1.f : 0.f) > 0.f;   // a row refreshes on its own two lanes' evidence only
       float t0 = -INFINITY;
 #pragma unroll
       for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, MASKED ? keep_or_neg_inf(s[r], vis, r) : s[r]);
       rescale_rows(st, 0, row_trig, max_xor32(t0), c);
+      set_limit();
       prob_block<T, MASKED>(s, c, st.mc[0], vis, pk, blk);
     }
     st.lsum[0] += blk;
@@ -1981,7 +1988,8 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   const float mc_new = m_new == -INFINITY ? 0.f : m_new * c;
 #pragma unroll
   for (int x = 0; x < NK; ++x) {
-    // a wavefront that saw no key has nothing accumulated: factor 0, kept away from exp2(+inf)
+    // a wavefront that saw no key has nothing accumulated (the first score sets a reference): factor 0, kept away from
+    // exp2(+inf)
     fk[x] = mk[x] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk[x] * c - mc_new);
     ltot = __builtin_fmaf(fk[x], state[(2 * x + 1) * 64], ltot);
   }

@@ -100,3 +100,29 @@ def test_key_bias_pipelined_kernel_head_dim_32(N, dtype, tuning):
             x[b, :, n:] = np.nan
     o, lse = run_ex(q, k, v, lens, dtype, 0.2, key_bias=bias, tuning=tuning)
     check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"bias d32 {N}")
+
+
+# one call per shape the library picks without a key bias, more than one block per wavefront
+SHAPES = {"d64_1x8": (64, 1, 600), "d64_2x4": (64, 12, 1001), "d64_3x4": (64, 12, 1500), "d64_2x2": (64, 12, 2500),
+          "d128_1x4": (128, 2, 600), "d128_2x4": (128, 8, 1500), "d128_4x2": (128, 8, 2600), "d32_1x4": (32, 24, 600),
+          "d32_2x2": (32, 24, 1500)}
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_split_kernel_first_block_without_a_finite_score(name, dtype):
+    """Keys whose scores are -infinity fill the first block of one wavefront after the other: it takes its reference from a
+    later block, and the keys of that block count - also where they are all so far below 0 that they vanish against 0."""
+    D, H, N = SHAPES[name]
+    _, q, k, v = draw(7200 + N, 1, 1, N, D, dtype)
+    rep = lambda x: np.repeat(x, H, axis=1)
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    for g, shift in ((0, 0.0), (1, -40.0), (0, 40.0), (7, -40.0), (2, 0.0)):
+        q2, k2 = q.copy(), k.copy()
+        q2[..., 1], k2[..., 1] = 40.0, shift          # every score moved by 40 * shift * scale
+        k2[..., 32 * g: 32 * g + 32, 0] = -np.inf
+        o_ref, lse_ref = attention_oracle(q2, k2, v, None, D ** -0.5)
+        o, lse = run_ex(rep(q2), rep(k2), rep(v), None, dtype, D ** -0.5)
+        check_against(o[:, :1], lse[:, :1], o_ref, lse_ref, None, dtype, label=f"{name} block {g} shift {shift}")
+        assert (o == o[:, :1]).all() and (lse == lse[:, :1]).all()
