@@ -1965,10 +1965,13 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   // group x to wavefront x % NK, which finishes it
   constexpr int G = 4 * DB;
   float4* const part = (float4*)lds + (size_t)qb * (NK - 1) * G * 64 + lane;       // [group][contributor][lane]
-  float* const state = (float*)(lds + L::kPart) + (size_t)qb * NK * 2 * 64 + lane; // [wavefront][reference, sum][lane]
+  // [wavefront][reference times c, sum][lane].  The reference goes through as the rounded product the probabilities were
+  // formed against (-infinity: none); forming it again here would let the compiler fuse it into the subtraction below,
+  // unrounded, and put a wavefront's share off by 2^(half a spacing of it) - 4 % at scores of 10^6
+  float* const state = (float*)(lds + L::kPart) + (size_t)qb * NK * 2 * 64 + lane;
   uint16_t* const patch = lds + L::kPart + L::kState + qb * epi_patch(D);
   constexpr int kEpiStride = epi_stride(D);
-  state[(2 * g + 0) * 64] = w.st.m_ref[0];
+  state[(2 * g + 0) * 64] = w.st.m_ref[0] == -INFINITY ? -INFINITY : w.st.mc[0];
   state[(2 * g + 1) * 64] = w.st.lsum[0];
 #pragma unroll
   for (int x = 0; x < G; ++x) {
@@ -1979,18 +1982,18 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
     }
   }
   __syncthreads();
-  float mk[NK], m_new = -INFINITY, fk[NK], ltot = 0.f;
+  float mk[NK], mc_new = -INFINITY, fk[NK], ltot = 0.f;
 #pragma unroll
   for (int x = 0; x < NK; ++x) {
     mk[x] = state[(2 * x + 0) * 64];
-    m_new = fmaxf(m_new, mk[x]);
+    mc_new = fmaxf(mc_new, mk[x]);
   }
-  const float mc_new = m_new == -INFINITY ? 0.f : m_new * c;
+  if (mc_new == -INFINITY) mc_new = 0.f;
 #pragma unroll
   for (int x = 0; x < NK; ++x) {
     // a wavefront that saw no key has nothing accumulated (the first score sets a reference): factor 0, kept away from
     // exp2(+inf)
-    fk[x] = mk[x] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk[x] * c - mc_new);
+    fk[x] = mk[x] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk[x] - mc_new);
     ltot = __builtin_fmaf(fk[x], state[(2 * x + 1) * 64], ltot);
   }
   ltot = sum_xor32(ltot);

@@ -126,3 +126,26 @@ def test_split_kernel_first_block_without_a_finite_score(name, dtype):
         o, lse = run_ex(rep(q2), rep(k2), rep(v), None, dtype, D ** -0.5)
         check_against(o[:, :1], lse[:, :1], o_ref, lse_ref, None, dtype, label=f"{name} block {g} shift {shift}")
         assert (o == o[:, :1]).all() and (lse == lse[:, :1]).all()
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_split_kernel_merge_of_large_references(name, dtype):
+    """Wavefronts whose references are large and differ: scores 1024000 + g / 8 in the blocks of number g mod 8, exact in
+    fp32.  The probabilities of a wavefront are formed against its reference times log2(e) ROUNDED to fp32 (spacing 1/8
+    here), so the merge has to weigh them against that same number; against the unrounded product a wavefront's share is
+    up to 2^(1/16), 4 %, off.  Values are +1 and -1 by g's parity: a share that is off shows in o in full."""
+    D, H, N = SHAPES[name]
+    g = np.arange(N) // 32 % 8
+    q = np.zeros((1, H, N, D), np.float32)
+    k = np.zeros((1, H, N, D), np.float32)
+    q[..., 0], q[..., 1] = 1024.0, 1.0
+    k[..., 0], k[..., 1] = 1000.0, g / 8
+    v = np.zeros((1, H, N, D), np.float32)
+    v[...] = np.where(g % 2 == 0, 1.0, -1.0)[:, None]
+    w = np.exp(g / 8.0)
+    want = (w * np.where(g % 2 == 0, 1.0, -1.0)).sum() / w.sum()
+    o, lse = run_ex(q, k, v, None, dtype, 1.0)
+    # a probability is rounded to 2^-12 (fp16) or 2^-9 (bf16) of itself, o likewise
+    assert np.abs(o - want).max() <= (2.0 ** -11 if dtype == "fp16" else 2.0 ** -8), np.abs(o - want).max()
+    assert np.abs(lse - (1024000.0 + np.log(w.sum()))).max() <= 0.5   # eight fp32 spacings there
