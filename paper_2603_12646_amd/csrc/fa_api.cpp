@@ -261,8 +261,12 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   // a key bias runs 128-row kernels only unless it can ride on the pipelined global kernel, which has no variant that
   // also rotates (a rotation done ahead of the call is gone from p by now)
   const bool windowed = p->window_left >= 0 || p->window_right >= 0;
+  // The pipelined kernels hold a key's bias divided by |scale|.  Below |scale| = 2e-34 that leaves the range of fp32 for
+  // biases that 16-bit types can hold (and 0 / |scale| is 0 * infinity); the masked kernel never divides.
+  const float inv_abs_scale = p->scale != 0.0f ? 1.0f / std::fabs(p->scale) : 0.0f;
+  const bool bias_can_be_divided = p->scale != 0.0f && std::isfinite(65504.0f * inv_abs_scale);
   const bool bias_on_masked_kernel =
-      p->key_bias && (windowed || p->rope_cos || p->scale == 0.0f || (p->tuning & 0xF0u) == FA_TUNE_V_SCALAR);
+      p->key_bias && (windowed || p->rope_cos || !bias_can_be_divided || (p->tuning & 0xF0u) == FA_TUNE_V_SCALAR);
   int bm = 128;
   if (p->head_dim == 64 && !bias_on_masked_kernel) {
     // 384 (12 wavefronts x 32 rows), 512 (8 wavefronts x 64 rows) and the mixed launch exist for
@@ -311,7 +315,9 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   a.batch = p->batch; a.heads = p->heads; a.max_len = p->max_len; a.head_dim = p->head_dim;
   a.key_bias = p->key_bias;
   a.kb_stride = p->key_bias_stride ? p->key_bias_stride : p->max_len;
-  a.inv_abs_scale = p->scale != 0.0f ? 1.0f / std::fabs(p->scale) : 0.0f;
+  // (bfloat16 biases near the type's largest: the factor log2(e), under which they are infinite, before the division)
+  a.bias_pre = p->dtype == FA_DTYPE_BF16 && std::fabs(p->scale) > 0.6931f ? kLog2e : 1.0f;
+  a.inv_abs_scale = bias_can_be_divided ? inv_abs_scale / a.bias_pre : 0.0f;
   a.rope_cos = p->rope_cos;
   a.rope_sin = p->rope_sin;
   a.rope_stride = p->rope_stride ? p->rope_stride : p->head_dim / 2;

@@ -13,7 +13,8 @@ struct FaKernelArgs {
   const int32_t* seq_lens;  // device, may be null
   const void* key_bias;     // device, [batch][kb_stride] 16-bit values, may be null
   int64_t kb_stride;        // elements between batch rows of key_bias
-  float inv_abs_scale;      // 1 / |scale| (0 when scale is 0): key bias in raw-score units
+  float bias_pre;           // factor taken before inv_abs_scale: 1, or log2(e) (bfloat16, |scale| > ln 2)
+  float inv_abs_scale;      // 1 / (|scale| bias_pre): key bias in raw-score units (0: not to be divided, masked kernel)
   const float* rope_cos;    // device, [max_len][rope_stride] fp32 tables, or null: q and k are rotated
   const float* rope_sin;    // by position (pairs (f, f + head_dim/2)) and rounded to 16 bits first
   int64_t rope_stride;      // floats between table rows (>= head_dim / 2, multiple of 4)

@@ -93,6 +93,7 @@ constexpr float kPLimit = 16384.f;
 struct F16 {
   typedef half8 v8;
   static constexpr bool kSumRounded = true;
+  static constexpr bool kWideRange = false;   // its values times any factor below 2^112 are finite fp32 numbers
   static __device__ __forceinline__ floatx16 mfma(v8 a, v8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
@@ -118,6 +119,7 @@ struct F16 {
 struct BF16 {
   typedef bf8 v8;
   static constexpr bool kSumRounded = false;
+  static constexpr bool kWideRange = true;
   static __device__ __forceinline__ floatx16 mfma(v8 a, v8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
@@ -493,6 +495,22 @@ __device__ __forceinline__ void simple_block(RowState<NQB, D>& st, const typenam
       }
     }
   }
+}
+
+// A key's bias in raw-score units.  The host sends no call here whose |scale| is too small for this (inv_abs_scale = 0 then).
+// bfloat16 holds biases whose product with log2(e) is no finite fp32 number: infinite ones then (a key excluded, as in the
+// masked kernel).  A reference of such a bias that is finite while its product with c = |scale| log2(e) is not would turn
+// rows into NaN, so where |scale| > ln 2 the factor log2(e) comes first (bias_pre; 1 elsewhere, where the largest fp32
+// number times c is finite).  SATURATE: below |scale| = ln 2 a quotient past the largest fp32 number stops there instead of
+// excluding the key, as the masked kernel has it; for kernels that convert each bias once, or ran the masked kernel's
+// values before (in the loop of the pipelined kernel it takes wavefront 0 1-3 % of a short call).
+template <class T, bool SATURATE>
+__device__ __forceinline__ float bias_over_scale(const FaKernelArgs& a, uint16_t bits) {
+  const float b = T::to_float(bits);
+  if (!T::kWideRange) return b * a.inv_abs_scale;
+  const float x = b * a.bias_pre * a.inv_abs_scale;
+  if (!SATURATE) return x;
+  return __builtin_fabsf(b) <= 2.356e38f ? fminf(fmaxf(x, -3.4028234e38f), 3.4028234e38f) : b * INFINITY;
 }
 
 // ---- pieces shared by both kernels ----------------------------------------------------
@@ -1116,7 +1134,7 @@ __global__ __launch_bounds__(kThreads, 2) void fa_fwd_window_resident_kernel(con
     // one value per thread: key b_lo*32 + tid (256 resident keys, 256 threads)
     const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
     const int jg = b_lo * 32 + tid;
-    lds_bias[tid] = T::to_float(bp[jg < N ? jg : N - 1]) * a.inv_abs_scale;
+    lds_bias[tid] = bias_over_scale<T, true>(a, bp[jg < N ? jg : N - 1]);
   }
 
   const int qw0 = q0 + wave * 32;
@@ -1366,7 +1384,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
   if (BIAS) {   // one value per thread: key b_lo*32 + tid (256 keys, 256 threads)
     const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
     const int jg = b_lo * 32 + tid;
-    lds_bias[tid] = T::to_float(bp[jg < N ? jg : N - 1]) * a.inv_abs_scale;
+    lds_bias[tid] = bias_over_scale<T, true>(a, bp[jg < N ? jg : N - 1]);
   }
 
   const int qw0 = q0 + wave * 32;
@@ -1795,7 +1813,7 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   for (int t = 0; t < pairs; ++t) load_pair(t, steps_req);
   if (BIAS) {
     const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
-    for (int j = tid; j < ((N + 31) & ~31); j += THREADS) lds_bias[j] = T::to_float(bp[j < N ? j : N - 1]) * a.inv_abs_scale;
+    for (int j = tid; j < ((N + 31) & ~31); j += THREADS) lds_bias[j] = bias_over_scale<T, true>(a, bp[j < N ? j : N - 1]);
   }
 
   // only now the sequence length
@@ -2083,7 +2101,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   // bias of key j in raw-score units (index clamped: keys outside [0, n) are never used unmasked)
   auto bias_of = [&](int j) {
     j = j < 0 ? 0 : (j < N ? j : N - 1);
-    return T::to_float(bp[j]) * a.inv_abs_scale;
+    return bias_over_scale<T, D == 32>(a, bp[j]);
   };
 
   if (q0 >= n) {
@@ -2634,17 +2652,17 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     rows = 32 * (a.split >> 4);
     if (!kern) return (int)hipErrorInvalidValue;
   } else
-  if (!(a.key_bias && (rope || !(a.c > 0.f))) && !global && v_path == 0 && bm == 128 && slice_fits_32bit &&
+  if (!(a.key_bias && (rope || !(a.inv_abs_scale > 0.f))) && !global && v_path == 0 && bm == 128 && slice_fits_32bit &&
       win_blocks <= kResBlocks && wave_blocks <= kTwoPhaseBlocks && win_kernel != 1 &&
       !(latency_bound && !rope && win_kernel != 2)) {
     // local layer with a narrow two-sided window (the paper's 63/64), any head_dim
     kern = rope ? twophase_kernel<T, kTwoPhaseRope>(a.head_dim)
                 : (a.key_bias ? twophase_kernel<T, kTwoPhaseBias>(a.head_dim) : twophase_kernel<T, kTwoPhasePlain>(a.head_dim));
-  } else if (a.key_bias && !rope && !global && v_path == 0 && a.c > 0.f && a.head_dim == kD && bm == 128 && slice_fits_32bit &&
+  } else if (a.key_bias && !rope && !global && v_path == 0 && a.inv_abs_scale > 0.f && a.head_dim == kD && bm == 128 && slice_fits_32bit &&
       win_blocks <= kResBlocks) {
     // additive key bias on a local layer whose key range stays resident in LDS
     kern = fa_fwd_window_resident_kernel<T, true>;
-  } else if (a.key_bias && !rope && global && v_path == 0 && a.c > 0.f) {
+  } else if (a.key_bias && !rope && global && v_path == 0 && a.inv_abs_scale > 0.f) {
     // additive key bias on a global layer: the pipelined kernel with the bias as MFMA C operand
     if (bm == 256 && a.head_dim != 128) rows = 256;
     if (a.head_dim == 32) kern = rows == 256 ? fa_fwd_global_kernel<T, 32, 2, 4, true> : fa_fwd_global_kernel<T, 32, 1, 4, true>;

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2603_12646_amd as fa
-from oracle.attention_oracle import attention_oracle
+from oracle.attention_oracle import attention_oracle, attention_oracle_rows
 from workloads import draw, round_to_storage
 
 from tests.gpu_util import FA_DT, check_against, poison, run_ex, to_dev
@@ -87,3 +87,39 @@ def test_heads_first_order_gives_the_bits_of_the_linear_order(D, rope, N, lens):
     assert not torch.isnan(got[0][0]).any() and torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
     for b, n in enumerate(lens or []):
         assert (got[0][0][b, n:] == 0).all() and torch.isneginf(got[0][1][b, :, n:]).all()
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("left,right,N", [(63, 64, 300), (-1, -1, 300), (-1, -1, 5000)])
+@pytest.mark.parametrize("dtype,scale", [("fp16", 1e-39), ("fp16", -1e-36), ("bf16", 1e-39), ("bf16", 1e-36)])
+def test_key_bias_with_a_tiny_scale(D, left, right, N, dtype, scale):
+    """A scale so small that bias / |scale| leaves the range of fp32: the softmax is that of the bias alone."""
+    _, q, k, v = draw(4300 + D, 1, 2, N, D, dtype)
+    rng = np.random.default_rng(D)
+    bias = round_to_storage(rng.standard_normal((1, N)).astype(np.float32), dtype)
+    bias[0, rng.random(N) < 0.3] = round_to_storage(np.full((1,), -65504.0, np.float32), dtype)[0]
+    o, lse = run_ex(q, k, v, None, dtype, scale, left, right, key_bias=bias)
+    rows = np.unique(np.concatenate([np.arange(0, 200), np.arange(N - 70, N)]))
+    for h in range(2):
+        o_ref, lse_ref = attention_oracle_rows(q, k, v, 0, h, rows, N, scale, left, right, key_bias=bias)
+        check_against(o[:, h:h + 1, rows], lse[:, h:h + 1, rows], o_ref[None, None], lse_ref[None, None], None, dtype,
+                      relative=True, label=f"tiny scale D{D} h{h}")
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("left,right,N", [(63, 64, 300), (63, 64, 3000), (-1, -1, 300), (-1, -1, 5000)])
+@pytest.mark.parametrize("scale", [1.0, 0.75, 0.125])
+def test_key_bias_of_the_types_lowest_value(D, left, right, N, scale):
+    """bfloat16's lowest finite value as the padding bias, on the first keys (left padding) and scattered ones: those keys
+    have weight 0 for every row that sees another."""
+    B, H = 1, 12
+    _, q, k, v = draw(4400 + D, B, 1, N, D, "bf16", qk_gain=0.3)
+    rep = lambda x: np.repeat(x, H, axis=1)
+    bias = np.zeros((B, N), np.float32)
+    bias[0, :40] = bias[0, 100::3] = torch.finfo(torch.bfloat16).min
+    o, lse = run_ex(rep(q), rep(k), rep(v), None, "bf16", scale, left, right, key_bias=bias)
+    rows = np.unique(np.concatenate([np.arange(0, 260), np.arange(N - 70, N)]))
+    o_ref, lse_ref = attention_oracle_rows(q, k, v, 0, 0, rows, N, scale, left, right, key_bias=bias)
+    check_against(o[:, :1, rows], lse[:, :1, rows], o_ref[None, None], lse_ref[None, None], None, "bf16", relative=True,
+                  label=f"lowest D{D} {scale}")
+    assert (o == o[:, :1]).all()

@@ -161,15 +161,29 @@ int main() {
               return 1;
             }
           }
+  // a scale by which a bias cannot be divided in fp32: the masked kernel as well, said to the launcher by inv_abs_scale = 0
+  p.rope_cos = p.rope_sin = nullptr;
+  p.tuning = 0;
+  for (int d : {32, 64, 128})
+    for (int n : {300, 8192})
+      for (float s : {0.0f, 1e-45f, 1e-39f, -1e-36f, 1e-34f, 3e-34f, -0.125f, 8.0f}) {
+        p.head_dim = d; p.batch = 1; p.heads = 24; p.max_len = n; p.scale = s;
+        const bool divides = s > 2e-34f || s < -2e-34f;
+        if (fa_fwd_ex(&p) != 0 || (last.inv_abs_scale > 0.f) != divides || (!divides && (last_bm != 128 || last.split))) {
+          printf("FAILED d %d n %d scale %g: bm %d split %x inv %g\n", d, n, s, last_bm, last.split, last.inv_abs_scale);
+          return 1;
+        }
+      }
   printf("ok\n");
   return 0;
 }
 """
 
 
-def test_bias_with_a_rotation_in_the_call_keeps_the_masked_kernels_rows(tmp_path):
-    """A key bias and a rotation inside the call together run the masked kernel, whose workgroups hold 128 rows: the grid
-    has to be made of 128-row tiles whatever the size or the forced shape, or the rows past the first tiles stay unwritten."""
+def test_bias_with_a_rotation_in_the_call_or_a_tiny_scale_keeps_the_masked_kernels_rows(tmp_path):
+    """A key bias together with a rotation inside the call, or with a scale that it cannot be divided by, runs the masked
+    kernel, whose workgroups hold 128 rows: the grid has to be made of 128-row tiles whatever the size or the forced shape,
+    or the rows past the first tiles stay unwritten."""
     if shutil.which("g++") is None:
         pytest.skip("no g++")
     src, exe, csrc = tmp_path / "driver.cpp", tmp_path / "driver", ROOT / "paper_2603_12646_amd" / "csrc"
