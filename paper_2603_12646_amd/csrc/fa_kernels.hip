@@ -335,7 +335,8 @@ __device__ __forceinline__ float keep_or_neg_inf(float x, uint32_t vis, int r) {
 // uses), two per v_dot2c instruction.  bf16: the unrounded fp32 values are summed; with
 // 8 mantissa bits the rounded sum would cost lse up to ~2e-3 when a row sees only a
 // handful of keys.  vis: bit r set = accumulator element r is a visible key.
-template <class T, bool MASKED>
+// SUM32: the unrounded values are summed in fp16 as well.
+template <class T, bool MASKED, bool SUM32 = false>
 __device__ __forceinline__ void prob_block(const floatx16& sv, float c, float mcq, uint32_t vis,
                                            uint32_t (&pk)[8], float& blk) {
   const float nmc = -mcq;
@@ -349,12 +350,12 @@ __device__ __forceinline__ void prob_block(const floatx16& sv, float c, float mc
       e1 = keep_or_zero(e1, vis, 2 * r + 1);
     }
     pk[r] = T::pack2(e0, e1);
-    if (!T::kSumRounded) {
+    if (SUM32 || !T::kSumRounded) {
       l0 += e0;
       l1 += e1;
     }
   }
-  if (T::kSumRounded) {
+  if (!SUM32 && T::kSumRounded) {
     l0 = T::sum2_first(pk[0]);
     l1 = T::sum2_first(pk[1]);
 #pragma unroll
@@ -502,8 +503,8 @@ __device__ __forceinline__ void simple_block(RowState<NQB, D>& st, const typenam
 // masked kernel).  A reference of such a bias that is finite while its product with c = |scale| log2(e) is not would turn
 // rows into NaN, so where |scale| > ln 2 the factor log2(e) comes first (bias_pre; 1 elsewhere, where the largest fp32
 // number times c is finite).  SATURATE: below |scale| = ln 2 a quotient past the largest fp32 number stops there instead of
-// excluding the key, as the masked kernel has it; for kernels that convert each bias once, or ran the masked kernel's
-// values before (in the loop of the pipelined kernel it takes wavefront 0 1-3 % of a short call).
+// excluding the key, as the masked kernel has it: for the head sizes whose biased calls would otherwise run that kernel (it
+// takes wavefront 0 of the pipelined kernel 1-3 % of a short call).
 template <class T, bool SATURATE>
 __device__ __forceinline__ float bias_over_scale(const FaKernelArgs& a, uint16_t bits) {
   const float b = T::to_float(bits);
@@ -511,6 +512,15 @@ __device__ __forceinline__ float bias_over_scale(const FaKernelArgs& a, uint16_t
   const float x = b * a.bias_pre * a.inv_abs_scale;
   if (!SATURATE) return x;
   return __builtin_fabsf(b) <= 2.356e38f ? fminf(fmaxf(x, -3.4028234e38f), 3.4028234e38f) : b * INFINITY;
+}
+
+// bias of a 32-key block (32 floats in LDS, raw-score units) added to its scores
+__device__ __forceinline__ void add_bias(floatx16& s, const float* bblk, int hh) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const float4 b4 = *(const float4*)&bblk[8 * g + 4 * hh];
+    s[4 * g + 0] += b4.x; s[4 * g + 1] += b4.y; s[4 * g + 2] += b4.z; s[4 * g + 3] += b4.w;
+  }
 }
 
 // ---- pieces shared by both kernels ----------------------------------------------------
@@ -1134,7 +1144,7 @@ __global__ __launch_bounds__(kThreads, 2) void fa_fwd_window_resident_kernel(con
     // one value per thread: key b_lo*32 + tid (256 resident keys, 256 threads)
     const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
     const int jg = b_lo * 32 + tid;
-    lds_bias[tid] = bias_over_scale<T, true>(a, bp[jg < N ? jg : N - 1]);
+    lds_bias[tid] = bias_over_scale<T, false>(a, bp[jg < N ? jg : N - 1]);
   }
 
   const int qw0 = q0 + wave * 32;
@@ -1264,12 +1274,16 @@ constexpr int kTwoPhaseBlocks = 5;
 //   Rotation: the K blocks are rotated in place in LDS, once for the four wavefronts.  What that costs is the angle
 //   tables: 256 bytes per K row, as much as its K and V, so a thread requests its rows' entries right behind the K
 //   loads and holds them in registers (the score accumulators are not live yet) until K has landed.
-//   Bias: each key's bias divided by |scale| is the C operand of its block's first score product.
+//   Bias, head_dim 32 and 128: each key's bias divided by |scale| is added to its block's finished scores, so that a score
+//   near -65504 is rounded once, not in every product of the chain, and the row sums are those of the unrounded
+//   probabilities, both as in the masked kernel.  head_dim 64: it is the C operand of its block's first score product and
+//   fp16 sums are those of the rounded probabilities, both as in the resident kernel (which small calls of this head size
+//   run); adding it afterwards does not fit the 128 registers of four wavefronts per SIMD (8K tokens 14 -> 319 us).
 enum { kTwoPhasePlain = 0, kTwoPhaseRope = 1, kTwoPhaseBias = 2 };
 
 template <class T, int D, int OPT = kTwoPhasePlain>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twophase_kernel(const FaKernelArgs a) {
-  constexpr bool ROPE = OPT == kTwoPhaseRope, BIAS = OPT == kTwoPhaseBias;
+  constexpr bool ROPE = OPT == kTwoPhaseRope, BIAS = OPT == kTwoPhaseBias, BIAS_LAST = BIAS && D != 64;
   constexpr int BM = kWaves * 32;
   constexpr int KS = D / 16, DB = D / 32;
   constexpr int kBlk = 32 * D;  // elements per block
@@ -1381,10 +1395,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
       held[x][3] = sn[1];
     }
   }
-  if (BIAS) {   // one value per thread: key b_lo*32 + tid (256 keys, 256 threads)
+  uint16_t bias_bits = 0;   // one value per thread: key b_lo*32 + tid (256 keys, 256 threads); used once K has landed
+  if (BIAS) {
     const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
     const int jg = b_lo * 32 + tid;
-    lds_bias[tid] = bias_over_scale<T, true>(a, bp[jg < N ? jg : N - 1]);
+    bias_bits = bp[jg < N ? jg : N - 1];
   }
 
   const int qw0 = q0 + wave * 32;
@@ -1419,6 +1434,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
 
   // ---- phase 1: scores of every visible block
   wait_direct_loads();
+  if (BIAS) lds_bias[tid] = bias_over_scale<T, BIAS_LAST>(a, bias_bits);
   __syncthreads();
   if (ROPE) {
 #pragma unroll
@@ -1448,7 +1464,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
 #pragma unroll
   for (int i = 0; i < kTwoPhaseBlocks; ++i) {
     if (i < cnt) {
-      if (BIAS) {
+      if (BIAS && !BIAS_LAST) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const float4 b4 = *(const float4*)&lds_bias[(fb + i - b_lo) * 32 + 8 * g + 4 * hh];
@@ -1461,6 +1477,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
       const uint16_t* kblk = &lds[(fb + i - b_lo) * kBlk];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) sc[i] = T::mfma(load_k_frag_swz_d<T, D>(kblk, l32, hh, ks), qreg[0][ks], sc[i]);
+      if (BIAS_LAST) add_bias(sc[i], &lds_bias[(fb + i - b_lo) * 32], hh);
     }
   }
   __syncthreads();  // every wavefront has its K fragments out of the region
@@ -1512,8 +1529,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
     if (i < cnt2) {
       uint32_t pk[8];
       float blk;
-      if (vis[i] == 0xFFFFu) prob_block<T, false>(sc[i], c, st.mc[0], vis[i], pk, blk);
-      else prob_block<T, true>(sc[i], c, st.mc[0], vis[i], pk, blk);
+      if (vis[i] == 0xFFFFu) prob_block<T, false, BIAS_LAST>(sc[i], c, st.mc[0], vis[i], pk, blk);
+      else prob_block<T, true, BIAS_LAST>(sc[i], c, st.mc[0], vis[i], pk, blk);
       st.lsum[0] += blk;
       pr[i][0] = as_v8<T>(make_uint4(pk[0], pk[1], pk[2], pk[3]));
       pr[i][1] = as_v8<T>(make_uint4(pk[4], pk[5], pk[6], pk[7]));
@@ -1599,6 +1616,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
 template <class T, int D, bool BIAS>
 struct SplitWave {
   static constexpr int KS = D / 16, DB = D / 32;
+  // head_dim 32 with a bias: the bias is added to finished scores and row sums are unrounded, as in the masked kernel
+  // (head_dim 64 / 128: the bias is the C operand, as in the pipelined kernel)
+  static constexpr bool BIAS_LAST = BIAS && D == 32, BIAS_FIRST = BIAS && !BIAS_LAST;
   RowState<1, D> st;
   typename T::v8 q[KS];
   uint32_t kfo[KS], vfo[DB];   // per-lane operand offsets (16-bit elements) into a swizzled 32-row block
@@ -1636,11 +1656,12 @@ struct SplitWave {
     const int hh = lane >> 5;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const float4 b4 = BIAS ? *(const float4*)&bblk[8 * g + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 b4 = BIAS_FIRST ? *(const float4*)&bblk[8 * g + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
       s[4 * g + 0] = b4.x; s[4 * g + 1] = b4.y; s[4 * g + 2] = b4.z; s[4 * g + 3] = b4.w;
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) s = T::mfma(k_frag(kblk, ks), q[ks], s);
+    if (BIAS_LAST) add_bias(s, bblk, hh);
   }
   __device__ __forceinline__ void accumulate(const typename T::v8 (&p)[2], const uint16_t* vblk) {
 #pragma unroll
@@ -1662,7 +1683,7 @@ struct SplitWave {
   __device__ __forceinline__ void softmax(const floatx16& s, typename T::v8 (&p)[2], uint32_t vis, bool alive, float c) {
     uint32_t pk[8];
     float blk;
-    prob_block<T, MASKED>(s, c, st.mc[0], vis, pk, blk);
+    prob_block<T, MASKED, BIAS_LAST>(s, c, st.mc[0], vis, pk, blk);
     const bool trig = alive && !(blk <= sum_limit);   // (also catches a NaN sum)
     if (__any(trig)) {
       const bool row_trig = sum_xor32(trig ? 1.f : 0.f) > 0.f;   // a row refreshes on its own two lanes' evidence only
@@ -1671,7 +1692,7 @@ struct SplitWave {
       for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, MASKED ? keep_or_neg_inf(s[r], vis, r) : s[r]);
       rescale_rows(st, 0, row_trig, max_xor32(t0), c);
       set_limit();
-      prob_block<T, MASKED>(s, c, st.mc[0], vis, pk, blk);
+      prob_block<T, MASKED, BIAS_LAST>(s, c, st.mc[0], vis, pk, blk);
     }
     st.lsum[0] += blk;
     p[0] = as_v8<T>(make_uint4(pk[0], pk[1], pk[2], pk[3]));
@@ -1691,7 +1712,7 @@ struct SplitWave {
     for (int i = 0; i < 2 * DB; ++i) va[i] = vt_frag(v_prev, i / DB, i % DB);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const float4 b4 = BIAS ? *(const float4*)&b_next[8 * g + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 b4 = BIAS_FIRST ? *(const float4*)&b_next[8 * g + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
       s_nxt[4 * g + 0] = b4.x; s_nxt[4 * g + 1] = b4.y; s_nxt[4 * g + 2] = b4.z; s_nxt[4 * g + 3] = b4.w;
     }
     static_assert(KS == 2 * DB, "one score product alternates with one output product");
@@ -1700,6 +1721,7 @@ struct SplitWave {
       s_nxt = T::mfma(ka[i], q[i], s_nxt);
       st.oacc[0][i % DB] = T::mfma(va[i], p_prev[i / DB], st.oacc[0][i % DB]);
     }
+    if (BIAS_LAST) add_bias(s_nxt, b_next, hh);
     softmax<false>(s_cur, p_cur, 0xFFFFu, alive, c);
   }
 };
@@ -1813,7 +1835,7 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   for (int t = 0; t < pairs; ++t) load_pair(t, steps_req);
   if (BIAS) {
     const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
-    for (int j = tid; j < ((N + 31) & ~31); j += THREADS) lds_bias[j] = bias_over_scale<T, true>(a, bp[j < N ? j : N - 1]);
+    for (int j = tid; j < ((N + 31) & ~31); j += THREADS) lds_bias[j] = bias_over_scale<T, D == 32>(a, bp[j < N ? j : N - 1]);
   }
 
   // only now the sequence length
@@ -2053,7 +2075,9 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
 // ======================================================================================
 // BIAS: the additive key bias rides on the score product: the bias of a key block, divided
 // by |scale|, is the C operand of the block's first MFMA, so the scores arrive with the bias
-// already in them and the vector work is unchanged.  Bias values are staged per K tile
+// already in them and the vector work is unchanged.
+// (head_dim 32: it is added to the finished scores, and the row sums are those of the
+// unrounded probabilities, as in the masked kernel.)  Bias values are staged per K tile
 // through a register of wavefront 0 into a small LDS array with the tile's two stages.
 // NW: wavefronts per workgroup (4, 8 or 12).  All of them share ONE pair of K/V stages, so the
 // tile traffic from L2 into LDS per flop falls with NW; a workgroup of 8 or 12 wavefronts
@@ -2082,6 +2106,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   static_assert(NW == 4 || NW == 8 || NW == 12, "4, 8 or 12 wavefronts");
   constexpr int THREADS = NW * 64;
   constexpr int BM = NW * 32 * NQB;
+  constexpr bool BIAS_LAST = BIAS && D == 32, BIAS_FIRST = BIAS && !BIAS_LAST;
   constexpr int KS = D / 16;  // k-steps of a score block
   constexpr int DB = D / 32;  // 32-row blocks of O^T
   constexpr int SK = stride_k(D), SV = stride_v(D);
@@ -2296,15 +2321,14 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) sA[r] = 0.f;
-    if (BIAS) {
-      bias_frag(&lds_bias[kBN + 32]);
-      sA = bcur;
-    }
+    if (BIAS) bias_frag(&lds_bias[kBN + 32]);
+    if (BIAS_FIRST) sA = bcur;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       ka[ks] = k_frag(&lds_k[kBN * D + 32 * D], ks);
       sA = T::mfma(ka[ks], qreg[0][ks], sA);
     }
+    if (BIAS_LAST) sA += bcur;
     if (!BIAS) {
       // Every query block takes the maximum of its scores against key block 0 as its first
       // reference, here, once (nothing is accumulated yet, so there is nothing to rescale): the
@@ -2334,7 +2358,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     // kPLimit, an infinity included, pushes it over).  Only then - rarely - is the exact
     // block maximum computed, the reference refreshed and the block redone.
     auto softmax_block = [&](const floatx16& sv, float mcq, uint32_t (&pk)[8], float& blk) {
-      prob_block<T, false>(sv, c, mcq, 0xFFFFu, pk, blk);
+      prob_block<T, false, BIAS_LAST>(sv, c, mcq, 0xFFFFu, pk, blk);
     };
     // One unit.  QB: query block of the current scores; NQ: query block of the next
     // unit; PQ: query block of the previous unit; LOAD: this unit starts a new key block
@@ -2353,7 +2377,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         if (BIAS) bias_frag(bblk);
       }
       // the first product of the score block takes the bias (or zero) as its C operand
-      if (BIAS) {
+      if (BIAS_FIRST) {
         s_nxt = bcur;
       } else {
 #pragma unroll
@@ -2366,6 +2390,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         s_nxt = T::mfma(ka[ks], qreg[NQ][ks], s_nxt);
         st.oacc[PQ][ks % DB] = T::mfma(va[ks / DB][ks % DB], p_prev[ks / DB], st.oacc[PQ][ks % DB]);
       }
+      if (BIAS_LAST) s_nxt += bcur;
       uint32_t pk[8];
       float blk;
       softmax_block(s_cur, st.mc[QB], pk, blk);

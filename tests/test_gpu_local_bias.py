@@ -123,3 +123,41 @@ def test_key_bias_of_the_types_lowest_value(D, left, right, N, scale):
     check_against(o[:, :1, rows], lse[:, :1, rows], o_ref[None, None], lse_ref[None, None], None, "bf16", relative=True,
                   label=f"lowest D{D} {scale}")
     assert (o == o[:, :1]).all()
+
+
+@pytest.mark.parametrize("tuning", [0, fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256])
+@pytest.mark.parametrize("D,left,right", [(32, 63, 64), (128, 63, 64), (32, -1, -1)])
+def test_key_bias_rounds_a_score_once(D, left, right, tuning):
+    """The paper's padding value on EVERY key: a score near -65504 is a sum of score and bias that fp32 holds to half a
+    spacing, and that one rounding (of bias / scale, by at most d = 2^-24 * 65504 here) is all that may show.  With every
+    probability off by at most d + 2^-11 (its own rounding to fp16) relative, o is off by that times the mean distance of
+    the values from it (and the numerator alone carries the rounding to fp16, as o does once more)."""
+    N = 600
+    scale = D ** -0.5
+    _, q, k, v = draw(4500 + D, 1, 2, N, D, "fp16", qk_gain=1.7)
+    bias = np.full((1, N), -65504.0, np.float32)
+    o, lse = run_ex(q, k, v, None, "fp16", scale, left, right, key_bias=bias,
+                    tuning=tuning | (0 if left < 0 else fa.FA_TUNE_WIN_TWO_PHASE))
+    x = 65504.0 / scale
+    d = 0.5 * np.spacing(np.float32(x)) * scale
+    assert d <= 2.0 ** -24 * 65504
+    o_ref, lse_ref, P = attention_oracle(q, k, v, None, scale, left, right, key_bias=bias, return_p=True)
+    spread = np.stack([(P[0, h][:, :, None] * np.abs(v[0, h][None] - o_ref[0, h][:, None])).sum(1) for h in range(2)])[None]
+    bound = 1.01 * (d + 2.0 ** -11) * spread + 2.0 ** -10 * np.abs(o_ref) + 2e-5
+    worst = (np.abs(o - o_ref) / bound).max()
+    assert worst <= 1.0, worst
+
+
+@pytest.mark.parametrize("tuning", [0, fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256])
+@pytest.mark.parametrize("D,left,right", [(32, 63, 64), (128, 63, 64), (32, -1, -1)])
+def test_key_bias_row_sums_are_kept_in_fp32(D, left, right, tuning):
+    """lse of fp16 calls with a key bias comes from the probabilities before they are rounded to 16 bits: off by a few
+    fp32 spacings, not by the 2^-12 of a rounded probability."""
+    N = 600
+    _, q, k, v = draw(4600 + D, 1, 2, N, D, "fp16", qk_gain=1.7)
+    bias = round_to_storage(np.random.default_rng(D).standard_normal((1, N)).astype(np.float32), "fp16")
+    o, lse = run_ex(q, k, v, None, "fp16", D ** -0.5, left, right, key_bias=bias,
+                    tuning=tuning | (0 if left < 0 else fa.FA_TUNE_WIN_TWO_PHASE))
+    o_ref, lse_ref = attention_oracle(q, k, v, None, D ** -0.5, left, right, key_bias=bias)
+    # scores up to 60 carry half an fp32 spacing (2^-19 there) per product step, the sum of up to 600 terms 2^-24 each
+    assert np.abs(lse - lse_ref).max() <= 3e-5, np.abs(lse - lse_ref).max()
