@@ -122,7 +122,9 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
 // NK wavefronts that split the keys), or 0 where the other kernels are faster.  Its workgroups have a compute unit to
 // themselves (head_dim 32: half or a quarter of one), so a shape is taken only where the call fits the 256 units in one
 // round - a second, thin round costs as much as the first - and the fewest rows per workgroup that do fit are the
-// fastest; behind these head_dim 64 has a shape of which three fit a unit.  Measured, fp16, 12 x 64 / 8 x 128 / 24 x 32,
+// fastest; behind these head_dim 64 has a shape of which three fit a unit.  What has to fit are the IDS: every XCD takes an
+// eighth of each batch element's tiles, rounded up, so 3 x 12 heads x 197 tokens are 252 tiles of 32 rows but 264 ids (7.7 us
+// in 128 rows, 11.0 in 32; 3 x 12 x 603 with a bias 13.8 in 128 rows, 20.3 in 96).  Measured, fp16, 12 x 64 / 8 x 128 / 24 x 32,
 // against the 128-row kernel (us per call):
 //   head_dim 64   32 rows: 512 tokens 7.6 -> 6.2;  64 rows: 1024 13.6 -> 11.1, 1280 17.2 -> 11.8, 5 x 256 7.3 -> 6.6;
 //                 96 rows: 1400 18.9 -> 15.7, 2000 24.9 -> 20.3, but 3 x 450 9.7 -> 10.0 (short sequences do not repay
@@ -141,22 +143,21 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
 //                 the 128-row kernel has its thin second round (257 - 384 tiles): 1400 21.3 -> 18.5, 2048 29.2 -> 25.5,
 //                 2 x 700 13.0 -> 12.9; beyond it 2400 33.0 -> 35.3.
 int choose_split(const fa_params& p) {
-  const int64_t bh = (int64_t)p.batch * p.heads;
-  auto tiles = [&](int rows) { return ((int64_t)p.max_len + rows - 1) / rows * bh; };
+  auto ids = [&](int rows) { return (((int64_t)p.max_len + rows - 1) / rows * p.heads + 7) / 8 * 8 * p.batch; };
   const bool bias = p.key_bias != nullptr;
   if (p.max_len <= 64) return 0;
   if (p.head_dim == 64) {
-    if (tiles(64) <= 256) return tiles(32) <= 256 && p.max_len > 128 ? 0x18 : 0x24;
-    if (tiles(96) <= 256 && p.max_len >= (bias ? 448 : 640)) return 0x34;
-    if (bias) return tiles(128) <= 256 && p.max_len >= 512 ? 0x42 : 0;
-    if (tiles(128) <= 192 && p.max_len >= 1536) return 0x42;
-    if (tiles(64) <= 768 && p.max_len >= (tiles(128) <= 256 ? 704 : 480)) return 0x22;
+    if (ids(64) <= 256) return ids(32) <= 256 && p.max_len > 128 ? 0x18 : 0x24;
+    if (ids(96) <= 256 && p.max_len >= (bias ? 448 : 640)) return 0x34;
+    if (bias) return ids(128) <= 256 && p.max_len >= 512 ? 0x42 : 0;
+    if (ids(128) <= 192 && p.max_len >= 1536) return 0x42;
+    if (ids(64) <= 768 && p.max_len >= (ids(128) <= 256 ? 704 : 480)) return 0x22;
   } else if (p.head_dim == 128) {
-    if (tiles(64) <= 256) return tiles(32) <= 256 ? 0x14 : 0x24;
-    if (tiles(128) <= 256 && p.max_len >= (bias ? 256 : 640)) return 0x42;
+    if (ids(64) <= 256) return ids(32) <= 256 ? 0x14 : 0x24;
+    if (ids(128) <= 256 && p.max_len >= (bias ? 256 : 640)) return 0x42;
   } else {
-    if (!bias && tiles(32) <= 512 && p.max_len >= 256) return 0x14;
-    if (tiles(64) <= 768 && (bias || (tiles(64) > 512 && p.max_len >= 640))) return 0x22;
+    if (!bias && ids(32) <= 512 && p.max_len >= 256) return 0x14;
+    if (ids(64) <= 768 && (bias || (ids(64) > 512 && p.max_len >= 640))) return 0x22;
   }
   return 0;
 }

@@ -1,5 +1,5 @@
 """The host's choice of a split-kernel shape, walked on the CPU with stub launchers: a shape is one the kernels exist in,
-its grid matches its rows per workgroup and fits the 256 compute units in one round, and calls that the kernel does not
+its grid matches its rows per workgroup and its ids fit the 256 compute units in one round, and calls that the kernel does not
 cover (windows, a rotation in the call, a long key bias, forced shapes) never get one."""
 import pathlib
 import shutil
@@ -49,7 +49,9 @@ int main() {
               EXPECT(d == 64 ? (s == 0x18 || s == 0x24 || s == 0x34 || s == 0x42 || (s == 0x22 && !biased))
                              : (d == 128 ? (s == 0x14 || s == 0x24 || s == 0x42) : (s == 0x14 || s == 0x22)));
               EXPECT(last_bm == 32 * nq && last.n_qtiles == (n + 32 * nq - 1) / (32 * nq));
-              EXPECT(last.total_tiles == last.n_qtiles * b * h && last.total_tiles <= (d == 32 || s == 0x22 ? 768 : 256));
+              // every XCD's eighth of each batch element's tiles, rounded up, is launched: these ids have to fit in one round
+              const long ids = 8L * last.xcd_per * b, round = s == 0x22 ? 768 : (d == 32 && !biased ? 512 : 256);
+              EXPECT(last.total_tiles == last.n_qtiles * b * h && ids >= last.total_tiles && ids <= round);
               EXPECT(!biased || n <= kSplitBiasKeys);
             }
             p.window_left = 63; p.window_right = 64;
