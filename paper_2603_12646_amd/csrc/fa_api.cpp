@@ -128,8 +128,7 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
 // against the 128-row kernel (us per call):
 //   head_dim 64   32 rows: 512 tokens 7.6 -> 6.2;  64 rows: 1024 13.6 -> 11.1, 1280 17.2 -> 11.8, 5 x 256 7.3 -> 6.6;
 //                 96 rows: 1400 18.9 -> 15.7, 2000 24.9 -> 20.3, but 3 x 450 9.7 -> 10.0 (short sequences do not repay
-//                 the merge of a 12-wavefront workgroup);  128 rows: 1900 of 2048 22.5 -> 21.3, but 2 x 1024 15.1 -> 15.2,
-//                 4 x 400 9.2 -> 10.5.  (A round too many: 2 x 700 in 64 rows 18.2 against 12.0.)
+//                 the merge of a 12-wavefront workgroup).  (A round too many: 2 x 700 in 64 rows 18.2 against 12.0.)
 //                 64 rows on four wavefronts, three workgroups per unit: up to 768 of them; in particular where the
 //                 128-row kernel has one to one and a half workgroups per unit: 2500 30.1 -> 27.0, 2 x 1300 24.1 -> 17.2,
 //                 3072 50.3 -> 44.7, 4096 64.4 -> 62.2, 4 x 900 19.8 -> 18.7, 8 x 500 13.6 -> 13.1, but 6 x 450
@@ -150,7 +149,6 @@ int choose_split(const fa_params& p) {
     if (ids(64) <= 256) return ids(32) <= 256 && p.max_len > 128 ? 0x18 : 0x24;
     if (ids(96) <= 256 && p.max_len >= (bias ? 448 : 640)) return 0x34;
     if (bias) return ids(128) <= 256 && p.max_len >= 512 ? 0x42 : 0;
-    if (ids(128) <= 192 && p.max_len >= 1536) return 0x42;
     if (ids(64) <= 768 && p.max_len >= (ids(128) <= 256 ? 704 : 480)) return 0x22;
   } else if (p.head_dim == 128) {
     if (ids(64) <= 256) return ids(32) <= 256 ? 0x14 : 0x24;

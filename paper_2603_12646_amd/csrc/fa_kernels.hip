@@ -2634,7 +2634,7 @@ Kernel split_kernel(int head_dim, int split) {
     case 64 * 256 + 0x18: return fa_fwd_split_kernel<T, 64, 1, 8, 2, 2, BIAS>;
     case 64 * 256 + 0x24: return fa_fwd_split_kernel<T, 64, 2, 4, 4, 2, BIAS>;
     case 64 * 256 + 0x34: return fa_fwd_split_kernel<T, 64, 3, 4, BIAS ? 3 : 4, 3, BIAS>;
-    case 64 * 256 + 0x42: return fa_fwd_split_kernel<T, 64, 4, 2, 4, 2, BIAS>;
+    case 64 * 256 + 0x42: return BIAS ? (Kernel)fa_fwd_split_kernel<T, 64, 4, 2, 4, 2, true> : nullptr;
     // (three workgroups per unit; without a key bias only: with one its LDS would allow two)
     case 64 * 256 + 0x22: return BIAS ? nullptr : (Kernel)fa_fwd_split_kernel<T, 64, 2, 2, 2, 3, false>;
     case 128 * 256 + 0x14: return fa_fwd_split_kernel<T, 128, 1, 4, 2, 1, BIAS>;

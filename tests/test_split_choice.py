@@ -46,7 +46,7 @@ int main() {
             if (last.split) {
               ++taken;
               const int nq = last.split >> 4, s = last.split;
-              EXPECT(d == 64 ? (s == 0x18 || s == 0x24 || s == 0x34 || s == 0x42 || (s == 0x22 && !biased))
+              EXPECT(d == 64 ? (s == 0x18 || s == 0x24 || s == 0x34 || (biased ? s == 0x42 : s == 0x22))
                              : (d == 128 ? (s == 0x14 || s == 0x24 || s == 0x42) : (s == 0x14 || s == 0x22)));
               EXPECT(last_bm == 32 * nq && last.n_qtiles == (n + 32 * nq - 1) / (32 * nq));
               // every XCD's eighth of each batch element's tiles, rounded up, is launched: these ids have to fit in one round
@@ -65,6 +65,29 @@ int main() {
             p.tuning = 0; p.scale = 0.0f;
             EXPECT(fa_fwd_ex(&p) == 0 && (!biased || last.split == 0));
           }
+  // no shape is there for one size: of one sequence of 1 - 48 heads each is taken for many head counts, and at many lengths
+  p.scale = 0.125f; p.batch = 1; p.tuning = 0;
+  for (int d : {32, 64, 128})
+    for (int biased = 0; biased < 2; ++biased) {
+      static int head_counts[256], lengths[256];
+      std::memset(head_counts, 0, sizeof head_counts);
+      std::memset(lengths, 0, sizeof lengths);
+      for (int h = 1; h <= 48; ++h) {
+        bool here[256] = {};
+        for (int n = 65; n <= kSplitBiasKeys; ++n) {
+          p.head_dim = d; p.heads = h; p.max_len = n; p.key_bias = biased ? buf : nullptr;
+          if (fa_fwd_ex(&p) != 0) return 1;
+          here[last.split] = true;
+          ++lengths[last.split];
+        }
+        for (int s = 0; s < 256; ++s) head_counts[s] += here[s];
+      }
+      for (int s = 1; s < 256; ++s)
+        if (lengths[s] && (head_counts[s] < 12 || lengths[s] < 100 * head_counts[s])) {
+          printf("FAILED head_dim %d bias %d shape %x: %d head counts, %d lengths\n", d, biased, s, head_counts[s], lengths[s]);
+          return 1;
+        }
+    }
   p.scale = 0.125f; p.key_bias = buf; p.batch = 1; p.heads = 1; p.head_dim = 64;
   p.max_len = kSplitBiasKeys; EXPECT(fa_fwd_ex(&p) == 0 && last.split != 0);
   p.max_len = kSplitBiasKeys + 1; EXPECT(fa_fwd_ex(&p) == 0 && last.split == 0);
