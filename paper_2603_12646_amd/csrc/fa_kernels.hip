@@ -1992,7 +1992,9 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
       if (NQ > 1) __syncthreads();
       w.accumulate(pA, v_slot(nfs - 1));
     }
-    if (steps > nfs) {
+    // (a block that lies past the end as a whole has no part in the result; its row without a reference would only take the
+    // detour for one)
+    if (32 * (nfs * NK + g) < n) {
       w.template softmax<true>(sA, pA, visible_bits(32 * (nfs * NK + g), hh, 0, n - 1), alive, c);
       w.accumulate(pA, v_slot(nfs));
     }
