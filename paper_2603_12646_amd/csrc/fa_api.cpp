@@ -119,43 +119,57 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
 }
 
 // Shape of the split kernel for a global layer, 16 * NQ + NK (NQ blocks of 32 query rows per workgroup, each shared by
-// NK wavefronts that split the keys), or 0 where the other kernels are faster.  Its workgroups have a compute unit to
-// themselves (head_dim 32: half or a quarter of one), so a shape is taken only where the call fits the 256 units in one
-// round - a second, thin round costs as much as the first - and the fewest rows per workgroup that do fit are the
-// fastest; behind these head_dim 64 has a shape of which three fit a unit.  What has to fit are the IDS: every XCD takes an
-// eighth of each batch element's tiles, rounded up, so 3 x 12 heads x 197 tokens are 252 tiles of 32 rows but 264 ids (7.7 us
-// in 128 rows, 11.0 in 32; 3 x 12 x 603 with a bias 13.8 in 128 rows, 20.3 in 96).  Measured, fp16, 12 x 64 / 8 x 128 / 24 x 32,
-// against the 128-row kernel (us per call):
-//   head_dim 64   32 rows: 512 tokens 7.6 -> 6.2;  64 rows: 1024 13.6 -> 11.1, 1280 17.2 -> 11.8, 5 x 256 7.3 -> 6.6;
-//                 96 rows: 1400 18.9 -> 15.7, 2000 24.9 -> 20.3, but 3 x 450 9.7 -> 10.0 (short sequences do not repay
-//                 the merge of a 12-wavefront workgroup).  (A round too many: 2 x 700 in 64 rows 18.2 against 12.0.)
-//                 64 rows on four wavefronts, three workgroups per unit: up to 768 of them; in particular where the
-//                 128-row kernel has one to one and a half workgroups per unit: 2500 30.1 -> 27.0, 2 x 1300 24.1 -> 17.2,
-//                 3072 50.3 -> 44.7, 4096 64.4 -> 62.2, 4 x 900 19.8 -> 18.7, 8 x 500 13.6 -> 13.1, but 6 x 450
-//                 13.0 -> 13.3, 5 x 400 9.3 -> 10.5; 2 x 1024 15.0 -> 13.8, 3 x 700 12.3 -> 12.1, but 3 x 600 10.7 -> 11.1.
-//                 At 64 tokens there is nothing to split: 5.3 -> 5.7.
-//                 With a key bias, whose pipelined kernel is slower, the lines lie lower: 3 x 450 11.5 -> 10.4,
-//                 3 x 600 13.9 -> 13.0, 4 x 400 10.8 -> 11.4.
-//   head_dim 128  32 rows: 512 13.6 -> 8.4;  64 rows: 2048 37 -> 24;  128 rows: 4 x 640 16.8 -> 15.5, 4096 75 -> 65, but
-//                 8 x 512 15.6 -> 15.8.  With a bias 16 x 256 13.5 -> 12.3.
-//   head_dim 32   32 rows (two workgroups per unit): 512 8.0 -> 6.8, 2 x 300 6.9 -> 6.3, 4 x 160 5.5 -> 5.8;  64 rows where
-//                 the 128-row kernel has its thin second round (257 - 384 tiles): 1400 21.3 -> 18.5, 2048 29.2 -> 25.5,
-//                 2 x 700 13.0 -> 12.9; beyond it 2400 33.0 -> 35.3.
+// NK wavefronts that split the keys), or 0 where the other kernels are faster.  A shape is taken only where the call's
+// workgroups fit the 256 units in one round - a second, thin round costs as much as the first.  What has to fit are the
+// IDS: every XCD takes an eighth of each batch element's tiles, rounded up, so 3 x 12 heads x 197 tokens are 252 tiles of 32
+// rows but 264 ids (7.7 us in 128 rows, 11.0 in 32).  The host knows max_len only, not the lengths.  All lines below are
+// from a sweep of 1 - 16 sequences x 4 - 32 heads x 65 - 4096 tokens, full and at 0.7 and 0.45 of max_len, in both types;
+// us per call, the 128 / 256-row kernels -> the shape:
+//   head_dim 64   32 rows on four wavefronts (two workgroups per unit): 12 heads x 110 tokens 6.0 -> 4.8, 200 6.7 -> 5.3,
+//                 380 8.3 -> 6.0, 512 9.0 -> 6.3 (on eight 6.3; 230 of 512 5.4, on eight 6.1); on eight from 640: 4 heads x
+//                 1024 13.8 -> 8.0.  At 64 tokens there is nothing to split.
+//                 64 rows: on four wavefronts, three workgroups per unit, 850 12.5 -> 10.4, 1024 13.6 -> 10.9, 1250
+//                 16.1 -> 12.4; on eight where the workgroups are short, 3 x 230 7.3 -> 6.5 (four: 6.8), or nearly alone, 4
+//                 heads x 3500 36.4 -> 23.0 (26.3).
+//                 96 rows (bf16): 1440 19.0 -> 17.4, 1750 21.7 -> 18.8, 2 x 880 13.5 -> 13.1; one sequence of 1000 tokens
+//                 in a tensor of 2000 loses (12.3 -> 13.0), and of 400 in 880 more (8.9 -> 10.0), where a batch does not.
+//                 64 rows, three per unit, beyond 256: where the 128-row kernel fits one round as well it pays for long
+//                 sequences, in fp16 from 1000 tokens (15.1 -> 13.8; 2 x 740 12.5 -> 12.1) but in bf16, whose 128-row
+//                 kernel spends less on the probabilities, from 2000 (2048 23.4 -> 22.8; 1024 14.1 -> 14.5; 2 x 1200 full
+//                 17.1 -> 17.2, ragged 16.5 -> 15.1); where that kernel needs a thin second round, from 480 (3 x 880 20.1 -> 14.7,
+//                 2900 49 -> 42; 6 x 400 12.0 -> 12.7).
+//                 With a key bias, whose pipelined kernel is slower: 64 rows 600 12.6 -> 9.4, 96 rows 4 x 460 11.7 -> 10.7,
+//                 128 rows 2400 43 -> 30, but 4 x 512 10.9 -> 11.5.
+//   head_dim 128  32 rows: 512 13.6 -> 8.4, 105 8.1 -> 6.4;  64 rows: 2048 37 -> 24;  128 rows: 4 x 640
+//                 16.8 -> 15.5, 4096 75 -> 65, but 8 x 512 15.6 -> 15.8.  With a bias 16 x 256 13.5 -> 12.3.
+//   head_dim 32   32 rows (two workgroups per unit; with a bias one): 24 heads x 512 7.8 -> 7.0, 1024 11.8 -> 9.4 at 12 heads;
+//                 64 rows, three per unit, where the 128-row kernel has its thin second round: 1500 22.5 -> 20.7, 2048
+//                 29.3 -> 26.7, but 2 x 700 11.9 -> 12.7.  With a bias 12 heads x 600 11.0 -> 7.2 in 32 rows, 1024
+//                 15.6 -> 11.9 in 64; 2 x 24 heads x 470 9.7 -> 10.4.
 int choose_split(const fa_params& p) {
   auto ids = [&](int rows) { return (((int64_t)p.max_len + rows - 1) / rows * p.heads + 7) / 8 * 8 * p.batch; };
-  const bool bias = p.key_bias != nullptr;
-  if (p.max_len <= 64) return 0;
-  if (p.head_dim == 64) {
-    if (ids(64) <= 256) return ids(32) <= 256 && p.max_len > 128 ? 0x18 : 0x24;
-    if (ids(96) <= 256 && p.max_len >= (bias ? 448 : 640)) return 0x34;
-    if (bias) return ids(128) <= 256 && p.max_len >= 512 ? 0x42 : 0;
-    if (ids(64) <= 768 && p.max_len >= (ids(128) <= 256 ? 704 : 480)) return 0x22;
+  const int n = p.max_len;
+  const bool bias = p.key_bias != nullptr, fp16 = p.dtype == FA_DTYPE_F16, one = p.batch == 1;
+  if (n <= 64) return 0;
+  if (p.head_dim == 64 && bias) {
+    if (ids(64) <= 256) return ids(32) <= 256 && n > 128 ? 0x18 : 0x24;
+    if (ids(96) <= 256 && n >= 448) return 0x34;
+    if (ids(128) <= 256 && n >= 560) return 0x42;
+  } else if (p.head_dim == 64) {
+    if (ids(32) <= 256) return n < 640 ? 0x14 : 0x18;
+    if (ids(64) <= 256) return n >= 1600 || (n >= 200 && n < 560) ? 0x24 : 0x22;
+    if (ids(96) <= 256 && n >= (one ? 1200 : 860)) return 0x34;
+    if (ids(128) <= 256) return n >= (fp16 ? (one ? 1000 : 700) : (one ? 2000 : 1100)) ? 0x22 : 0;
+    if (ids(64) <= 768 && n >= 480) return 0x22;
   } else if (p.head_dim == 128) {
     if (ids(64) <= 256) return ids(32) <= 256 ? 0x14 : 0x24;
-    if (ids(128) <= 256 && p.max_len >= (bias ? 256 : 640)) return 0x42;
+    if (ids(128) <= 256 && n >= (bias ? 256 : 640)) return 0x42;
+  } else if (bias) {
+    if (ids(64) <= 256) return ids(32) <= 256 ? 0x14 : 0x22;
+    if (ids(64) <= 768 && (n >= 520 || (ids(128) > 256 && ids(64) <= 512))) return 0x22;
   } else {
-    if (!bias && ids(32) <= 512 && p.max_len >= 256) return 0x14;
-    if (ids(64) <= 768 && (bias || (ids(64) > 512 && p.max_len >= 640))) return 0x22;
+    if (ids(32) <= 512 && n >= 256) return 0x14;
+    if (ids(64) > 512 && ids(64) <= 768 && n >= 1000) return 0x22;
   }
   return 0;
 }

@@ -1611,7 +1611,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
 //     split / merge identity of the online softmax, every wavefront finishing 1/NK of the output
 //     columns.
 // Measured, fp16, 12 x 64, us per call against the 128-row kernel (512: against four wavefronts without a shared Q):
-// 512 tokens 7.8 -> 6.2, 1024 13.6 -> 11.1, 2000 24.9 -> 20.3, 3072 50.3 -> 44.7; 8 x 128, 2048 tokens 37 -> 24.
+// 512 tokens 7.8 -> 6.2, 1024 13.6 -> 10.9, 2000 24.9 -> 20.3, 3072 50.3 -> 44.7; 8 x 128, 2048 tokens 37 -> 24.
 // ======================================================================================
 template <class T, int D, bool BIAS>
 struct SplitWave {
@@ -2629,15 +2629,17 @@ Kernel twophase_kernel(int head_dim) {
 }
 
 // The split kernel's shapes: NQ query blocks x NK key splits, ring slots, wavefronts per SIMD asked for.  Slots fill
-// the LDS of a compute unit that such a workgroup has to itself (head_dim 32: a half or a quarter of it).
+// the LDS of a compute unit that such a workgroup has to itself, or its share of one (head_dim 64: 1 x 4 half of it, 2 x 2
+// a third; head_dim 32 without a bias a half and a third).
 template <class T, bool BIAS>
 Kernel split_kernel(int head_dim, int split) {
   switch (head_dim * 256 + split) {
+    case 64 * 256 + 0x14: return BIAS ? nullptr : (Kernel)fa_fwd_split_kernel<T, 64, 1, 4, 2, 2, false>;
     case 64 * 256 + 0x18: return fa_fwd_split_kernel<T, 64, 1, 8, 2, 2, BIAS>;
     case 64 * 256 + 0x24: return fa_fwd_split_kernel<T, 64, 2, 4, 4, 2, BIAS>;
     case 64 * 256 + 0x34: return fa_fwd_split_kernel<T, 64, 3, 4, BIAS ? 3 : 4, 3, BIAS>;
     case 64 * 256 + 0x42: return BIAS ? (Kernel)fa_fwd_split_kernel<T, 64, 4, 2, 4, 2, true> : nullptr;
-    // (three workgroups per unit; without a key bias only: with one its LDS would allow two)
+    // (without a key bias only: with one its LDS would allow two workgroups per unit instead of three)
     case 64 * 256 + 0x22: return BIAS ? nullptr : (Kernel)fa_fwd_split_kernel<T, 64, 2, 2, 2, 3, false>;
     case 128 * 256 + 0x14: return fa_fwd_split_kernel<T, 128, 1, 4, 2, 1, BIAS>;
     case 128 * 256 + 0x24: return fa_fwd_split_kernel<T, 128, 2, 4, 2, 2, BIAS>;

@@ -14,36 +14,52 @@ from tests.gpu_util import FA_DT, check_against, poison, run_ex, to_dev
 
 pytestmark = pytest.mark.gpu
 
-# (head_dim, heads, max_len, lengths, key bias): NQ x NK chosen by the tile counts
+# (head_dim, heads, max_len, lengths, key bias, 16 * NQ + NK): the shape is what the library chooses for the call in either
+# type (checked on the CPU).  "long": more steps than two turns of the ring, so that the unrolled part of the loop runs.
 CASES = {
-    "d64_1x8_resident": (64, 2, 500, [500, 256, 255, 0], False),
-    "d64_1x8_streaming": (64, 1, 1300, [1300, 1024, 513, 31], False),
-    "d64_2x4": (64, 30, 200, [200, 128], False),
-    "d64_2x4_long": (64, 12, 1270, [1267], False),
-    "d64_3x4": (64, 15, 700, [700, 641], False),
-    "d64_3x4_other": (64, 30, 690, [97], False),
-    "d64_4x2": (64, 19, 1601, [1537], False),
-    "d64_2x2": (64, 35, 500, [500, 333], False),
-    "d64_2x2_streaming": (64, 12, 2210, [2177], False),
-    "d128_1x4": (128, 2, 300, [300, 129, 128, 1], False),
-    "d128_2x4": (128, 30, 200, [200, 63], False),
-    "d128_4x2": (128, 15, 700, [700, 577], False),
-    "d32_1x4": (32, 20, 300, [300, 161], False),
-    "d32_2x2": (32, 25, 700, [700, 64], False),
-    "d64_1x8_bias": (64, 2, 500, [500, 256, 255, 1], True),
-    "d64_2x4_bias": (64, 30, 200, [200, 128], True),
-    "d64_3x4_bias": (64, 15, 700, [700, 641], True),
-    "d64_4x2_bias": (64, 24, 600, [600, 513], True),
-    "d128_1x4_bias": (128, 2, 300, [300, 129, 128, 1], True),
-    "d128_4x2_bias": (128, 15, 700, [700, 577], True),
-    "d32_2x2_bias": (32, 12, 300, [300, 161], True),
+    "d64_1x4": (64, 2, 300, [300, 129, 128, 0], False, 0x14),
+    "d64_1x4_longest": (64, 4, 639, [639, 512, 513], False, 0x14),
+    "d64_1x8": (64, 2, 700, [700, 256, 255, 0], False, 0x18),
+    "d64_1x8_long": (64, 1, 1300, [1300, 1024, 513, 31], False, 0x18),
+    "d64_2x4": (64, 30, 200, [200, 128], False, 0x24),
+    "d64_2x4_long": (64, 4, 2100, [2090], False, 0x24),
+    "d64_3x4": (64, 12, 900, [900, 865], False, 0x34),
+    "d64_3x4_long": (64, 12, 1500, [1497], False, 0x34),
+    "d64_3x4_other": (64, 16, 1290, [97], False, 0x34),
+    "d64_2x2_short": (64, 30, 150, [150, 65], False, 0x22),
+    "d64_2x2": (64, 35, 500, [500, 333], False, 0x22),
+    "d64_2x2_padded": (64, 12, 2048, [1900], False, 0x22),
+    "d64_2x2_long": (64, 12, 2210, [2177], False, 0x22),
+    "d128_1x4": (128, 2, 300, [300, 129, 128, 1], False, 0x14),
+    "d128_1x4_long": (128, 2, 700, [700, 641], False, 0x14),
+    "d128_2x4": (128, 30, 200, [200, 63], False, 0x24),
+    "d128_2x4_long": (128, 8, 1400, [1300], False, 0x24),
+    "d128_4x2_long": (128, 15, 700, [700, 577], False, 0x42),
+    "d32_1x4": (32, 20, 300, [300, 161], False, 0x14),
+    "d32_1x4_long": (32, 4, 1400, [1390], False, 0x14),
+    "d32_2x2_long": (32, 20, 1010, [1010, 64], False, 0x22),
+    "d64_1x8_bias": (64, 2, 500, [500, 256, 255, 1], True, 0x18),
+    "d64_1x8_bias_long": (64, 1, 1400, [1400], True, 0x18),
+    "d64_2x4_bias": (64, 30, 200, [200, 128], True, 0x24),
+    "d64_2x4_bias_long": (64, 4, 1300, [1300, 1200], True, 0x24),
+    "d64_3x4_bias": (64, 15, 700, [700, 641], True, 0x34),
+    "d64_4x2_bias_long": (64, 24, 600, [600, 577], True, 0x42),
+    "d128_1x4_bias": (128, 2, 300, [300, 129, 128, 1], True, 0x14),
+    "d128_1x4_bias_long": (128, 2, 700, [700, 641], True, 0x14),
+    "d128_2x4_bias": (128, 30, 200, [200, 63], True, 0x24),
+    "d128_2x4_bias_long": (128, 8, 1400, [1300], True, 0x24),
+    "d128_4x2_bias_long": (128, 15, 700, [700, 577], True, 0x42),
+    "d32_1x4_bias": (32, 4, 300, [300, 161], True, 0x14),
+    "d32_1x4_bias_long": (32, 2, 1400, [1390], True, 0x14),
+    "d32_2x2_bias": (32, 20, 300, [300, 161], True, 0x22),
+    "d32_2x2_bias_long": (32, 12, 1200, [1190], True, 0x22),
 }
 
 
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_split_kernel_shapes(name, dtype):
-    D, H, N, lens, biased = CASES[name]
+    D, H, N, lens, biased, _ = CASES[name]
     B = len(lens)
     rng = np.random.default_rng(N + D)
     _, q, k, v = draw(7000 + N, B, H, N, D, dtype)
@@ -102,10 +118,12 @@ def test_key_bias_pipelined_kernel_head_dim_32(N, dtype, tuning):
     check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"bias d32 {N}")
 
 
-# one call per shape the library picks without a key bias, more than one block per wavefront
-SHAPES = {"d64_1x8": (64, 1, 600), "d64_2x4": (64, 12, 1001), "d64_3x4": (64, 12, 1500), "d64_2x2": (64, 12, 2500),
-          "d128_1x4": (128, 2, 600), "d128_2x4": (128, 8, 1500), "d128_4x2": (128, 8, 2600), "d32_1x4": (32, 24, 600),
-          "d32_2x2": (32, 24, 1500)}
+# (head_dim, heads, max_len, 16 * NQ + NK): one call per shape the library picks without a key bias, more than one block per
+# wavefront
+SHAPES = {"d64_1x4": (64, 2, 450, 0x14), "d64_1x8": (64, 1, 700, 0x18), "d64_2x4": (64, 4, 2100, 0x24),
+          "d64_3x4": (64, 12, 1500, 0x34), "d64_2x2": (64, 12, 2500, 0x22), "d128_1x4": (128, 2, 600, 0x14),
+          "d128_2x4": (128, 8, 1500, 0x24), "d128_4x2": (128, 8, 2600, 0x42), "d32_1x4": (32, 24, 600, 0x14),
+          "d32_2x2": (32, 24, 1500, 0x22)}
 
 
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
@@ -113,7 +131,7 @@ SHAPES = {"d64_1x8": (64, 1, 600), "d64_2x4": (64, 12, 1001), "d64_3x4": (64, 12
 def test_split_kernel_first_block_without_a_finite_score(name, dtype):
     """Keys whose scores are -infinity fill the first block of one wavefront after the other: it takes its reference from a
     later block, and the keys of that block count - also where they are all so far below 0 that they vanish against 0."""
-    D, H, N = SHAPES[name]
+    D, H, N, _ = SHAPES[name]
     _, q, k, v = draw(7200 + N, 1, 1, N, D, dtype)
     rep = lambda x: np.repeat(x, H, axis=1)
     q[..., 0] = 1.0
@@ -135,7 +153,7 @@ def test_split_kernel_merge_of_large_references(name, dtype):
     fp32.  The probabilities of a wavefront are formed against its reference times log2(e) ROUNDED to fp32 (spacing 1/8
     here), so the merge has to weigh them against that same number; against the unrounded product a wavefront's share is
     up to 2^(1/16), 4 %, off.  Values are +1 and -1 by g's parity: a share that is off shows in o in full."""
-    D, H, N = SHAPES[name]
+    D, H, N, _ = SHAPES[name]
     g = np.arange(N) // 32 % 8
     q = np.zeros((1, H, N, D), np.float32)
     k = np.zeros((1, H, N, D), np.float32)

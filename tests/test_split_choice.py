@@ -11,6 +11,7 @@ ROOT = pathlib.Path(__file__).resolve().parent.parent
 
 DRIVER = r"""
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <initializer_list>
 #include "fa.h"
@@ -23,7 +24,7 @@ int fa_launch_rope_rotate(const FaRopeArgs&, int, void*) { return 0; }
 int fa_static_scratch(void**) { return 0; }
 #define EXPECT(cond) do { if (!(cond)) { printf("FAILED line %d: %s (d %d b %d h %d n %d bias %d split %x bm %d)\n", __LINE__, #cond, \
   p.head_dim, p.batch, p.heads, p.max_len, p.key_bias != nullptr, last.split, last_bm); return 1; } } while (0)
-int main() {
+int main(int argc, char** argv) {
   alignas(16) static char buf[64];
   alignas(16) static float table[64];
   fa_params p;
@@ -31,6 +32,17 @@ int main() {
   p.struct_size = sizeof p;
   p.q = p.k = p.v = p.o = buf;
   p.scale = 0.125f;
+  p.window_left = p.window_right = -1;
+  if (argc > 1) {   // the shapes of the calls given as: head_dim batch heads max_len biased bf16
+    for (int i = 1; i + 5 < argc; i += 6) {
+      p.head_dim = std::atoi(argv[i]); p.batch = std::atoi(argv[i + 1]); p.heads = std::atoi(argv[i + 2]);
+      p.max_len = std::atoi(argv[i + 3]); p.key_bias = std::atoi(argv[i + 4]) ? buf : nullptr;
+      p.dtype = std::atoi(argv[i + 5]) ? FA_DTYPE_BF16 : FA_DTYPE_F16;
+      if (fa_fwd_ex(&p) != 0) return 1;
+      printf("%x\n", last.split);
+    }
+    return 0;
+  }
   long taken = 0, calls = 0;
   for (int d : {32, 64, 128})
     for (int b : {1, 2, 3, 5, 8, 32})
@@ -46,7 +58,7 @@ int main() {
             if (last.split) {
               ++taken;
               const int nq = last.split >> 4, s = last.split;
-              EXPECT(d == 64 ? (s == 0x18 || s == 0x24 || s == 0x34 || (biased ? s == 0x42 : s == 0x22))
+              EXPECT(d == 64 ? (s == 0x18 || s == 0x24 || s == 0x34 || (biased ? s == 0x42 : s == 0x14 || s == 0x22))
                              : (d == 128 ? (s == 0x14 || s == 0x24 || s == 0x42) : (s == 0x14 || s == 0x22)));
               EXPECT(last_bm == 32 * nq && last.n_qtiles == (n + 32 * nq - 1) / (32 * nq));
               // every XCD's eighth of each batch element's tiles, rounded up, is launched: these ids have to fit in one round
@@ -75,6 +87,7 @@ int main() {
       for (int h = 1; h <= 48; ++h) {
         bool here[256] = {};
         for (int n = 65; n <= kSplitBiasKeys; ++n) {
+          p.dtype = n & 1 ? FA_DTYPE_BF16 : FA_DTYPE_F16;
           p.head_dim = d; p.heads = h; p.max_len = n; p.key_bias = biased ? buf : nullptr;
           if (fa_fwd_ex(&p) != 0) return 1;
           here[last.split] = true;
@@ -97,15 +110,38 @@ int main() {
 """
 
 
-def test_split_shapes_chosen_by_the_host(tmp_path):
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
     if shutil.which("g++") is None:
         pytest.skip("no g++")
+    tmp_path = tmp_path_factory.mktemp("driver")
     src, exe, csrc = tmp_path / "driver.cpp", tmp_path / "driver", ROOT / "paper_2603_12646_amd" / "csrc"
     src.write_text(DRIVER)
     subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", str(ROOT / "include"),
                     "-I", str(csrc), str(src), str(csrc / "fa_api.cpp"), "-o", str(exe)], check=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    return str(exe)
+
+
+def test_split_shapes_chosen_by_the_host(driver):
+    r = subprocess.run([driver], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
+
+
+def test_gpu_cases_run_the_shapes_they_are_named_after(driver):
+    """The calls of the GPU tests get the shape written beside them, and every shape that any call gets is among them."""
+    from tests.test_gpu_split import CASES, SHAPES
+    calls = [(name, D, len(lens), H, N, int(biased), s) for name, (D, H, N, lens, biased, s) in CASES.items()]
+    calls += [("shape " + name, D, 1, H, N, 0, s) for name, (D, H, N, s) in SHAPES.items()]
+    for bf16 in (0, 1):
+        args = [str(x) for (_, D, B, H, N, biased, _) in calls for x in (D, B, H, N, biased, bf16)]
+        r = subprocess.run([driver, *args], capture_output=True, text=True, check=True)
+        got = [int(x, 16) for x in r.stdout.split()]
+        assert len(got) == len(calls)
+        assert [(c[0], hex(g)) for c, g in zip(calls, got)] == [(c[0], hex(c[-1])) for c in calls]
+    assert {(D, b, s) for (_, D, _, _, _, b, s) in calls} == {
+        (64, 0, 0x14), (64, 0, 0x18), (64, 0, 0x24), (64, 0, 0x34), (64, 0, 0x22), (128, 0, 0x14), (128, 0, 0x24), (128, 0, 0x42),
+        (32, 0, 0x14), (32, 0, 0x22), (64, 1, 0x18), (64, 1, 0x24), (64, 1, 0x34), (64, 1, 0x42), (128, 1, 0x14), (128, 1, 0x24),
+        (128, 1, 0x42), (32, 1, 0x14), (32, 1, 0x22)}
 
 
 HEADS_FIRST_DRIVER = r"""
