@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2603_12646_amd as fa
-from oracle.attention_oracle import attention_oracle
+from oracle.attention_oracle import attention_oracle, attention_oracle_rows
 from workloads import draw, round_to_storage
 
 from tests.gpu_util import FA_DT, check_against, poison, run_ex, to_dev
@@ -167,3 +167,30 @@ def test_split_kernel_merge_of_large_references(name, dtype):
     # a probability is rounded to 2^-12 (fp16) or 2^-9 (bf16) of itself, o likewise
     assert np.abs(o - want).max() <= (2.0 ** -11 if dtype == "fp16" else 2.0 ** -8), np.abs(o - want).max()
     assert np.abs(lse - (1024000.0 + np.log(w.sum()))).max() <= 0.5   # eight fp32 spacings there
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("D,H,N,tuning", [(64, 1, 600, fa.FA_TUNE_BM_128), (64, 1, 600, fa.FA_TUNE_BM_256), (64, 12, 6000, 0),
+                                          (128, 1, 600, fa.FA_TUNE_BM_128), (128, 1, 600, fa.FA_TUNE_BM_256),
+                                          (32, 1, 600, fa.FA_TUNE_BM_128), (32, 1, 600, fa.FA_TUNE_BM_256)])
+def test_pipelined_kernel_first_block_without_a_finite_score(D, H, N, tuning, dtype):
+    """The same on the kernels that do not split the keys: rows whose scores against the first 32 keys are -infinity take
+    their reference from a later block, also where all scores are far below 0 or where those of the second half, or of the
+    ragged last tile (whose masked code refreshes by another rule), are higher."""
+    _, q, k, v = draw(7300 + N, 1, 1, N, D, dtype)
+    rep = lambda x: np.repeat(x, H, axis=1)
+    q[..., 0], q[..., 1] = 1.0, 40.0
+    k[..., 0], k[..., 1] = 0.0, 0.0
+    k[..., :32, 0] = -np.inf
+    for first, base, scale in ((N + 1, 0.0, D ** -0.5), (N // 2, 0.0, D ** -0.5), (N - 20, 0.0, D ** -0.5),
+                               (N + 1, -40.0, D ** -0.5), (N + 1, 40.0, D ** -0.5), (N // 2, -40.0, 1.0)):
+        k2, q2 = k.copy(), q.copy()
+        if scale == 1.0:
+            q2[..., 2:] *= 0.125                      # (the lowest reference is another one there)
+        k2[..., 1] = base                             # every score moved by 40 * base * scale
+        k2[..., first:, 1] = 4.0                      # 160 * scale higher from key `first` on
+        rows = np.unique(np.concatenate([np.arange(0, 64), np.arange(N - 40, N)]))
+        o_ref, lse_ref = attention_oracle_rows(q2, k2, v, 0, 0, rows, N, scale)
+        o, lse = run_ex(rep(q2), rep(k2), rep(v), None, dtype, scale, tuning=tuning)
+        check_against(o[:, :1, rows], lse[:, :1, rows], o_ref[None, None], lse_ref[None, None], None, dtype,
+                      label=f"pipelined D{D} {tuning} from {first} base {base} scale {scale}")
