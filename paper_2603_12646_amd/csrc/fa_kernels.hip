@@ -300,14 +300,14 @@ struct RowState {
 
 // Refresh the reference of rows whose block maximum ran away from it.  Each lane
 // decides on its own row's evidence only, so a row's arithmetic never depends on
-// which other rows share its wavefront.  REF_SET: every row has a reference already.
-template <bool REF_SET = false, int NQB, int D>
+// which other rows share its wavefront.
+template <int NQB, int D>
 __device__ __forceinline__ void rescale_rows(RowState<NQB, D>& st, int qb, bool refresh, float tmax, float c) {
   const float m_new = refresh ? tmax : st.m_ref[qb];
-  const float mc_new = (!REF_SET && m_new == -INFINITY) ? 0.f : m_new * c;
+  const float mc_new = (m_new == -INFINITY) ? 0.f : m_new * c;
   // nothing has been accumulated while the old reference is -inf: keep 0 * alpha out of
   // reach of an infinite alpha
-  const float alpha = (!REF_SET && st.m_ref[qb] == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(st.mc[qb] - mc_new);
+  const float alpha = (st.m_ref[qb] == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(st.mc[qb] - mc_new);
   st.m_ref[qb] = m_new;
   st.mc[qb] = mc_new;
   st.lsum[qb] *= alpha;
@@ -2337,8 +2337,9 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       // units then need no "has this row a reference yet" test.  With a key bias block 0 can be
       // masked out entirely, so those kernels keep the test.
       // No score above -infinity there (infinite inputs): the lowest reference whose product with c is finite, so that
-      // the first score that is one overflows against it and refreshes it.
-      const float lowest = c > 1.f ? -3e38f / c : -3.4028234e38f;
+      // the first score that is one overflows against it and refreshes it.  (As a median, which leaves the loop as the compiler
+      // schedules it without: a maximum cost batches of 578 - 2048 tokens 0.9 %, this 0.3 - 0.5 %.)
+      const float lowest = -3.4e38f * fminf(1.f, __builtin_amdgcn_rcpf(c));
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
         floatx16 s0 = sA;
@@ -2351,9 +2352,9 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         float t0 = fmaxf(s0[0], s0[1]);
 #pragma unroll
         for (int r = 2; r < 16; r += 2) t0 = fmaxf(fmaxf(t0, s0[r]), s0[r + 1]);
-        const float tmax = max_xor32(t0);
-        st.m_ref[qb] = fmaxf(tmax, lowest);
-        st.mc[qb] = st.m_ref[qb] * c;
+        const float tmax = __builtin_amdgcn_fmed3f(max_xor32(t0), lowest, INFINITY);
+        st.m_ref[qb] = tmax;
+        st.mc[qb] = tmax == -INFINITY ? 0.f : tmax * c;
       }
     }
     __syncthreads();  // stage 1 is refilled during iteration 0
@@ -2365,10 +2366,6 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     auto softmax_block = [&](const floatx16& sv, float mcq, uint32_t (&pk)[8], float& blk) {
       prob_block<T, false, BIAS_LAST>(sv, c, mcq, 0xFFFFu, pk, blk);
     };
-    // Without a bias every row has a reference, and the refresh needs no test for one.  Left out in fp16 only, where the
-    // loop around it is scheduled better for that (one sequence of 8K: 201.3 us against 202.6); in bf16 it is the reverse
-    // (three of 16K: 1534 against 1520).
-    constexpr bool kRefSet = !BIAS && std::is_same<T, F16>::value;
     // One unit.  QB: query block of the current scores; NQ: query block of the next
     // unit; PQ: query block of the previous unit; LOAD: this unit starts a new key block
     // for both matrix products (fragments come from kblk / vblk), otherwise the
@@ -2413,7 +2410,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         for (int r = 2; r < 16; r += 2) t0 = fmaxf(fmaxf(t0, s_cur[r]), s_cur[r + 1]);
         const float tmax = max_xor32(t0);
         // the accumulator of this query block already holds P.V of all earlier key blocks
-        rescale_rows<kRefSet>(st, QB, row_trig, tmax, c);
+        rescale_rows(st, QB, row_trig, tmax, c);
         softmax_block(s_cur, st.mc[QB], pk, blk);
       }
       st.lsum[QB] += blk;
