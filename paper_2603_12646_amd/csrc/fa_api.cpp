@@ -126,8 +126,9 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
 // from a sweep of 1 - 16 sequences x 4 - 32 heads x 65 - 4096 tokens, full and at 0.7 and 0.45 of max_len, in both types;
 // us per call, the 128 / 256-row kernels -> the shape:
 //   head_dim 64   32 rows on four wavefronts (two workgroups per unit): 12 heads x 110 tokens 6.0 -> 4.8, 200 6.7 -> 5.3,
-//                 380 8.3 -> 6.0, 512 9.0 -> 6.3 (on eight 6.3; 230 of 512 5.4, on eight 6.1); on eight from 640: 4 heads x
-//                 1024 13.8 -> 8.0.  At 64 tokens there is nothing to split.
+//                 380 8.3 -> 6.0, 230 of 512 5.4 (on eight 6.1); on eight from 640, 4 heads x 1024 13.8 -> 8.0, and without
+//                 lengths, where every row is there, from 385: 512 9.0 -> 6.3 (on four 6.3 - 6.4), 540 6.9 (7.2), but 384
+//                 6.2 (5.8).  At 64 tokens there is nothing to split.
 //                 64 rows: on four wavefronts, three workgroups per unit, 850 12.5 -> 10.4, 1024 13.6 -> 10.9, 1250
 //                 16.1 -> 12.4; on eight where the workgroups are short, 3 x 230 7.3 -> 6.5 (four: 6.8), or nearly alone, 4
 //                 heads x 3500 36.4 -> 23.0 (26.3).
@@ -156,7 +157,7 @@ int choose_split(const fa_params& p) {
     if (ids(96) <= 256 && n >= 448) return 0x34;
     if (ids(128) <= 256 && n >= 560) return 0x42;
   } else if (p.head_dim == 64) {
-    if (ids(32) <= 256) return n < 640 ? 0x14 : 0x18;
+    if (ids(32) <= 256) return n < (p.seq_lens ? 640 : 385) ? 0x14 : 0x18;
     if (ids(64) <= 256) return n >= 1600 || (n >= 200 && n < 560) ? 0x24 : 0x22;
     if (ids(96) <= 256 && n >= (one ? 1200 : 860)) return 0x34;
     if (ids(128) <= 256) return n >= (fp16 ? (one ? 1000 : 700) : (one ? 2000 : 1100)) ? 0x22 : 0;

@@ -33,11 +33,12 @@ int main(int argc, char** argv) {
   p.q = p.k = p.v = p.o = buf;
   p.scale = 0.125f;
   p.window_left = p.window_right = -1;
-  if (argc > 1) {   // the shapes of the calls given as: head_dim batch heads max_len biased bf16
-    for (int i = 1; i + 5 < argc; i += 6) {
+  if (argc > 1) {   // the shapes of the calls given as: head_dim batch heads max_len biased bf16 lengths
+    for (int i = 1; i + 6 < argc; i += 7) {
       p.head_dim = std::atoi(argv[i]); p.batch = std::atoi(argv[i + 1]); p.heads = std::atoi(argv[i + 2]);
       p.max_len = std::atoi(argv[i + 3]); p.key_bias = std::atoi(argv[i + 4]) ? buf : nullptr;
       p.dtype = std::atoi(argv[i + 5]) ? FA_DTYPE_BF16 : FA_DTYPE_F16;
+      p.seq_lens = std::atoi(argv[i + 6]) ? (const int32_t*)table : nullptr;
       if (fa_fwd_ex(&p) != 0) return 1;
       printf("%x\n", last.split);
     }
@@ -88,6 +89,7 @@ int main(int argc, char** argv) {
         bool here[256] = {};
         for (int n = 65; n <= kSplitBiasKeys; ++n) {
           p.dtype = n & 1 ? FA_DTYPE_BF16 : FA_DTYPE_F16;
+          p.seq_lens = n & 2 ? (const int32_t*)table : nullptr;
           p.head_dim = d; p.heads = h; p.max_len = n; p.key_bias = biased ? buf : nullptr;
           if (fa_fwd_ex(&p) != 0) return 1;
           here[last.split] = true;
@@ -130,15 +132,16 @@ def test_split_shapes_chosen_by_the_host(driver):
 def test_gpu_cases_run_the_shapes_they_are_named_after(driver):
     """The calls of the GPU tests get the shape written beside them, and every shape that any call gets is among them."""
     from tests.test_gpu_split import CASES, SHAPES
-    calls = [(name, D, len(lens), H, N, int(biased), s) for name, (D, H, N, lens, biased, s) in CASES.items()]
-    calls += [("shape " + name, D, 1, H, N, 0, s) for name, (D, H, N, s) in SHAPES.items()]
+    calls = [(name, D, len(lens), H, N, int(biased), 1, s) for name, (D, H, N, lens, biased, s) in CASES.items()]
+    calls += [("shape " + name, D, 1, H, N, 0, 0, s) for name, (D, H, N, s) in SHAPES.items()]
     for bf16 in (0, 1):
-        args = [str(x) for (_, D, B, H, N, biased, _) in calls for x in (D, B, H, N, biased, bf16)]
+        args = [str(x) for (_, D, B, H, N, biased, lengths, _) in calls
+                for x in (D, B, H, N, biased, bf16, lengths)]
         r = subprocess.run([driver, *args], capture_output=True, text=True, check=True)
         got = [int(x, 16) for x in r.stdout.split()]
         assert len(got) == len(calls)
         assert [(c[0], hex(g)) for c, g in zip(calls, got)] == [(c[0], hex(c[-1])) for c in calls]
-    assert {(D, b, s) for (_, D, _, _, _, b, s) in calls} == {
+    assert {(D, b, s) for (_, D, _, _, _, b, _, s) in calls} == {
         (64, 0, 0x14), (64, 0, 0x18), (64, 0, 0x24), (64, 0, 0x34), (64, 0, 0x22), (128, 0, 0x14), (128, 0, 0x24), (128, 0, 0x42),
         (32, 0, 0x14), (32, 0, 0x22), (64, 1, 0x18), (64, 1, 0x24), (64, 1, 0x34), (64, 1, 0x42), (128, 1, 0x14), (128, 1, 0x24),
         (128, 1, 0x42), (32, 1, 0x14), (32, 1, 0x22)}
