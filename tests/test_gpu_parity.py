@@ -34,9 +34,9 @@ TUNINGS = {
     "mixed_linear": fa.FA_TUNE_BM_MIXED | fa.FA_TUNE_MAP_LINEAR,
     "mixed_xcd": fa.FA_TUNE_BM_MIXED | fa.FA_TUNE_MAP_XCD,
 }
-# Small global calls take the key-split kernel by themselves (at most 256 blocks of 32 query
-# rows, more than 128 tokens); the small-shape tests below therefore run three times: the
-# library's choice, the pipelined kernel forced, the key-split kernel forced; and with the
+# Small global calls of more than 64 tokens take the split kernel by themselves, in a shape that
+# depends on the call; the small-shape tests below therefore run three times: the library's
+# choice, the pipelined kernel forced, the split kernel's eight-wavefront shape forced; and with the
 # 12- and 8-wavefront shapes of the pipelined kernel (384 and 512 rows per workgroup).
 GLOBAL_KERNELS = {"auto": 0, "bm128": fa.FA_TUNE_BM_128, "bm32": fa.FA_TUNE_BM_32,
                   "bm384": fa.FA_TUNE_BM_384, "bm512": fa.FA_TUNE_BM_512, "mixed": fa.FA_TUNE_BM_MIXED}
@@ -259,16 +259,16 @@ def test_strided_inputs_global_layer(kern):
 
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 @pytest.mark.parametrize("B,H,N,lens", [
-    (1, 1, 2100, [2049]),       # 17 blocks per wavefront: the ring of four slots is refilled many times
+    (1, 1, 2100, [2049]),       # nine steps of 256 keys: the ring of two slots is refilled many times
     (1, 2, 700, [40]),          # first ring requested from max_len, sequence far shorter: blocks fetched and dropped
-    (2, 1, 640, [97, 640]),     # wavefront 3 has one partial block / five full ones
-    (1, 3, 130, [65]),          # wavefront 3 (and 2 for most rows) has no block at all
+    (2, 1, 640, [97, 640]),     # wavefront 3 has one block of one key / three full ones
+    (1, 3, 130, [65]),          # wavefronts 3 - 7 have no block at all, 2 one of one key
     (1, 1, 4128, [4128]),       # exactly 129 blocks
     (3, 1, 513, [0, 513, 1]),   # empty sequence, one key
 ])
 def test_key_split_kernel_ring_and_ragged_ends(dtype, B, H, N, lens):
-    """The key-split kernel forced on shapes that exercise its private ring, the early
-    request of blocks past the sequence end, wavefronts without work, and the merge of
+    """The split kernel forced (32 rows, eight wavefronts) on shapes that exercise its ring, the
+    early request of blocks past the sequence end, wavefronts without work, and the merge of
     partial results when some of them are empty; padded rows hold NaN."""
     _, q, k, v = draw(1400 + N, B, H, N, 64, dtype)
     o_ref, lse_ref = attention_oracle(q, k, v, lens, 0.125)
@@ -620,8 +620,9 @@ def _random_bias(seed, B, N, dtype, holes=True, gain=2.0):
 @pytest.mark.parametrize("left,right", [(-1, -1), (63, 64), (0, 5), (70, -1)])
 def test_key_bias_random_values_and_holes(D, dtype, left, right, tuning):
     """The operator's pad_bias input (paper Sec. 4.1.3, Eq. 1) with arbitrary values and
-    -inf holes, on top of sequence lengths and windows.  Global layers of head_dim 64 / 128
-    take the pipelined kernel (128- and 256-row tiles), everything else the masked kernel."""
+    -inf holes, on top of sequence lengths and windows.  Global layers take the split kernel or,
+    forced, the pipelined one (128- and 256-row tiles), the 63/64 window the resident or the
+    two-phase kernel, everything else the masked kernel."""
     B, H, N = 2, 2, 333
     _, q, k, v = draw(800 + D, B, H, N, D, dtype)
     lens = [333, 150]
@@ -635,8 +636,9 @@ def test_key_bias_random_values_and_holes(D, dtype, left, right, tuning):
 @pytest.mark.parametrize("N", [1, 31, 33, 64, 65, 127, 129, 257, 640])
 @pytest.mark.parametrize("D", [64, 128])
 def test_key_bias_global_lengths_around_tile_edges(D, N):
-    """Pipelined kernel with a bias: prologue only, tail only, several tiles plus a tail;
-    negative scale and scale 0 as well (scale 0 falls back to the masked kernel)."""
+    """Pipelined kernel with a bias (and what the library takes by itself, the split kernel from
+    65 tokens): prologue only, tail only, several tiles plus a tail; negative scale and scale 0 as
+    well (scale 0 falls back to the masked kernel)."""
     B, H = 2, 2
     for dtype in ("fp16", "bf16"):
         _, q, k, v = draw(820 + N + D, B, H, N, D, dtype)
@@ -646,9 +648,10 @@ def test_key_bias_global_lengths_around_tile_edges(D, N):
         lens = [N, max(1, N - 7)]
         for scale in (0.11, -0.2, 0.0):
             o_ref, lse_ref = attention_oracle(q, k, v, lens, scale, key_bias=bias)
-            o, lse = run_ex(q, k, v, lens, dtype, scale, key_bias=bias)
-            check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True,
-                          label=f"bias {dtype} D={D} N={N} scale={scale}")
+            for tuning in (0, fa.FA_TUNE_BM_128):
+                o, lse = run_ex(q, k, v, lens, dtype, scale, key_bias=bias, tuning=tuning)
+                check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True,
+                              label=f"bias {dtype} D={D} N={N} scale={scale} {tuning}")
 
 
 def test_key_bias_8k_sampled_rows():
@@ -771,7 +774,7 @@ def test_named_large_configs_sampled_rows(name):
 def test_quarter_million_tokens_sampled_rows(dtype, window, tuning):
     """Eight times the longest named workload: one head of 262 144 tokens (a key-padding tail
     of 1 000), where row offsets pass 2^24 bytes and a row's sum runs over 261 144 keys.
-    Global (pipelined and key-split kernels), the 128-key window and a 700-key window (ring
+    Global (pipelined and split kernels), the 128-key window and a 700-key window (ring
     kernel); sampled rows against the oracle, padded rows exhaustively."""
     B, H, N, D = 1, 1, 262144, 64
     n = N - 1000

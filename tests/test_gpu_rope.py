@@ -90,7 +90,7 @@ def test_rope_zero_angles_leave_the_result_bit_identical():
     _, q, k, v = draw(9300, B, H, N, D, "bf16")
     ones, zeros = np.ones((N, D // 2), np.float32), np.zeros((N, D // 2), np.float32)
     # (the same kernel on both sides: a call this small without a rotation would otherwise take the
-    # key-split / resident pipelined kernels, whose summation order differs)
+    # split / resident pipelined kernels, whose summation order differs)
     for left, right, tuning in ((-1, -1, fa.FA_TUNE_BM_128), (63, 64, fa.FA_TUNE_WIN_TWO_PHASE), (70, -1, fa.FA_TUNE_V_SCALAR)):
         o1, lse1 = run_rope(q, k, v, lens, "bf16", 0.125, ones, zeros, left, right, tuning)
         qd, kd, vd = to_dev(q, "bf16"), to_dev(k, "bf16"), to_dev(v, "bf16")
@@ -167,7 +167,7 @@ def test_rope_rotation_ahead_of_the_call_with_lent_scratch(D, B, H, N, lens, dty
     scale = 1.0 / np.sqrt(D)
     need = fa.fa_rope_scratch_bytes(B, H, N, D)
     assert need == 2 * B * H * N * D * 2
-    # the pipelined kernel on both sides (a small plain call would take the key-split kernel, whose
+    # the pipelined kernel on both sides (a small plain call would take the split kernel, whose
     # summation order differs); the 8K case is left to the library: mixed shapes against 128 rows
     tun = fa.FA_TUNE_BM_128 if N <= 1024 else 0
     o_in, lse_in = run_rope(q, k, v, lens, dtype, scale, c32, s32, tuning=tun)
