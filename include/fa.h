@@ -186,8 +186,10 @@ typedef struct fa_params {
                                 layers: 8 wavefronts x 32 rows on one pair of K/V stages */
 #define FA_TUNE_BM_32 0x3u   /* 32 query rows, eight wavefronts split the keys (global layers of
                                 head_dim 64 without a key bias; ignored otherwise).  The library
-                                picks this or another shape that splits the keys by itself when
-                                the call's query tiles number at most one per compute unit. */
+                                picks this or another shape that splits the keys by itself for
+                                small global calls of more than 64 tokens: up to one workgroup
+                                per compute unit, or two or three where the shape allows them,
+                                by lines that depend on head size, type, key bias and length. */
 #define FA_TUNE_BM_384 0x4u  /* 12 wavefronts x 32 query rows sharing one K/V stage (global layers of
                                 head_dim 64 without a key bias; ignored otherwise) */
 #define FA_TUNE_BM_512 0x5u  /* 8 wavefronts x 64 query rows sharing one K/V stage (same restriction) */

@@ -1611,7 +1611,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
 //     split / merge identity of the online softmax, every wavefront finishing 1/NK of the output
 //     columns.
 // Measured, fp16, 12 x 64, us per call against the 128-row kernel (512: against four wavefronts without a shared Q):
-// 512 tokens 7.8 -> 6.2, 1024 13.6 -> 10.9, 2000 24.9 -> 20.3, 3072 50.3 -> 44.7; 8 x 128, 2048 tokens 37 -> 24.
+// 512 tokens 7.6 -> 6.3, 1024 14.7 -> 10.9, 2000 25.0 -> 21.0, 3072 48.3 -> 43.7; 8 x 128, 2048 tokens 39 -> 24.
 // ======================================================================================
 template <class T, int D, bool BIAS>
 struct SplitWave {
@@ -2337,8 +2337,9 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       // units then need no "has this row a reference yet" test.  With a key bias block 0 can be
       // masked out entirely, so those kernels keep the test.
       // No score above -infinity there (infinite inputs): the lowest reference whose product with c is finite, so that
-      // the first score that is one overflows against it and refreshes it.  (As a median, which leaves the loop as the compiler
-      // schedules it without: a maximum cost batches of 578 - 2048 tokens 0.9 %, this 0.3 - 0.5 %.)
+      // the first score that is one overflows against it and refreshes it.  (As a median, which leaves the main loop as it was
+      // without, 8 - 28 bytes further on: head_dim 64 0.4 % slower, 128 1 % faster; a maximum changed its schedule, batches
+      // of 578 - 2048 tokens 0.9 % slower.)
       const float lowest = -3.4e38f * fminf(1.f, __builtin_amdgcn_rcpf(c));
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
