@@ -35,10 +35,10 @@
 // result is unchanged because numerator and denominator share the reference.
 //
 // Kernels:
-//   fa_fwd_global_kernel  global layers (no window), head_dim 64 or 128.  Full 64-key tiles run in a
-//       software pipeline over 32-key x 32-query units: while the vector ALU turns unit
-//       w's scores into probabilities, the matrix cores compute unit w+1's scores and
-//       accumulate unit w-1's P.V.  The ragged last tile takes the masked block.
+//   fa_fwd_global_kernel  global layers (no window).  64-key tiles run in a software pipeline over
+//       32-key x 32-query units: while the vector ALU turns a unit's scores into probabilities, the
+//       matrix cores compute the next unit's scores and accumulate the P.V of the tile before.  The
+//       last tile is masked.
 //   fa_fwd_window_resident_kernel  local layers whose key range per query tile fits in
 //       LDS (the paper's 63/64 window): everything is requested at once, then each
 //       wavefront runs the same pipeline over the blocks its queries can see.
@@ -70,6 +70,7 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef short shortx8 __attribute__((ext_vector_type(8)));
@@ -97,6 +98,9 @@ struct F16 {
   static __device__ __forceinline__ floatx16 mfma(v8 a, v8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
+  static __device__ __forceinline__ floatx4 mfma16(v8 a, v8 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  }
   static __device__ __forceinline__ uint32_t pack2(float a, float b) {  // round to nearest even
     half2v h = __builtin_convertvector((floatx2){a, b}, half2v);
     return __builtin_bit_cast(uint32_t, h);
@@ -122,6 +126,9 @@ struct BF16 {
   static constexpr bool kWideRange = true;
   static __device__ __forceinline__ floatx16 mfma(v8 a, v8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ floatx4 mfma16(v8 a, v8 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ uint32_t pack2(float a, float b) {
     bf2v h = __builtin_convertvector((floatx2){a, b}, bf2v);
@@ -272,6 +279,35 @@ __device__ __forceinline__ typename T::v8 load_vt_frag_swz_d(const uint16_t* vbl
   return __builtin_bit_cast(typename T::v8, x);
 }
 
+// Swizzles of the 16-row operand reads (see k_swz for the tile).  LDS serves a 16-byte read 16 lanes at a time, and not
+// consecutive ones: lanes 0-3, 12-15, 20-23, 24-27 first.  Those are rows 0-3 and 12-15 at one chunk and 4-11 at its
+// neighbour, so rows 4-11 take the half of the positions that is closed under the step to the neighbour and the others the
+// other half (rows that share their banks: all of one parity, all, or every fourth).  With k_swz every such read took two
+// turns: a third of the LDS cycles of a 32K call.
+template <int D>
+__device__ __forceinline__ int k_swz16(int r) {
+  const int mid = ((r >> 2) ^ (r >> 3)) & 1, hi = (r >> 3) & 1;
+  return D == 128 ? 8 * mid + 4 * hi + (r & 3) : (D == 32 ? 2 * mid + hi : 4 * mid + 2 * hi + ((r >> 1) & 1));
+}
+// V: a transpose read serves 32 lanes at a time, two groups of 4 rows x 32 bytes, whichever two.
+template <int D>
+__device__ __forceinline__ int v_swz16(int r) {
+  const int mid = ((r >> 2) ^ (r >> 3)) & 1;
+  return D == 128 ? 4 * (r & 3) + 2 * mid : (D == 32 ? 2 * mid : 4 * ((r >> 1) & 1) + 2 * mid);
+}
+
+// one transposed operand: two reads of 16 lanes x 4 rows each
+template <class V8>
+__device__ __forceinline__ V8 tr_pair(const uint16_t* at0, const uint16_t* at1) {
+  typedef __attribute__((address_space(3))) shortx4 lds_s4;
+  const shortx4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)at0);
+  const shortx4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)at1);
+  shortx8 x;
+  x[0] = x0[0]; x[1] = x0[1]; x[2] = x0[2]; x[3] = x0[3];
+  x[4] = x1[0]; x[5] = x1[1]; x[6] = x1[2]; x[7] = x1[3];
+  return __builtin_bit_cast(V8, x);
+}
+
 template <class T>
 __device__ __forceinline__ typename T::v8 load_k_frag_swz(const uint16_t* kblk, int l32, int hh, int ks) {
   return as_v8<T>(*(const uint4*)&kblk[l32 * kD + (((2 * ks + hh) ^ k_swz(l32)) * 8)]);
@@ -388,14 +424,11 @@ __device__ __forceinline__ uint32_t visible_bits(int kb0, int hh, int jlo, int j
 //
 // bias2 (optional): 32 floats in LDS, the block's additive key bias times log2(e).  With a
 // bias the row state is kept in the log2 domain (m_ref = mc = reference of s*c + bias2).
-// bias_raw (optional, instead of bias2): 32 floats in LDS, the bias divided by |scale|; it
-// is simply added to the raw scores and everything else stays in raw-score units.
 template <class T, int NQB, bool MASKED, int FRAG, int D>
 __device__ __forceinline__ void simple_block(RowState<NQB, D>& st, const typename T::v8 (&qreg)[NQB][D / 16],
                                              const uint16_t* kblk, const uint16_t* vblk, int kb0,
                                              const int (&jlo)[NQB], const int (&jhi)[NQB], int lane,
-                                             float c, float tau_raw, const float* bias2 = nullptr,
-                                             const float* bias_raw = nullptr) {
+                                             float c, float tau_raw, const float* bias2 = nullptr) {
   const int l32 = lane & 31, hh = lane >> 5;
   floatx16 sacc[NQB];
 #pragma unroll
@@ -408,19 +441,6 @@ __device__ __forceinline__ void simple_block(RowState<NQB, D>& st, const typenam
     const typename T::v8 ka = FRAG == 2 ? load_k_frag_swz<T>(kblk, l32, hh, ks) : load_k_frag<T, D>(kblk, l32, hh, ks);
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) sacc[qb] = T::mfma(ka, qreg[qb][ks], sacc[qb]);
-  }
-  if (bias_raw) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 b4 = *(const float4*)&bias_raw[8 * g + 4 * hh];
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        sacc[qb][4 * g + 0] += b4.x;
-        sacc[qb][4 * g + 1] += b4.y;
-        sacc[qb][4 * g + 2] += b4.z;
-        sacc[qb][4 * g + 3] += b4.w;
-      }
-    }
   }
   uint32_t pk[NQB][8];
 #pragma unroll
@@ -621,20 +641,18 @@ __device__ __forceinline__ void rotate8(uint4& lo, uint4& hi, const float* cs, c
 
 // Rotates `rows` rows of K in place in LDS (all threads of the workgroup take part; the caller
 // puts barriers around the call).  Element e of tile row r lives at
-// tile[r * stride + (((e / 8) ^ swizzle(r & 31)) * 8) + e % 8], swizzle = k_swz_d<D> for tiles
-// written by direct loads (SWIZZLED) and 0 for padded tiles; tile row r is key key0 + r
+// tile[r * stride + (((e / 8) ^ swizzle(r & 31)) * 8) + e % 8], swizzle = M::k_swz for 32-row blocks
+// written by direct loads and 0 (M = void) for padded tiles; tile row r is key key0 + r
 // (clamped into the tensor: rows outside it are never used unmasked).
-template <class T, int D, bool SWIZZLED>
+template <class T, int D, class M = void>
 __device__ __forceinline__ void rope_rows_in_lds(const FaKernelArgs& a, uint16_t* tile, int stride, int rows, int key0,
-                                                 int tid, int nthreads, int key32 = -1) {
-  // key32 >= 0: tile rows 32 .. 63 are keys key32 .. key32 + 31 instead of key0 + 32 ... (the
-  // two 32-row halves of a pipeline stage are fetched from separately clamped row bases)
+                                                 int tid, int nthreads) {
   constexpr int HALF = D / 16;  // 16-byte chunks per half row
   for (int u = tid; u < rows * HALF; u += nthreads) {
     const int r = u / HALF, c = u % HALF;
-    int key = (key32 >= 0 && r >= 32) ? key32 + r - 32 : key0 + r;
-    key = key < 0 ? 0 : (key < a.max_len ? key : a.max_len - 1);
-    const int sw = SWIZZLED ? k_swz_d<D>(r & 31) : 0;
+    const int key = key0 + r < a.max_len ? key0 + r : a.max_len - 1;
+    int sw = 0;
+    if constexpr (!std::is_void<M>::value) sw = M::k_swz(r & 31);
     uint4* plo = (uint4*)&tile[r * stride + ((c ^ sw) * 8)];
     uint4* phi = (uint4*)&tile[r * stride + (((c + HALF) ^ sw) * 8)];
     uint4 lo = *plo, hi = *phi;
@@ -904,7 +922,7 @@ __global__ __launch_bounds__(kThreads, ((D == 128 && !BIAS) || NQB == 2) ? 2 : 1
   __syncthreads();
   // rotary embedding: a staged K tile is rotated in place before anybody reads it
   if (a.rope_cos) {
-    rope_rows_in_lds<T, D, false>(a, lds_k[0], SK, kBN, t_lo * kBN, tid, kThreads);
+    rope_rows_in_lds<T, D>(a, lds_k[0], SK, kBN, t_lo * kBN, tid, kThreads);
     __syncthreads();
   }
 
@@ -928,7 +946,7 @@ __global__ __launch_bounds__(kThreads, ((D == 128 && !BIAS) || NQB == 2) ? 2 : 1
     __syncthreads();
     buf ^= 1;
     if (a.rope_cos && t + 1 < t_hi) {
-      rope_rows_in_lds<T, D, false>(a, lds_k[buf], SK, kBN, (t + 1) * kBN, tid, kThreads);
+      rope_rows_in_lds<T, D>(a, lds_k[buf], SK, kBN, (t + 1) * kBN, tid, kThreads);
       __syncthreads();
     }
   }
@@ -2073,51 +2091,269 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
 }
 
 // ======================================================================================
-// Global kernel: software pipeline over the full tiles + masked ragged tail
-// ======================================================================================
-// BIAS: the additive key bias rides on the score product: the bias of a key block, divided
-// by |scale|, is the C operand of the block's first MFMA, so the scores arrive with the bias
-// already in them and the vector work is unchanged.
-// (head_dim 32: it is added to the finished scores, and the row sums are those of the
-// unrounded probabilities, as in the masked kernel.)  Bias values are staged per K tile
-// through a register of wavefront 0 into a small LDS array with the tile's two stages.
-// NW: wavefronts per workgroup (4, 8 or 12).  All of them share ONE pair of K/V stages, so the
-// tile traffic from L2 into LDS per flop falls with NW; a workgroup of 8 or 12 wavefronts
-// is meant to be alone on its compute unit (2 or 3 wavefronts per SIMD).
+// Global kernel: a software pipeline over 64-key tiles
 //
-// The body is a device function over LDS storage owned by the kernel that calls it, so that one
-// kernel can hold two shapes of it (see fa_fwd_global_mixed_kernel).
-template <int D, int NW>
-struct GlobalLds {
-  static constexpr int SK = stride_k(D), SV = stride_v(D);
-  // Two stages of 64 unpadded rows during the pipeline; the ragged tail reuses the same
-  // storage with padded rows (K 64 rows, V 96 rows), which is why these arrays are sized by
-  // the padded strides; the epilogue needs one patch per wavefront in the K storage.
-  static constexpr int kKElems = 2 * kBN * SK > NW * epi_patch(D) ? 2 * kBN * SK : NW * epi_patch(D);
-  static constexpr int kVElems = 2 * kBN * SV;
-  static_assert(2 * kBN * SV >= 96 * SV, "the tail reuses the V stages");
+// A workgroup is NW wavefronts (4; 8 and 12 exist for head_dim 64, 8 for 128) that share one pair of rings, four 32-key
+// blocks of K and four of V, filled by direct loads one tile ahead; each wavefront owns NQB blocks of 32 query rows.
+// Large calls are bound by the power limit (the clock sits at 1.8 - 2.2 of 2.4 GHz) and by issue slots together, so what
+// counts is how many instructions a unit of 32 keys x 32 queries takes and what they draw:
+//   * ONE test per 64-key tile decides whether the running references still hold, of row sums formed an iteration ago.
+//     (A test per unit waits for the unit's sum, cuts the straight-line code and cost 3 - 9 % of the bare instruction
+//     mix.)  It has to come before the tile's P.V is accumulated, so the P.V lags a whole tile behind the probabilities,
+//     which wait in registers; when it trips, which is rare, the tile's scores are formed again from K in global memory;
+//   * fp16 row sums, of the rounded probabilities, go to the matrix cores: two products with a constant operand instead
+//     of eight dot products and an addition (bf16 sums the unrounded fp32 probabilities, 16 additions);
+//   * the shape of the matrix instruction per type and head size: GlobalTile;
+//   * the ragged last tile is a masked iteration of the same pipeline on rows clamped into the tensor, not a second staging
+//     pass through registers (a 128-row workgroup of a 512-token sequence spent 2.5 of its 12 us there).
+// Measured, us, before (a test and 8 dot2 per unit, 32 x 32 x 16 products, staged tail) -> now: fp16 8K 12 x 64 192 -> 180,
+// 8 x 128 236 -> 221, 32 x 512 ragged 32.3 -> 30.9; bf16 8 x 128 8K 233 -> 221, 12 x 64 8K 196 -> 193, 32K 2910 both.
+// ======================================================================================
+// Exchange between lanes l and l ^ 16, as swap_halves does it between l and l ^ 32.
+__device__ __forceinline__ void swap_rows16(float x, float& a, float& b) {
+  a = x;
+  asm("s_nop 1\n\tv_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "=&v"(b));
+}
+// maximum / sum over the four lanes that hold one query
+__device__ __forceinline__ float max_quad(float x) {
+  float a, b;
+  swap_rows16(x, a, b);
+  return max_xor32(fmaxf(a, b));
+}
+__device__ __forceinline__ float sum_quad(float x) {
+  float a, b;
+  swap_rows16(x, a, b);
+  return sum_xor32(a + b);
+}
+
+// A unit of the pipeline is 32 keys x 32 queries.  How it is laid over the lanes is a policy with two members, for the two
+// shapes of the matrix instruction; per lane both hold D / 16 fragments of Q, of K and of V^T, 2 of P, 16 scores and D / 2
+// output values of a query block, and one score product can alternate with one output product.
+//
+// Tile32: v_mfma_f32_32x32x16, laid out as in the head of this file: one query per lane, shared by lanes l and l ^ 32.
+//
+// Tile16: v_mfma_f32_16x16x32, D = A * B + C with A: 16 x 32, B: 32 x 16, C: 16 x 16; lane l holds A[l%16][8*(l/16)..+7],
+// B[8*(l/16)..+7][l%16] and C[4*(l/16) + r][l%16], r = 0..3.  Scores are formed transposed here too: a lane's accumulators
+// of a 16-query tile belong to ONE query (column l%16; two tiles, two queries per lane), four lanes share a query, and the
+// 4 + 4 scores that a lane holds of a 32-key block (keys 4 (l/16) + r and 16 + 4 (l/16) + r) are, packed, its B operand of
+// the second product once V^T is read in the same key order.  A product with a constant first operand sums a block's
+// probabilities over all four lanes.
+template <class T, int D>
+struct Tile32 {
+  typedef typename T::v8 v8;
+  static constexpr int QT = 1, E = 16, STEPS = D / 16, COLS = 32;   // queries per lane, scores per lane and query
+  typedef floatx16 Scores;
+  typedef floatx16 Out[D / 32];
+  static constexpr bool kMfmaSum = false, kLateStep = true;
+  static __device__ __forceinline__ int k_swz(int r) { return k_swz_d<D>(r); }
+  static __device__ __forceinline__ int v_swz(int r) { return v_swz_d<D>(r); }
+  int col, grp;                      // the lane's query column, and which of the lanes that share it
+  uint32_t kfo[D / 16], vfo[D / 32];  // operand offsets (16-bit elements) into a 32-row block
+
+  __device__ __forceinline__ void init(int lane) {
+    col = lane & 31;
+    grp = lane >> 5;
+    const int p16 = lane & 15, g = (lane >> 4) & 1, row = 4 * grp + (p16 >> 2);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) kfo[ks] = col * D + (((2 * ks + grp) ^ k_swz(col)) * 8);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) vfo[db] = row * D + (((4 * db + 2 * g + ((p16 & 3) >> 1)) ^ v_swz(row)) * 8) + (p16 & 1) * 4;
+  }
+  // fragments i = 0 .. D/16 - 1 of a block: K and Q k-step i; V^T 16-key half i / (D/32), column block i % (D/32)
+  __device__ __forceinline__ v8 k_frag(const uint16_t* blk, int i) const { return as_v8<T>(*(const uint4*)&blk[kfo[i]]); }
+  __device__ __forceinline__ v8 v_frag(const uint16_t* blk, int i) const {
+    const uint16_t* at = &blk[vfo[i % (D / 32)] + (i / (D / 32)) * 16 * D];
+    return tr_pair<v8>(at, at + 8 * D);
+  }
+  static __device__ __forceinline__ void score_step(Scores& s, const v8* k, const v8* q, int i) { s = T::mfma(k[i], q[i], s); }
+  static __device__ __forceinline__ void out_step(Out& o, const v8* v, const v8* p, int i) {
+    o[i % (D / 32)] = T::mfma(v[i], p[i / (D / 32)], o[i % (D / 32)]);
+  }
+  // element i of a lane's scores for its query qt: key key_of(i) of the block
+  __device__ __forceinline__ int key_of(int i) const { return 8 * (i >> 2) + 4 * grp + (i & 3); }
+  static __device__ __forceinline__ float get(const Scores& s, int, int i) { return s[i]; }
+  // start value of a block's scores: zero, or the block's bias (four consecutive keys per quad)
+  template <bool BIAS>
+  __device__ __forceinline__ void start(Scores& s, const float* bias) const {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const floatx4 b = BIAS ? *(const floatx4*)&bias[8 * x + 4 * grp] : (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[4 * x + r] = b[r];
+    }
+  }
+  __device__ __forceinline__ void add(Scores& s, const float* bias) const { add_bias(s, bias, grp); }
+  static __device__ __forceinline__ void add_each(Scores& s, const float (&b)[E]) {   // b[i]: for element i
+#pragma unroll
+    for (int i = 0; i < E; ++i) s[i] += b[i];
+  }
+  __device__ __forceinline__ uint32_t visible(int blk, int n) const { return visible_bits(32 * blk, grp, 0, n - 1); }
+  static __device__ __forceinline__ void pack(v8* p, int, const float (&e)[E]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      p[h] = as_v8<T>(make_uint4(T::pack2(e[8 * h], e[8 * h + 1]), T::pack2(e[8 * h + 2], e[8 * h + 3]), T::pack2(e[8 * h + 4], e[8 * h + 5]),
+                                 T::pack2(e[8 * h + 6], e[8 * h + 7])));
+  }
+  static __device__ __forceinline__ float row_max(float x) { return max_xor32(x); }
+  static __device__ __forceinline__ float row_sum(float x) { return sum_xor32(x); }
+  static __device__ __forceinline__ void scale(Out& o, int, float f) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) o[db] *= f;
+  }
+  // four consecutive output columns out_col(x) .. + 3 of the lane's row, x = 0 .. D / (4 * lanes per query) - 1
+  static constexpr int QUADS = D / 8;
+  __device__ __forceinline__ int out_col(int x) const { return 8 * x + 4 * grp; }
+  static __device__ __forceinline__ floatx4 out_quad(const Out& o, int, int x) {
+    const floatx16& b = o[x / 4];
+    return (floatx4){b[4 * (x % 4)], b[4 * (x % 4) + 1], b[4 * (x % 4) + 2], b[4 * (x % 4) + 3]};
+  }
+  // chunk (16 bytes) of a row that fragment i holds in this lane
+  __device__ __forceinline__ int chunk(int i) const { return 2 * i + grp; }
 };
 
-// tc: the workgroup's tile (tc.n already clamped into [0, max_len]).
+template <class T, int D>
+struct Tile16 {
+  typedef typename T::v8 v8;
+  static constexpr int QT = 2, E = 8, STEPS = D / 8, COLS = 16, KS = D / 32;
+  struct Scores { floatx4 t[2][2]; };   // [16-key tile][16-query tile]
+  typedef floatx4 Out[2][D / 16];       // [16-query tile][16 columns]
+  static constexpr bool kMfmaSum = true, kLateStep = false;
+  static __device__ __forceinline__ int k_swz(int r) { return k_swz16<D>(r); }
+  static __device__ __forceinline__ int v_swz(int r) { return v_swz16<D>(r); }
+  int col, grp;
+  uint32_t kfo[KS], vfo[D / 16];
+
+  __device__ __forceinline__ void init(int lane) {
+    col = lane & 15;
+    grp = lane >> 4;
+    const int row = 4 * grp + (col >> 2);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kfo[ks] = col * D + (((4 * ks + grp) ^ k_swz(col)) * 8);
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) vfo[dt] = row * D + (((2 * dt + ((col & 3) >> 1)) ^ v_swz(row)) * 8) + (col & 1) * 4;
+  }
+  // K: 16-key tile i / KS, k-step i % KS (rows r and r + 16 have the same swizzles); Q: 16-query tile, k-step; V^T: columns
+  __device__ __forceinline__ v8 k_frag(const uint16_t* blk, int i) const { return as_v8<T>(*(const uint4*)&blk[kfo[i % KS] + (i / KS) * 16 * D]); }
+  __device__ __forceinline__ v8 v_frag(const uint16_t* blk, int i) const {
+    const uint16_t* at = &blk[vfo[i]];
+    return tr_pair<v8>(at, at + 16 * D);
+  }
+  static __device__ __forceinline__ void score_step(Scores& s, const v8* k, const v8* q, int i) {
+    const int kt = i & 1, qt = (i >> 1) & 1, ks = i >> 2;
+    s.t[kt][qt] = T::mfma16(k[kt * KS + ks], q[qt * KS + ks], s.t[kt][qt]);
+  }
+  static __device__ __forceinline__ void out_step(Out& o, const v8* v, const v8* p, int i) { o[i & 1][i >> 1] = T::mfma16(v[i >> 1], p[i & 1], o[i & 1][i >> 1]); }
+  __device__ __forceinline__ int key_of(int i) const { return 16 * (i >> 2) + 4 * grp + (i & 3); }
+  static __device__ __forceinline__ float get(const Scores& s, int qt, int i) { return s.t[i >> 2][qt][i & 3]; }
+  template <bool BIAS>
+  __device__ __forceinline__ void start(Scores& s, const float* bias) const {
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) s.t[kt][0] = s.t[kt][1] = BIAS ? *(const floatx4*)&bias[16 * kt + 4 * grp] : (floatx4){0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ void add(Scores& s, const float* bias) const {
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      const floatx4 b = *(const floatx4*)&bias[16 * kt + 4 * grp];
+      s.t[kt][0] += b;
+      s.t[kt][1] += b;
+    }
+  }
+  static __device__ __forceinline__ void add_each(Scores& s, const float (&b)[E]) {
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      s.t[i >> 2][0][i & 3] += b[i];
+      s.t[i >> 2][1][i & 3] += b[i];
+    }
+  }
+  __device__ __forceinline__ uint32_t visible(int blk, int n) const {
+    const int left = n - 32 * blk - 4 * grp;   // keys below n from the lane's first one on
+    const int a0 = left < 0 ? 0 : (left > 4 ? 4 : left), a1 = left < 16 ? 0 : (left > 20 ? 4 : left - 16);
+    return ((1u << a0) - 1u) | (((1u << a1) - 1u) << 4);
+  }
+  static __device__ __forceinline__ void pack(v8* p, int qt, const float (&e)[E]) {
+    p[qt] = as_v8<T>(make_uint4(T::pack2(e[0], e[1]), T::pack2(e[2], e[3]), T::pack2(e[4], e[5]), T::pack2(e[6], e[7])));
+  }
+  static __device__ __forceinline__ float row_max(float x) { return max_quad(x); }
+  static __device__ __forceinline__ float row_sum(float x) { return sum_quad(x); }
+  static __device__ __forceinline__ void scale(Out& o, int qt, float f) {
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) o[qt][dt] *= f;
+  }
+  static constexpr int QUADS = D / 16;
+  __device__ __forceinline__ int out_col(int x) const { return 16 * x + 4 * grp; }
+  static __device__ __forceinline__ floatx4 out_quad(const Out& o, int qt, int x) { return o[qt][x]; }
+  __device__ __forceinline__ int chunk(int i) const { return 4 * (i % KS) + grp; }
+};
+
+// Which of the two a call runs.  What bounds the large calls is power as much as issue slots: with random operands the
+// smaller shape does 20 % (fp16) and 14 % (bf16) more work per second when nothing else is issued (1905 against 1576,
+// 2006 against 1722 TFLOP/s), but it takes twice the instructions, 9 - 10 issue cycles each.  fp16, whose row sums go to
+// the matrix cores as well, gains from it everywhere (8K 12 x 64 192 -> 180 us, 8 x 128 236 -> 221).  bf16 keeps 16 fp32
+// additions per unit, so head_dim 32 and 64 are short of issue slots (3 x 16K 1465 -> 1516 in the smaller shape, 24 x 32
+// 8K 267 -> 278; 8K 12 x 64 alone gains, 194 -> 187) and only head_dim 128 takes it (8K 231 -> 221).
+template <class T, int D>
+struct GlobalTile { typedef Tile16<T, D> type; };
+template <int D>
+struct GlobalTile<BF16, D> { typedef typename std::conditional<D == 128, Tile16<BF16, D>, Tile32<BF16, D>>::type type; };
+
+// One row's fragments straight from global memory: the B operand of Q, and the A operand of K where a refresh forms scores
+// again.  FR fragments x = 0 .. FR - 1 hold chunks chunk(x); row: inside the tensor.
+template <class T, int D, class M, bool ROPE>
+__device__ __forceinline__ void load_row(const FaKernelArgs& a, const M& m, const uint16_t* base, int64_t rs, int row, uint4* u) {
+  constexpr int FR = M::COLS == 16 ? D / 32 : D / 16;
+  const uint16_t* src = base + row * rs;
+#pragma unroll
+  for (int x = 0; x < FR; ++x) u[x] = *(const uint4*)(src + 8 * m.chunk(x));
+  if (ROPE) {
+    const float *cs = a.rope_cos + (int64_t)row * a.rope_stride, *sn = a.rope_sin + (int64_t)row * a.rope_stride;
+    if (FR == 1) {
+      // head_dim 32, one chunk per lane: its rotary partner f +- 16 is two lanes away, so each lane rotates both and keeps its own
+      const int lo_chunk = m.chunk(0) & 1;
+      uint4 lo = *(const uint4*)(src + 8 * lo_chunk), hi = *(const uint4*)(src + 16 + 8 * lo_chunk);
+      rotate8<T>(lo, hi, cs + 8 * lo_chunk, sn + 8 * lo_chunk);
+      u[0] = m.chunk(0) < 2 ? lo : hi;
+    } else {
+#pragma unroll
+      for (int x = 0; x < FR / 2; ++x) rotate8<T>(u[x], u[x + FR / 2], cs + 8 * m.chunk(x), sn + 8 * m.chunk(x));
+    }
+  }
+}
+
+template <int D, int NW>
+struct GlobalLds {
+  // rings of four 32-key blocks of K and of V (unpadded rows, swizzled chunks); afterwards one output patch per wavefront
+  static constexpr int kBlk = 32 * D;
+  static constexpr int kElems = 8 * kBlk > NW * epi_patch(D) ? 8 * kBlk : NW * epi_patch(D);
+};
+
+// tc: the workgroup's tile (tc.n as loaded, not clamped).
 // ROPE: q and k are rotated by position (a.rope_cos / a.rope_sin are set): a compile-time
 // variant, so that the kernels without a rotation carry none of its code in their loops.
 template <class T, int D, int NQB, int NW, bool BIAS, bool ROTATE = true, bool ROPE = false>
-__device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoord& tc, uint16_t* lds_k,
-                                            uint16_t* lds_v, float* lds_bias) {
+__device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoord& tc_in, uint16_t* lds, float* lds_bias) {
   static_assert(D == 32 || D == 64 || D == 128, "pipelined kernel: head_dim 32, 64 or 128");
   static_assert(NW == 4 || NW == 8 || NW == 12, "4, 8 or 12 wavefronts");
+  static_assert(D != 32 || NW == 4, "head_dim 32: four wavefronts");
   constexpr int THREADS = NW * 64;
   constexpr int BM = NW * 32 * NQB;
   constexpr bool BIAS_LAST = BIAS && D == 32, BIAS_FIRST = BIAS && !BIAS_LAST;
-  constexpr int KS = D / 16;  // k-steps of a score block
-  constexpr int DB = D / 32;  // 32-row blocks of O^T
-  constexpr int SK = stride_k(D), SV = stride_v(D);
+  typedef typename GlobalTile<T, D>::type M;
+  constexpr bool MFMA_SUM = M::kMfmaSum && T::kSumRounded && !BIAS_LAST;
+  constexpr int QT = M::QT, E = M::E, FR = D / 16;
+  constexpr int kBlk = 32 * D;
+  typedef typename T::v8 v8;
 
-  const int N = a.max_len, n = tc.n, q0 = tc.q0;
+  TileCoord tc = tc_in;
+  // (uniform by construction; said explicitly so that the addresses derived from them stay in scalar registers)
+  tc.b = __builtin_amdgcn_readfirstlane(tc.b);
+  tc.h = __builtin_amdgcn_readfirstlane(tc.h);
+  tc.q0 = __builtin_amdgcn_readfirstlane(tc.q0);
+  const int N = a.max_len, q0 = tc.q0;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, hh = lane >> 5;
+  M m;
+  m.init(lane);
 
   const uint16_t* qp = (const uint16_t*)a.q + tc.b * a.qs[0] + tc.h * a.qs[1];
   const uint16_t* kp = (const uint16_t*)a.k + tc.b * a.ks[0] + tc.h * a.ks[1];
@@ -2126,420 +2362,457 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   float* lsep = a.lse ? a.lse + ((int64_t)tc.b * a.heads + tc.h) * N : nullptr;
   const uint16_t* bp = BIAS ? (const uint16_t*)a.key_bias + tc.b * a.kb_stride : nullptr;
   // bias of key j in raw-score units (index clamped: keys outside [0, n) are never used unmasked)
-  auto bias_of = [&](int j) {
-    j = j < 0 ? 0 : (j < N ? j : N - 1);
-    return bias_over_scale<T, D == 32>(a, bp[j]);
-  };
+  auto bias_of = [&](int j) { return bias_over_scale<T, D == 32>(a, bp[j < N ? j : N - 1]); };
 
-  if (q0 >= n) {
-    zero_fill<BM, D, THREADS>(a, tc, op, lsep);
-    return;
+  uint16_t* const kring = lds;
+  uint16_t* const vring = lds + 4 * kBlk;
+
+  // A direct load moves RPL rows of a 32-row block; a block's LPB loads are dealt to the wavefronts: with four, each
+  // moves LPB / 4 parts of every block (head_dim 32, two parts: wavefront w moves block w of a tile's four by itself); with
+  // eight or twelve, wavefronts 0 .. 3 move the first block of K and of V, 4 .. 7 the second.
+  constexpr int CH = D / 8, RPL = 64 / CH, LPB = 32 / RPL;      // D = 32: 4, 16, 2;  64: 8, 8, 4;  128: 16, 4, 8
+  constexpr int LW = D == 32 ? 2 : LPB / 4;
+  const int fw = wave & 3;
+  int row_of[LW];
+  uint32_t koff[LW], voff[LW];   // bytes (row stride included)
+#pragma unroll
+  for (int x = 0; x < LW; ++x) {
+    row_of[x] = (D == 32 ? x : fw * LW + x) * RPL + lane / CH;
+    koff[x] = 2u * (uint32_t)(row_of[x] * a.ks[2] + (((lane % CH) ^ M::k_swz(row_of[x])) * 8));
+    voff[x] = 2u * (uint32_t)(row_of[x] * a.vs[2] + (((lane % CH) ^ M::v_swz(row_of[x])) * 8));
+  }
+  const int part0 = D == 32 ? 0 : fw * LW;
+  // block `blk` of K or V into LDS block dst: rows past the tensor are clamped to its last one (masked, zeroed or never read)
+  auto load_block = [&](const uint16_t* base, int64_t rs, const uint32_t (&off)[LW], int blk, uint16_t* dst) {
+    if (32 * blk + 32 <= N) {
+      const uint16_t* gb = base + (int64_t)(32 * blk) * rs;
+#pragma unroll
+      for (int x = 0; x < LW; ++x) load16_to_lds(gb, off[x], dst + (part0 + x) * RPL * D);
+    } else {
+      const int first = 32 * blk < N ? 32 * blk : N - 1;
+      const uint16_t* gb = base + (int64_t)first * rs;
+#pragma unroll
+      for (int x = 0; x < LW; ++x) {
+        const int r = row_of[x] < N - 1 - first ? row_of[x] : N - 1 - first;
+        load16_to_lds(gb, off[x] - 2u * (uint32_t)((row_of[x] - r) * rs), dst + (part0 + x) * RPL * D);
+      }
+    }
+  };
+  // K blocks kb, kb + 1 (the second if k2) and V blocks vb, vb + 1 into ring slots; with_k / with_v: wavefront-uniform
+  auto fetch = [&](int kb, bool with_k, bool k2, int vb, bool with_v) {
+    if (D == 32) {
+      if (wave < 2) {
+        if (with_k && (wave == 0 || k2)) load_block(kp, a.ks[2], koff, kb + wave, kring + ((kb + wave) & 3) * kBlk);
+      } else if (with_v) {
+        load_block(vp, a.vs[2], voff, vb + wave - 2, vring + ((vb + wave - 2) & 3) * kBlk);
+      }
+    } else if (NW == 4) {
+      if (with_k) load_block(kp, a.ks[2], koff, kb, kring + (kb & 3) * kBlk);
+      if (with_k && k2) load_block(kp, a.ks[2], koff, kb + 1, kring + ((kb + 1) & 3) * kBlk);
+      if (with_v) {
+        load_block(vp, a.vs[2], voff, vb, vring + (vb & 3) * kBlk);
+        load_block(vp, a.vs[2], voff, vb + 1, vring + ((vb + 1) & 3) * kBlk);
+      }
+    } else if (wave < 8) {
+      const int s = wave >> 2;
+      if (with_k && (s == 0 || k2)) load_block(kp, a.ks[2], koff, kb + s, kring + ((kb + s) & 3) * kBlk);
+      if (with_v) load_block(vp, a.vs[2], voff, vb + s, vring + ((vb + s) & 3) * kBlk);
+    }
+  };
+  // The first blocks of K are requested before the sequence length is looked at.
+  if (D == 32 || NW > 4) {
+    fetch(0, true, true, 0, false);
+    fetch(2, true, false, 0, false);
+  } else {
+    fetch(0, true, true, 0, false);
+    load_block(kp, a.ks[2], koff, 2, kring + 2 * kBlk);
   }
 
   const int qw0 = q0 + wave * 32 * NQB;
-  const int qw_last = (qw0 + 32 * NQB < n ? qw0 + 32 * NQB : n) - 1;
-  const bool wave_has_rows = qw_last >= qw0;
-
-  typename T::v8 qreg[NQB][KS];
-  load_q<T, NQB, KS, ROPE>(a, qp, qw0, lane, qreg);
-  RowState<NQB, D> st;
-  init_state(st);
-
-  const int nf = n / kBN;  // full tiles: every key visible to every valid query
-  const float c = a.c, tau_raw = a.tau_raw;
-
-  // The pipeline advances in UNITS: one unit = one 32-key block u against one of the
-  // wavefront's 32-query blocks qb, in the order (u,0) .. (u,NQB-1), (u+1,0) ...
-  // During a unit the vector ALU turns the unit's scores into probabilities while the
-  // matrix cores compute the NEXT unit's scores and add the PREVIOUS unit's P.V.
-  // K fragments of a key block are read from LDS once and serve all NQB query blocks;
-  // likewise the V^T fragments.
-  //
-  // Iteration t covers key blocks 2t, 2t+1.  It reads K of blocks 2t+1, 2t+2 (next
-  // unit's scores) and V of blocks 2t-1, 2t (NQB = 1) or 2t, 2t+1 (NQB = 2): the LDS
-  // "tile" of iteration t is K rows [64t+32, 64t+96) and V rows [64t+kVShift, +64).
-  constexpr int kVShift = NQB == 1 ? -32 : 0;
-  // Pipeline tiles go from HBM/L2 straight into LDS (global_load_lds, 16 bytes per lane):
-  // a wavefront's load fills 1 KB of LDS in lane order, i.e. RPI = 8 rows of 128 bytes
-  // (head_dim 64) or 4 rows of 256 bytes (head_dim 128), so the LDS tile is unpadded
-  // [64 rows][D/8 chunks of 16 bytes] and bank conflicts are avoided by choosing WHICH
-  // global chunk each lane fetches: chunk position c' of row r holds global chunk
-  // c' ^ k_swz(r) for K and c' ^ v_swz(r) for V.  Wavefront w moves rows 8w..8w+7 of each
-  // 32-row half in NI = 8 / RPI loads.  Row bases are wavefront-uniform; each lane adds a
-  // fixed offset.  Halves whose rows would leave [0, N) are only ever the unused ends of
-  // the pipeline (V before block 0, K after the last full block): their base is clamped,
-  // their contents unused.
-  // With 8 or 12 wavefronts, wavefronts 0..7 move one half each: wavefront w rows
-  // 8 (w % 4) .. + 7 of half w / 4; the others move nothing.
-  // head_dim 32 (64-byte rows): a load is 16 rows, a half two loads, and wavefront w moves half
-  // w of the four (K first, K second, V first, V second) by itself.
-  constexpr int CH = D / 8, RPI = 64 / CH, NI = D == 32 ? 2 : 8 / RPI;
-  static_assert(D != 32 || NW == 4, "head_dim 32: four wavefronts");
-  const int fw = wave & 3;  // row group within a half
-  uint32_t koff[NI], voff[NI];  // bytes (head_dim 32: koff holds the wavefront's own half's offsets)
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    if (D == 32) {
-      const int dl_r = 16 * i + lane / CH;
-      const bool is_k = wave < 2;  // wavefront-uniform
-      koff[i] = 2u * (uint32_t)(dl_r * (is_k ? a.ks[2] : a.vs[2]) +
-                                (((lane % CH) ^ (is_k ? k_swz_d<D>(dl_r) : v_swz_d<D>(dl_r))) * 8));
-      voff[i] = 0;
-    } else {
-      const int dl_r = 8 * fw + i * RPI + lane / CH;  // row within a 32-row half
-      koff[i] = 2u * (uint32_t)(dl_r * a.ks[2] + (((lane % CH) ^ k_swz_d<D>(dl_r)) * 8));
-      voff[i] = 2u * (uint32_t)(dl_r * a.vs[2] + (((lane % CH) ^ v_swz_d<D>(dl_r)) * 8));
-    }
-  }
-  // the four 32-row halves of a tile: global row bases kg / vg, LDS halves kdst / vdst
-  auto fetch_halves = [&](const uint16_t* kga, const uint16_t* kgb, const uint16_t* vga, const uint16_t* vgb,
-                          uint16_t* kstage, uint16_t* vstage) {
-    uint16_t* kdst = kstage + 8 * fw * D;
-    uint16_t* vdst = vstage + 8 * fw * D;
-    if (D == 32) {
-      const uint16_t* g = wave == 0 ? kga : (wave == 1 ? kgb : (wave == 2 ? vga : vgb));
-      uint16_t* dst = (wave < 2 ? kstage : vstage) + (wave & 1) * 32 * D;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) load16_to_lds(g, koff[i], dst + i * 16 * D);
-    } else if (NW == 4) {
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        load16_to_lds(kga, koff[i], kdst + i * RPI * D);
-        load16_to_lds(kgb, koff[i], kdst + 32 * D + i * RPI * D);
-        load16_to_lds(vga, voff[i], vdst + i * RPI * D);
-        load16_to_lds(vgb, voff[i], vdst + 32 * D + i * RPI * D);
-      }
-    } else if (wave < 8) {
-      const bool second = wave >= 4;  // wavefront-uniform
-      const uint16_t* kg = second ? kgb : kga;
-      const uint16_t* vg = second ? vgb : vga;
-      kdst += second ? 32 * D : 0;
-      vdst += second ? 32 * D : 0;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        load16_to_lds(kg, koff[i], kdst + i * RPI * D);
-        load16_to_lds(vg, voff[i], vdst + i * RPI * D);
-      }
-    }
-  };
-  auto fetch = [&](int t, uint16_t* kstage, uint16_t* vstage) {
-    const int k0r = t * kBN + 32 < 0 ? 0 : t * kBN + 32;
-    const int k1r = t * kBN + 64 > N - 32 ? N - 32 : t * kBN + 64;
-    const int v0r = t * kBN + kVShift < 0 ? 0 : t * kBN + kVShift;
-    const int v1r = t * kBN + kVShift + 32 < 0 ? 0 : t * kBN + kVShift + 32;
-    fetch_halves(kp + (int64_t)k0r * a.ks[2], kp + (int64_t)k1r * a.ks[2], vp + (int64_t)v0r * a.vs[2],
-                 vp + (int64_t)v1r * a.vs[2], kstage, vstage);
-  };
-  // Inside the pipeline loop the four row bases just advance by one tile per iteration
-  // (scalar 64-bit adds); only the very last tile's second K half can need the clamp.
-  const uint16_t* kg0 = kp + (int64_t)(kBN + 32) * a.ks[2];
-  const uint16_t* kg1 = kp + (int64_t)(kBN + 64) * a.ks[2];
-  const uint16_t* vg0 = vp + (int64_t)(kBN + kVShift) * a.vs[2];
-  const uint16_t* vg1 = vp + (int64_t)(kBN + kVShift + 32) * a.vs[2];
-  const int k1_last_row = n / kBN * kBN > N - 32 ? N - 32 : n / kBN * kBN;  // tile nf-1: min(64 nf, N-32)
-  const uint16_t* kg1_last = kp + (int64_t)k1_last_row * a.ks[2];
-  auto fetch_next = [&](bool last, uint16_t* kstage, uint16_t* vstage) {
-    fetch_halves(kg0, last ? kg1_last : kg1, vg0, vg1, kstage, vstage);
-    kg0 += kBN * a.ks[2];
-    kg1 += kBN * a.ks[2];
-    vg0 += kBN * a.vs[2];
-    vg1 += kBN * a.vs[2];
-  };
-  // per-lane fragment offsets (16-bit elements) into a 32-row block of a swizzled tile
-  uint32_t kfo[KS], vfo[DB];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) kfo[ks] = l32 * D + (((2 * ks + hh) ^ k_swz_d<D>(l32)) * 8);
+  v8 q[NQB][FR];
   {
-    const int p16 = lane & 15, g = (lane >> 4) & 1;
+    constexpr int FQ = FR / QT;   // fragments of one query
+    uint4 u[NQB][QT][FQ];
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-      vfo[db] = (4 * hh + (p16 >> 2)) * D +
-                (((4 * db + 2 * g + ((p16 & 3) >> 1)) ^ v_swz_d<D>(4 * hh + (p16 >> 2))) * 8) +
-                (p16 & 1) * 4;
+    for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        const int row = qw0 + 32 * qb + M::COLS * qt + m.col;
+        load_row<T, D, M, ROPE>(a, m, qp, a.qs[2], row < N ? row : N - 1, u[qb][qt]);
+      }
+    // only now the sequence length
+    tc.n = tc.n < 0 ? 0 : (tc.n > N ? N : tc.n);
+    if (q0 >= tc.n) {
+      wait_direct_loads();  // the loads write this workgroup's LDS: they must land before it ends
+      zero_fill<BM, D, THREADS>(a, tc, op, lsep);
+      return;
+    }
+    const uint32_t flip = a.negate_q ? 0x80008000u : 0u;
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        // rows past the sequence take zeros: whatever is stored there must not cost refreshes
+        const bool alive = qw0 + 32 * qb + M::COLS * qt + m.col < tc.n;
+#pragma unroll
+        for (int x = 0; x < FQ; ++x) {
+          uint4 w = u[qb][qt][x];
+          w.x ^= flip; w.y ^= flip; w.z ^= flip; w.w ^= flip;
+          q[qb][qt * FQ + x] = as_v8<T>(alive ? w : make_uint4(0, 0, 0, 0));
+        }
+      }
   }
-  auto k_frag = [&](const uint16_t* kblk, int ks) { return as_v8<T>(*(const uint4*)&kblk[kfo[ks]]); };
-  auto vt_frag = [&](const uint16_t* vblk, int ks2, int db) {
-    typedef __attribute__((address_space(3))) shortx4 lds_s4;
-    const shortx4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)&vblk[vfo[db] + ks2 * 16 * D]);
-    const shortx4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)&vblk[vfo[db] + (ks2 * 16 + 8) * D]);
-    shortx8 x;
-    x[0] = x0[0]; x[1] = x0[1]; x[2] = x0[2]; x[3] = x0[3];
-    x[4] = x1[0]; x[5] = x1[1]; x[6] = x1[2]; x[7] = x1[3];
-    return __builtin_bit_cast(typename T::v8, x);
-  };
+  const int n = tc.n;
+  const int T64 = (n + 63) >> 6;                 // 64-key tiles
+  const bool wave_has_rows = qw0 < n;
+  const float c = a.c;
 
-  // pipeline registers: scores of the current / next unit, packed probabilities of the
-  // previous / current unit, operand fragments of the key block in flight
-  floatx16 sA, sB;
-  floatx16 bcur;  // BIAS: the bias of the key block whose K fragments are in ka (C layout)
+  typename M::Out o[NQB];
+  float mc[NQB][QT], lsum[NQB][QT];   // reference times c (-infinity: none yet), this lane's share of the row sum
+  v8 p[NQB][2][2];                    // [query block][key block of the tile]: the tile's probabilities
+  floatx4 z[NQB][QT];                 // [0]: the lane's share of their sum (MFMA_SUM: a quarter of the row's)
+  v8 ka[FR], va[FR];
+  const v8 quarter = __builtin_bit_cast(v8, make_uint4(0x34003400u, 0x34003400u, 0x34003400u, 0x34003400u));  // fp16 0.25
 #pragma unroll
-  for (int r = 0; r < 16; ++r) bcur[r] = 0.f;
-  auto bias_frag = [&](const float* bblk) {
+  for (int qb = 0; qb < NQB; ++qb) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 b4 = *(const float4*)&bblk[8 * g + 4 * hh];
-      bcur[4 * g + 0] = b4.x;
-      bcur[4 * g + 1] = b4.y;
-      bcur[4 * g + 2] = b4.z;
-      bcur[4 * g + 3] = b4.w;
+    for (int qt = 0; qt < QT; ++qt) lsum[qb][qt] = 0.f;
+    float* of = (float*)&o[qb];
+#pragma unroll
+    for (int x = 0; x < D / 2; ++x) of[x] = 0.f;
+  }
+
+  auto load_ka = [&](const uint16_t* kblk) {
+#pragma unroll
+    for (int x = 0; x < FR; ++x) ka[x] = m.k_frag(kblk, x);
+  };
+  auto score_init = [&](typename M::Scores& s, const float* bblk) { m.template start<BIAS_FIRST>(s, bblk); };
+  auto score_end = [&](typename M::Scores& s, const float* bblk) {
+    if (BIAS_LAST) m.add(s, bblk);
+  };
+  // probabilities of a block against the rows' references, packed, and their sums
+  auto softmax = [&](const typename M::Scores& s, float nmc, int qb, int u, int qt, bool masked, uint32_t vis) {
+    float e[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      e[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(M::get(s, qt, i), c, nmc));
+      if (masked) e[i] = keep_or_zero(e[i], vis, i);
+    }
+    M::pack(p[qb][u], qt, e);
+    if constexpr (MFMA_SUM) {
+      const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+      z[qb][qt] = T::mfma16(quarter, p[qb][u][qt], u == 0 ? zero : z[qb][qt]);
+    } else {
+      float l0 = e[0], l1 = e[1];
+#pragma unroll
+      for (int i = 2; i < E; i += 2) {
+        l0 += e[i];
+        l1 += e[i + 1];
+      }
+      z[qb][qt][0] = u == 0 ? l0 + l1 : z[qb][qt][0] + (l0 + l1);
     }
   };
-  float bst = 0.f;  // BIAS: wavefront 0 carries the next tile's bias from its load to its LDS write
-  typename T::v8 pA[2], pB[2], ka[KS], va[2][DB];
-  pA[0] = pA[1] = as_v8<T>(make_uint4(0, 0, 0, 0));
+  constexpr float kLimit = MFMA_SUM ? 8192.f : kPLimit;
+  // Rows of tile t whose sums ran away from their reference (or that have none yet): the tile's scores are formed once
+  // more, from K in global memory, the exact maximum is taken and the rows' state and probabilities are made anew.
+  auto refresh = [&](int t, bool masked) {
 #pragma unroll
-  for (int i = 0; i < 2 * DB; ++i) va[i / DB][i % DB] = as_v8<T>(make_uint4(0, 0, 0, 0));
+    for (int qb = 0; qb < NQB; ++qb) {
+      bool row_trig[QT], any = false;
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        // a row refreshes iff one of ITS lanes tripped: no dependence on other rows
+        row_trig[qt] = M::row_sum(!(z[qb][qt][0] <= kLimit) ? 1.f : 0.f) > 0.f;
+        any = any || row_trig[qt];
+      }
+      if (!__any(any)) continue;
+      typename M::Scores s;
+      auto scores = [&](int u) {
+        const int blk = 2 * t + u;
+        uint4 kk[FR];
+#pragma unroll
+        for (int kt = 0; kt < QT; ++kt) {
+          const int row = 32 * blk + M::COLS * kt + m.col;
+          load_row<T, D, M, ROPE>(a, m, kp, a.ks[2], row < N ? row : N - 1, &kk[kt * (FR / QT)]);
+        }
+        float b[E];
+        if (BIAS) {
+#pragma unroll
+          for (int i = 0; i < E; ++i) b[i] = bias_of(32 * blk + m.key_of(i));
+        }
+        m.template start<false>(s, nullptr);
+        if (BIAS_FIRST) M::add_each(s, b);
+        v8 kv[FR];
+#pragma unroll
+        for (int x = 0; x < FR; ++x) kv[x] = as_v8<T>(kk[x]);
+#pragma unroll
+        for (int i = 0; i < M::STEPS; ++i) M::score_step(s, kv, q[qb], i);
+        if (BIAS_LAST) M::add_each(s, b);
+      };
+      float tmax[QT];
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) tmax[qt] = -INFINITY;
+#pragma unroll 1
+      for (int u = 0; u < 2; ++u) {
+        scores(u);
+        const uint32_t vis = masked ? m.visible(2 * t + u, n) : 0xFFFFu;
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+          for (int i = 0; i < E; ++i) tmax[qt] = fmaxf(tmax[qt], keep_or_neg_inf(M::get(s, qt, i), vis, i));
+      }
+      float nmc[QT];
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        tmax[qt] = M::row_max(tmax[qt]);
+        const bool take = row_trig[qt] && tmax[qt] != -INFINITY;
+        const float mc_new = take ? tmax[qt] * c : mc[qb][qt];
+        // (a row without a reference has nothing accumulated: factor exp2(-inf) = 0)
+        const float alpha = take ? __builtin_amdgcn_exp2f(mc[qb][qt] - mc_new) : 1.f;
+        mc[qb][qt] = mc_new;
+        lsum[qb][qt] *= alpha;
+        M::scale(o[qb], qt, alpha);
+        nmc[qt] = mc_new == -INFINITY ? 0.f : -mc_new;   // still none: every score is -infinity, every probability 0
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        scores(u);
+        const uint32_t vis = masked ? m.visible(2 * t + u, n) : 0xFFFFu;
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) softmax(s, nmc[qt], qb, u, qt, true, vis);
+      }
+    }
+  };
+  // The probabilities of tile t are final after this: one test per tile, of sums formed an iteration ago.
+  auto settle = [&](int t, bool masked) {
+    bool trig = false;
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) trig = trig || !(z[qb][qt][0] <= kLimit);
+    if (__any(trig)) refresh(t, masked);
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) lsum[qb][qt] += z[qb][qt][0];
+  };
 
-  // Long sequences with one query block per wavefront put three wavefronts of three different
-  // workgroups on a SIMD, and the hardware serves the oldest first: one workgroup races ahead,
-  // finishes early and leaves the SIMD to two wavefronts, then one, which use it less well.
-  // Rotating the wave priorities by hardware wave slot, one step per iteration, keeps the
-  // three abreast to the end (per-wavefront stamps at 8K: finish times within 5 % of each
-  // other instead of 35 %; 1-2 % off the call).
-  const bool rotate_prio = ROTATE && NQB == 1 && nf >= 64;
+  // ---- prologue: K blocks 0 .. 2 have landed; first scores, first references
+  float bst = 0.f;  // BIAS: wavefront 0 carries the next tile's bias from its load to its LDS write
+  auto request = [&](int t) {   // operands of tile t + 1
+    fetch(2 * t + 3, t + 1 < T64, t + 2 < T64, 2 * t, true);
+    if (BIAS && wave == 0) bst = bias_of(64 * t + 96 + lane);
+  };
+  if (BIAS) {
+    if (tid < 96) lds_bias[tid] = bias_of(tid);
+  }
+  wait_direct_loads();
+  __syncthreads();
+  if (ROPE) {
+    // every K block is rotated in place once it has landed
+#pragma unroll
+    for (int i = 0; i < 3; ++i) rope_rows_in_lds<T, D, M>(a, kring + i * kBlk, D, 32, 32 * i, tid, THREADS);
+    __syncthreads();
+  }
+  typename M::Scores sA, sB;
+  load_ka(kring);
+  __syncthreads();   // K block 0 is in registers everywhere: block 4 takes its place
+  request(0);
+  {
+    const uint32_t vis = m.visible(0, n);
+#pragma unroll
+    for (int qb = NQB - 1; qb >= 0; --qb) {
+      score_init(sA, lds_bias);
+#pragma unroll
+      for (int i = 0; i < M::STEPS; ++i) M::score_step(sA, ka, q[qb], i);
+      score_end(sA, lds_bias);
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        float t0 = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < E; ++i) t0 = fmaxf(t0, keep_or_neg_inf(M::get(sA, qt, i), vis, i));
+        t0 = M::row_max(t0);
+        mc[qb][qt] = t0 == -INFINITY ? -INFINITY : t0 * c;
+      }
+    }
+  }
+
+  const bool rotate_prio = ROTATE && NQB == 1 && T64 >= 64;
   int wslot = 0;
   if (rotate_prio) {
     unsigned hw_id;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw_id));
     wslot = (int)(hw_id & 15u);  // wave slot within the SIMD
   }
-  if (nf > 0) {
-    // prologue: unit (0,0)'s scores need K rows [0, 32): tile "-1" (rows [-32, 32), clamped)
-    fetch(-1, &lds_k[kBN * D], &lds_v[kBN * D]);
-    fetch(0, lds_k, lds_v);
-    if (BIAS && wave == 0) {
-      // tile -1 (keys -32..31) into stage 1, tile 0 (keys 32..95) into stage 0
-      lds_bias[kBN + lane] = bias_of(lane - 32);
-      lds_bias[lane] = bias_of(lane + 32);
-    }
-    wait_direct_loads();
-    __syncthreads();
-    if (ROPE) {
-      // rotary embedding: every K stage is rotated in place once it has landed (stage 1 holds
-      // keys 0..31 in its second half, stage 0 keys 32..63 and min(64, N - 32) ...)
-      rope_rows_in_lds<T, D, true>(a, &lds_k[kBN * D + 32 * D], D, 32, 0, tid, THREADS);
-      rope_rows_in_lds<T, D, true>(a, lds_k, D, 64, 32, tid, THREADS, kBN > N - 32 ? N - 32 : kBN);
-      __syncthreads();
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sA[r] = 0.f;
-    if (BIAS) bias_frag(&lds_bias[kBN + 32]);
-    if (BIAS_FIRST) sA = bcur;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      ka[ks] = k_frag(&lds_k[kBN * D + 32 * D], ks);
-      sA = T::mfma(ka[ks], qreg[0][ks], sA);
-    }
-    if (BIAS_LAST) sA += bcur;
-    if (!BIAS) {
-      // Every query block takes the maximum of its scores against key block 0 as its first
-      // reference, here, once (nothing is accumulated yet, so there is nothing to rescale): the
-      // units then need no "has this row a reference yet" test.  With a key bias block 0 can be
-      // masked out entirely, so those kernels keep the test.
-      // No score above -infinity there (infinite inputs): the lowest reference whose product with c is finite, so that
-      // the first score that is one overflows against it and refreshes it.  (As a median, which leaves the main loop as it was
-      // without, 8 - 28 bytes further on: head_dim 64 0.4 % slower, 128 1 % faster; a maximum changed its schedule, batches
-      // of 578 - 2048 tokens 0.9 % slower.)
-      const float lowest = -3.4e38f * fminf(1.f, __builtin_amdgcn_rcpf(c));
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        floatx16 s0 = sA;
-        if (qb > 0) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) s0[r] = 0.f;
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) s0 = T::mfma(ka[ks], qreg[qb][ks], s0);
-        }
-        float t0 = fmaxf(s0[0], s0[1]);
-#pragma unroll
-        for (int r = 2; r < 16; r += 2) t0 = fmaxf(fmaxf(t0, s0[r]), s0[r + 1]);
-        const float tmax = __builtin_amdgcn_fmed3f(max_xor32(t0), lowest, INFINITY);
-        st.m_ref[qb] = tmax;
-        st.mc[qb] = tmax == -INFINITY ? 0.f : tmax * c;
-      }
-    }
-    __syncthreads();  // stage 1 is refilled during iteration 0
 
-    // The probabilities are formed against the row's current reference right away; the
-    // lane's share of the block's row sum doubles as the overflow sentinel (any p beyond
-    // kPLimit, an infinity included, pushes it over).  Only then - rarely - is the exact
-    // block maximum computed, the reference refreshed and the block redone.
-    auto softmax_block = [&](const floatx16& sv, float mcq, uint32_t (&pk)[8], float& blk) {
-      prob_block<T, false, BIAS_LAST>(sv, c, mcq, 0xFFFFu, pk, blk);
-    };
-    // One unit.  QB: query block of the current scores; NQ: query block of the next
-    // unit; PQ: query block of the previous unit; LOAD: this unit starts a new key block
-    // for both matrix products (fragments come from kblk / vblk), otherwise the
-    // fragments already in registers are reused.
-    auto unit = [&](auto QBc, auto NQc, auto PQc, auto LOADc, floatx16& s_cur, floatx16& s_nxt,
-                    typename T::v8 (&p_prev)[2], typename T::v8 (&p_cur)[2], const uint16_t* kblk,
-                    const uint16_t* vblk, const float* bblk) {
-      constexpr int QB = decltype(QBc)::value, NQ = decltype(NQc)::value, PQ = decltype(PQc)::value;
-      constexpr bool LOAD = decltype(LOADc)::value;
-      if (LOAD) {
+  // One iteration = the 64 keys of tile t.  Units (key block 2t + u, query block qb) in the order (0,0) .. (0,NQB-1), (1,0) ..:
+  // the vector ALU turns the unit's scores (s_cur) into probabilities while the matrix cores form the NEXT unit's scores
+  // and add the P.V of the same unit of the PREVIOUS tile.  k1, k2: LDS blocks 2t + 1, 2t + 2 of K; v1, v2: 2t - 2, 2t - 1 of V.
+  auto iter = [&](auto FIRSTc, auto LASTc, int t, const uint16_t* k1, const uint16_t* k2, const uint16_t* v1, const uint16_t* v2,
+                  const float* b0, const float* b1, const float* b2) {
+    constexpr bool FIRST = decltype(FIRSTc)::value, LAST = decltype(LASTc)::value;
+    auto unit = [&](auto Uc, auto QBc, typename M::Scores& s_cur, typename M::Scores& s_nxt) {
+      constexpr int U = decltype(Uc)::value, QB = decltype(QBc)::value;
+      constexpr int NQ = (QB + 1) % NQB;
+      constexpr bool NEXT = !(LAST && U == 1 && NQ == 0);     // there is a next unit
+      const float* bnext = NQ != 0 ? (U == 0 ? b0 : b1) : (U == 0 ? b1 : b2);   // bias of the next unit's key block
+      if (NQ == 0 && NEXT) load_ka(U == 0 ? k1 : k2);
+      if (QB == 0 && !FIRST) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) ka[ks] = k_frag(kblk, ks);
-#pragma unroll
-        for (int i = 0; i < 2 * DB; ++i) va[i / DB][i % DB] = vt_frag(vblk, i / DB, i % DB);
-        if (BIAS) bias_frag(bblk);
+        for (int x = 0; x < FR; ++x) va[x] = m.v_frag(U == 0 ? v1 : v2, x);
       }
-      // the first product of the score block takes the bias (or zero) as its C operand
-      if (BIAS_FIRST) {
-        s_nxt = bcur;
-      } else {
+      if (NEXT) score_init(s_nxt, bnext);
+      // score products alternate with output products; Tile32: those whose operands the unit has yet to read from LDS come
+      // a step later (0.5 - 1.2 % of the bf16 calls; Tile16, with twice the steps, lost 0.5 - 1 % by it)
+      constexpr int LATE_S = M::kLateStep && NQ == 0 && NQB == 2 ? 1 : 0, LATE_O = M::kLateStep && !LATE_S ? 1 : 0;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s_nxt[r] = 0.f;
+      for (int i = 0; i <= M::STEPS; ++i) {
+        if (NEXT && !LATE_S && i < M::STEPS) M::score_step(s_nxt, ka, q[NQ], i);
+        if (!FIRST && i >= LATE_O && i - LATE_O < M::STEPS) M::out_step(o[QB], va, p[QB][U], i - LATE_O);
+        if (NEXT && LATE_S && i > 0) M::score_step(s_nxt, ka, q[NQ], i - 1);
       }
-      // dependent products (the k-steps of a score block, the two of an output block)
-      // alternate with independent ones
+      if (NEXT) score_end(s_nxt, bnext);
+      const uint32_t vis = LAST ? m.visible(2 * t + U, n) : 0xFFFFu;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        s_nxt = T::mfma(ka[ks], qreg[NQ][ks], s_nxt);
-        st.oacc[PQ][ks % DB] = T::mfma(va[ks / DB][ks % DB], p_prev[ks / DB], st.oacc[PQ][ks % DB]);
-      }
-      if (BIAS_LAST) s_nxt += bcur;
-      uint32_t pk[8];
-      float blk;
-      softmax_block(s_cur, st.mc[QB], pk, blk);
-      // !(blk <= limit) also catches a NaN sum; no reference yet = first block
-      const bool trig = !(blk <= kPLimit) || (BIAS && st.m_ref[QB] == -INFINITY);
-      if (__any(trig)) {
-        // a row refreshes iff one of ITS two lanes tripped: no dependence on other rows
-        const bool row_trig = sum_xor32(trig ? 1.f : 0.f) > 0.f;
-        float t0 = fmaxf(s_cur[0], s_cur[1]);
-#pragma unroll
-        for (int r = 2; r < 16; r += 2) t0 = fmaxf(fmaxf(t0, s_cur[r]), s_cur[r + 1]);
-        const float tmax = max_xor32(t0);
-        // the accumulator of this query block already holds P.V of all earlier key blocks
-        rescale_rows(st, QB, row_trig, tmax, c);
-        softmax_block(s_cur, st.mc[QB], pk, blk);
-      }
-      st.lsum[QB] += blk;
-      p_cur[0] = as_v8<T>(make_uint4(pk[0], pk[1], pk[2], pk[3]));
-      p_cur[1] = as_v8<T>(make_uint4(pk[4], pk[5], pk[6], pk[7]));
+      for (int qt = 0; qt < QT; ++qt) softmax(s_cur, -mc[QB][qt], QB, U, qt, LAST, vis);
+      __builtin_amdgcn_sched_barrier(0);   // (units moved into each other cost registers, and at bf16 1 % of the time)
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-
-    // One iteration on LDS stage STAGE (a compile-time constant, so every LDS address is a
-    // per-lane register plus an immediate); the other stage is being filled meanwhile.
-    auto iter = [&](auto STAGEc, int t) {
-      constexpr int STAGE = decltype(STAGEc)::value;
-      const uint16_t* kt = &lds_k[STAGE * kBN * D];
-      const uint16_t* vt = &lds_v[STAGE * kBN * D];
-      const float* bt = &lds_bias[BIAS ? STAGE * kBN : 0];
+    if constexpr (NQB == 1) {
+      unit(I0{}, I0{}, sA, sB);
+      unit(I1{}, I0{}, sB, sA);
+    } else {
+      unit(I0{}, I0{}, sA, sB);
+      unit(I0{}, I1{}, sB, sA);
+      unit(I1{}, I0{}, sA, sB);
+      unit(I1{}, I1{}, sB, sA);
+    }
+  };
+  // the tile's operands have landed, in every wavefront's share
+  auto landed = [&](int t) {
+    if (BIAS && wave == 0) lds_bias[(64 * t + 32 + lane) & 255] = bst;
+    wait_direct_loads();
+    __syncthreads();
+    if (ROPE) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        rope_rows_in_lds<T, D, M>(a, kring + ((2 * t + 1 + i) & 3) * kBlk, D, 32, 32 * (2 * t + 1 + i), tid, THREADS);
+      __syncthreads();
+    }
+  };
+  auto kblk = [&](int b) { return kring + (b & 3) * kBlk; };
+  auto vblk = [&](int b) { return vring + (b & 3) * kBlk; };
+  auto bblk = [&](int b) { return lds_bias + (BIAS ? (b & 7) * 32 : 0); };
+  using No = std::false_type;
+  using Yes = std::true_type;
+  int t = 0;
+  if (T64 > 1) {
+    if (wave_has_rows) iter(Yes{}, No{}, 0, kblk(1), kblk(2), nullptr, nullptr, bblk(0), bblk(1), bblk(2));
+    auto steady = [&](auto ODDc, int t) {
+      constexpr int ODD = decltype(ODDc)::value;   // t & 1: ring slots are compile-time constants
       if (rotate_prio) {
         const int ph = (t + wslot) % 3;
         if (ph == 0) __builtin_amdgcn_s_setprio(2);
         else if (ph == 1) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
       }
-      // the stage being filled was last read in iteration t-1; every wavefront is past
-      // that iteration's barrier
-      if (t + 1 < nf) {
-        fetch_next(t + 2 == nf, &lds_k[(STAGE ^ 1) * kBN * D], &lds_v[(STAGE ^ 1) * kBN * D]);
-        if (BIAS && wave == 0) bst = bias_of((t + 1) * kBN + 32 + lane);
-      }
+      landed(t);
+      request(t);
       if (wave_has_rows) {
-        if constexpr (NQB == 1) {
-          unit(I0{}, I0{}, I0{}, std::true_type{}, sA, sB, pA, pB, kt, vt, bt);
-          unit(I0{}, I0{}, I0{}, std::true_type{}, sB, sA, pB, pA, kt + 32 * D, vt + 32 * D, bt + 32);
-        } else {
-          unit(I0{}, I1{}, I1{}, std::false_type{}, sA, sB, pA, pB, kt, vt, bt);
-          unit(I1{}, I0{}, I0{}, std::true_type{}, sB, sA, pB, pA, kt, vt, bt);
-          unit(I0{}, I1{}, I1{}, std::false_type{}, sA, sB, pA, pB, kt, vt, bt);
-          unit(I1{}, I0{}, I0{}, std::true_type{}, sB, sA, pB, pA, kt + 32 * D, vt + 32 * D, bt + 32);
-        }
-      }
-      // the other bias stage was last read in iteration t-1
-      if (BIAS && wave == 0 && t + 1 < nf) lds_bias[(STAGE ^ 1) * kBN + lane] = bst;
-      wait_direct_loads();  // this wavefront's share of the next tile has landed
-      __syncthreads();
-      if (ROPE && t + 1 < nf) {
-        rope_rows_in_lds<T, D, true>(a, &lds_k[(STAGE ^ 1) * kBN * D], D, 64, (t + 1) * kBN + 32, tid, THREADS,
-                                     t + 2 == nf ? k1_last_row : (t + 1) * kBN + 64);
-        __syncthreads();
+        settle(t - 1, false);
+        iter(No{}, No{}, t, kblk(2 * ODD + 1), kblk(2 * ODD + 2), vblk(2 * ODD - 2), vblk(2 * ODD - 1), bblk(2 * t), bblk(2 * t + 1), bblk(2 * t + 2));
       }
     };
-    int t = 0;
-    for (; t + 1 < nf; t += 2) {
-      iter(I0{}, t);
-      iter(I1{}, t + 1);
+    t = 1;
+    for (; t + 2 < T64; t += 2) {
+      steady(std::integral_constant<int, 1>{}, t);
+      steady(std::integral_constant<int, 0>{}, t + 1);
     }
-    if (t < nf) iter(I0{}, t);
+    if (t + 1 < T64) {
+      steady(std::integral_constant<int, 1>{}, t);
+      ++t;
+    }
     if (rotate_prio) __builtin_amdgcn_s_setprio(0);
-  }
-
-  // ---- drain + ragged tail -------------------------------------------------------------
-  // lds_v rows 0..31: V of the last full block (its P.V is still pending);
-  // lds_v rows 32..95 and lds_k rows 0..63: the partial tile [64 nf, 64 nf + 64).
-  const int tail = n - nf * kBN;
-  {
-    const int base = nf * kBN;
-    for (int i = tid; i < 96 * CH; i += THREADS) {
-      const int row = i / CH, c8 = (i % CH) * 8;
-      const int jg = base - 32 + row;
-      const int jc = jg < 0 ? 0 : (jg < N ? jg : N - 1);
-      uint4 vv = *(const uint4*)(vp + jc * a.vs[2] + c8);
-      if (jg >= n) vv = make_uint4(0, 0, 0, 0);  // 0 * (anything stored in the padding) must be 0
-      *(uint4*)&lds_v[row * SV + c8] = vv;
+    // t = T64 - 1: the last tile, masked
+    landed(t);
+    request(t);
+    if (wave_has_rows) {
+      settle(t - 1, false);
+      iter(No{}, Yes{}, t, kblk(2 * t + 1), nullptr, vblk(2 * t - 2), vblk(2 * t - 1), bblk(2 * t), bblk(2 * t + 1), nullptr);
     }
-    if (tail > 0) {
-      for (int i = tid; i < 64 * CH; i += THREADS) {
-        const int row = i / CH, c8 = (i % CH) * 8;
-        const int jg = base + row;
-        const int jc = jg < N ? jg : N - 1;
-        *(uint4*)&lds_k[row * SK + c8] = *(const uint4*)(kp + jc * a.ks[2] + c8);
+  } else {
+    if (wave_has_rows) iter(Yes{}, Yes{}, 0, kblk(1), nullptr, nullptr, nullptr, bblk(0), bblk(1), nullptr);
+  }
+  // ---- drain: V of the last tile; rows at or beyond n are overwritten with zeros by the lanes that fetched them
+  // (0 * whatever is stored in the padding must be 0)
+  wait_direct_loads();
+  {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const bool mine = D == 32 ? wave == 2 + s : (NW == 4 || (wave >> 2) == s);
+      if (mine) {
+#pragma unroll
+        for (int x = 0; x < LW; ++x)
+          if (32 * (2 * t + s) + row_of[x] >= n) *(uint4*)&vblk(2 * t + s)[row_of[x] * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
       }
-      if (BIAS && wave == 0) lds_bias[lane] = bias_of(base + lane);  // every stage is free after the loop
     }
   }
   __syncthreads();
-  if (ROPE && tail > 0) {
-    rope_rows_in_lds<T, D, false>(a, lds_k, SK, 64, nf * kBN, tid, THREADS);
-    __syncthreads();
-  }
   if (wave_has_rows) {
-    if (nf > 0) {
-      // after an even number of units the pending probabilities sit in pA; they belong
-      // to the last full key block and the wavefront's last query block
+    settle(t, true);
 #pragma unroll
-      for (int ks2 = 0; ks2 < 2; ++ks2)
+    for (int u = 0; u < 2; ++u) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const typename T::v8 vf = load_vt_frag<T, D>(lds_v, lane, ks2, db);
-          st.oacc[NQB - 1][db] = T::mfma(vf, pA[ks2], st.oacc[NQB - 1][db]);
-        }
+      for (int x = 0; x < FR; ++x) va[x] = m.v_frag(vblk(2 * t + u), x);
+#pragma unroll
+      for (int i = 0; i < M::STEPS; ++i)
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) M::out_step(o[qb], va, p[qb][u], i);
     }
-    if (tail > 0) {
-      int jlo[NQB], jhi[NQB];
+  }
+  __syncthreads();  // all operands consumed: the rings become the output patches
+
+  // ---- epilogue: o = O / l, cast, transposed through a private LDS patch so that whole rows are stored; lse
+  {
+    constexpr int kEpiStride = epi_stride(D);
+    uint16_t* const patch = lds + wave * epi_patch(D);
 #pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        jlo[qb] = 0;
-        jhi[qb] = n - 1;
+    for (int qb = 0; qb < NQB; ++qb) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        const int r = M::COLS * qt + m.col, ig = qw0 + 32 * qb + r;
+        const float ltot = M::row_sum(lsum[qb][qt]);
+        const bool live = ig < n && ltot > 0.f;
+        const float inv = live ? 1.0f / ltot : 0.f;
+#pragma unroll
+        for (int x = 0; x < M::QUADS; ++x) {
+          const floatx4 v = M::out_quad(o[qb], qt, x);
+          // padded rows and rows with no visible key: zeros
+          *(uint2*)&patch[r * kEpiStride + m.out_col(x)] =
+              live ? make_uint2(T::pack2(v[0] * inv, v[1] * inv), T::pack2(v[2] * inv, v[3] * inv)) : make_uint2(0, 0);
+        }
+        if (lsep && m.grp == 0 && ig < N) lsep[ig] = live ? (mc[qb][qt] + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
       }
+      // same wavefront writes and reads the patch: program order is enough
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        const int kb0 = nf * kBN + kb * 32;
-        if (kb0 >= n) continue;
-        simple_block<T, NQB, true, 0>(st, qreg, &lds_k[kb * 32 * SK], &lds_v[(32 + kb * 32) * SV], kb0,
-                                      jlo, jhi, lane, c, tau_raw, nullptr, BIAS ? &lds_bias[kb * 32] : nullptr);
+      for (int pass = 0; pass < 32 / RPL; ++pass) {
+        const int r = pass * RPL + lane / CH;
+        const uint4 v = *(const uint4*)&patch[r * kEpiStride + (lane % CH) * 8];
+        const int row = qw0 + 32 * qb + r;
+        if (row < N) *(uint4*)(op + row * a.os[2] + (lane % CH) * 8) = v;
       }
     }
   }
-  __syncthreads();  // tail consumed: the K storage becomes the epilogue patches
-  epilogue<T, NQB>(a, st, op, lsep, qw0, n, lane, lds_k + wave * epi_patch(D));
 }
 
 template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
-  typedef GlobalLds<D, NW> L;
-  __shared__ __attribute__((aligned(16))) uint16_t lds_k[L::kKElems];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_v[L::kVElems];
-  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 2 * kBN : 4];  // [stage][tile row], bias / |scale|
+  __shared__ __attribute__((aligned(16))) uint16_t lds[GlobalLds<D, NW>::kElems];
+  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 256 : 4];  // ring of eight key blocks, bias / |scale|
   TileCoord tc;
-  if (!locate_tile<NW * 32 * NQB>(a, tc)) return;
-  global_body<T, D, NQB, NW, BIAS, true, ROPE>(a, tc, lds_k, lds_v, lds_bias);
+  if (!locate_tile<NW * 32 * NQB, false>(a, tc)) return;
+  global_body<T, D, NQB, NW, BIAS, true, ROPE>(a, tc, lds, lds_bias);
 }
 
 // ======================================================================================
@@ -2557,10 +2830,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void fa_fwd_global_kernel
 // ======================================================================================
 template <class T>
 __global__ __launch_bounds__(kThreads, 2) void fa_fwd_global_mixed_kernel(const FaKernelArgs a) {
-  typedef GlobalLds<kD, 4> L;
-  __shared__ __attribute__((aligned(16))) uint16_t lds_k[L::kKElems];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_v[L::kVElems];
-  __shared__ __attribute__((aligned(16))) float lds_bias[4];
+  __shared__ __attribute__((aligned(16))) uint16_t lds[GlobalLds<kD, 4>::kElems];
   const int N = a.max_len, H = a.heads;
   int n = N;
   if (a.seq_lens) {
@@ -2578,10 +2848,10 @@ __global__ __launch_bounds__(kThreads, 2) void fa_fwd_global_mixed_kernel(const 
   tc.q0 = __builtin_amdgcn_readfirstlane(m.q0);
   if (m.kind == 1) {
     tc.qt = m.q0 >> 8;
-    global_body<T, kD, 2, 4, false, false>(a, tc, lds_k, lds_v, lds_bias);
+    global_body<T, kD, 2, 4, false, false>(a, tc, lds, nullptr);
   } else if (m.kind == 2) {
     tc.qt = m.q0 >> 7;
-    global_body<T, kD, 1, 4, false, false>(a, tc, lds_k, lds_v, lds_bias);
+    global_body<T, kD, 1, 4, false, false>(a, tc, lds, nullptr);
   } else if (m.kind == 3) {
     // tiles T .. ceil(max_len / 128) - 1 of every head are padding only: o = 0, lse = -inf.
     // The spare ids share them out in a strided loop (there are normally more ids than tiles).

@@ -1,0 +1,56 @@
+"""GPU parity of the pipelined global kernel at the edges of its 64-key tiles (one key, one block, a block and one, whole tiles,
+one past them) in every shape, with scores that jump at chosen keys, so that references have to be refreshed - in the first
+and the second block of a tile, in the first, an inner and the masked last tile, several tiles in a row - and rows whose
+first keys are all excluded.  Against the fp64 oracle with the bounds of the other parity tests."""
+import numpy as np
+import pytest
+
+import paper_2603_12646_amd as fa
+from oracle.attention_oracle import attention_oracle
+from workloads import draw, round_to_storage
+
+from tests.gpu_util import check_against, run_ex
+
+pytestmark = pytest.mark.gpu
+
+LENS = [1, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 192, 193, 255, 256, 321, 0]
+N = 330
+
+
+def inputs(head_dim, dtype, spikes):
+    """Scores of about N(0, 1); key j of `spikes` scores about `spikes[j]` higher with every second query row."""
+    _, q, k, v = draw(77, len(LENS), 2, N, head_dim, dtype)
+    q[:, :, ::2, 0] = 4.0
+    q[:, :, 1::2, 0] = 0.0
+    k[:, :, :, 0] = 0.0
+    for j, height in spikes.items():
+        k[:, :, j, 0] = height * np.sqrt(head_dim) / 4.0
+    return q, round_to_storage(k, dtype), v
+
+
+@pytest.mark.parametrize("spikes", [{}, {40: 30.0}, {70: 14.0, 100: 28.0, 140: 42.0, 200: 300.0}, {5: 60.0, 64: 90.0, 320: 130.0}],
+                         ids=["flat", "first_tile", "rising", "last_tile"])
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256, fa.FA_TUNE_BM_512], ids=["128", "256", "512"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+def test_tile_edges_and_refreshes(head_dim, dtype, tuning, spikes):
+    q, k, v = inputs(head_dim, dtype, spikes)
+    scale = 1.0 / np.sqrt(head_dim)
+    o_ref, lse_ref = attention_oracle(q, k, v, LENS, scale, -1, -1)
+    o, lse = run_ex(q, k, v, LENS, dtype, scale, tuning=tuning)
+    check_against(o, lse, o_ref, lse_ref, LENS, dtype, relative=True)   # (a spiked row is one V row: outputs of up to 4)
+
+
+@pytest.mark.parametrize("first", [20, 40, 64, 100, 200])
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256], ids=["128", "256"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+def test_bias_excludes_first_keys(head_dim, dtype, tuning, first):
+    """No reference until key `first`: in the first or second block of a tile, or after whole excluded tiles."""
+    q, k, v = inputs(head_dim, dtype, {150: 40.0})
+    bias = np.zeros((len(LENS), N), dtype=np.float32)
+    bias[:, :first] = -np.inf
+    scale = 1.0 / np.sqrt(head_dim)
+    o_ref, lse_ref = attention_oracle(q, k, v, LENS, scale, -1, -1, key_bias=bias)
+    o, lse = run_ex(q, k, v, LENS, dtype, scale, tuning=tuning, key_bias=bias)
+    check_against(o, lse, o_ref, lse_ref, LENS, dtype, relative=True)
