@@ -30,6 +30,7 @@ struct FaKernelArgs {
   int32_t total_tiles;  // batch * heads * n_qtiles
   int32_t map_xcd;  // nonzero: each XCD owns a contiguous eighth of every batch element's tiles
   int32_t heads_first;  // with map_xcd: consecutive tiles are the heads of one query tile (else the query tiles of one head)
+  int32_t longest_first;  // with map_xcd: the batch's sequences in order of falling length, to an eighth of max_len (at most 64 of them)
   int32_t xcd_per;  // ceil(heads * n_qtiles / 8)
   int32_t split;    // split kernel: 16 * NQ + NK (blocks of 32 query rows x key splits per workgroup), 0 = another kernel
   int32_t late_n;   // split kernel: loads are issued before the sequence length is looked at

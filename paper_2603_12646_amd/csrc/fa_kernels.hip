@@ -550,9 +550,10 @@ struct TileCoord {
 
 // CLAMP = false leaves tc.n as loaded (the caller clamps it into [0, max_len] when it first
 // needs it, so that the wait for the load can come after other work).
+// LONGEST_FIRST: the kernel also knows the order of sequences by falling length (a.longest_first).
 // HEADS_FIRST: the kernel also knows the heads-first order (a.heads_first); the others keep the query tiles of one head in
 // a row, which is an order of the same tiles.
-template <int BM, bool CLAMP = true, bool HEADS_FIRST = false>
+template <int BM, bool CLAMP = true, bool HEADS_FIRST = false, bool LONGEST_FIRST = false>
 __device__ __forceinline__ bool locate_tile(const FaKernelArgs& a, TileCoord& tc) {
   if (a.map_xcd) {
     // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  Tiles of
@@ -565,6 +566,22 @@ __device__ __forceinline__ bool locate_tile(const FaKernelArgs& a, TileCoord& tc
     const int t = x * per + (j - tc.b * per);
     const bool heads_first = HEADS_FIRST && a.heads_first;
     if (tc.b >= a.batch || (!heads_first && t >= a.heads * a.n_qtiles)) return false;
+    if (LONGEST_FIRST && a.longest_first) {
+      // tc.b is a rank so far: lane l holds sequence l's length; the sequences are taken by eighths of max_len, those of one
+      // eighth as they come
+      const int lane = threadIdx.x & 63;
+      const int len = lane < a.batch ? a.seq_lens[lane] : INT32_MIN;
+      uint64_t longer = 0, in = 0;       // sequences above the eighth, sequences of it
+#pragma unroll
+      for (int e = 7; e >= 0; --e) {
+        const uint64_t down = e > 0 ? __ballot(len > (a.max_len >> 3) * e) : __ballot(lane < a.batch);
+        if (in == 0 && tc.b < __popcll(down)) in = down & ~longer;
+        if (in == 0) longer = down;
+      }
+      const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0));
+      const uint64_t mine = __ballot(((in >> lane) & 1) && at == tc.b - __popcll(longer));
+      tc.b = __ffsll((unsigned long long)mine) - 1;
+    }
     if (heads_first) {
       // all heads of a query tile in a row: the angle tables, or the lines that narrow heads share, are read once per XCD
       int n = a.max_len;
@@ -2811,7 +2828,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void fa_fwd_global_kernel
   __shared__ __attribute__((aligned(16))) uint16_t lds[GlobalLds<D, NW>::kElems];
   __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 256 : 4];  // ring of eight key blocks, bias / |scale|
   TileCoord tc;
-  if (!locate_tile<NW * 32 * NQB, false>(a, tc)) return;
+  if (!locate_tile<NW * 32 * NQB, false, false, true>(a, tc)) return;
   global_body<T, D, NQB, NW, BIAS, true, ROPE>(a, tc, lds, lds_bias);
 }
 

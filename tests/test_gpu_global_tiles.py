@@ -54,3 +54,16 @@ def test_bias_excludes_first_keys(head_dim, dtype, tuning, first):
     o_ref, lse_ref = attention_oracle(q, k, v, LENS, scale, -1, -1, key_bias=bias)
     o, lse = run_ex(q, k, v, LENS, dtype, scale, tuning=tuning, key_bias=bias)
     check_against(o, lse, o_ref, lse_ref, LENS, dtype, relative=True)
+
+
+@pytest.mark.parametrize("batch", [2, 3, 33, 64, 65])
+def test_ragged_batch_order(batch):
+    """Sequences taken by falling length (up to 64 of them): every row of every one, with equal, empty and out-of-range lengths."""
+    n, heads, head_dim = 650, 1, 32
+    lens = np.random.Generator(np.random.PCG64(batch)).integers(-20, n + 20, batch)
+    lens[0], lens[-1] = 650, 81
+    lens[batch // 2] = lens[0]
+    _, q, k, v = draw(5, batch, heads, n, head_dim, "fp16")
+    o_ref, lse_ref = attention_oracle(q, k, v, lens, 0.25, -1, -1)
+    o, lse = run_ex(q, k, v, lens, "fp16", 0.25, tuning=fa.FA_TUNE_BM_128)
+    check_against(o, lse, o_ref, lse_ref, lens, "fp16")
