@@ -2131,6 +2131,12 @@ __device__ __forceinline__ void swap_rows16(float x, float& a, float& b) {
   a = x;
   asm("s_nop 1\n\tv_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "=&v"(b));
 }
+// maximum over the wavefront
+__device__ __forceinline__ float row_max64(float x) {
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) x = fmaxf(x, __shfl_xor(x, d));
+  return x;
+}
 // maximum / sum over the four lanes that hold one query
 __device__ __forceinline__ float max_quad(float x) {
   float a, b;
@@ -2199,7 +2205,7 @@ struct Tile32 {
       for (int r = 0; r < 4; ++r) s[4 * x + r] = b[r];
     }
   }
-  __device__ __forceinline__ void add(Scores& s, const float* bias) const { add_bias(s, bias, grp); }
+  static __device__ __forceinline__ void add(Scores& s, const Scores& bias) { s += bias; }
   static __device__ __forceinline__ void add_each(Scores& s, const float (&b)[E]) {   // b[i]: for element i
 #pragma unroll
     for (int i = 0; i < E; ++i) s[i] += b[i];
@@ -2267,14 +2273,6 @@ struct Tile16 {
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) s.t[kt][0] = s.t[kt][1] = BIAS ? *(const floatx4*)&bias[16 * kt + 4 * grp] : (floatx4){0.f, 0.f, 0.f, 0.f};
   }
-  __device__ __forceinline__ void add(Scores& s, const float* bias) const {
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const floatx4 b = *(const floatx4*)&bias[16 * kt + 4 * grp];
-      s.t[kt][0] += b;
-      s.t[kt][1] += b;
-    }
-  }
   static __device__ __forceinline__ void add_each(Scores& s, const float (&b)[E]) {
 #pragma unroll
     for (int i = 0; i < E; ++i) {
@@ -2308,10 +2306,10 @@ struct Tile16 {
 // the matrix cores as well, gains from it everywhere (8K 12 x 64 192 -> 180 us, 8 x 128 236 -> 221).  bf16 keeps 16 fp32
 // additions per unit, so head_dim 32 and 64 are short of issue slots (3 x 16K 1465 -> 1516 in the smaller shape, 24 x 32
 // 8K 267 -> 278; 8K 12 x 64 alone gains, 194 -> 187) and only head_dim 128 takes it (8K 231 -> 221).
-template <class T, int D>
-struct GlobalTile { typedef Tile16<T, D> type; };
-template <int D>
-struct GlobalTile<BF16, D> { typedef typename std::conditional<D == 128, Tile16<BF16, D>, Tile32<BF16, D>>::type type; };
+template <class T, int D, bool SUM32>
+struct GlobalTile {
+  typedef typename std::conditional<D == 128 || (T::kSumRounded && !SUM32), Tile16<T, D>, Tile32<T, D>>::type type;
+};
 
 // One row's fragments straight from global memory: the B operand of Q, and the A operand of K where a refresh forms scores
 // again.  FR fragments x = 0 .. FR - 1 hold chunks chunk(x); row: inside the tensor.
@@ -2354,7 +2352,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   constexpr int THREADS = NW * 64;
   constexpr int BM = NW * 32 * NQB;
   constexpr bool BIAS_LAST = BIAS && D == 32, BIAS_FIRST = BIAS && !BIAS_LAST;
-  typedef typename GlobalTile<T, D>::type M;
+  typedef typename GlobalTile<T, D, BIAS_LAST>::type M;
   constexpr bool MFMA_SUM = M::kMfmaSum && T::kSumRounded && !BIAS_LAST;
   constexpr int QT = M::QT, E = M::E, FR = D / 16;
   constexpr int kBlk = 32 * D;
@@ -2480,7 +2478,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       }
   }
   const int n = tc.n;
-  const int T64 = (n + 63) >> 6;                 // 64-key tiles
+  int nk = n, T64 = (n + 63) >> 6;               // keys that count, 64-key tiles
   const bool wave_has_rows = qw0 < n;
   const float c = a.c;
 
@@ -2499,13 +2497,15 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     for (int x = 0; x < D / 2; ++x) of[x] = 0.f;
   }
 
-  auto load_ka = [&](const uint16_t* kblk) {
+  typename M::Scores bcur;   // BIAS_LAST: the bias of the key block in ka (head_dim 32 has the registers, and its units are short)
+  auto load_ka = [&](const uint16_t* kblk, const float* bblk) {
 #pragma unroll
     for (int x = 0; x < FR; ++x) ka[x] = m.k_frag(kblk, x);
+    if (BIAS_LAST) m.template start<true>(bcur, bblk);
   };
   auto score_init = [&](typename M::Scores& s, const float* bblk) { m.template start<BIAS_FIRST>(s, bblk); };
-  auto score_end = [&](typename M::Scores& s, const float* bblk) {
-    if (BIAS_LAST) m.add(s, bblk);
+  auto score_end = [&](typename M::Scores& s) {
+    if constexpr (BIAS_LAST) M::add(s, bcur);   // (Tile32 always)
   };
   // probabilities of a block against the rows' references, packed, and their sums
   auto softmax = [&](const typename M::Scores& s, float nmc, int qb, int u, int qt, bool masked, uint32_t vis) {
@@ -2572,7 +2572,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
 #pragma unroll 1
       for (int u = 0; u < 2; ++u) {
         scores(u);
-        const uint32_t vis = masked ? m.visible(2 * t + u, n) : 0xFFFFu;
+        const uint32_t vis = masked ? m.visible(2 * t + u, nk) : 0xFFFFu;
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
@@ -2582,8 +2582,10 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
         tmax[qt] = M::row_max(tmax[qt]);
-        const bool take = row_trig[qt] && tmax[qt] != -INFINITY;
-        const float mc_new = take ? tmax[qt] * c : mc[qb][qt];
+        // (a reference only rises: the tile of a row that was expected to be cold may still lie below it)
+        const float mc_tile = tmax[qt] == -INFINITY ? -INFINITY : tmax[qt] * c;
+        const bool take = row_trig[qt] && mc_tile > mc[qb][qt];
+        const float mc_new = take ? mc_tile : mc[qb][qt];
         // (a row without a reference has nothing accumulated: factor exp2(-inf) = 0)
         const float alpha = take ? __builtin_amdgcn_exp2f(mc[qb][qt] - mc_new) : 1.f;
         mc[qb][qt] = mc_new;
@@ -2594,7 +2596,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         scores(u);
-        const uint32_t vis = masked ? m.visible(2 * t + u, n) : 0xFFFFu;
+        const uint32_t vis = masked ? m.visible(2 * t + u, nk) : 0xFFFFu;
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) softmax(s, nmc[qt], qb, u, qt, true, vis);
       }
@@ -2623,6 +2625,37 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   if (BIAS) {
     if (tid < 96) lds_bias[tid] = bias_of(tid);
   }
+  // BIAS: keys end .. n - 1 have biases below -1000 (log2 domain), top_bias is at least the largest of them (raw units).
+  // 512 keys per step from the end, while the first K blocks are on their way; 2 us that a short sequence does not earn back
+  // (24 x 512 31.8 -> 34.8, 4 x 1000 24.9 -> 26.6).
+  int end = n;
+  float top_bias = -INFINITY;
+  if constexpr (BIAS) {
+    while (n >= 1024 && end > 0) {
+      const int first = end - 512 + 8 * lane;   // the lane's eight keys
+      uint16_t raw[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) raw[i] = bp[first + i < 0 ? 0 : first + i];
+      int last = -1;
+      float low = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float x = bias_over_scale<T, D == 32>(a, raw[i]);
+        if (first + i >= 0) {
+          if (!(x * c <= -1000.f)) last = i;
+          else low = fmaxf(low, x);
+        }
+      }
+      top_bias = fmaxf(top_bias, low);   // (that of some ordinary step's cold keys too: larger at most)
+      const uint64_t warm = __ballot(last >= 0);
+      if (warm) {
+        const int at = 63 - __clzll((long long)warm);
+        end = end - 512 + 8 * at + __builtin_amdgcn_readlane(last, at) + 1;
+        break;
+      }
+      end -= 512;
+    }
+  }
   wait_direct_loads();
   __syncthreads();
   if (ROPE) {
@@ -2632,17 +2665,17 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     __syncthreads();
   }
   typename M::Scores sA, sB;
-  load_ka(kring);
+  load_ka(kring, lds_bias);
   __syncthreads();   // K block 0 is in registers everywhere: block 4 takes its place
   request(0);
   {
-    const uint32_t vis = m.visible(0, n);
+    const uint32_t vis = m.visible(0, nk);
 #pragma unroll
     for (int qb = NQB - 1; qb >= 0; --qb) {
       score_init(sA, lds_bias);
 #pragma unroll
       for (int i = 0; i < M::STEPS; ++i) M::score_step(sA, ka, q[qb], i);
-      score_end(sA, lds_bias);
+      score_end(sA);
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
         float t0 = -INFINITY;
@@ -2650,6 +2683,83 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         for (int i = 0; i < E; ++i) t0 = fmaxf(t0, keep_or_neg_inf(M::get(sA, qt, i), vis, i));
         t0 = M::row_max(t0);
         mc[qb][qt] = t0 == -INFINITY ? -INFINITY : t0 * c;
+      }
+    }
+  }
+
+  // Padding given as a bias (-65504 per padded key) is still a score, but its probability is exactly 0 beside any ordinary
+  // key: below 2^-25 for fp16, whose sums are those of the rounded values, below the fp32 range otherwise.  The keys after
+  // the last one whose bias is above -1000 (in the log2 domain) leave the call if that can be shown ahead of it: with the
+  // largest |k| among them, every row's |q|_1, and its first reference (references only rise); and if their V is finite (0
+  // times it is 0).  Showing it takes one pass over their K and V without arithmetic on them.
+  // Measured, us, without -> with: 8 x 2048 (1024 -) fp16 121.7 -> 112.6, 16 x 1500 (700 -) 140 -> 134, 1 x 8192 (5000) 8 x 128 239 -> 194,
+  // bf16 1 x 16804 (7024) 1075 -> 654; without padding the search costs 0 - 2 %.
+  if constexpr (BIAS) {
+    // (a pass takes 3 us and 0.5 us per tile, a tile in the pipeline 1.6: from eight tiles on)
+    if (end > 0 && (end + 63) / 64 + 8 <= T64) {
+      uint32_t* const shared = (uint32_t*)(lds_bias + 256);   // [0] largest |k|, [1] largest |v| (bits), [2] a wavefront refuses
+      if (tid < 3) shared[tid] = 0;
+      top_bias = row_max64(top_bias);
+      uint32_t kbits = 0, vbits = 0;   // pairs of magnitudes as 16-bit integers (an infinity or a NaN is above all others)
+      typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+      auto grow = [](uint32_t& m, uint4 x) {
+        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, m), __builtin_bit_cast(us2, w[i] & 0x7FFF7FFFu)));
+      };
+      constexpr int RS = THREADS / CH;
+      constexpr int AHEAD = D == 128 ? 4 : 6;   // rows of K and of V that a thread has under way
+      for (int r = end + tid / CH; r < n; r += AHEAD * RS) {
+        uint4 kx[AHEAD], vx[AHEAD];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+          const int rr = r + i * RS < n ? r + i * RS : r;
+          kx[i] = *(const uint4*)(kp + rr * a.ks[2] + (tid % CH) * 8);
+          vx[i] = *(const uint4*)(vp + rr * a.vs[2] + (tid % CH) * 8);
+        }
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+          grow(kbits, kx[i]);
+          grow(vbits, vx[i]);
+        }
+      }
+      __syncthreads();
+      kbits = (kbits & 0xFFFFu) > (kbits >> 16) ? kbits & 0xFFFFu : kbits >> 16;
+      vbits = (vbits & 0xFFFFu) > (vbits >> 16) ? vbits & 0xFFFFu : vbits >> 16;
+      // (magnitudes below 2^16 as integers are exact and ordered as floats)
+      kbits = (uint32_t)row_max64((float)kbits);
+      vbits = (uint32_t)row_max64((float)vbits);
+      if (lane == 0) {
+        atomicMax(&shared[0], kbits);
+        atomicMax(&shared[1], vbits);
+      }
+      __syncthreads();
+      const uint32_t inf = T::kWideRange ? 0x7F80u : 0x7C00u;
+      const float kmax = T::to_float((uint16_t)shared[0]);
+      bool nothing = shared[0] < inf && shared[1] < inf;
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) {
+          float q1 = 0.f;
+#pragma unroll
+          for (int x = 0; x < FR / QT; ++x) {
+            const uint4 w = __builtin_bit_cast(uint4, q[qb][qt * (FR / QT) + x]);
+            const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              q1 += __builtin_fabsf(T::to_float((uint16_t)ww[i])) + __builtin_fabsf(T::to_float((uint16_t)(ww[i] >> 16)));
+          }
+          // (1.01: the roundings of the bound and of the score itself)
+          const float most = __builtin_fmaf(M::row_sum(q1) * 1.01f, kmax, top_bias * 0.99f);
+          nothing = nothing && __builtin_fmaf(most, c, -mc[qb][qt]) < (MFMA_SUM ? -26.f : -160.f);
+        }
+      if (!__all(nothing)) shared[2] = 1;
+      __syncthreads();
+      if (shared[2] == 0) {
+        nk = end;
+        T64 = (end + 63) >> 6;
       }
     }
   }
@@ -2673,7 +2783,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       constexpr int NQ = (QB + 1) % NQB;
       constexpr bool NEXT = !(LAST && U == 1 && NQ == 0);     // there is a next unit
       const float* bnext = NQ != 0 ? (U == 0 ? b0 : b1) : (U == 0 ? b1 : b2);   // bias of the next unit's key block
-      if (NQ == 0 && NEXT) load_ka(U == 0 ? k1 : k2);
+      if (NQ == 0 && NEXT) load_ka(U == 0 ? k1 : k2, bnext);
       if (QB == 0 && !FIRST) {
 #pragma unroll
         for (int x = 0; x < FR; ++x) va[x] = m.v_frag(U == 0 ? v1 : v2, x);
@@ -2688,8 +2798,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         if (!FIRST && i >= LATE_O && i - LATE_O < M::STEPS) M::out_step(o[QB], va, p[QB][U], i - LATE_O);
         if (NEXT && LATE_S && i > 0) M::score_step(s_nxt, ka, q[NQ], i - 1);
       }
-      if (NEXT) score_end(s_nxt, bnext);
-      const uint32_t vis = LAST ? m.visible(2 * t + U, n) : 0xFFFFu;
+      if (NEXT) score_end(s_nxt);
+      const uint32_t vis = LAST ? m.visible(2 * t + U, nk) : 0xFFFFu;
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) softmax(s_cur, -mc[QB][qt], QB, U, qt, LAST, vis);
       __builtin_amdgcn_sched_barrier(0);   // (units moved into each other cost registers, and at bf16 1 % of the time)
@@ -2761,7 +2871,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   } else {
     if (wave_has_rows) iter(Yes{}, Yes{}, 0, kblk(1), nullptr, nullptr, nullptr, bblk(0), bblk(1), nullptr);
   }
-  // ---- drain: V of the last tile; rows at or beyond n are overwritten with zeros by the lanes that fetched them
+  // ---- drain: V of the last tile; rows at or beyond nk are overwritten with zeros by the lanes that fetched them
   // (0 * whatever is stored in the padding must be 0)
   wait_direct_loads();
   {
@@ -2771,7 +2881,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       if (mine) {
 #pragma unroll
         for (int x = 0; x < LW; ++x)
-          if (32 * (2 * t + s) + row_of[x] >= n) *(uint4*)&vblk(2 * t + s)[row_of[x] * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
+          if (32 * (2 * t + s) + row_of[x] >= nk) *(uint4*)&vblk(2 * t + s)[row_of[x] * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
       }
     }
   }
@@ -2824,9 +2934,11 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
 }
 
 template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false>
-__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
+// (one block of rows per wavefront at head_dim 64: 168 registers for three wavefronts per SIMD, asked for where the compiler
+// would take a few more: 16 x 700 with a bias 38.5 -> 49.8 us at two)
+__global__ __launch_bounds__(NW * 64, NW == 4 ? (BIAS && D == 64 && NQB == 1 ? 3 : 2) : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[GlobalLds<D, NW>::kElems];
-  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 256 : 4];  // ring of eight key blocks, bias / |scale|
+  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 260 : 4];  // ring of eight key blocks, bias / |scale|; three words of the pass over padding
   TileCoord tc;
   if (!locate_tile<NW * 32 * NQB, false, false, true>(a, tc)) return;
   global_body<T, D, NQB, NW, BIAS, true, ROPE>(a, tc, lds, lds_bias);

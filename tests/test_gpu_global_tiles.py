@@ -67,3 +67,41 @@ def test_ragged_batch_order(batch):
     o_ref, lse_ref = attention_oracle(q, k, v, lens, 0.25, -1, -1)
     o, lse = run_ex(q, k, v, lens, "fp16", 0.25, tuning=fa.FA_TUNE_BM_128)
     check_against(o, lse, o_ref, lse_ref, lens, "fp16")
+
+
+PAD_N, PAD_ENDS = 1100, [1, 64, 65, 300, 576, 588, 640, 1099]
+
+
+def padded(head_dim, dtype, value):
+    _, q, k, v = draw(9, len(PAD_ENDS), 1, PAD_N, head_dim, dtype)
+    bias = np.zeros((len(PAD_ENDS), PAD_N), dtype=np.float32)
+    for b, end in enumerate(PAD_ENDS):
+        bias[b, end:] = value
+    return q, k, v, bias
+
+
+@pytest.mark.parametrize("value", [-65504.0, -np.inf, -750.0])
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256], ids=["128", "256"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+def test_padding_by_bias_leaves_the_call(head_dim, dtype, tuning, value):
+    """Tails of keys whose bias makes them count for nothing, fewer and more than the eight tiles from which they are looked
+    at; in the last sequence two keys of the tail count all the same, by their size."""
+    q, k, v, bias = padded(head_dim, dtype, round_to_storage(np.float32([value]), dtype)[0])
+    scale = 1.0 / np.sqrt(head_dim)
+    if value == -750.0:
+        q[3, :, :, 0] = 64.0
+        k[3, :, [700, 1000], 0] = 900.0 / 64.0 / scale     # 150 above the bias, and above the ordinary keys
+    o_ref, lse_ref = attention_oracle(q, round_to_storage(k, dtype), v, None, scale, -1, -1, key_bias=bias)
+    o, lse = run_ex(q, round_to_storage(k, dtype), v, None, dtype, scale, tuning=tuning, key_bias=bias)
+    check_against(o, lse, o_ref, lse_ref, None, dtype, relative=True)
+
+
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+def test_padding_by_bias_with_infinite_values(head_dim):
+    """A probability of 0 times an infinite V is NaN, in the padding too: such a tail stays in the call."""
+    q, k, v, bias = padded(head_dim, "fp16", -65504.0)
+    v[3, :, 900, 5] = np.inf
+    o, _ = run_ex(q, k, v, None, "fp16", 1.0 / np.sqrt(head_dim), tuning=fa.FA_TUNE_BM_128, key_bias=bias)
+    assert np.isnan(o[3, :, :, 5]).all()
+    assert np.isfinite(np.delete(o[3], 5, axis=-1)).all() and np.isfinite(np.delete(o, 3, axis=0)).all()
