@@ -362,8 +362,9 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   // Ragged batches on the pipelined kernel: long sequences first, so that the short tiles fill the last round.  Finding the
   // r-th sequence takes a workgroup 1 us before its first load, which short tiles do not earn back: us, 12 x 64, as they
   // come -> longest first: 12 x 700 (300 -) 20.9 -> 20.1, 16 x 1024 (600 -) 49.1 -> 48.0, 3 x 16K (9000 -) 1476 -> 1465, but
-  // 32 x 512 (256 -) 30.9 -> 30.3, (480 -) 36.7 -> 37.7.
-  a.longest_first = a.map_xcd && !windowed && p->seq_lens && p->batch > 1 && p->batch <= 64 && p->max_len >= 640;
+  // 32 x 512 (256 -) 30.9 -> 30.3, (480 -) 36.7 -> 37.7; and where one round holds the call, nothing (6 x 700 8 x 128 23.6 -> 25.4).
+  a.longest_first = a.map_xcd && !windowed && p->seq_lens && p->batch > 1 && p->batch <= 64 && p->max_len >= 640 &&
+                    total > (bm == 128 && p->head_dim != 128 ? 768 : 512);
   const int64_t per = ((int64_t)p->heads * n_qtiles + 7) / 8;
   if (8 * per * p->batch > 0x7FFFFFF0LL) return FA_ERR_BAD_SHAPE;
   a.xcd_per = (int32_t)per;

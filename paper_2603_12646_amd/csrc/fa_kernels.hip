@@ -2413,35 +2413,33 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       }
     }
   };
-  // K blocks kb, kb + 1 (the second if k2) and V blocks vb, vb + 1 into ring slots; with_k / with_v: wavefront-uniform
-  auto fetch = [&](int kb, bool with_k, bool k2, int vb, bool with_v) {
+  // K blocks kb (if k1), kb + 1 (if k2) and V blocks vb, vb + 1 (if v) into ring slots
+  auto fetch = [&](int kb, bool k1, bool k2, int vb, bool v) {
     if (D == 32) {
       if (wave < 2) {
-        if (with_k && (wave == 0 || k2)) load_block(kp, a.ks[2], koff, kb + wave, kring + ((kb + wave) & 3) * kBlk);
-      } else if (with_v) {
+        if (wave == 0 ? k1 : k2) load_block(kp, a.ks[2], koff, kb + wave, kring + ((kb + wave) & 3) * kBlk);
+      } else if (v) {
         load_block(vp, a.vs[2], voff, vb + wave - 2, vring + ((vb + wave - 2) & 3) * kBlk);
       }
     } else if (NW == 4) {
-      if (with_k) load_block(kp, a.ks[2], koff, kb, kring + (kb & 3) * kBlk);
-      if (with_k && k2) load_block(kp, a.ks[2], koff, kb + 1, kring + ((kb + 1) & 3) * kBlk);
-      if (with_v) {
+      if (k1) load_block(kp, a.ks[2], koff, kb, kring + (kb & 3) * kBlk);
+      if (k2) load_block(kp, a.ks[2], koff, kb + 1, kring + ((kb + 1) & 3) * kBlk);
+      if (v) {
         load_block(vp, a.vs[2], voff, vb, vring + (vb & 3) * kBlk);
         load_block(vp, a.vs[2], voff, vb + 1, vring + ((vb + 1) & 3) * kBlk);
       }
     } else if (wave < 8) {
       const int s = wave >> 2;
-      if (with_k && (s == 0 || k2)) load_block(kp, a.ks[2], koff, kb + s, kring + ((kb + s) & 3) * kBlk);
-      if (with_v) load_block(vp, a.vs[2], voff, vb + s, vring + ((vb + s) & 3) * kBlk);
+      if (s == 0 ? k1 : k2) load_block(kp, a.ks[2], koff, kb + s, kring + ((kb + s) & 3) * kBlk);
+      if (v) load_block(vp, a.vs[2], voff, vb + s, vring + ((vb + s) & 3) * kBlk);
     }
   };
-  // The first blocks of K are requested before the sequence length is looked at.
-  if (D == 32 || NW > 4) {
-    fetch(0, true, true, 0, false);
-    fetch(2, true, false, 0, false);
-  } else {
-    fetch(0, true, true, 0, false);
-    load_block(kp, a.ks[2], koff, 2, kring + 2 * kBlk);
-  }
+  // The first K blocks, as far as the tensor reaches, are requested before the sequence length is looked at; in longer
+  // tensors the rest of tile 1's operands (K block 3, V blocks 0 and 1) with them.  us, without -> with: 16 x 700 with a bias
+  // 41.8 -> 39.6, 16 x 1024 49.7 -> 49.3, but 7 x 542 14.0 -> 14.2, 32 x 128 9.2 -> 9.9 (more to wait for before the first product).
+  const bool early = N >= 640;
+  fetch(0, true, 32 < N, 0, early);
+  fetch(2, 64 < N, early, 0, false);
 
   const int qw0 = q0 + wave * 32 * NQB;
   v8 q[NQB][FR];
@@ -2616,10 +2614,36 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       for (int qt = 0; qt < QT; ++qt) lsum[qb][qt] += z[qb][qt][0];
   };
 
-  // ---- prologue: K blocks 0 .. 2 have landed; first scores, first references
+  // ---- prologue: the first blocks have landed; first scores, first references
   float bst = 0.f;  // BIAS: wavefront 0 carries the next tile's bias from its load to its LDS write
+  // row bases of the next request: K block 2 t + 3, V block 2 t
+  const int64_t k32 = 32 * a.ks[2], v32 = 32 * a.vs[2];
+  const uint16_t *kreq = kp + 3 * k32, *vreq = vp;
   auto request = [&](int t) {   // operands of tile t + 1
-    fetch(2 * t + 3, t + 1 < T64, t + 2 < T64, 2 * t, true);
+    if (NW == 4 && D != 32 && t > 0 && 64 * t + 160 <= N) {
+      // Every row exists (rows past the sequence are loaded for nothing at its end): the bases just advance.  (General
+      // addresses each time were 40 - 60 scalar instructions per tile: 32K bf16 2845 -> 2794 us, 3 x 16K 1438 -> 1410, 8 x 2048
+      // (1500 -) fp16 96.7 -> 91.5, with a bias (1024 -) 111.8 -> 107.9.)
+#pragma unroll
+      for (int x = 0; x < LW; ++x) {
+        load16_to_lds(kreq, koff[x], kring + ((2 * t + 3) & 3) * kBlk + (part0 + x) * RPL * D);
+        load16_to_lds(kreq + k32, koff[x], kring + ((2 * t + 4) & 3) * kBlk + (part0 + x) * RPL * D);
+        load16_to_lds(vreq, voff[x], vring + ((2 * t) & 3) * kBlk + (part0 + x) * RPL * D);
+        load16_to_lds(vreq + v32, voff[x], vring + ((2 * t + 1) & 3) * kBlk + (part0 + x) * RPL * D);
+      }
+    } else if (NW == 8 && t > 0 && 64 * t + 160 <= N) {
+      const int s = wave >> 2;
+#pragma unroll
+      for (int x = 0; x < LW; ++x) {
+        load16_to_lds(kreq + s * k32, koff[x], kring + ((2 * t + 3 + s) & 3) * kBlk + (part0 + x) * RPL * D);
+        load16_to_lds(vreq + s * v32, voff[x], vring + ((2 * t + s) & 3) * kBlk + (part0 + x) * RPL * D);
+      }
+    } else {
+      const bool there = t == 0 && early;   // (all but K block 4)
+      fetch(2 * t + 3, !there && t + 1 < T64, t + 2 < T64, 2 * t, !there);
+    }
+    kreq += 2 * k32;
+    vreq += 2 * v32;
     if (BIAS && wave == 0) bst = bias_of(64 * t + 96 + lane);
   };
   if (BIAS) {
@@ -2661,7 +2685,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   if (ROPE) {
     // every K block is rotated in place once it has landed
 #pragma unroll
-    for (int i = 0; i < 3; ++i) rope_rows_in_lds<T, D, M>(a, kring + i * kBlk, D, 32, 32 * i, tid, THREADS);
+    for (int i = 0; i < 3; ++i) rope_rows_in_lds<T, D, M>(a, kring + i * kBlk, D, 32, 32 * i, tid, THREADS);   // (block 3: with tile 1)
     __syncthreads();
   }
   typename M::Scores sA, sB;
@@ -2802,7 +2826,9 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       const uint32_t vis = LAST ? m.visible(2 * t + U, nk) : 0xFFFFu;
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) softmax(s_cur, -mc[QB][qt], QB, U, qt, LAST, vis);
-      __builtin_amdgcn_sched_barrier(0);   // (units moved into each other cost registers, and at bf16 1 % of the time)
+      // Units moved into each other cost registers (the variants with a bias or a rotation spill), and Tile32 1 % of its time;
+      // Tile16 gains 1 - 2 % by it (8K 12 x 64 179 -> 176 us), 7 x 542 2 %.
+      if (M::COLS == 32 || BIAS || ROPE) __builtin_amdgcn_sched_barrier(0);
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
