@@ -146,11 +146,13 @@ struct BF16 {
 // a = x of the lower lane of the pair and b = x of the upper one, in both lanes.
 // v_permlane32_swap exchanges lanes 32..63 of its first register with lanes 0..31 of
 // its second.  Written as asm because the compiler folds the builtin's two results
-// into one when both inputs are the same value; the s_nops cover the VALU-write ->
-// permlane-read hazards the compiler cannot see inside an asm block.
+// into one when both inputs are the same value; the s_nop covers the VALU-write ->
+// permlane-read hazard the compiler cannot see inside an asm block.  Both registers come into
+// the block with a value: one that it merely wrote could still be the destination of a matrix
+// product under way, whose late write the compiler only guards against where it sees the other.
 __device__ __forceinline__ void swap_halves(float x, float& a, float& b) {
-  a = x;
-  asm("s_nop 1\n\tv_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "=&v"(b));
+  a = b = x;
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
 __device__ __forceinline__ float max_xor32(float x) {
   float a, b;
@@ -2128,8 +2130,8 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
 // ======================================================================================
 // Exchange between lanes l and l ^ 16, as swap_halves does it between l and l ^ 32.
 __device__ __forceinline__ void swap_rows16(float x, float& a, float& b) {
-  a = x;
-  asm("s_nop 1\n\tv_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "=&v"(b));
+  a = b = x;
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
 // maximum over the wavefront
 __device__ __forceinline__ float row_max64(float x) {
