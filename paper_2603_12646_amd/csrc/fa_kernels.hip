@@ -2151,6 +2151,8 @@ __device__ __forceinline__ float sum_quad(float x) {
   return sum_xor32(a + b);
 }
 
+__device__ __forceinline__ const uint16_t* bytes_on(const uint16_t* p, uint32_t bytes) { return (const uint16_t*)((const char*)p + bytes); }
+
 // A unit of the pipeline is 32 keys x 32 queries.  How it is laid over the lanes is a policy with two members, for the two
 // shapes of the matrix instruction; per lane both hold D / 16 fragments of Q, of K and of V^T, 2 of P, 16 scores and D / 2
 // output values of a query block, and one score product can alternate with one output product.
@@ -2173,29 +2175,36 @@ struct Tile32 {
   static __device__ __forceinline__ int k_swz(int r) { return k_swz_d<D>(r); }
   static __device__ __forceinline__ int v_swz(int r) { return v_swz_d<D>(r); }
   int col, grp;                      // the lane's query column, and which of the lanes that share it
-  uint32_t kfo[D / 16], vfo[D / 32];  // operand offsets (16-bit elements) into a 32-row block
+  uint32_t kfo[D / 16], vfo[D / 32];  // operand offsets (bytes) into a 32-row block
 
+  __device__ __forceinline__ void place(int lane) { col = lane & 31, grp = lane >> 5; }
+  // to the other half of a ring of eight blocks
+  __device__ __forceinline__ void flip() {
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) kfo[ks] ^= 4 * 32 * D * 2;
+  }
   __device__ __forceinline__ void init(int lane) {
-    col = lane & 31;
-    grp = lane >> 5;
+    place(lane);
     const int p16 = lane & 15, g = (lane >> 4) & 1, row = 4 * grp + (p16 >> 2);
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) kfo[ks] = col * D + (((2 * ks + grp) ^ k_swz(col)) * 8);
+    for (int ks = 0; ks < D / 16; ++ks) kfo[ks] = 2 * (col * D + ((2 * ks + grp) ^ k_swz(col)) * 8);
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) vfo[db] = row * D + (((4 * db + 2 * g + ((p16 & 3) >> 1)) ^ v_swz(row)) * 8) + (p16 & 1) * 4;
+    for (int db = 0; db < D / 32; ++db) vfo[db] = 2 * (row * D + ((4 * db + 2 * g + ((p16 & 3) >> 1)) ^ v_swz(row)) * 8 + (p16 & 1) * 4);
   }
   // fragments i = 0 .. D/16 - 1 of a block: K and Q k-step i; V^T 16-key half i / (D/32), column block i % (D/32)
-  __device__ __forceinline__ v8 k_frag(const uint16_t* blk, int i) const { return as_v8<T>(*(const uint4*)&blk[kfo[i]]); }
+  __device__ __forceinline__ v8 k_frag(const uint16_t* blk, int i) const { return as_v8<T>(*(const uint4*)bytes_on(blk, kfo[i])); }
   __device__ __forceinline__ v8 v_frag(const uint16_t* blk, int i) const {
-    const uint16_t* at = &blk[vfo[i % (D / 32)] + (i / (D / 32)) * 16 * D];
+    const uint16_t* at = bytes_on(blk, vfo[i % (D / 32)]) + (i / (D / 32)) * 16 * D;
     return tr_pair<v8>(at, at + 8 * D);
   }
   static __device__ __forceinline__ void score_step(Scores& s, const v8* k, const v8* q, int i) { s = T::mfma(k[i], q[i], s); }
+  // the K fragment of step i, and whether no step before uses it
+  static constexpr int frag_of(int i) { return i; }
+  static constexpr bool first_use(int) { return true; }
   static __device__ __forceinline__ void out_step(Out& o, const v8* v, const v8* p, int i) {
     o[i % (D / 32)] = T::mfma(v[i], p[i / (D / 32)], o[i % (D / 32)]);
   }
-  // element i of a lane's scores for its query qt: key key_of(i) of the block
-  __device__ __forceinline__ int key_of(int i) const { return 8 * (i >> 2) + 4 * grp + (i & 3); }
+  // element i of a lane's scores for its query qt: key 8 (i / 4) + 4 grp + i % 4 of the block
   static __device__ __forceinline__ float get(const Scores& s, int, int i) { return s[i]; }
   // start value of a block's scores: zero, or the block's bias (four consecutive keys per quad)
   template <bool BIAS>
@@ -2208,10 +2217,6 @@ struct Tile32 {
     }
   }
   static __device__ __forceinline__ void add(Scores& s, const Scores& bias) { s += bias; }
-  static __device__ __forceinline__ void add_each(Scores& s, const float (&b)[E]) {   // b[i]: for element i
-#pragma unroll
-    for (int i = 0; i < E; ++i) s[i] += b[i];
-  }
   __device__ __forceinline__ uint32_t visible(int blk, int n) const { return visible_bits(32 * blk, grp, 0, n - 1); }
   static __device__ __forceinline__ void pack(v8* p, int, const float (&e)[E]) {
 #pragma unroll
@@ -2248,39 +2253,37 @@ struct Tile16 {
   int col, grp;
   uint32_t kfo[KS], vfo[D / 16];
 
+  __device__ __forceinline__ void place(int lane) { col = lane & 15, grp = lane >> 4; }
+  __device__ __forceinline__ void flip() {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kfo[ks] ^= 4 * 32 * D * 2;
+  }
   __device__ __forceinline__ void init(int lane) {
-    col = lane & 15;
-    grp = lane >> 4;
+    place(lane);
     const int row = 4 * grp + (col >> 2);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kfo[ks] = col * D + (((4 * ks + grp) ^ k_swz(col)) * 8);
+    for (int ks = 0; ks < KS; ++ks) kfo[ks] = 2 * (col * D + ((4 * ks + grp) ^ k_swz(col)) * 8);
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) vfo[dt] = row * D + (((2 * dt + ((col & 3) >> 1)) ^ v_swz(row)) * 8) + (col & 1) * 4;
+    for (int dt = 0; dt < D / 16; ++dt) vfo[dt] = 2 * (row * D + ((2 * dt + ((col & 3) >> 1)) ^ v_swz(row)) * 8 + (col & 1) * 4);
   }
   // K: 16-key tile i / KS, k-step i % KS (rows r and r + 16 have the same swizzles); Q: 16-query tile, k-step; V^T: columns
-  __device__ __forceinline__ v8 k_frag(const uint16_t* blk, int i) const { return as_v8<T>(*(const uint4*)&blk[kfo[i % KS] + (i / KS) * 16 * D]); }
+  __device__ __forceinline__ v8 k_frag(const uint16_t* blk, int i) const { return as_v8<T>(*(const uint4*)(bytes_on(blk, kfo[i % KS]) + (i / KS) * 16 * D)); }
   __device__ __forceinline__ v8 v_frag(const uint16_t* blk, int i) const {
-    const uint16_t* at = &blk[vfo[i]];
+    const uint16_t* at = bytes_on(blk, vfo[i]);
     return tr_pair<v8>(at, at + 16 * D);
   }
   static __device__ __forceinline__ void score_step(Scores& s, const v8* k, const v8* q, int i) {
     const int kt = i & 1, qt = (i >> 1) & 1, ks = i >> 2;
     s.t[kt][qt] = T::mfma16(k[kt * KS + ks], q[qt * KS + ks], s.t[kt][qt]);
   }
+  static constexpr int frag_of(int i) { return (i & 1) * KS + (i >> 2); }
+  static constexpr bool first_use(int i) { return !(i & 2); }
   static __device__ __forceinline__ void out_step(Out& o, const v8* v, const v8* p, int i) { o[i & 1][i >> 1] = T::mfma16(v[i >> 1], p[i & 1], o[i & 1][i >> 1]); }
-  __device__ __forceinline__ int key_of(int i) const { return 16 * (i >> 2) + 4 * grp + (i & 3); }
   static __device__ __forceinline__ float get(const Scores& s, int qt, int i) { return s.t[i >> 2][qt][i & 3]; }
   template <bool BIAS>
   __device__ __forceinline__ void start(Scores& s, const float* bias) const {
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) s.t[kt][0] = s.t[kt][1] = BIAS ? *(const floatx4*)&bias[16 * kt + 4 * grp] : (floatx4){0.f, 0.f, 0.f, 0.f};
-  }
-  static __device__ __forceinline__ void add_each(Scores& s, const float (&b)[E]) {
-#pragma unroll
-    for (int i = 0; i < E; ++i) {
-      s.t[i >> 2][0][i & 3] += b[i];
-      s.t[i >> 2][1][i & 3] += b[i];
-    }
   }
   __device__ __forceinline__ uint32_t visible(int blk, int n) const {
     const int left = n - 32 * blk - 4 * grp;   // keys below n from the lane's first one on
@@ -2331,16 +2334,30 @@ __device__ __forceinline__ void load_row(const FaKernelArgs& a, const M& m, cons
       u[0] = m.chunk(0) < 2 ? lo : hi;
     } else {
 #pragma unroll
-      for (int x = 0; x < FR / 2; ++x) rotate8<T>(u[x], u[x + FR / 2], cs + 8 * m.chunk(x), sn + 8 * m.chunk(x));
+      for (int x = 0; x < FR / 2; ++x) {
+        if (D == 128) __builtin_amdgcn_sched_barrier(0);   // (one pair's table rows at a time: 16 registers)
+        rotate8<T>(u[x], u[x + FR / 2], cs + 8 * m.chunk(x), sn + 8 * m.chunk(x));
+      }
     }
   }
 }
 
+// The lane index, formed where it is needed: values derived from it outside the main loop then need no register through it.
+// (Only the scalar mask comes out of an asm block: a vector register written in one may still be the destination of a matrix
+// product under way, which the compiler waits for where it sees the write.)
+__device__ __forceinline__ int lane_now() {
+  uint32_t ones;
+  asm volatile("s_mov_b32 %0, -1" : "=s"(ones));
+  return (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0));
+}
+
 template <int D, int NW>
 struct GlobalLds {
-  // rings of four 32-key blocks of K and of V (unpadded rows, swizzled chunks); afterwards one output patch per wavefront
-  static constexpr int kBlk = 32 * D;
-  static constexpr int kElems = 8 * kBlk > NW * epi_patch(D) ? 8 * kBlk : NW * epi_patch(D);
+  // Rings of 32-key blocks of K and of V (unpadded rows, swizzled chunks); afterwards one output patch per wavefront.  Four
+  // blocks of each are what the pipeline needs; four more of K keep a tile's own until its probabilities are final, so that a
+  // refresh need not fetch them again (head_dim 128: a unit's LDS holds two workgroups without them, one with).
+  static constexpr int kBlk = 32 * D, kKBlocks = D == 128 ? 4 : 8;
+  static constexpr int kElems = (kKBlocks + 4) * kBlk > NW * epi_patch(D) ? (kKBlocks + 4) * kBlk : NW * epi_patch(D);
 };
 
 // tc: the workgroup's tile (tc.n as loaded, not clamped).
@@ -2367,7 +2384,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   tc.q0 = __builtin_amdgcn_readfirstlane(tc.q0);
   const int N = a.max_len, q0 = tc.q0;
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
+  int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   M m;
   m.init(lane);
@@ -2381,8 +2398,14 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   // bias of key j in raw-score units (index clamped: keys outside [0, n) are never used unmasked)
   auto bias_of = [&](int j) { return bias_over_scale<T, D == 32>(a, bp[j < N ? j : N - 1]); };
 
+  // slot (b + 5) % KN of the K ring: with eight, blocks 2 t + 1 .. 2 t + 4 (t odd) are the lower or the upper four
+  constexpr int KN = GlobalLds<D, NW>::kKBlocks;
   uint16_t* const kring = lds;
-  uint16_t* const vring = lds + 4 * kBlk;
+  uint16_t* const vring = lds + KN * kBlk;
+  auto kblk = [&](int b) { return kring + ((b + 5) & (KN - 1)) * kBlk; };
+  int khalf = 0;   // the half of the ring that the operand offsets m.kfo include
+  auto kops = [&](int b) { return kblk(b) - khalf; };   // what m.k_frag takes for block b
+  auto vblk = [&](int b) { return vring + (b & 3) * kBlk; };
 
   // A direct load moves RPL rows of a 32-row block; a block's LPB loads are dealt to the wavefronts: with four, each
   // moves LPB / 4 parts of every block (head_dim 32, two parts: wavefront w moves block w of a tile's four by itself); with
@@ -2390,58 +2413,73 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   constexpr int CH = D / 8, RPL = 64 / CH, LPB = 32 / RPL;      // D = 32: 4, 16, 2;  64: 8, 8, 4;  128: 16, 4, 8
   constexpr int LW = D == 32 ? 2 : LPB / 4;
   const int fw = wave & 3;
-  int row_of[LW];
+  auto row_of = [&](int x, int lane) { return (D == 32 ? x : fw * LW + x) * RPL + lane / CH; };
   uint32_t koff[LW], voff[LW];   // bytes (row stride included)
 #pragma unroll
   for (int x = 0; x < LW; ++x) {
-    row_of[x] = (D == 32 ? x : fw * LW + x) * RPL + lane / CH;
-    koff[x] = 2u * (uint32_t)(row_of[x] * a.ks[2] + (((lane % CH) ^ M::k_swz(row_of[x])) * 8));
-    voff[x] = 2u * (uint32_t)(row_of[x] * a.vs[2] + (((lane % CH) ^ M::v_swz(row_of[x])) * 8));
+    const int r = row_of(x, lane);
+    koff[x] = 2u * (uint32_t)(r * a.ks[2] + (((lane % CH) ^ M::k_swz(r)) * 8));
+    voff[x] = 2u * (uint32_t)(r * a.vs[2] + (((lane % CH) ^ M::v_swz(r)) * 8));
+    if (D == 32) koff[x] = voff[x] = wave < 2 ? koff[x] + 0u : voff[x] + 0u;   // (the wavefront's own block's)
   }
   const int part0 = D == 32 ? 0 : fw * LW;
-  // block `blk` of K or V into LDS block dst: rows past the tensor are clamped to its last one (masked, zeroed or never read)
-  auto load_block = [&](const uint16_t* base, int64_t rs, const uint32_t (&off)[LW], int blk, uint16_t* dst) {
-    if (32 * blk + 32 <= N) {
-      const uint16_t* gb = base + (int64_t)(32 * blk) * rs;
-#pragma unroll
-      for (int x = 0; x < LW; ++x) load16_to_lds(gb, off[x], dst + (part0 + x) * RPL * D);
-    } else {
-      const int first = 32 * blk < N ? 32 * blk : N - 1;
-      const uint16_t* gb = base + (int64_t)first * rs;
-#pragma unroll
-      for (int x = 0; x < LW; ++x) {
-        const int r = row_of[x] < N - 1 - first ? row_of[x] : N - 1 - first;
-        load16_to_lds(gb, off[x] - 2u * (uint32_t)((row_of[x] - r) * rs), dst + (part0 + x) * RPL * D);
-      }
-    }
-  };
   // K blocks kb (if k1), kb + 1 (if k2) and V blocks vb, vb + 1 (if v) into ring slots
   auto fetch = [&](int kb, bool k1, bool k2, int vb, bool v) {
     if (D == 32) {
-      if (wave < 2) {
-        if (wave == 0 ? k1 : k2) load_block(kp, a.ks[2], koff, kb + wave, kring + ((kb + wave) & 3) * kBlk);
-      } else if (v) {
-        load_block(vp, a.vs[2], voff, vb + wave - 2, vring + ((vb + wave - 2) & 3) * kBlk);
-      }
-    } else if (NW == 4) {
-      if (k1) load_block(kp, a.ks[2], koff, kb, kring + (kb & 3) * kBlk);
-      if (k2) load_block(kp, a.ks[2], koff, kb + 1, kring + ((kb + 1) & 3) * kBlk);
-      if (v) {
-        load_block(vp, a.vs[2], voff, vb, vring + (vb & 3) * kBlk);
-        load_block(vp, a.vs[2], voff, vb + 1, vring + ((vb + 1) & 3) * kBlk);
+      if (wave < 2 ? (wave == 0 ? k1 : k2) : v) {
+#pragma unroll
+        for (int x = 0; x < LW; ++x) {
+          if (wave < 2) load16_to_lds(kp + (int64_t)(32 * (kb + wave)) * a.ks[2], koff[x], kblk(kb + wave) + x * RPL * D);
+          else load16_to_lds(vp + (int64_t)(32 * (vb + wave - 2)) * a.vs[2], voff[x], vblk(vb + wave - 2) + x * RPL * D);
+        }
       }
     } else if (wave < 8) {
-      const int s = wave >> 2;
-      if (s == 0 ? k1 : k2) load_block(kp, a.ks[2], koff, kb + s, kring + ((kb + s) & 3) * kBlk);
-      if (v) load_block(vp, a.vs[2], voff, vb + s, vring + ((vb + s) & 3) * kBlk);
+      const int s0 = NW == 4 ? 0 : wave >> 2, s1 = NW == 4 ? 1 : s0;
+#pragma unroll
+      for (int s = 0; s < (NW == 4 ? 2 : 1); ++s) {
+        const int b = s == 0 ? s0 : s1;
+#pragma unroll
+        for (int x = 0; x < LW; ++x) {
+          if (b == 0 ? k1 : k2) load16_to_lds(kp + (int64_t)(32 * (kb + b)) * a.ks[2], koff[x], kblk(kb + b) + (part0 + x) * RPL * D);
+          if (v) load16_to_lds(vp + (int64_t)(32 * (vb + b)) * a.vs[2], voff[x], vblk(vb + b) + (part0 + x) * RPL * D);
+        }
+      }
+    }
+  };
+  // The same where rows lie past the tensor: they are clamped to its last one (masked, zeroed or never read).  Rolled up over
+  // the two blocks: this is the end of a sequence, and its copies would be a third of the kernel.
+  auto fetch_clamped = [&](int kb, bool k1, bool k2, int vb, bool v) {
+    auto load = [&](const uint16_t* base, int64_t rs, const uint32_t (&off)[LW], int blk, uint16_t* dst) {
+      const int first = 32 * blk < N ? 32 * blk : N - 1;
+      const uint16_t* gb = base + (int64_t)first * rs;
+      const int lane = lane_now();
+#pragma unroll
+      for (int x = 0; x < LW; ++x) {
+        const int past = row_of(x, lane) - (N - 1 - first);
+        load16_to_lds(gb, off[x] - 2u * (uint32_t)((past > 0 ? past : 0) * rs), dst + (part0 + x) * RPL * D);
+      }
+    };
+#pragma unroll 1
+    for (int s = 0; s < 2; ++s) {
+      const bool k_mine = D == 32 ? wave == s : (NW == 4 || (wave >> 2) == s), v_mine = D == 32 ? wave == 2 + s : k_mine;
+      if (k_mine && (s == 0 ? k1 : k2)) load(kp, a.ks[2], koff, kb + s, kblk(kb + s));
+      if (v_mine && v) load(vp, a.vs[2], voff, vb + s, vblk(vb + s));
     }
   };
   // The first K blocks, as far as the tensor reaches, are requested before the sequence length is looked at; in longer
   // tensors the rest of tile 1's operands (K block 3, V blocks 0 and 1) with them.  us, without -> with: 16 x 700 with a bias
   // 41.8 -> 39.6, 16 x 1024 49.7 -> 49.3, but 7 x 542 14.0 -> 14.2, 32 x 128 9.2 -> 9.9 (more to wait for before the first product).
   const bool early = N >= 640;
-  fetch(0, true, 32 < N, 0, early);
-  fetch(2, 64 < N, early, 0, false);
+  if (early) {
+    fetch(0, true, true, 0, true);
+    fetch(2, true, true, 0, false);
+  } else if (N >= 96) {
+    fetch(0, true, true, 0, false);
+    fetch(2, true, false, 0, false);
+  } else {
+    fetch_clamped(0, true, 32 < N, 0, false);
+    fetch_clamped(2, 64 < N, false, 0, false);
+  }
 
   const int qw0 = q0 + wave * 32 * NQB;
   v8 q[NQB][FR];
@@ -2483,7 +2521,10 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   const float c = a.c;
 
   typename M::Out o[NQB];
-  float mc[NQB][QT], lsum[NQB][QT];   // reference times c (-infinity: none yet), this lane's share of the row sum
+  // Reference times c, this lane's share of the row sum.  kNoRef: no key of a finite score yet.  Such keys (-infinity) have
+  // probability 0 against it, the first one that counts has an infinite one, which forces a refresh.
+  float mc[NQB][QT], lsum[NQB][QT];
+  constexpr float kNoRef = -3.4e38f;
   v8 p[NQB][2][2];                    // [query block][key block of the tile]: the tile's probabilities
   floatx4 z[NQB][QT];                 // [0]: the lane's share of their sum (MFMA_SUM: a quarter of the row's)
   v8 ka[FR], va[FR];
@@ -2530,75 +2571,73 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     }
   };
   constexpr float kLimit = MFMA_SUM ? 8192.f : kPLimit;
-  // Rows of tile t whose sums ran away from their reference (or that have none yet): the tile's scores are formed once
-  // more, from K in global memory, the exact maximum is taken and the rows' state and probabilities are made anew.
+  // Rows of tile t whose sums ran away from their reference, or that found the first key that counts: the tile's scores are
+  // formed again, its maximum is the new reference if it is above the old one, and the probabilities are made anew.  Each
+  // row decides on its own lanes' evidence: no dependence on the rows that share its wavefront.
   auto refresh = [&](int t, bool masked) {
+    auto vis_of = [&](int u) { return masked ? m.visible(2 * t + u, nk) : 0xFFFFu; };
+    auto row_any = [&](bool x) { return M::row_sum(x ? 1.f : 0.f) > 0.f; };
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
       bool row_trig[QT], any = false;
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
-        // a row refreshes iff one of ITS lanes tripped: no dependence on other rows
-        row_trig[qt] = M::row_sum(!(z[qb][qt][0] <= kLimit) ? 1.f : 0.f) > 0.f;
+        // (a row that is NaN already stays it; & and not &&: exchanges between lanes run with all lanes on)
+        row_trig[qt] = row_any(!(z[qb][qt][0] <= kLimit)) & !row_any(lsum[qb][qt] != lsum[qb][qt]);
         any = any || row_trig[qt];
       }
       if (!__any(any)) continue;
-      typename M::Scores s;
-      auto scores = [&](int u) {
-        const int blk = 2 * t + u;
-        uint4 kk[FR];
+      typename M::Scores s[2];
 #pragma unroll
-        for (int kt = 0; kt < QT; ++kt) {
-          const int row = 32 * blk + M::COLS * kt + m.col;
-          load_row<T, D, M, ROPE>(a, m, kp, a.ks[2], row < N ? row : N - 1, &kk[kt * (FR / QT)]);
-        }
-        float b[E];
-        if (BIAS) {
-#pragma unroll
-          for (int i = 0; i < E; ++i) b[i] = bias_of(32 * blk + m.key_of(i));
-        }
-        m.template start<false>(s, nullptr);
-        if (BIAS_FIRST) M::add_each(s, b);
-        v8 kv[FR];
-#pragma unroll
-        for (int x = 0; x < FR; ++x) kv[x] = as_v8<T>(kk[x]);
-#pragma unroll
-        for (int i = 0; i < M::STEPS; ++i) M::score_step(s, kv, q[qb], i);
-        if (BIAS_LAST) M::add_each(s, b);
-      };
-      float tmax[QT];
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) tmax[qt] = -INFINITY;
-#pragma unroll 1
       for (int u = 0; u < 2; ++u) {
-        scores(u);
-        const uint32_t vis = masked ? m.visible(2 * t + u, nk) : 0xFFFFu;
+        const int blk = 2 * t + u;
+        v8 kv[FR];
+        if constexpr (KN == 8) {
 #pragma unroll
-        for (int qt = 0; qt < QT; ++qt)
+          for (int x = 0; x < FR; ++x) kv[x] = m.k_frag(kops(blk), x);
+        } else {
+          __builtin_amdgcn_sched_barrier(0);   // (one block's rows at a time)
+          uint4 kk[FR];
+          M mr;
+          mr.place(lane_now());
 #pragma unroll
-          for (int i = 0; i < E; ++i) tmax[qt] = fmaxf(tmax[qt], keep_or_neg_inf(M::get(s, qt, i), vis, i));
+          for (int kt = 0; kt < QT; ++kt) {
+            const int row = 32 * blk + M::COLS * kt + mr.col;
+            load_row<T, D, M, ROPE>(a, mr, kp, a.ks[2], row < N ? row : N - 1, &kk[kt * (FR / QT)]);
+          }
+#pragma unroll
+          for (int x = 0; x < FR; ++x) kv[x] = as_v8<T>(kk[x]);
+        }
+        const float* b = lds_bias + (BIAS ? (blk & 7) * 32 : 0);
+        m.template start<BIAS_FIRST>(s[u], b);
+#pragma unroll
+        for (int i = 0; i < M::STEPS; ++i) M::score_step(s[u], kv, q[qb], i);
+        if constexpr (BIAS_LAST) {
+          typename M::Scores bs;
+          m.template start<true>(bs, b);
+          M::add(s[u], bs);
+        }
       }
-      float nmc[QT];
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
-        tmax[qt] = M::row_max(tmax[qt]);
+        if (QT > 1 && !ROPE && !__any(row_trig[qt])) continue;   // (with a rotation: registers)
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const uint32_t vis = vis_of(u);
+#pragma unroll
+          for (int i = 0; i < E; ++i) tmax = fmaxf(tmax, keep_or_neg_inf(M::get(s[u], qt, i), vis, i));
+        }
         // (a reference only rises: the tile of a row that was expected to be cold may still lie below it)
-        const float mc_tile = tmax[qt] == -INFINITY ? -INFINITY : tmax[qt] * c;
-        const bool take = row_trig[qt] && mc_tile > mc[qb][qt];
-        const float mc_new = take ? mc_tile : mc[qb][qt];
-        // (a row without a reference has nothing accumulated: factor exp2(-inf) = 0)
-        const float alpha = take ? __builtin_amdgcn_exp2f(mc[qb][qt] - mc_new) : 1.f;
-        mc[qb][qt] = mc_new;
+        const float mc_tile = M::row_max(tmax) * c, mc_old = mc[qb][qt];
+        const bool take = row_trig[qt] && mc_tile > mc_old;
+        const float alpha = take ? __builtin_amdgcn_exp2f(mc_old - mc_tile) : 1.f;
+        if (take) mc[qb][qt] = mc_tile;
         lsum[qb][qt] *= alpha;
         M::scale(o[qb], qt, alpha);
-        nmc[qt] = mc_new == -INFINITY ? 0.f : -mc_new;   // still none: every score is -infinity, every probability 0
-      }
+        // (a row that keeps its reference gets the same probabilities once more)
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        scores(u);
-        const uint32_t vis = masked ? m.visible(2 * t + u, nk) : 0xFFFFu;
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) softmax(s, nmc[qt], qb, u, qt, true, vis);
+        for (int u = 0; u < 2; ++u) softmax(s[u], -mc[qb][qt], qb, u, qt, true, vis_of(u));
       }
     }
   };
@@ -2622,27 +2661,40 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   const int64_t k32 = 32 * a.ks[2], v32 = 32 * a.vs[2];
   const uint16_t *kreq = kp + 3 * k32, *vreq = vp;
   auto request = [&](int t) {   // operands of tile t + 1
-    if (NW == 4 && D != 32 && t > 0 && 64 * t + 160 <= N) {
+    if (t == 0 && early) {
+      fetch(3, false, 2 < T64, 0, false);   // (all but K block 4 are on their way)
+    } else if ((t > 0 || T64 > 1) && 64 * t + 160 <= N) {
       // Every row exists (rows past the sequence are loaded for nothing at its end): the bases just advance.  (General
       // addresses each time were 40 - 60 scalar instructions per tile: 32K bf16 2845 -> 2794 us, 3 x 16K 1438 -> 1410, 8 x 2048
       // (1500 -) fp16 96.7 -> 91.5, with a bias (1024 -) 111.8 -> 107.9.)
+      if (D == 32) {
+        if (wave < 2) {
 #pragma unroll
-      for (int x = 0; x < LW; ++x) {
-        load16_to_lds(kreq, koff[x], kring + ((2 * t + 3) & 3) * kBlk + (part0 + x) * RPL * D);
-        load16_to_lds(kreq + k32, koff[x], kring + ((2 * t + 4) & 3) * kBlk + (part0 + x) * RPL * D);
-        load16_to_lds(vreq, voff[x], vring + ((2 * t) & 3) * kBlk + (part0 + x) * RPL * D);
-        load16_to_lds(vreq + v32, voff[x], vring + ((2 * t + 1) & 3) * kBlk + (part0 + x) * RPL * D);
-      }
-    } else if (NW == 8 && t > 0 && 64 * t + 160 <= N) {
-      const int s = wave >> 2;
+          for (int x = 0; x < LW; ++x) load16_to_lds(kreq + wave * k32, koff[x], kblk(2 * t + 3 + wave) + x * RPL * D);
+        } else {
 #pragma unroll
-      for (int x = 0; x < LW; ++x) {
-        load16_to_lds(kreq + s * k32, koff[x], kring + ((2 * t + 3 + s) & 3) * kBlk + (part0 + x) * RPL * D);
-        load16_to_lds(vreq + s * v32, voff[x], vring + ((2 * t + s) & 3) * kBlk + (part0 + x) * RPL * D);
+          for (int x = 0; x < LW; ++x) load16_to_lds(vreq + (wave - 2) * v32, voff[x], vblk(2 * t + wave - 2) + x * RPL * D);
+        }
+      } else if (NW == 4) {
+#pragma unroll
+        for (int x = 0; x < LW; ++x) {
+          load16_to_lds(kreq, koff[x], kblk(2 * t + 3) + (part0 + x) * RPL * D);
+          load16_to_lds(kreq + k32, koff[x], kblk(2 * t + 4) + (part0 + x) * RPL * D);
+          load16_to_lds(vreq, voff[x], vblk(2 * t) + (part0 + x) * RPL * D);
+          load16_to_lds(vreq + v32, voff[x], vblk(2 * t + 1) + (part0 + x) * RPL * D);
+        }
+      } else if (wave < 8) {
+        const int s = wave >> 2;
+#pragma unroll
+        for (int x = 0; x < LW; ++x) {
+          load16_to_lds(kreq + s * k32, koff[x], kblk(2 * t + 3 + s) + (part0 + x) * RPL * D);
+          load16_to_lds(vreq + s * v32, voff[x], vblk(2 * t + s) + (part0 + x) * RPL * D);
+        }
       }
+    } else if (t + 2 >= T64 && 64 * t + 64 <= N && (t + 1 >= T64 || 64 * t + 128 <= N)) {
+      fetch(2 * t + 3, t + 1 < T64, false, 2 * t, true);   // (the last two requests of a sequence that fills whole blocks)
     } else {
-      const bool there = t == 0 && early;   // (all but K block 4)
-      fetch(2 * t + 3, !there && t + 1 < T64, t + 2 < T64, 2 * t, !there);
+      fetch_clamped(2 * t + 3, t + 1 < T64, t + 2 < T64, 2 * t, true);
     }
     kreq += 2 * k32;
     vreq += 2 * v32;
@@ -2687,12 +2739,12 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   if (ROPE) {
     // every K block is rotated in place once it has landed
 #pragma unroll
-    for (int i = 0; i < 3; ++i) rope_rows_in_lds<T, D, M>(a, kring + i * kBlk, D, 32, 32 * i, tid, THREADS);   // (block 3: with tile 1)
+    for (int i = 0; i < 3; ++i) rope_rows_in_lds<T, D, M>(a, kblk(i), D, 32, 32 * i, tid, THREADS);   // (block 3: with tile 1)
     __syncthreads();
   }
   typename M::Scores sA, sB;
-  load_ka(kring, lds_bias);
-  __syncthreads();   // K block 0 is in registers everywhere: block 4 takes its place
+  load_ka(kops(0), lds_bias);
+  if (KN == 4) __syncthreads();   // K block 0 is in registers everywhere: block 4 takes its place
   request(0);
   {
     const uint32_t vis = m.visible(0, nk);
@@ -2707,8 +2759,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         float t0 = -INFINITY;
 #pragma unroll
         for (int i = 0; i < E; ++i) t0 = fmaxf(t0, keep_or_neg_inf(M::get(sA, qt, i), vis, i));
-        t0 = M::row_max(t0);
-        mc[qb][qt] = t0 == -INFINITY ? -INFINITY : t0 * c;
+        mc[qb][qt] = fmaxf(M::row_max(t0) * c, kNoRef);
       }
     }
   }
@@ -2851,19 +2902,16 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     __syncthreads();
     if (ROPE) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        rope_rows_in_lds<T, D, M>(a, kring + ((2 * t + 1 + i) & 3) * kBlk, D, 32, 32 * (2 * t + 1 + i), tid, THREADS);
+      for (int i = 0; i < 2; ++i) rope_rows_in_lds<T, D, M>(a, kblk(2 * t + 1 + i), D, 32, 32 * (2 * t + 1 + i), tid, THREADS);
       __syncthreads();
     }
   };
-  auto kblk = [&](int b) { return kring + (b & 3) * kBlk; };
-  auto vblk = [&](int b) { return vring + (b & 3) * kBlk; };
   auto bblk = [&](int b) { return lds_bias + (BIAS ? (b & 7) * 32 : 0); };
   using No = std::false_type;
   using Yes = std::true_type;
   int t = 0;
   if (T64 > 1) {
-    if (wave_has_rows) iter(Yes{}, No{}, 0, kblk(1), kblk(2), nullptr, nullptr, bblk(0), bblk(1), bblk(2));
+    if (wave_has_rows) iter(Yes{}, No{}, 0, kops(1), kops(2), nullptr, nullptr, bblk(0), bblk(1), bblk(2));
     auto steady = [&](auto ODDc, int t) {
       constexpr int ODD = decltype(ODDc)::value;   // t & 1: ring slots are compile-time constants
       if (rotate_prio) {
@@ -2876,32 +2924,38 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       request(t);
       if (wave_has_rows) {
         settle(t - 1, false);
-        iter(No{}, No{}, t, kblk(2 * ODD + 1), kblk(2 * ODD + 2), vblk(2 * ODD - 2), vblk(2 * ODD - 1), bblk(2 * t), bblk(2 * t + 1), bblk(2 * t + 2));
+        const uint16_t* k1 = kring + 2 * (1 - ODD) * kBlk;   // kops(2 t + 1)
+        iter(No{}, No{}, t, k1, k1 + kBlk, vblk(2 * ODD - 2), vblk(2 * ODD - 1), bblk(2 * t), bblk(2 * t + 1), bblk(2 * t + 2));
       }
     };
     t = 1;
-    for (; t + 2 < T64; t += 2) {
+    while (t + 1 < T64) {
       steady(std::integral_constant<int, 1>{}, t);
-      steady(std::integral_constant<int, 0>{}, t + 1);
-    }
-    if (t + 1 < T64) {
-      steady(std::integral_constant<int, 1>{}, t);
+      if (++t + 1 >= T64) break;
+      steady(std::integral_constant<int, 0>{}, t);
       ++t;
+      if (KN == 8) {
+        m.flip();
+        khalf ^= 4 * kBlk;
+      }
     }
     if (rotate_prio) __builtin_amdgcn_s_setprio(0);
+    if (!BIAS) m.place(lane_now());
     // t = T64 - 1: the last tile, masked
     landed(t);
     request(t);
     if (wave_has_rows) {
       settle(t - 1, false);
-      iter(No{}, Yes{}, t, kblk(2 * t + 1), nullptr, vblk(2 * t - 2), vblk(2 * t - 1), bblk(2 * t), bblk(2 * t + 1), nullptr);
+      iter(No{}, Yes{}, t, kops(2 * t + 1), nullptr, vblk(2 * t - 2), vblk(2 * t - 1), bblk(2 * t), bblk(2 * t + 1), nullptr);
     }
   } else {
-    if (wave_has_rows) iter(Yes{}, Yes{}, 0, kblk(1), nullptr, nullptr, nullptr, bblk(0), bblk(1), nullptr);
+    if (wave_has_rows) iter(Yes{}, Yes{}, 0, kops(1), nullptr, nullptr, nullptr, bblk(0), bblk(1), nullptr);
   }
   // ---- drain: V of the last tile; rows at or beyond nk are overwritten with zeros by the lanes that fetched them
   // (0 * whatever is stored in the padding must be 0)
   wait_direct_loads();
+  lane = lane_now();
+  m.place(lane);
   {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -2909,7 +2963,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       if (mine) {
 #pragma unroll
         for (int x = 0; x < LW; ++x)
-          if (32 * (2 * t + s) + row_of[x] >= nk) *(uint4*)&vblk(2 * t + s)[row_of[x] * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
+          if (32 * (2 * t + s) + row_of(x, lane) >= nk) *(uint4*)&vblk(2 * t + s)[row_of(x, lane) * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
       }
     }
   }
@@ -2964,7 +3018,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
 template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false>
 // (one block of rows per wavefront at head_dim 64: 168 registers for three wavefronts per SIMD, asked for where the compiler
 // would take a few more: 16 x 700 with a bias 38.5 -> 49.8 us at two)
-__global__ __launch_bounds__(NW * 64, NW == 4 ? (BIAS && D == 64 && NQB == 1 ? 3 : 2) : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
+__global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 && NQB == 1 && !ROPE ? 3 : 2) : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[GlobalLds<D, NW>::kElems];
   __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 260 : 4];  // ring of eight key blocks, bias / |scale|; three words of the pass over padding
   TileCoord tc;
@@ -3143,7 +3197,7 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     else kern = rows == 256 ? fa_fwd_global_kernel<T, 64, 2, 4, false, true> : fa_fwd_global_kernel<T, 64, 1, 4, false, true>;
   } else if (a.head_dim == 128 && global && v_path == 0) {
     if (bm == 256) {
-      kern = fa_fwd_global_kernel<T, 128, 1, 8>;   // eight wavefronts on one pair of K/V stages
+      kern = fa_fwd_global_kernel<T, 128, 1, 8>;   // eight wavefronts on one pair of rings
       threads = 512;
       rows = 256;
     } else {

@@ -105,3 +105,49 @@ def test_padding_by_bias_with_infinite_values(head_dim):
     o, _ = run_ex(q, k, v, None, "fp16", 1.0 / np.sqrt(head_dim), tuning=fa.FA_TUNE_BM_128, key_bias=bias)
     assert np.isnan(o[3, :, :, 5]).all()
     assert np.isfinite(np.delete(o[3], 5, axis=-1)).all() and np.isfinite(np.delete(o, 3, axis=0)).all()
+
+
+def one_jump_per_row(head_dim, dtype, n, lens, heads, height=20.0):
+    """Row i scores `height` higher with one key of tile i % 16 than with the others of N(0, 1): each tile refreshes some rows."""
+    _, q, k, v = draw(78, len(lens), heads, n, head_dim, dtype)
+    q[..., :16], k[..., :16] = 0.0, 0.0
+    for g in range(16):
+        q[:, :, g::16, g] = 4.0
+        k[:, :, 64 * g + 37 * g % 64, g] = height * np.sqrt(head_dim) / 4.0
+    return q, round_to_storage(k, dtype), v
+
+
+@pytest.mark.parametrize("head_dim,heads", [(32, 1), (64, 1), (128, 1)])
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256, fa.FA_TUNE_BM_384, fa.FA_TUNE_BM_512, fa.FA_TUNE_BM_MIXED],
+                         ids=["128", "256", "384", "512", "mixed"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_refresh_in_every_tile(head_dim, heads, dtype, tuning):
+    n, lens = 1100, [1100, 1061]
+    if tuning == fa.FA_TUNE_BM_MIXED:
+        lens = lens[1:]
+    q, k, v = one_jump_per_row(head_dim, dtype, n, lens, heads)
+    scale = 1.0 / np.sqrt(head_dim)
+    o_ref, lse_ref = attention_oracle(q[:, -1:], k[:, -1:], v[:, -1:], lens, scale, -1, -1)
+    o, lse = run_ex(q, k, v, lens, dtype, scale, tuning=tuning)
+    check_against(o[:, -1:], lse[:, -1:], o_ref, lse_ref, lens, dtype, relative=True)
+
+
+@pytest.mark.parametrize("head_dim,heads", [(32, 1), (64, 1), (128, 1)])
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256], ids=["128", "256"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_long_excluded_prefixes(head_dim, heads, dtype, tuning):
+    """Sequences whose first keys, up to all of them, are excluded: no key counts for many tiles, then rows take their first
+    reference in the middle of a tile, at its edge, in the last tile or never; one of those keys scores far higher."""
+    n, first = 900, [0, 33, 64, 500, 511, 640, 863, 864, 899, 900]
+    _, q, k, v = draw(79, len(first), heads, n, head_dim, dtype)
+    bias = np.zeros((len(first), n), dtype=np.float32)
+    for b, j in enumerate(first):
+        bias[b, :j] = -np.inf
+    q[..., 0], k[..., 0] = 4.0, 0.0
+    k[:, :, 870, 0] = 7.0 * np.sqrt(head_dim)
+    k = round_to_storage(k, dtype)
+    scale = 1.0 / np.sqrt(head_dim)
+    o_ref, lse_ref = attention_oracle(q[:, -1:], k[:, -1:], v[:, -1:], None, scale, -1, -1, key_bias=bias)
+    o, lse = run_ex(q, k, v, None, dtype, scale, tuning=tuning, key_bias=bias)
+    assert (o[-1] == 0).all() and np.isneginf(lse[-1]).all()
+    check_against(o[:, -1:], lse[:, -1:], o_ref, lse_ref, None, dtype, relative=True)

@@ -1,8 +1,65 @@
-"""What the kernels' sources and builds have to keep."""
+"""What the built kernels ask of a compute unit, read from the metadata that the compiler writes beside them in the library:
+no kernel uses private memory (the runtime would have to back it on the device at a first launch)."""
 import os
 import re
+import struct
+
+import pytest
 
 import paper_2603_12646_amd as fa
+
+msgpack = pytest.importorskip("msgpack")   # the metadata's encoding
+
+
+def code_objects(data):
+    """The gfx950 code objects of a library's offload bundles."""
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    at = data.find(magic)
+    while at >= 0:
+        (count,) = struct.unpack_from("<Q", data, at + len(magic))
+        pos = at + len(magic) + 8
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", data, pos)
+            name = data[pos + 24:pos + 24 + length].decode()
+            pos += 24 + length
+            if "gfx950" in name and size:
+                yield data[at + offset:at + offset + size]
+        at = data.find(magic, at + 1)
+
+
+def kernels_of(code):
+    """Metadata of the kernels of a code object: the AMDGPU note (type 32) of its note sections."""
+    shoff, shentsize, shnum = struct.unpack_from("<Q", code, 0x28)[0], *struct.unpack_from("<HH", code, 0x3A)
+    for i in range(shnum):
+        kind, _, _, offset, size = struct.unpack_from("<IQQQQ", code, shoff + i * shentsize + 4)
+        if kind != 7:   # SHT_NOTE
+            continue
+        pos = offset
+        while pos < offset + size:
+            namesz, descsz, note = struct.unpack_from("<III", code, pos)
+            name = code[pos + 12:pos + 12 + namesz].rstrip(b"\0")
+            desc = pos + 12 + (namesz + 3) // 4 * 4
+            if name == b"AMDGPU" and note == 32:
+                yield from msgpack.unpackb(code[desc:desc + descsz])["amdhsa.kernels"]
+            pos = desc + (descsz + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    if not os.path.exists(fa.LIB_PATH):
+        from paper_2603_12646_amd.build import build_library
+        build_library(verbose=False)
+    with open(fa.LIB_PATH, "rb") as f:
+        data = f.read()
+    found = {k[".name"]: k for code in code_objects(data) for k in kernels_of(code)}
+    assert len(found) > 40
+    return found
+
+
+def test_no_private_memory(kernels):
+    assert {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if k[".private_segment_fixed_size"]} == {}
+    assert not [n for n, k in kernels.items() if k[".uses_dynamic_stack"]]
+
 
 
 def test_exchanges_write_no_register_in_an_asm_block_alone():
