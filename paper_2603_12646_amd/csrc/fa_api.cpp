@@ -98,6 +98,9 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
   const bool windowed = p.window_left >= 0 || p.window_right >= 0;
   if (windowed) return 128;
   const int64_t bh = (int64_t)p.batch * p.heads;
+  // At head_dim 32 the key-bias variant has four wavefronts per SIMD on 128 rows and two on 256: us, 12 heads, 128 -> 256 rows,
+  // 12 x 700 24.2 -> 27.5, 8 x 2048 95 -> 101, 1 x 10000 271 -> 286; nowhere of 40 calls in either type the other way.
+  if (p.head_dim == 32 && p.key_bias) return 128;
   if (p.batch > 1 && p.max_len < 2048) {
     // batches of short sequences (ragged lengths leave many tiles empty, which the model
     // below cannot see).  Measured: 768 tiles of 256 rows are 1-5 % faster at 128, 1536 and

@@ -2307,13 +2307,14 @@ struct Tile16 {
 
 // Which of the two a call runs.  What bounds the large calls is power as much as issue slots: with random operands the
 // smaller shape does 20 % (fp16) and 14 % (bf16) more work per second when nothing else is issued (1905 against 1576,
-// 2006 against 1722 TFLOP/s), but it takes twice the instructions, 9 - 10 issue cycles each.  fp16, whose row sums go to
-// the matrix cores as well, gains from it everywhere (8K 12 x 64 192 -> 180 us, 8 x 128 236 -> 221).  bf16 keeps 16 fp32
-// additions per unit, so head_dim 32 and 64 are short of issue slots (3 x 16K 1465 -> 1516 in the smaller shape, 24 x 32
-// 8K 267 -> 278; 8K 12 x 64 alone gains, 194 -> 187) and only head_dim 128 takes it (8K 231 -> 221).
-template <class T, int D, bool SUM32>
+// 2006 against 1722 TFLOP/s), but it takes twice the instructions, 9 - 10 issue cycles each.  fp16 at head_dim 64, whose row
+// sums go to the matrix cores as well, gains from it (8K 12 x 64 192 -> 180 us; in one short round neither: 3 x 1500 30.3, 30.4).
+// bf16 keeps 16 fp32 additions per unit and loses (3 x 16K 1465 -> 1516), and so does head_dim 32 in both types, whose units
+// hold twice the softmax per product and whose two queries per lane cost it a wavefront per SIMD (fp16 8K 24 x 32 254 -> 278).
+// head_dim 128 gains (8K 8 x 128 fp16 236 -> 221, bf16 231 -> 217).
+template <class T, int D>
 struct GlobalTile {
-  typedef typename std::conditional<D == 128 || (T::kSumRounded && !SUM32), Tile16<T, D>, Tile32<T, D>>::type type;
+  typedef typename std::conditional<D == 128 || (D == 64 && T::kSumRounded), Tile16<T, D>, Tile32<T, D>>::type type;
 };
 
 // One row's fragments straight from global memory: the B operand of Q, and the A operand of K where a refresh forms scores
@@ -2371,8 +2372,9 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   constexpr int THREADS = NW * 64;
   constexpr int BM = NW * 32 * NQB;
   constexpr bool BIAS_LAST = BIAS && D == 32, BIAS_FIRST = BIAS && !BIAS_LAST;
-  typedef typename GlobalTile<T, D, BIAS_LAST>::type M;
-  constexpr bool MFMA_SUM = M::kMfmaSum && T::kSumRounded && !BIAS_LAST;
+  typedef typename GlobalTile<T, D>::type M;
+  // row sums of the rounded probabilities (fp16) on the matrix cores or by dot products, else of the unrounded ones
+  constexpr bool ROUNDED = T::kSumRounded && !BIAS_LAST, MFMA_SUM = M::kMfmaSum && ROUNDED, DOT_SUM = !M::kMfmaSum && ROUNDED;
   constexpr int QT = M::QT, E = M::E, FR = D / 16;
   constexpr int kBlk = 32 * D;
   typedef typename T::v8 v8;
@@ -2561,11 +2563,18 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
       z[qb][qt] = T::mfma16(quarter, p[qb][u][qt], u == 0 ? zero : z[qb][qt]);
     } else {
-      float l0 = e[0], l1 = e[1];
+      float l0, l1;
+      if constexpr (DOT_SUM) {
+        const uint4 w0 = __builtin_bit_cast(uint4, p[qb][u][0]), w1 = __builtin_bit_cast(uint4, p[qb][u][1]);
+        l0 = T::sum2(w1.z, T::sum2(w1.x, T::sum2(w0.z, T::sum2_first(w0.x))));
+        l1 = T::sum2(w1.w, T::sum2(w1.y, T::sum2(w0.w, T::sum2_first(w0.y))));
+      } else {
+        l0 = e[0], l1 = e[1];
 #pragma unroll
-      for (int i = 2; i < E; i += 2) {
-        l0 += e[i];
-        l1 += e[i + 1];
+        for (int i = 2; i < E; i += 2) {
+          l0 += e[i];
+          l1 += e[i + 1];
+        }
       }
       z[qb][qt][0] = u == 0 ? l0 + l1 : z[qb][qt][0] + (l0 + l1);
     }
@@ -3017,8 +3026,9 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
 
 template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false>
 // (one block of rows per wavefront at head_dim 64: 168 registers for three wavefronts per SIMD, asked for where the compiler
-// would take a few more: 16 x 700 with a bias 38.5 -> 49.8 us at two)
-__global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 && NQB == 1 && !ROPE ? 3 : 2) : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
+// would take a few more: 16 x 700 with a bias 38.5 -> 49.8 us at two.  At head_dim 32 one block has room for four, two for
+// three: 8K bf16 272 -> 247, 16 x 700 46.6 -> 43.3, with a bias 59.8 -> 51.2.)
+__global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 && NQB == 1 && !ROPE ? 3 : D == 32 && !ROPE ? (NQB == 1 ? 4 : (BIAS ? 2 : 3)) : 2) : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[GlobalLds<D, NW>::kElems];
   __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 260 : 4];  // ring of eight key blocks, bias / |scale|; three words of the pass over padding
   TileCoord tc;

@@ -1,5 +1,6 @@
 """What the built kernels ask of a compute unit, read from the metadata that the compiler writes beside them in the library:
-no kernel uses private memory (the runtime would have to back it on the device at a first launch)."""
+no kernel uses private memory (the runtime would have to back it on the device at a first launch), and the pipelined global
+kernel keeps the wavefronts per SIMD and the workgroups per unit that its tile shapes are chosen for."""
 import os
 import re
 import struct
@@ -9,6 +10,8 @@ import pytest
 import paper_2603_12646_amd as fa
 
 msgpack = pytest.importorskip("msgpack")   # the metadata's encoding
+
+UNIT_LDS = 160 * 1024
 
 
 def code_objects(data):
@@ -60,6 +63,28 @@ def test_no_private_memory(kernels):
     assert {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if k[".private_segment_fixed_size"]} == {}
     assert not [n for n, k in kernels.items() if k[".uses_dynamic_stack"]]
 
+
+def test_global_kernels_keep_their_occupancy(kernels):
+    """Wavefronts per SIMD from 512 registers in steps of eight; four-wavefront workgroups put one wavefront on each SIMD."""
+    seen = set()
+    for name, k in kernels.items():
+        m = re.search(r"fa_fwd_global_kernelINS_\d+(B?F16)ELi(\d+)ELi(\d)ELi(\d+)ELb(\d)ELb(\d)", name)
+        if not m or m.group(6) == "1":
+            continue
+        head_dim, blocks, waves, bias, rope = (int(x) for x in m.groups()[1:])
+        registers = k[".vgpr_count"] + k.get(".agpr_count", 0)
+        per_simd = 512 // (-(-registers // 8) * 8)
+        if waves > 4:
+            want = waves // 4
+        elif head_dim == 32:
+            want = 4 if blocks == 1 else (2 if bias else 3)
+        else:
+            want = 3 if head_dim == 64 and blocks == 1 else 2
+        assert per_simd >= want, (name, registers)
+        groups = 1 if waves > 4 else want
+        assert groups * k[".group_segment_fixed_size"] <= UNIT_LDS, (name, k[".group_segment_fixed_size"])
+        seen.add((m.group(1), head_dim, blocks, waves, bias, rope))
+    assert len(seen) >= 26
 
 
 def test_exchanges_write_no_register_in_an_asm_block_alone():
