@@ -115,7 +115,10 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
   // rounds of 256-row pairs with 128-row workgroups on what remains (beyond 1024; between the
   // two a single round of the larger shapes does as well)
   if (allow_mixed && (w128 <= 768 || w128 > 1024) && mixed_fits(p)) return 0;
-  const double c128 = shape_cost(w128, 3, 4, 1.08), c256 = shape_cost(w256, 2, 8, 1.0),
+  // What a block of 128-row workgroups costs more.  A rotation in the call is done once per query tile (us, 12 x 64, 128 -> 256
+  // rows: 7 x 2048 138 -> 118, 12 x 2048 218 -> 193, but 6 x 2048 in a thin second round of the larger ones 105 -> 115).
+  const double rel = p.rope_cos && p.head_dim != 32 ? 1.2 : 1.08;
+  const double c128 = shape_cost(w128, 3, 4, rel), c256 = shape_cost(w256, 2, 8, 1.0),
                c512 = shape_cost(w512, 1, 16, 0.98);
   if (c512 < c256 && c512 < c128 && w512 <= 256) return 512;   // 512 only where one round holds the call
   // (a tie goes to the larger shape, but with a key bias to the smaller one: 8 x 2048 121.7 against 124.5 us)

@@ -658,22 +658,18 @@ __device__ __forceinline__ void rotate8(uint4& lo, uint4& hi, const float* cs, c
   hi = make_uint4(hi_out[0], hi_out[1], hi_out[2], hi_out[3]);
 }
 
-// Rotates `rows` rows of K in place in LDS (all threads of the workgroup take part; the caller
-// puts barriers around the call).  Element e of tile row r lives at
-// tile[r * stride + (((e / 8) ^ swizzle(r & 31)) * 8) + e % 8], swizzle = M::k_swz for 32-row blocks
-// written by direct loads and 0 (M = void) for padded tiles; tile row r is key key0 + r
-// (clamped into the tensor: rows outside it are never used unmasked).
-template <class T, int D, class M = void>
+// Rotates `rows` rows of K in place in a padded LDS tile (all threads of the workgroup take part; the
+// caller puts barriers around the call).  Tile row r is key key0 + r (clamped into the tensor: rows
+// outside it are never used unmasked).
+template <class T, int D>
 __device__ __forceinline__ void rope_rows_in_lds(const FaKernelArgs& a, uint16_t* tile, int stride, int rows, int key0,
                                                  int tid, int nthreads) {
   constexpr int HALF = D / 16;  // 16-byte chunks per half row
   for (int u = tid; u < rows * HALF; u += nthreads) {
     const int r = u / HALF, c = u % HALF;
     const int key = key0 + r < a.max_len ? key0 + r : a.max_len - 1;
-    int sw = 0;
-    if constexpr (!std::is_void<M>::value) sw = M::k_swz(r & 31);
-    uint4* plo = (uint4*)&tile[r * stride + ((c ^ sw) * 8)];
-    uint4* phi = (uint4*)&tile[r * stride + (((c + HALF) ^ sw) * 8)];
+    uint4* plo = (uint4*)&tile[r * stride + c * 8];
+    uint4* phi = (uint4*)&tile[r * stride + (c + HALF) * 8];
     uint4 lo = *plo, hi = *phi;
     rotate8<T>(lo, hi, a.rope_cos + (int64_t)key * a.rope_stride + 8 * c, a.rope_sin + (int64_t)key * a.rope_stride + 8 * c);
     *plo = lo;
@@ -2468,6 +2464,45 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       if (v_mine && v) load(vp, a.vs[2], voff, vb + s, vblk(vb + s));
     }
   };
+  // ROPE: K blocks are rotated in place once they have landed: a chain of LDS reads, arithmetic and LDS writes between two
+  // barriers.  The table rows are read a tile ahead where there are registers for them.  A thread has eight pairs of one row of
+  // a block, the same ones every time, so that its offset in LDS stays in a register and a block's base is scalar (formed each
+  // time: 2K 12 x 64 38.9 -> 41.4 us); all threads work on both blocks at once (block by block, half of them idle: 44.4).
+  static_assert(!ROPE || NW == 4, "rotation: four wavefronts");
+  constexpr int HALF = D / 16, BLOCK_UNITS = 32 * HALF;   // 16-byte chunks per half row; a workgroup has 1, 2 or 4 times a block's
+  auto rot_row = [&](int tid) { return (tid % BLOCK_UNITS) / HALF; };
+  auto rot_ch = [&](int tid) { return tid % HALF; };
+  const uint32_t rot_lds = rot_row(tid) * D + (rot_ch(tid) ^ M::k_swz(rot_row(tid))) * 8;
+  struct Angles {
+    float c[8], s[8];
+  };
+  // (whole wavefronts: a block's units are a multiple of 64)
+  auto rot_there = [&](int x, int units) { return (x + 1) * THREADS <= units || x * THREADS + wave * 64 < units; };
+  auto rot_blk = [&](int b, int x) { return b + (x * THREADS + wave * 64) / BLOCK_UNITS; };
+  // the angles of pass x over the blocks from b on
+  auto load_angles = [&](int b, int x, Angles& t) {
+    // (rows past the tensor are never used unmasked: its last one's angles)
+    const int first = 32 * rot_blk(b, x), base = first < N ? first : N - 1, id = D == 128 ? tid : wave * 64 + lane_now();
+    const int row = rot_row(id) < N - 1 - base ? rot_row(id) : N - 1 - base;
+    const int64_t off = (int64_t)base * a.rope_stride + (row * a.rope_stride + 8 * rot_ch(id));
+    const float *cp = a.rope_cos + off, *sp = a.rope_sin + off;
+#pragma unroll
+    for (int i = 0; i < 8; i += 4) {
+      *(float4*)&t.c[i] = *(const float4*)(cp + i);
+      *(float4*)&t.s[i] = *(const float4*)(sp + i);
+    }
+  };
+  auto rotate_unit = [&](int b, int x, const Angles& t) {
+    uint16_t* at = kblk(rot_blk(b, x));
+    uint4 *lo_at = (uint4*)&at[rot_lds], *hi_at = (uint4*)&at[rot_lds ^ (8 * HALF)];
+    uint4 lo = *lo_at, hi = *hi_at;
+    rotate8<T>(lo, hi, t.c, t.s);
+    *lo_at = lo;
+    *hi_at = hi;
+  };
+  constexpr int TILE_UNITS = 2 * BLOCK_UNITS;   // a tile's two blocks: a pass, half a pass or (head_dim 128) two passes
+  constexpr bool AHEAD = ROPE && (D == 64 || (D == 32 && NQB == 1));
+  Angles ahead;
   // The first K blocks, as far as the tensor reaches, are requested before the sequence length is looked at; in longer
   // tensors the rest of tile 1's operands (K block 3, V blocks 0 and 1) with them.  us, without -> with: 16 x 700 with a bias
   // 41.8 -> 39.6, 16 x 1024 49.7 -> 49.3, but 7 x 542 14.0 -> 14.2, 32 x 128 9.2 -> 9.9 (more to wait for before the first product).
@@ -2708,6 +2743,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     kreq += 2 * k32;
     vreq += 2 * v32;
     if (BIAS && wave == 0) bst = bias_of(64 * t + 96 + lane);
+    if (AHEAD && rot_there(0, TILE_UNITS)) load_angles(2 * t + 3, 0, ahead);
   };
   if (BIAS) {
     if (tid < 96) lds_bias[tid] = bias_of(tid);
@@ -2746,9 +2782,13 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   wait_direct_loads();
   __syncthreads();
   if (ROPE) {
-    // every K block is rotated in place once it has landed
 #pragma unroll
-    for (int i = 0; i < 3; ++i) rope_rows_in_lds<T, D, M>(a, kblk(i), D, 32, 32 * i, tid, THREADS);   // (block 3: with tile 1)
+    for (int x = 0; x * THREADS < 3 * BLOCK_UNITS; ++x) {   // (block 3: with tile 1)
+      if (!rot_there(x, 3 * BLOCK_UNITS)) continue;
+      Angles t;
+      load_angles(0, x, t);
+      rotate_unit(0, x, t);
+    }
     __syncthreads();
   }
   typename M::Scores sA, sB;
@@ -2910,8 +2950,17 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     wait_direct_loads();
     __syncthreads();
     if (ROPE) {
+      if (AHEAD) {
+        if (rot_there(0, TILE_UNITS)) rotate_unit(2 * t + 1, 0, ahead);
+      } else {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) rope_rows_in_lds<T, D, M>(a, kblk(2 * t + 1 + i), D, 32, 32 * (2 * t + 1 + i), tid, THREADS);
+        for (int x = 0; x * THREADS < TILE_UNITS; ++x) {
+          if (!rot_there(x, TILE_UNITS)) continue;
+          Angles now;
+          load_angles(2 * t + 1, x, now);
+          rotate_unit(2 * t + 1, x, now);
+        }
+      }
       __syncthreads();
     }
   };
@@ -3028,7 +3077,7 @@ template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false>
 // (one block of rows per wavefront at head_dim 64: 168 registers for three wavefronts per SIMD, asked for where the compiler
 // would take a few more: 16 x 700 with a bias 38.5 -> 49.8 us at two.  At head_dim 32 one block has room for four, two for
 // three: 8K bf16 272 -> 247, 16 x 700 46.6 -> 43.3, with a bias 59.8 -> 51.2.)
-__global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 && NQB == 1 && !ROPE ? 3 : D == 32 && !ROPE ? (NQB == 1 ? 4 : (BIAS ? 2 : 3)) : 2) : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
+__global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 && NQB == 1 ? 3 : D == 32 ? (NQB == 1 ? 4 : (BIAS ? 2 : 3)) : 2) : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[GlobalLds<D, NW>::kElems];
   __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 260 : 4];  // ring of eight key blocks, bias / |scale|; three words of the pass over padding
   TileCoord tc;

@@ -198,3 +198,29 @@ def test_rope_rotation_ahead_of_the_call_with_lent_scratch(D, B, H, N, lens, dty
                      scratch=scratch, scratch_bytes=need, tuning=tun)
         torch.cuda.synchronize()
         assert np.array_equal(o.double().cpu().numpy(), o_sc) and np.array_equal(lse.double().cpu().numpy(), lse_sc)
+
+
+# (head_dim 128 with few 128-row tiles and with many: 20 and 400)
+@pytest.mark.parametrize("D,H", [(32, 1), (64, 1), (128, 1), (128, 20)])
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256], ids=["128", "256"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_rope_with_scores_that_jump(D, H, dtype, tuning):
+    """Rows that have to take a new reference in every second tile: their scores are formed again, of rotated keys.  Frequency 0 has
+    angle 0 and carries the jumps, the other pairs turn as ever."""
+    N, lens = 1200, [1200, 1075]
+    c32, s32, c64, s64 = tables(N, D)
+    for c, s in ((c32, s32), (c64, s64)):
+        c[:, 0], s[:, 0] = 1.0, 0.0
+    _, q, k, v = draw(9700 + D, 2, H, N, D, dtype)
+    q[..., [0, D // 2]], k[..., [0, D // 2]] = 0.0, 0.0
+    q[:, :, ::2, 0] = q[:, :, 1::2, D // 2] = 4.0
+    # Jumping keys hold nothing else: a rotated element may round to the neighbour of the oracle's, 2^-8 of it in bf16, which
+    # moves one key's score by up to 2^-8 4 . 1 / sqrt(128) = 1.4e-3: past the bound on lse where that key alone counts.
+    k[:, :, 45::128] = 0.0
+    for i, j in enumerate(range(45, N, 128)):     # each 20 above the one before, for half of the rows
+        k[:, :, j, 0 if i % 2 else D // 2] = (i // 2 + 1) * 20.0 * np.sqrt(D) / 4.0
+    k = round_to_storage(k, dtype)
+    scale = 1.0 / np.sqrt(D)
+    o_ref, lse_ref = attention_oracle_rope(q[:, -1:], k[:, -1:], v[:, -1:], c64, s64, dtype, lens, scale)
+    o, lse = run_rope(q, k, v, lens, dtype, scale, c32, s32, tuning=tuning)
+    check_against(o[:, -1:], lse[:, -1:], o_ref, lse_ref, lens, dtype, relative=True, label=f"rope jumps D{D} {dtype}")

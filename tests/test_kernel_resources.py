@@ -69,7 +69,7 @@ def test_global_kernels_keep_their_occupancy(kernels):
     seen = set()
     for name, k in kernels.items():
         m = re.search(r"fa_fwd_global_kernelINS_\d+(B?F16)ELi(\d+)ELi(\d)ELi(\d+)ELb(\d)ELb(\d)", name)
-        if not m or m.group(6) == "1":
+        if not m:
             continue
         head_dim, blocks, waves, bias, rope = (int(x) for x in m.groups()[1:])
         registers = k[".vgpr_count"] + k.get(".agpr_count", 0)
@@ -84,7 +84,7 @@ def test_global_kernels_keep_their_occupancy(kernels):
         groups = 1 if waves > 4 else want
         assert groups * k[".group_segment_fixed_size"] <= UNIT_LDS, (name, k[".group_segment_fixed_size"])
         seen.add((m.group(1), head_dim, blocks, waves, bias, rope))
-    assert len(seen) >= 26
+    assert len(seen) >= 36
 
 
 def test_exchanges_write_no_register_in_an_asm_block_alone():
