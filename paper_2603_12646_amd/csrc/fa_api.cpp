@@ -307,8 +307,10 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
     const int64_t bh = (int64_t)p->batch * p->heads;
     const int64_t w128 = (((int64_t)p->max_len + 127) / 128) * bh, w256 = (((int64_t)p->max_len + 255) / 256) * bh;
     bm = shape_cost(w256, 1, 8, 1.0) < shape_cost(w128, 2, 4, 1.03) ? 256 : 128;
-    // short sequences in one round take 128 rows: 5 x 900 30.3 -> 27.3 us, 6 x 700 24.3 -> 22.7, but 1 x 6000 148 -> 154
-    if (w128 <= 512 && p->max_len < 2048) bm = 128;
+    // Where one round holds the 128-row workgroups of a batch with lengths they win by the empty tiles: us, 256 -> 128 rows, bf16,
+    // 3 x 1500 (1000 -) 39.9 -> 34.0, 2 x 3500 (2000 -) 87 -> 73, but 7 x 1000 (900 -) 33.0 -> 35.4; one sequence, 1 x 8192 (7900) 222 -> 229;
+    // full: 3 x 1500 40.3 -> 42.2, 2 x 3000 75.4 -> 79.6.
+    if (w128 <= 512 && p->seq_lens && p->batch > 1) bm = 128;
     if (t_bm == FA_TUNE_BM_128) bm = 128;
     if (t_bm == FA_TUNE_BM_256) bm = 256;
   } else if (p->head_dim == 32 && !windowed && !bias_on_masked_kernel && t_v != FA_TUNE_V_SCALAR) {

@@ -2307,11 +2307,15 @@ struct Tile16 {
 // sums go to the matrix cores as well, gains from it (8K 12 x 64 192 -> 180 us; in one short round neither: 3 x 1500 30.3, 30.4).
 // bf16 keeps 16 fp32 additions per unit and loses (3 x 16K 1465 -> 1516), and so does head_dim 32 in both types, whose units
 // hold twice the softmax per product and whose two queries per lane cost it a wavefront per SIMD (fp16 8K 24 x 32 254 -> 278).
-// head_dim 128 gains (8K 8 x 128 fp16 236 -> 221, bf16 231 -> 217).
+// head_dim 128 gains in large calls (8K 8 x 128 fp16 236 -> 221, bf16 231 -> 217); calls of little more than one 128-row
+// workgroup per unit run at full clock, and there the larger shape does: kFewTiles.
 template <class T, int D>
 struct GlobalTile {
   typedef typename std::conditional<D == 128 || (D == 64 && T::kSumRounded), Tile16<T, D>, Tile32<T, D>>::type type;
 };
+// us, Tile16 -> Tile32, fp16, bf16, 8 x 128: 288 tiles of 128 rows (3 x 1500) 44.4 -> 41.9, 43.5 -> 40.3; 320 (5 x 900) 31.4 -> 29.8,
+// 30.9 -> 28.9, (1 x 5000) 121 -> 118, 119 -> 114; but 384 (8 x 700) 25.7 -> 26.7, 25.7 -> 25.4; 448 (2 x 3500) 95 -> 98, 91 -> 91.
+constexpr int kFewTiles = 352;
 
 // One row's fragments straight from global memory: the B operand of Q, and the A operand of K where a refresh forms scores
 // again.  FR fragments x = 0 .. FR - 1 hold chunks chunk(x); row: inside the tensor.
@@ -2360,7 +2364,7 @@ struct GlobalLds {
 // tc: the workgroup's tile (tc.n as loaded, not clamped).
 // ROPE: q and k are rotated by position (a.rope_cos / a.rope_sin are set): a compile-time
 // variant, so that the kernels without a rotation carry none of its code in their loops.
-template <class T, int D, int NQB, int NW, bool BIAS, bool ROTATE = true, bool ROPE = false>
+template <class T, int D, int NQB, int NW, bool BIAS, bool ROTATE = true, bool ROPE = false, class M = typename GlobalTile<T, D>::type>
 __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoord& tc_in, uint16_t* lds, float* lds_bias) {
   static_assert(D == 32 || D == 64 || D == 128, "pipelined kernel: head_dim 32, 64 or 128");
   static_assert(NW == 4 || NW == 8 || NW == 12, "4, 8 or 12 wavefronts");
@@ -2368,7 +2372,6 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   constexpr int THREADS = NW * 64;
   constexpr int BM = NW * 32 * NQB;
   constexpr bool BIAS_LAST = BIAS && D == 32, BIAS_FIRST = BIAS && !BIAS_LAST;
-  typedef typename GlobalTile<T, D>::type M;
   // row sums of the rounded probabilities (fp16) on the matrix cores or by dot products, else of the unrounded ones
   constexpr bool ROUNDED = T::kSumRounded && !BIAS_LAST, MFMA_SUM = M::kMfmaSum && ROUNDED, DOT_SUM = !M::kMfmaSum && ROUNDED;
   constexpr int QT = M::QT, E = M::E, FR = D / 16;
@@ -3073,7 +3076,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   }
 }
 
-template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false>
+template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false, class M = typename GlobalTile<T, D>::type>
 // (one block of rows per wavefront at head_dim 64: 168 registers for three wavefronts per SIMD, asked for where the compiler
 // would take a few more: 16 x 700 with a bias 38.5 -> 49.8 us at two.  At head_dim 32 one block has room for four, two for
 // three: 8K bf16 272 -> 247, 16 x 700 46.6 -> 43.3, with a bias 59.8 -> 51.2.)
@@ -3082,7 +3085,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 && NQB == 1 ? 3 : D == 
   __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 260 : 4];  // ring of eight key blocks, bias / |scale|; three words of the pass over padding
   TileCoord tc;
   if (!locate_tile<NW * 32 * NQB, false, false, true>(a, tc)) return;
-  global_body<T, D, NQB, NW, BIAS, true, ROPE>(a, tc, lds, lds_bias);
+  global_body<T, D, NQB, NW, BIAS, true, ROPE, M>(a, tc, lds, lds_bias);
 }
 
 // ======================================================================================
@@ -3207,6 +3210,7 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
   const int win_blocks = (a.wl >= 0 && a.wr >= 0) ? (127 + a.wr) / 32 + (a.wl + 31) / 32 + 1 : 1 << 30;
   // 32-key blocks the 32 queries of one wavefront can see (they start at a multiple of 32)
   const int wave_blocks = (a.wl >= 0 && a.wr >= 0) ? (31 + a.wr) / 32 + (a.wl + 31) / 32 + 1 : 1 << 30;
+  const bool few = ((int64_t)a.max_len + 127) / 128 * a.batch * a.heads <= kFewTiles;
   Kernel kern = nullptr;
   unsigned threads = kThreads;
   int rows = 128;   // query rows per workgroup of the kernel chosen below: what the grid has to be made for
@@ -3240,7 +3244,7 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     // additive key bias on a global layer: the pipelined kernel with the bias as MFMA C operand
     if (bm == 256 && a.head_dim != 128) rows = 256;
     if (a.head_dim == 32) kern = rows == 256 ? fa_fwd_global_kernel<T, 32, 2, 4, true> : fa_fwd_global_kernel<T, 32, 1, 4, true>;
-    else if (a.head_dim == 128) kern = fa_fwd_global_kernel<T, 128, 1, 4, true>;
+    else if (a.head_dim == 128) kern = few ? fa_fwd_global_kernel<T, 128, 1, 4, true, false, Tile32<T, 128>> : fa_fwd_global_kernel<T, 128, 1, 4, true>;
     else if (rows == 256) kern = fa_fwd_global_kernel<T, 64, 2, 4, true>;
     else kern = fa_fwd_global_kernel<T, 64, 1, 4, true>;
   } else if (a.key_bias) {
@@ -3251,16 +3255,17 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
   } else if (rope && global && v_path == 0) {
     // rotation on a global layer: the pipelined kernel's four-wavefront shapes
     if (bm == 256 && a.head_dim != 128) rows = 256;
-    if (a.head_dim == 128) kern = fa_fwd_global_kernel<T, 128, 1, 4, false, true>;
+    // (the same arithmetic as a call whose q and k were rotated ahead of it, few tiles or many: the same bits)
+    if (a.head_dim == 128) kern = few ? fa_fwd_global_kernel<T, 128, 1, 4, false, true, Tile32<T, 128>> : fa_fwd_global_kernel<T, 128, 1, 4, false, true>;
     else if (a.head_dim == 32) kern = rows == 256 ? fa_fwd_global_kernel<T, 32, 2, 4, false, true> : fa_fwd_global_kernel<T, 32, 1, 4, false, true>;
     else kern = rows == 256 ? fa_fwd_global_kernel<T, 64, 2, 4, false, true> : fa_fwd_global_kernel<T, 64, 1, 4, false, true>;
   } else if (a.head_dim == 128 && global && v_path == 0) {
     if (bm == 256) {
-      kern = fa_fwd_global_kernel<T, 128, 1, 8>;   // eight wavefronts on one pair of rings
+      kern = few ? fa_fwd_global_kernel<T, 128, 1, 8, false, false, Tile32<T, 128>> : fa_fwd_global_kernel<T, 128, 1, 8>;   // eight wavefronts on one pair of rings
       threads = 512;
       rows = 256;
     } else {
-      kern = fa_fwd_global_kernel<T, 128, 1, 4>;
+      kern = few ? fa_fwd_global_kernel<T, 128, 1, 4, false, false, Tile32<T, 128>> : fa_fwd_global_kernel<T, 128, 1, 4>;
     }
   } else if (a.head_dim == 32 && global && v_path == 0) {
     if (bm == 256) rows = 256;

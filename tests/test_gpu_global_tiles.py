@@ -56,17 +56,24 @@ def test_bias_excludes_first_keys(head_dim, dtype, tuning, first):
     check_against(o, lse, o_ref, lse_ref, LENS, dtype, relative=True)
 
 
+@pytest.mark.parametrize("head_dim,rows", [(32, 128), (64, 256), (128, 128)])
 @pytest.mark.parametrize("batch", [2, 3, 33, 64, 65])
-def test_ragged_batch_order(batch):
-    """Sequences taken by falling length (up to 64 of them): every row of every one, with equal, empty and out-of-range lengths."""
-    n, heads, head_dim = 650, 1, 32
+def test_ragged_batch_order(batch, head_dim, rows):
+    """Sequences taken by falling length (2 to 64 of them, of 640 tokens and more, on more workgroups than one round holds):
+    every row of every one, with unsorted, equal, empty and out-of-range lengths.  65: as they come."""
+    n, round_tiles = 650, 768 if rows == 128 and head_dim != 128 else 512
+    tiles = (n + rows - 1) // rows
+    heads = round_tiles // (tiles * batch) + 1
+    assert tiles * batch * heads > round_tiles
     lens = np.random.Generator(np.random.PCG64(batch)).integers(-20, n + 20, batch)
-    lens[0], lens[-1] = 650, 81
+    lens[0], lens[-1] = 333, 650
     lens[batch // 2] = lens[0]
     _, q, k, v = draw(5, batch, heads, n, head_dim, "fp16")
-    o_ref, lse_ref = attention_oracle(q, k, v, lens, 0.25, -1, -1)
-    o, lse = run_ex(q, k, v, lens, "fp16", 0.25, tuning=fa.FA_TUNE_BM_128)
-    check_against(o, lse, o_ref, lse_ref, lens, "fp16")
+    h = sorted({0, heads // 2, heads - 1})          # (the oracle on three heads: all run the same code)
+    o_ref, lse_ref = attention_oracle(q[:, h], k[:, h], v[:, h], lens, 0.25, -1, -1)
+    o, lse = run_ex(q, k, v, lens, "fp16", 0.25, tuning=fa.FA_TUNE_BM_128 if rows == 128 else fa.FA_TUNE_BM_256)
+    assert not np.isnan(o).any() and not np.isnan(lse).any()   # (outputs start as NaN)
+    check_against(o[:, h], lse[:, h], o_ref, lse_ref, lens, "fp16", relative=True)
 
 
 PAD_N, PAD_ENDS = 1100, [1, 64, 65, 300, 576, 588, 640, 1099]
@@ -86,7 +93,7 @@ def padded(head_dim, dtype, value):
 @pytest.mark.parametrize("head_dim", [32, 64, 128])
 def test_padding_by_bias_leaves_the_call(head_dim, dtype, tuning, value):
     """Tails of keys whose bias makes them count for nothing, fewer and more than the eight tiles from which they are looked
-    at; in the last sequence two keys of the tail count all the same, by their size."""
+    at; in sequence 3 two keys of the tail count all the same, by their size."""
     q, k, v, bias = padded(head_dim, dtype, round_to_storage(np.float32([value]), dtype)[0])
     scale = 1.0 / np.sqrt(head_dim)
     if value == -750.0:
@@ -107,6 +114,26 @@ def test_padding_by_bias_with_infinite_values(head_dim):
     assert np.isfinite(np.delete(o[3], 5, axis=-1)).all() and np.isfinite(np.delete(o, 3, axis=0)).all()
 
 
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256], ids=["128", "256"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+def test_padding_by_bias_below_a_length(head_dim, dtype, tuning):
+    """A length beside the bias: keys from it on do not exist, whatever q, k, v and the bias hold there, and the padded tail
+    ends at it."""
+    n, lens, ends = 1300, [1100, 1024, 1217, 1300], [300, 500, 640, 64]
+    _, q, k, v = draw(11, len(lens), 1, n, head_dim, dtype)
+    bias = np.zeros((len(lens), n), dtype=np.float32)
+    for b, (length, end) in enumerate(zip(lens, ends)):
+        bias[b, end:length] = -65504.0 if dtype == "fp16" else -65536.0
+    o_ref, lse_ref = attention_oracle(q, k, v, lens, 0.125, -1, -1, key_bias=bias)
+    for b, length in enumerate(lens):
+        q[b, :, length:] = k[b, :, length:] = np.nan
+        v[b, :, length:] = np.inf
+        bias[b, length:] = np.nan
+    o, lse = run_ex(q, k, v, lens, dtype, 0.125, tuning=tuning, key_bias=bias)
+    check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True)
+
+
 def one_jump_per_row(head_dim, dtype, n, lens, heads, height=20.0):
     """Row i scores `height` higher with one key of tile i % 16 than with the others of N(0, 1): each tile refreshes some rows."""
     _, q, k, v = draw(78, len(lens), heads, n, head_dim, dtype)
@@ -117,7 +144,8 @@ def one_jump_per_row(head_dim, dtype, n, lens, heads, height=20.0):
     return q, round_to_storage(k, dtype), v
 
 
-@pytest.mark.parametrize("head_dim,heads", [(32, 1), (64, 1), (128, 1)])
+# (head_dim 128 forms its scores in one of two ways, by the number of 128-row tiles: 18 and 360 here)
+@pytest.mark.parametrize("head_dim,heads", [(32, 1), (64, 1), (128, 1), (128, 20)])
 @pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256, fa.FA_TUNE_BM_384, fa.FA_TUNE_BM_512, fa.FA_TUNE_BM_MIXED],
                          ids=["128", "256", "384", "512", "mixed"])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
@@ -132,7 +160,7 @@ def test_refresh_in_every_tile(head_dim, heads, dtype, tuning):
     check_against(o[:, -1:], lse[:, -1:], o_ref, lse_ref, lens, dtype, relative=True)
 
 
-@pytest.mark.parametrize("head_dim,heads", [(32, 1), (64, 1), (128, 1)])
+@pytest.mark.parametrize("head_dim,heads", [(32, 1), (64, 1), (128, 1), (128, 12)])
 @pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256], ids=["128", "256"])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 def test_long_excluded_prefixes(head_dim, heads, dtype, tuning):
