@@ -98,10 +98,11 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
   const bool windowed = p.window_left >= 0 || p.window_right >= 0;
   if (windowed) return 128;
   const int64_t bh = (int64_t)p.batch * p.heads;
+  const bool plain64 = p.head_dim == 64 && !p.key_bias && !p.rope_cos;
   // At head_dim 32 the key-bias variant has four wavefronts per SIMD on 128 rows and two on 256: us, 12 heads, 128 -> 256 rows,
   // 12 x 700 24.2 -> 27.5, 8 x 2048 95 -> 101, 1 x 10000 271 -> 286; nowhere of 40 calls in either type the other way.
   if (p.head_dim == 32 && p.key_bias) return 128;
-  if (p.batch > 1 && p.max_len < 2048) {
+  if (p.batch > 1 && p.max_len < 2048 && (p.seq_lens || plain64)) {
     // batches of short sequences (ragged lengths leave many tiles empty, which the model
     // below cannot see).  Measured: 768 tiles of 256 rows are 1-5 % faster at 128, 1536 and
     // more 2-7 % faster at 256.
@@ -115,14 +116,16 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
   // rounds of 256-row pairs with 128-row workgroups on what remains (beyond 1024; between the
   // two a single round of the larger shapes does as well)
   if (allow_mixed && (w128 <= 768 || w128 > 1024) && mixed_fits(p)) return 0;
-  // What a block of 128-row workgroups costs more.  A rotation in the call is done once per query tile (us, 12 x 64, 128 -> 256
-  // rows: 7 x 2048 138 -> 118, 12 x 2048 218 -> 193, but 6 x 2048 in a thin second round of the larger ones 105 -> 115).
-  const double rel = p.rope_cos && p.head_dim != 32 ? 1.2 : 1.08;
+  // What a block of 128-row workgroups costs more: plain calls, and head_dim 32, 1.08.  A rotation in the call is done once per
+  // query tile (us, 12 x 64, 128 -> 256 rows: 7 x 2048 138 -> 118, 12 x 2048 218 -> 193, but 6 x 2048 in a thin second round
+  // of the larger ones 105 -> 115).  A key bias: one sequence leans to the larger tiles (16K, 9000 keys 583 -> 531), a batch, whose bias
+  // is its padding, to the smaller: tiles whose padded tail leaves the call are done early, and small ones fill up behind
+  // them (8 x 2048 (1024 -) 105 -> 110, 16 x 1024 (512 -) 64.2 -> 66.5; full, 118 -> 115 and 68.7 -> 64.9).
+  const double rel = p.head_dim == 32 ? 1.08 : (p.rope_cos ? 1.2 : (p.key_bias ? (p.batch > 1 ? 1.06 : 1.12) : 1.08));
   const double c128 = shape_cost(w128, 3, 4, rel), c256 = shape_cost(w256, 2, 8, 1.0),
                c512 = shape_cost(w512, 1, 16, 0.98);
   if (c512 < c256 && c512 < c128 && w512 <= 256) return 512;   // 512 only where one round holds the call
-  // (a tie goes to the larger shape, but with a key bias to the smaller one: 8 x 2048 121.7 against 124.5 us)
-  return c256 < c128 || (c256 == c128 && !p.key_bias) ? 256 : 128;
+  return c256 <= c128 ? 256 : 128;
 }
 
 // Shape of the split kernel for a global layer, 16 * NQ + NK (NQ blocks of 32 query rows per workgroup, each shared by
