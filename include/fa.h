@@ -42,7 +42,7 @@
  *   synchronises, never changes the current device.  Work is enqueued on `stream`
  *   (a hipStream_t passed as void*; NULL = the default stream) and the call
  *   returns immediately.  q, k, v are read-only; o and lse must not overlap them.
- *   Results are bitwise reproducible from run to run (no atomics).
+ *   Results are bitwise reproducible from run to run (no sum depends on the order of threads).
  *
  * Errors
  *   0  success (work enqueued).
@@ -171,7 +171,7 @@ typedef struct fa_params {
      one case: a rotation on a GLOBAL layer (no window).  There the in-call rotation turns every K
      tile once per query tile; with at least fa_rope_scratch_bytes(...) of scratch a first kernel
      rotates q and k once into the scratch and the attention kernel (in any of its tile shapes)
-     runs on the rotated copies: same bits, 8K tokens x 12 heads 0.27 -> 0.21 ms.  Too small a
+     runs on the rotated copies: same bits, 8K tokens x 12 heads 0.29 -> 0.21 ms.  Too small a
      scratch, a local layer or no rotation: ignored.  The scratch may be reused as soon as the
      stream has passed the call; two calls that overlap in time must not share it. */
   void* scratch;
@@ -183,7 +183,7 @@ typedef struct fa_params {
 #define FA_TUNE_BM_AUTO 0x0u
 #define FA_TUNE_BM_128 0x1u  /* 4 wavefronts x 32 query rows  */
 #define FA_TUNE_BM_256 0x2u  /* head_dim 64 and 32: 4 wavefronts x 64 query rows; head_dim 128 global
-                                layers: 8 wavefronts x 32 rows on one pair of K/V stages */
+                                layers: 8 wavefronts x 32 rows on one pair of K/V rings */
 #define FA_TUNE_BM_32 0x3u   /* 32 query rows, eight wavefronts split the keys (global layers of
                                 head_dim 64 without a key bias; ignored otherwise).  The library
                                 picks this or another shape that splits the keys by itself for

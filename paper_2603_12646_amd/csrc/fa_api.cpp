@@ -71,11 +71,12 @@ bool mixed_fits(const fa_params& p) {
   return p.batch == 1 && p.heads <= 256 && tiles * p.heads <= (1 << 20) && fa_mix_ids((int)tiles, p.heads) >= 0;
 }
 
-// Relative time of a global layer of head_dim 64 under a tile shape, from how its workgroups
+// Relative time of a global layer under a tile shape, from how its workgroups
 // fill 256 compute units: full rounds of `slots` workgroups per unit cost slots * blocks each
 // (blocks = 32-row query blocks per workgroup), a partly filled last round costs less (its
 // workgroups have their SIMDs more to themselves), and `rel` is the shape's cost per block
-// relative to the 256-row shape.  Fitted to sweeps of 2K - 32K tokens x 8 - 32 heads on MI355X.
+// relative to the 256-row shape.  Fitted to sweeps of 2K - 32K tokens x 8 - 32 heads of head_dim 64 on MI355X; the callers
+// say by `rel` what differs for a bias, a rotation and the other head sizes.
 double shape_cost(int64_t workgroups, int slots, int blocks, double rel) {
   const int64_t per_round = 256LL * slots;
   const int64_t full = workgroups / per_round, rest = workgroups % per_round;

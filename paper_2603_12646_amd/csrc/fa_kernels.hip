@@ -2108,16 +2108,19 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
 // ======================================================================================
 // Global kernel: a software pipeline over 64-key tiles
 //
-// A workgroup is NW wavefronts (4; 8 and 12 exist for head_dim 64, 8 for 128) that share one pair of rings, four 32-key
-// blocks of K and four of V, filled by direct loads one tile ahead; each wavefront owns NQB blocks of 32 query rows.
+// A workgroup is NW wavefronts (4; 8 and 12 exist for head_dim 64, 8 for 128) that share one pair of rings of 32-key blocks,
+// eight of K (head_dim 128: four) and four of V, filled by direct loads one tile ahead; each wavefront owns NQB blocks of 32
+// query rows.
 // Large calls are bound by the power limit (the clock sits at 1.8 - 2.2 of 2.4 GHz) and by issue slots together, so what
 // counts is how many instructions a unit of 32 keys x 32 queries takes and what they draw:
 //   * ONE test per 64-key tile decides whether the running references still hold, of row sums formed an iteration ago.
 //     (A test per unit waits for the unit's sum, cuts the straight-line code and cost 3 - 9 % of the bare instruction
 //     mix.)  It has to come before the tile's P.V is accumulated, so the P.V lags a whole tile behind the probabilities,
-//     which wait in registers; when it trips, which is rare, the tile's scores are formed again from K in global memory;
-//   * fp16 row sums, of the rounded probabilities, go to the matrix cores: two products with a constant operand instead
-//     of eight dot products and an addition (bf16 sums the unrounded fp32 probabilities, 16 additions);
+//     which wait in registers; when it trips, the tile's scores are formed again from K in LDS (head_dim 128: in global
+//     memory).  Rows with peaked probabilities trip often: 8K 12 x 64 fp16, q and k of 3 N(0, 1) 232 us, of 6 N(0, 1) 258,
+//     scores that rise by 100 along the keys 330 (306, 412 and 618 with K from global memory); head_dim 128 313, 391, 571;
+//   * fp16 row sums, of the rounded probabilities, go to the matrix cores where the smaller shape runs (two products with a
+//     constant operand instead of eight dot products and an addition), bf16 sums the unrounded fp32 ones, 16 additions;
 //   * the shape of the matrix instruction per type and head size: GlobalTile;
 //   * the ragged last tile is a masked iteration of the same pipeline on rows clamped into the tensor, not a second staging
 //     pass through registers (a 128-row workgroup of a 512-token sequence spent 2.5 of its 12 us there).
