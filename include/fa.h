@@ -171,7 +171,7 @@ typedef struct fa_params {
      one case: a rotation on a GLOBAL layer (no window).  There the in-call rotation turns every K
      tile once per query tile; with at least fa_rope_scratch_bytes(...) of scratch a first kernel
      rotates q and k once into the scratch and the attention kernel (in any of its tile shapes)
-     runs on the rotated copies: same bits, 8K tokens x 12 heads 0.29 -> 0.21 ms.  Too small a
+     runs on the rotated copies: same bits, 8K tokens x 12 heads 0.28 -> 0.20 ms.  Too small a
      scratch, a local layer or no rotation: ignored.  The scratch may be reused as soon as the
      stream has passed the call; two calls that overlap in time must not share it. */
   void* scratch;
