@@ -1305,8 +1305,12 @@ constexpr int kTwoPhaseBlocks = 5;
 
 // OPT: a rotation (kTwoPhaseRope) or a key bias (kTwoPhaseBias) is a compile-time variant.
 //   Rotation: the K blocks are rotated in place in LDS, once for the four wavefronts.  What that costs is the angle
-//   tables: 256 bytes per K row, as much as its K and V, so a thread requests its rows' entries right behind the K
-//   loads and holds them in registers (the score accumulators are not live yet) until K has landed.
+//   tables: 256 bytes per row, as much as its K and V.  So each row's entries are read once per workgroup: a wavefront
+//   rotates the K block of its own 32 queries' rows, the same entries rotate those queries, and one block of the halo; four
+//   lanes (head_dim 64) read a row side by side, and the queries change into the operand layout, one row per lane, through a
+//   small patch.  (Queries rotated where they are used, from table rows of their own, 32 rows per load instruction, took as
+//   long as all of K: us, rotated -> this, bf16, packed, 8K 12 x 64 16.8 -> 15.3, 8 x 128 22.6 -> 19.1, 24 x 32 16.9 -> 16.4,
+//   487 tokens 8.7 -> 7.6, 32K 12 x 64 64.0 -> 55.6; without a rotation 12.6 at 8K, 42 at 32K.)
 //   Bias, head_dim 32 and 128: each key's bias divided by |scale| is added to its block's finished scores, so that a score
 //   near -65504 is rounded once, not in every product of the chain, and the row sums are those of the unrounded
 //   probabilities, both as in the masked kernel.  head_dim 64: it is the C operand of its block's first score product and
@@ -1321,8 +1325,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
   constexpr int KS = D / 16, DB = D / 32;
   constexpr int kBlk = 32 * D;  // elements per block
   static_assert(kResBlocks * kBlk >= kWaves * epi_patch(D), "the region doubles as the epilogue patches");
-  __shared__ __attribute__((aligned(16))) uint16_t lds[kResBlocks * kBlk];
-  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? kResBlocks * 32 : 4];
+  // BIAS: the region is followed by the keys' biases; ROPE: by a patch per wavefront through which rotated Q rows reach the
+  // lanes of the operand layout, kQRows at a time (head_dim 64: 40 KB a workgroup, a quarter of the unit's LDS)
+  constexpr int kQRows = D == 32 ? 32 : 16;
+  __shared__ __attribute__((aligned(16))) uint16_t lds[kResBlocks * kBlk + (BIAS ? kResBlocks * 64 : ROPE ? kWaves * kQRows * D : 0)];
+  float* const lds_bias = (float*)(lds + kResBlocks * kBlk);
 
   TileCoord tc;
   if (!locate_tile<BM, false, ROPE || D == 32>(a, tc)) return;  // tc.n still as loaded: see below
@@ -1403,29 +1410,64 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
       }
     }
   };
-  request_blocks(kp, a.ks[2], true);
+  if (!ROPE) request_blocks(kp, a.ks[2], true);
 
-  // ROPE: item x of a thread is chunk pair tid % HALF of region row tid / HALF + x * RSTEP (its key clamped into the
-  // tensor: rows outside it are never used unmasked)
-  constexpr int HALF = D / 16, RSTEP = kThreads / HALF;
-  constexpr int kItems = kResBlocks * 32 / RSTEP;              // D = 32, 64, 128: 2, 4, 8
-  constexpr int kHeld = ROPE && D != 128 ? kItems : 0;          // items whose table entries are held (32, 64 registers)
-  const int rope_r = tid / HALF, rope_c = tid % HALF;
-  auto table_row = [&](int x) {
-    int key = b_lo * 32 + rope_r + x * RSTEP;
-    key = key < N ? key : N - 1;
-    return (int64_t)key * a.rope_stride + 8 * rope_c;
+  const int qw0 = q0 + wave * 32;
+  // ROPE: a wavefront fetches two of the region's blocks, the one whose keys are its own 32 queries and one of the four
+  // others, and rotates them in place: what it fetched it may read without a barrier.  An item of a lane is a pair of chunks
+  // (c, c + HALF) of one row, HALF lanes a row; the angles of the wavefront's own rows rotate its queries as well.
+  constexpr int HALF = D / 16, RI = 64 / HALF, NI = 32 / RI;    // lanes per row; rows per item, items per block: D = 32, 64, 128: 32, 1; 16, 2; 8, 4
+  const int own_blk = (q0 >> 5) - b_lo + wave;                   // (region-relative; tiles start at multiples of 128)
+  const int halo_blk = wave < own_blk - wave ? wave : wave + 4;
+  const bool halo_there = b_lo + halo_blk < b_hi_ld;             // wavefront-uniform
+  const int rope_c = lane % HALF;
+  struct Angles {
+    float4 c[2], s[2];
   };
-  float4 held[kHeld > 0 ? kHeld : 1][4];
+  uint4 q_raw[ROPE ? NI : 1][2];
+  Angles t_own[ROPE ? NI : 1], t_halo[ROPE ? NI : 1];
+  // the row of item x in a region block (clamped into the tensor: rows outside it are never used unmasked)
+  auto item_row = [&](int blk, int x) {
+    const int row = 32 * (b_lo + blk) + RI * x + lane / HALF;
+    return row < N ? row : N - 1;
+  };
+  auto load_angles = [&](int blk, int x, Angles& g) {
+    const int64_t at = (int64_t)item_row(blk, x) * a.rope_stride + 8 * rope_c;
+    const float4 *cs = (const float4*)(a.rope_cos + at), *sn = (const float4*)(a.rope_sin + at);
+    g.c[0] = cs[0]; g.c[1] = cs[1]; g.s[0] = sn[0]; g.s[1] = sn[1];
+  };
+  // item x of a 32-row block in LDS
+  auto lo_at = [&](uint16_t* blk, int x) { return (uint4*)&blk[(RI * x + lane / HALF) * D + ((rope_c ^ k_swz_d<D>(RI * x + lane / HALF)) * 8)]; };
+  auto hi_at = [&](uint16_t* blk, int x) { return (uint4*)&blk[(RI * x + lane / HALF) * D + (((rope_c + HALF) ^ k_swz_d<D>(RI * x + lane / HALF)) * 8)]; };
+  auto rotate_item = [&](uint16_t* blk, int x, const Angles& g) {
+    uint4 lo = *lo_at(blk, x), hi = *hi_at(blk, x);
+    rotate8<T>(lo, hi, (const float*)g.c, (const float*)g.s);
+    *lo_at(blk, x) = lo;
+    *hi_at(blk, x) = hi;
+  };
   if (ROPE) {
 #pragma unroll
-    for (int x = 0; x < kHeld; ++x) {
-      const float4* cs = (const float4*)(a.rope_cos + table_row(x));
-      const float4* sn = (const float4*)(a.rope_sin + table_row(x));
-      held[x][0] = cs[0];
-      held[x][1] = cs[1];
-      held[x][2] = sn[0];
-      held[x][3] = sn[1];
+    for (int x = 0; x < NI; ++x) {
+      const uint16_t* src = qp + item_row(own_blk, x) * a.qs[2] + 8 * rope_c;
+      q_raw[x][0] = *(const uint4*)src;
+      q_raw[x][1] = *(const uint4*)(src + 8 * HALF);
+      load_angles(own_blk, x, t_own[x]);
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int blk = s == 0 ? own_blk : halo_blk, first = 32 * (b_lo + blk);
+      if (b_lo + blk < b_hi_ld) {
+        const uint16_t* g = kp + (int64_t)first * a.ks[2];
+#pragma unroll
+        for (int x = 0; x < LPB; ++x) {
+          const int r = RPL * x + lane / CH, rc = r < N - 1 - first ? r : N - 1 - first;
+          load16_to_lds(g, 2u * ((uint32_t)rc * (uint32_t)a.ks[2] + (uint32_t)(((lane % CH) ^ k_swz_d<D>(r)) * 8)), lds + blk * kBlk + RPL * x * D);
+        }
+      }
+    }
+    if (halo_there) {
+#pragma unroll
+      for (int x = 0; x < NI; ++x) load_angles(halo_blk, x, t_halo[x]);
     }
   }
   uint16_t bias_bits = 0;   // one value per thread: key b_lo*32 + tid (256 keys, 256 threads); used once K has landed
@@ -1435,9 +1477,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
     bias_bits = bp[jg < N ? jg : N - 1];
   }
 
-  const int qw0 = q0 + wave * 32;
   typename T::v8 qreg[1][KS];
-  load_q<T, 1, KS, ROPE>(a, qp, qw0, lane, qreg);
+  if (!ROPE) load_q<T, 1, KS, false>(a, qp, qw0, lane, qreg);
 
   // only now the sequence length
   const int n = tc.n < 0 ? 0 : (tc.n > N ? N : tc.n);
@@ -1466,33 +1507,44 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
   cnt = cnt > kTwoPhaseBlocks ? kTwoPhaseBlocks : cnt;  // (the host routes no wider window here)
 
   // ---- phase 1: scores of every visible block
-  wait_direct_loads();
+  if (ROPE) {
+    uint16_t* const patch = lds + kResBlocks * kBlk + wave * kQRows * D;
+    const uint32_t flip = a.negate_q ? 0x80008000u : 0u;
+    // queries: rotated, through the patch, into the operand layout (the same wavefront writes and reads it: program order
+    // is enough)
+#pragma unroll
+    for (int half = 0; half < 32 / kQRows; ++half) {
+      uint16_t* const rows = patch - half * kQRows * D;   // where row 0 of the block would be
+#pragma unroll
+      for (int x = 0; x < NI; ++x) {
+        if (RI * x / kQRows != half) continue;
+        rotate8<T>(q_raw[x][0], q_raw[x][1], (const float*)t_own[x].c, (const float*)t_own[x].s);
+        *lo_at(rows, x) = q_raw[x][0];
+        *hi_at(rows, x) = q_raw[x][1];
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (l32 / kQRows == half) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          uint4 u = __builtin_bit_cast(uint4, load_k_frag_swz_d<T, D>(rows, l32, hh, ks));
+          u.x ^= flip; u.y ^= flip; u.z ^= flip; u.w ^= flip;
+          qreg[0][ks] = as_v8<T>(u);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    wait_direct_loads();
+#pragma unroll
+    for (int x = 0; x < NI; ++x) rotate_item(lds + own_blk * kBlk, x, t_own[x]);
+    if (halo_there) {
+#pragma unroll
+      for (int x = 0; x < NI; ++x) rotate_item(lds + halo_blk * kBlk, x, t_halo[x]);
+    }
+  } else {
+    wait_direct_loads();
+  }
   if (BIAS) lds_bias[tid] = bias_over_scale<T, BIAS_LAST>(a, bias_bits);
   __syncthreads();
-  if (ROPE) {
-#pragma unroll
-    for (int x = 0; x < kItems; ++x) {
-      const int r = rope_r + x * RSTEP;
-      if (r < (b_hi - b_lo) * 32) {
-        float4 tb[4];
-        if (x < kHeld) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) tb[e] = held[x < kHeld ? x : 0][e];
-        } else {
-          const float4* cs = (const float4*)(a.rope_cos + table_row(x));
-          const float4* sn = (const float4*)(a.rope_sin + table_row(x));
-          tb[0] = cs[0]; tb[1] = cs[1]; tb[2] = sn[0]; tb[3] = sn[1];
-        }
-        uint4* plo = (uint4*)&lds[r * D + ((rope_c ^ k_swz_d<D>(r & 31)) * 8)];
-        uint4* phi = (uint4*)&lds[r * D + (((rope_c + HALF) ^ k_swz_d<D>(r & 31)) * 8)];
-        uint4 lo4 = *plo, hi4 = *phi;
-        rotate8<T>(lo4, hi4, (const float*)&tb[0], (const float*)&tb[2]);
-        *plo = lo4;
-        *phi = hi4;
-      }
-    }
-    __syncthreads();
-  }
   floatx16 sc[kTwoPhaseBlocks];   // sc[i] is set and used for i < cnt only
 #pragma unroll
   for (int i = 0; i < kTwoPhaseBlocks; ++i) {

@@ -224,3 +224,20 @@ def test_rope_with_scores_that_jump(D, H, dtype, tuning):
     o_ref, lse_ref = attention_oracle_rope(q[:, -1:], k[:, -1:], v[:, -1:], c64, s64, dtype, lens, scale)
     o, lse = run_rope(q, k, v, lens, dtype, scale, c32, s32, tuning=tuning)
     check_against(o[:, -1:], lse[:, -1:], o_ref, lse_ref, lens, dtype, relative=True, label=f"rope jumps D{D} {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("left,right", [(63, 64), (0, 128), (128, 0), (96, 32), (1, 90)])
+def test_rope_local_halo_on_either_side(D, dtype, left, right):
+    """The two-phase window kernel deals a tile's key blocks to its wavefronts, each one's own queries' block and one of the
+    halo: from none to four halo blocks on the left, tensors and sequences that end inside a block, and a negative scale (the
+    sign goes on after the rotation)."""
+    B, H, N = 3, 2, 449
+    lens = [449, 258, 1]
+    _, q, k, v = draw(9800 + D, B, H, N, D, dtype)
+    c32, s32, c64, s64 = tables(N, D, base=300.0)
+    scale = -1.0 / np.sqrt(D)
+    o_ref, lse_ref = attention_oracle_rope(q, k, v, c64, s64, dtype, lens, scale, left, right)
+    o, lse = run_rope(q, k, v, lens, dtype, scale, c32, s32, left, right)
+    check_against(o, lse, o_ref, lse_ref, lens, dtype, label=f"rope halo D{D} {dtype} ({left},{right})")
