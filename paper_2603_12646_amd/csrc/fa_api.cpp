@@ -366,13 +366,14 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   a.map_xcd = t_map == FA_TUNE_MAP_LINEAR ? 0 : 1;
   // Local layers: the query tiles of one head in a row share the halo of their windows in the XCD's L2.  Two kinds of call
   // gain more from the heads of one query tile in a row, if an XCD's eighth is still several tiles deep: a rotation, whose
-  // table rows (as many bytes as K and V) are the same for all heads - measured, us, 8K tokens: head_dim 64 17.8 -> 16.8,
-  // 128 24.4 -> 22.5, 32 20.0 -> 17.2, but 2K (16 tiles) 13.7 -> 14.0 at head_dim 128 and 32 x 512 26.9 -> 27.9 - and heads
-  // of 32 side by side in a row, two of which share a 128-byte line: 32K packed 67 -> 53, 2K 7.1 -> 6.8, 32 x 1024 (8 tiles)
-  // 51.8 -> 53.1.  (Other calls: 8K head_dim 64 12.7 -> 12.9, 32K 41.9 -> 48.1; a rotation at head_dim 32 on dense tensors
-  // with padding, where the padding tiles then all come last: 16000 of 32768 48.5 -> 50.3.)
+  // table rows (as many bytes as K and V) are the same for all heads - measured, us, bf16: head_dim 64 2K 8.7 -> 8.35, 3K
+  // 11.4 -> 10.6, 5K 12.6 -> 11.5, 8K 16.3 -> 15.4, 4 x 4000 ragged 26.3 -> 25.1, 8 x 3000 38.2 -> 38.3, but 1K (8 tiles) 7.5 -> 7.7,
+  // 16 x 1000 27.8 -> 29.1, 32 x 512 26.4 -> 27.1; 128 1400 (11 tiles) 12.0 -> 11.5, 4 x 1500 18.4 -> 17.7, 8K 26.4 -> 20.4; 32 3K
+  // 10.0 -> 9.3, 8K 17.1 -> 16.3 - and heads of 32 side by side in a row, two of which share a 128-byte line: 32K packed 67 -> 53,
+  // 2K 7.1 -> 6.8, 32 x 1024 (8 tiles) 51.8 -> 53.1.  (Other calls: 8K head_dim 64 12.7 -> 12.9, 32K 41.9 -> 48.1; a rotation at
+  // head_dim 32 on dense tensors with padding, where the padding tiles then all come last: 16000 of 32768 48.5 -> 50.3.)
   a.heads_first = a.map_xcd && windowed &&
-                  ((p->rope_cos && n_qtiles >= 48 && (p->head_dim != 32 || !p->seq_lens)) || (p->head_dim == 32 && n_qtiles >= 16 && a.ks[1] == 32 && a.ks[2] >= 64));
+                  ((p->rope_cos && n_qtiles >= (p->head_dim == 128 ? 11 : 16) && (p->head_dim != 32 || !p->seq_lens)) || (p->head_dim == 32 && n_qtiles >= 16 && a.ks[1] == 32 && a.ks[2] >= 64));
   // Ragged batches on the pipelined kernel: long sequences first, so that the short tiles fill the last round.  Finding the
   // r-th sequence takes a workgroup 1 us before its first load, which short tiles do not earn back: us, 12 x 64, as they
   // come -> longest first: 12 x 700 (300 -) 20.9 -> 20.1, 16 x 1024 (600 -) 49.1 -> 48.0, 3 x 16K (9000 -) 1476 -> 1465, but
