@@ -119,10 +119,12 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
   if (allow_mixed && (w128 <= 768 || w128 > 1024) && mixed_fits(p)) return 0;
   // What a block of 128-row workgroups costs more: plain calls, and head_dim 32, 1.08.  A rotation in the call is done once per
   // query tile (us, 12 x 64, 128 -> 256 rows: 7 x 2048 138 -> 118, 12 x 2048 218 -> 193, but 6 x 2048 in a thin second round
-  // of the larger ones 105 -> 115).  A key bias: one sequence leans to the larger tiles (16K, 9000 keys 583 -> 531), a batch, whose bias
-  // is its padding, to the smaller: tiles whose padded tail leaves the call are done early, and small ones fill up behind
-  // them (8 x 2048 (1024 -) 105 -> 110, 16 x 1024 (512 -) 64.2 -> 66.5; full, 118 -> 115 and 68.7 -> 64.9).
-  const double rel = p.head_dim == 32 ? 1.08 : (p.rope_cos ? 1.2 : (p.key_bias ? (p.batch > 1 ? 1.06 : 1.12) : 1.08));
+  // of the larger ones 105 -> 115).  A key bias is padding as a rule, whose kernels make one pass over it per query tile: us,
+  // 12 x 64, 128 -> 256 rows, fp16 8 x 2048 (1024 -) 102 -> 97, 16 x 1024 61.5 -> 58.9, 12 x 3000 297 -> 270, but 12 x 1000 46 -> 49,
+  // 1 x 8192 155 -> 160, 2 x 12000 737 -> 735; bf16 8 x 2048 115 -> 107, 1 x 16K 553 -> 466, 1 x 24000 1131 -> 1000.  (Other
+  // biases lean to the smaller tiles in fp16: keys 100 - 130 excluded, 8 x 2048 110 -> 115, bf16 126 -> 122.)
+  const double rel_bias = p.dtype == FA_DTYPE_F16 ? 1.12 : 1.17;
+  const double rel = p.head_dim == 32 ? 1.08 : (p.rope_cos ? 1.2 : (p.key_bias ? rel_bias : 1.08));
   const double c128 = shape_cost(w128, 3, 4, rel), c256 = shape_cost(w256, 2, 8, 1.0),
                c512 = shape_cost(w512, 1, 16, 0.98);
   if (c512 < c256 && c512 < c128 && w512 <= 256) return 512;   // 512 only where one round holds the call

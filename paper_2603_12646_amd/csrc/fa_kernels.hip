@@ -2427,6 +2427,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   constexpr int THREADS = NW * 64;
   constexpr int BM = NW * 32 * NQB;
   constexpr bool BIAS_LAST = BIAS && D == 32, BIAS_FIRST = BIAS && !BIAS_LAST;
+  // a loop of its own for calls whose bias turns out to be padding alone (head_dim 32 has no registers for the choice)
+  constexpr bool PLAIN_LOOP = BIAS && D != 32;
   // row sums of the rounded probabilities (fp16) on the matrix cores or by dot products, else of the unrounded ones
   constexpr bool ROUNDED = T::kSumRounded && !BIAS_LAST, MFMA_SUM = M::kMfmaSum && ROUNDED, DOT_SUM = !M::kMfmaSum && ROUNDED;
   constexpr int QT = M::QT, E = M::E, FR = D / 16;
@@ -2565,6 +2567,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   // tensors the rest of tile 1's operands (K block 3, V blocks 0 and 1) with them.  us, without -> with: 16 x 700 with a bias
   // 41.8 -> 39.6, 16 x 1024 49.7 -> 49.3, but 7 x 542 14.0 -> 14.2, 32 x 128 9.2 -> 9.9 (more to wait for before the first product).
   const bool early = N >= 640;
+  auto first_fetch = [&] {
   if (early) {
     fetch(0, true, true, 0, true);
     fetch(2, true, true, 0, false);
@@ -2575,6 +2578,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     fetch_clamped(0, true, 32 < N, 0, false);
     fetch_clamped(2, 64 < N, false, 0, false);
   }
+  };
+  first_fetch();
 
   const int qw0 = q0 + wave * 32 * NQB;
   v8 q[NQB][FR];
@@ -2624,24 +2629,19 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   floatx4 z[NQB][QT];                 // [0]: the lane's share of their sum (MFMA_SUM: a quarter of the row's)
   v8 ka[FR], va[FR];
   const v8 quarter = __builtin_bit_cast(v8, make_uint4(0x34003400u, 0x34003400u, 0x34003400u, 0x34003400u));  // fp16 0.25
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) lsum[qb][qt] = 0.f;
-    float* of = (float*)&o[qb];
-#pragma unroll
-    for (int x = 0; x < D / 2; ++x) of[x] = 0.f;
-  }
 
   typename M::Scores bcur;   // BIAS_LAST: the bias of the key block in ka (head_dim 32 has the registers, and its units are short)
-  auto load_ka = [&](const uint16_t* kblk, const float* bblk) {
+  // (WITHc: with the bias; a call whose keys that count all have a bias of zero runs the loop without, see below)
+  auto load_ka = [&](auto WITHc, const uint16_t* kblk, const float* bblk) {
 #pragma unroll
     for (int x = 0; x < FR; ++x) ka[x] = m.k_frag(kblk, x);
-    if (BIAS_LAST) m.template start<true>(bcur, bblk);
+    if (BIAS_LAST && decltype(WITHc)::value) m.template start<true>(bcur, bblk);
   };
-  auto score_init = [&](typename M::Scores& s, const float* bblk) { m.template start<BIAS_FIRST>(s, bblk); };
-  auto score_end = [&](typename M::Scores& s) {
-    if constexpr (BIAS_LAST) M::add(s, bcur);   // (Tile32 always)
+  auto score_init = [&](auto WITHc, typename M::Scores& s, const float* bblk) { m.template start<BIAS_FIRST && decltype(WITHc)::value>(s, bblk); };
+  auto score_end = [&](auto WITHc, typename M::Scores& s) {
+    if constexpr (BIAS_LAST) {   // (Tile32 always)
+      if (decltype(WITHc)::value) M::add(s, bcur);
+    }
   };
   // probabilities of a block against the rows' references, packed, and their sums
   auto softmax = [&](const typename M::Scores& s, float nmc, int qb, int u, int qt, bool masked, uint32_t vis) {
@@ -2676,7 +2676,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   // Rows of tile t whose sums ran away from their reference, or that found the first key that counts: the tile's scores are
   // formed again, its maximum is the new reference if it is above the old one, and the probabilities are made anew.  Each
   // row decides on its own lanes' evidence: no dependence on the rows that share its wavefront.
-  auto refresh = [&](int t, bool masked) {
+  auto refresh = [&](auto WITHc, int t, bool masked) {
+    constexpr bool WITH = decltype(WITHc)::value;
     auto vis_of = [&](int u) { return masked ? m.visible(2 * t + u, nk) : 0xFFFFu; };
     auto row_any = [&](bool x) { return M::row_sum(x ? 1.f : 0.f) > 0.f; };
 #pragma unroll
@@ -2711,13 +2712,15 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
           for (int x = 0; x < FR; ++x) kv[x] = as_v8<T>(kk[x]);
         }
         const float* b = lds_bias + (BIAS ? (blk & 7) * 32 : 0);
-        m.template start<BIAS_FIRST>(s[u], b);
+        m.template start<BIAS_FIRST && WITH>(s[u], b);
 #pragma unroll
         for (int i = 0; i < M::STEPS; ++i) M::score_step(s[u], kv, q[qb], i);
         if constexpr (BIAS_LAST) {
-          typename M::Scores bs;
-          m.template start<true>(bs, b);
-          M::add(s[u], bs);
+          if (WITH) {
+            typename M::Scores bs;
+            m.template start<true>(bs, b);
+            M::add(s[u], bs);
+          }
         }
       }
 #pragma unroll
@@ -2744,13 +2747,13 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     }
   };
   // The probabilities of tile t are final after this: one test per tile, of sums formed an iteration ago.
-  auto settle = [&](int t, bool masked) {
+  auto settle = [&](auto WITHc, int t, bool masked) {
     bool trig = false;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) trig = trig || !(z[qb][qt][0] <= kLimit);
-    if (__any(trig)) refresh(t, masked);
+    if (__any(trig)) refresh(WITHc, t, masked);
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
@@ -2762,7 +2765,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   // row bases of the next request: K block 2 t + 3, V block 2 t
   const int64_t k32 = 32 * a.ks[2], v32 = 32 * a.vs[2];
   const uint16_t *kreq = kp + 3 * k32, *vreq = vp;
-  auto request = [&](int t) {   // operands of tile t + 1
+  auto request = [&](auto WITHc, int t) {   // operands of tile t + 1
     if (t == 0 && early) {
       fetch(3, false, 2 < T64, 0, false);   // (all but K block 4 are on their way)
     } else if ((t > 0 || T64 > 1) && 64 * t + 160 <= N) {
@@ -2800,42 +2803,52 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     }
     kreq += 2 * k32;
     vreq += 2 * v32;
-    if (BIAS && wave == 0) bst = bias_of(64 * t + 96 + lane);
+    if (decltype(WITHc)::value && wave == 0) bst = bias_of(64 * t + 96 + lane);
     if (AHEAD && rot_there(0, TILE_UNITS)) load_angles(2 * t + 3, 0, ahead);
   };
   if (BIAS) {
     if (tid < 96) lds_bias[tid] = bias_of(tid);
   }
-  // BIAS: keys end .. n - 1 have biases below -1000 (log2 domain), top_bias is at least the largest of them (raw units).
-  // 512 keys per step from the end, while the first K blocks are on their way; 2 us that a short sequence does not earn back
-  // (24 x 512 31.8 -> 34.8, 4 x 1000 24.9 -> 26.6).
+  // BIAS: keys end .. n - 1 have biases of -700 or less (-1010 in the log2 domain), none above top_bias (raw units), and plain: the
+  // keys before them have zeros.  While the first K blocks are on their way every wavefront looks through a quarter of the
+  // keys, 512 per step from the end, until it has seen a key that counts and then one with a bias.  In short tensors the search
+  // and the pass over the padding cost more than they give (24 x 512 (400 -) bf16 31.9 -> 34.3 us).
   int end = n;
   float top_bias = -INFINITY;
-  if constexpr (BIAS) {
-    while (n >= 1024 && end > 0) {
-      const int first = end - 512 + 8 * lane;   // the lane's eight keys
-      uint16_t raw[8];
+  bool plain = false;
+  int* const found = (int*)(lds_bias + 260);   // [wavefront][last key that counts, first with a bias, smallest cold bias's bits, -]
+  if (BIAS && early) {
+    constexpr uint32_t kCold = T::kWideRange ? 0xC42Fu : 0xE178u, kInf = T::kWideRange ? 0xFF80u : 0xFC00u;   // -700, -infinity
+    int last = -1, first_biased = INT32_MAX;
+    uint32_t cold = 0xFFFFu;
+    for (int at = (n - 1) / 512 - ((n - 1) / 512 - wave + NW) % NW; at >= 0 && (PLAIN_LOOP ? first_biased > last : last < 0); at -= NW) {
+      uint32_t raw[8];
+      const int first = 512 * at + 8 * lane;   // the lane's eight keys (those past the end: the last one again)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) raw[i] = bp[first + i < 0 ? 0 : first + i];
-      int last = -1;
-      float low = -INFINITY;
+      for (int i = 0; i < 8; ++i) raw[i] = bp[first + i < n ? first + i : n - 1];
+      uint32_t warm = 0, biased = 0;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float x = bias_over_scale<T, D == 32>(a, raw[i]);
-        if (first + i >= 0) {
-          if (!(x * c <= -1000.f)) last = i;
-          else low = fmaxf(low, x);
-        }
+        const bool is_cold = raw[i] - kCold <= kInf - kCold;   // (as integers: magnitudes rise; a NaN counts)
+        cold = is_cold && raw[i] < cold ? raw[i] : cold;       // (that of some keys before `end` too: above the others at most)
+        warm |= is_cold ? 0u : 1u << i;
+        biased |= (raw[i] & 0x7FFFu) != 0 ? 1u << i : 0u;
       }
-      top_bias = fmaxf(top_bias, low);   // (that of some ordinary step's cold keys too: larger at most)
-      const uint64_t warm = __ballot(last >= 0);
-      if (warm) {
-        const int at = 63 - __clzll((long long)warm);
-        end = end - 512 + 8 * at + __builtin_amdgcn_readlane(last, at) + 1;
-        break;
+      const uint64_t warms = __ballot(warm != 0), biases = __ballot(biased != 0);
+      if (last < 0 && warms) {
+        const int l = 63 - __clzll((long long)warms), key = 512 * at + 8 * l + 31 - __clz(__builtin_amdgcn_readlane((int)warm, l));
+        last = key < n ? key : n - 1;
       }
-      end -= 512;
+      if (biases) {
+        const int l = __ffsll((unsigned long long)biases) - 1;
+        first_biased = 512 * at + 8 * l + __ffs(__builtin_amdgcn_readlane((int)biased, l)) - 1;
+      }
     }
+    if (__any(cold < 0xFFFFu)) {
+#pragma unroll
+      for (int d = 1; d < 64; d *= 2) cold = min(cold, (uint32_t)__shfl_xor((int)cold, d));
+    }
+    if (lane == 0) *(int4*)&found[4 * wave] = make_int4(last, first_biased, (int)cold, 0);
   }
   wait_direct_loads();
   __syncthreads();
@@ -2849,18 +2862,123 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     }
     __syncthreads();
   }
+  if (BIAS && early) {
+    int last = -1, first_biased = INT32_MAX, cold = 0xFFFF;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int4 f = *(const int4*)&found[4 * w];
+      last = max(last, f.x);
+      first_biased = min(first_biased, f.y);
+      cold = min(cold, f.z);
+    }
+    end = __builtin_amdgcn_readfirstlane(last) + 1;
+    plain = PLAIN_LOOP && end > 0 && __builtin_amdgcn_readfirstlane(first_biased) >= end;
+    if (cold < 0xFFFF) top_bias = bias_over_scale<T, D == 32>(a, (uint16_t)cold);
+  }
   typename M::Scores sA, sB;
-  load_ka(kops(0), lds_bias);
+  const bool rotate_prio = ROTATE && NQB == 1 && T64 >= 64;
+  int wslot = 0;
+  if (rotate_prio) {
+    unsigned hw_id;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw_id));
+    wslot = (int)(hw_id & 15u);  // wave slot within the SIMD
+  }
+
+  // One iteration = the 64 keys of tile t.  Units (key block 2t + u, query block qb) in the order (0,0) .. (0,NQB-1), (1,0) ..:
+  // the vector ALU turns the unit's scores (s_cur) into probabilities while the matrix cores form the NEXT unit's scores
+  // and add the P.V of the same unit of the PREVIOUS tile.  k1, k2: LDS blocks 2t + 1, 2t + 2 of K; v1, v2: 2t - 2, 2t - 1 of V.
+  auto iter = [&](auto WITHc, auto FIRSTc, auto LASTc, int t, const uint16_t* k1, const uint16_t* k2, const uint16_t* v1, const uint16_t* v2,
+                  const float* b0, const float* b1, const float* b2) {
+    constexpr bool FIRST = decltype(FIRSTc)::value, LAST = decltype(LASTc)::value;
+    auto unit = [&](auto Uc, auto QBc, typename M::Scores& s_cur, typename M::Scores& s_nxt) {
+      constexpr int U = decltype(Uc)::value, QB = decltype(QBc)::value;
+      constexpr int NQ = (QB + 1) % NQB;
+      constexpr bool NEXT = !(LAST && U == 1 && NQ == 0);     // there is a next unit
+      const float* bnext = NQ != 0 ? (U == 0 ? b0 : b1) : (U == 0 ? b1 : b2);   // bias of the next unit's key block
+      if (NQ == 0 && NEXT) load_ka(WITHc, U == 0 ? k1 : k2, bnext);
+      if (QB == 0 && !FIRST) {
+#pragma unroll
+        for (int x = 0; x < FR; ++x) va[x] = m.v_frag(U == 0 ? v1 : v2, x);
+      }
+      if (NEXT) score_init(WITHc, s_nxt, bnext);
+      // Score products alternate with output products.  Those whose operands the unit has yet to read from LDS come later: Tile32
+      // by a step (0.5 - 1.2 % of the bf16 calls), Tile16 with a bias and two blocks by four of its eight (1 %: the next block's
+      // biases are read in front of its first product); Tile16 without lost 0.5 - 1 % by it.
+      constexpr int LATE_S = NQ == 0 && NQB == 2 ? (M::kLateStep ? 1 : decltype(WITHc)::value ? M::STEPS / 2 : 0) : 0;
+      constexpr int LATE_O = M::kLateStep && !LATE_S ? 1 : 0;
+#pragma unroll
+      for (int i = 0; i < M::STEPS + (LATE_S > LATE_O ? LATE_S : LATE_O); ++i) {
+        if (NEXT && !LATE_S && i < M::STEPS) M::score_step(s_nxt, ka, q[NQ], i);
+        if (!FIRST && i >= LATE_O && i - LATE_O < M::STEPS) M::out_step(o[QB], va, p[QB][U], i - LATE_O);
+        if (NEXT && LATE_S && i >= LATE_S) M::score_step(s_nxt, ka, q[NQ], i - LATE_S);
+      }
+      if (NEXT) score_end(WITHc, s_nxt);
+      const uint32_t vis = LAST ? m.visible(2 * t + U, nk) : 0xFFFFu;
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) softmax(s_cur, -mc[QB][qt], QB, U, qt, LAST, vis);
+      // Units moved into each other cost registers (the variants with a bias or a rotation spill), and Tile32 1 % of its time;
+      // Tile16 gains 1 - 2 % by it (8K 12 x 64 179 -> 176 us), 7 x 542 2 %.
+      if (M::COLS == 32 || (BIAS && (NQB == 2 || decltype(WITHc)::value)) || ROPE) __builtin_amdgcn_sched_barrier(0);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    if constexpr (NQB == 1) {
+      unit(I0{}, I0{}, sA, sB);
+      unit(I1{}, I0{}, sB, sA);
+    } else {
+      unit(I0{}, I0{}, sA, sB);
+      unit(I0{}, I1{}, sB, sA);
+      unit(I1{}, I0{}, sA, sB);
+      unit(I1{}, I1{}, sB, sA);
+    }
+  };
+  // the tile's operands have landed, in every wavefront's share
+  auto landed = [&](auto WITHc, int t) {
+    if (decltype(WITHc)::value && wave == 0) lds_bias[(64 * t + 32 + lane) & 255] = bst;
+    wait_direct_loads();
+    __syncthreads();
+    if (ROPE) {
+      if (AHEAD) {
+        if (rot_there(0, TILE_UNITS)) rotate_unit(2 * t + 1, 0, ahead);
+      } else {
+#pragma unroll
+        for (int x = 0; x * THREADS < TILE_UNITS; ++x) {
+          if (!rot_there(x, TILE_UNITS)) continue;
+          Angles now;
+          load_angles(2 * t + 1, x, now);
+          rotate_unit(2 * t + 1, x, now);
+        }
+      }
+      __syncthreads();
+    }
+  };
+  auto bblk = [&](int b) { return lds_bias + (BIAS ? (b & 7) * 32 : 0); };
+  using No = std::false_type;
+  using Yes = std::true_type;
+  // Everything from the first scores on, with the bias (WITHc) or without; false: the padding has a part in the result after
+  // all, nothing has been written.  Two copies, from the first scores to the stores: with anything but the operands' addresses
+  // common to both the variants spill.
+  auto tiles = [&](auto WITHc) {
+  constexpr bool WITH = decltype(WITHc)::value;
+#pragma unroll
+  for (int qb = 0; qb < NQB; ++qb) {
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) lsum[qb][qt] = 0.f;
+    float* of = (float*)&o[qb];
+#pragma unroll
+    for (int x = 0; x < D / 2; ++x) of[x] = 0.f;
+  }
+  load_ka(WITHc, kops(0), lds_bias);
   if (KN == 4) __syncthreads();   // K block 0 is in registers everywhere: block 4 takes its place
-  request(0);
+  request(WITHc, 0);
   {
     const uint32_t vis = m.visible(0, nk);
 #pragma unroll
     for (int qb = NQB - 1; qb >= 0; --qb) {
-      score_init(sA, lds_bias);
+      score_init(WITHc, sA, lds_bias);
 #pragma unroll
       for (int i = 0; i < M::STEPS; ++i) M::score_step(sA, ka, q[qb], i);
-      score_end(sA);
+      score_end(WITHc, sA);
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
         float t0 = -INFINITY;
@@ -2873,17 +2991,20 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
 
   // Padding given as a bias (-65504 per padded key) is still a score, but its probability is exactly 0 beside any ordinary
   // key: below 2^-25 for fp16, whose sums are those of the rounded values, below the fp32 range otherwise.  The keys after
-  // the last one whose bias is above -1000 (in the log2 domain) leave the call if that can be shown ahead of it: with the
+  // the last one whose bias is above -700 leave the call if that can be shown ahead of it: with the
   // largest |k| among them, every row's |q|_1, and its first reference (references only rise); and if their V is finite (0
   // times it is 0).  Showing it takes one pass over their K and V without arithmetic on them.
   // Measured, us, without -> with: 8 x 2048 (1024 -) fp16 121.7 -> 112.6, 16 x 1500 (700 -) 140 -> 134, 1 x 8192 (5000) 8 x 128 239 -> 194,
-  // bf16 1 x 16804 (7024) 1075 -> 654; without padding the search costs 0 - 2 %.
+  // bf16 1 x 16804 (7024) 1075 -> 654; without padding the search costs 0 - 1 %.
+  // Where the keys that are left have zeros for biases (padding is all there is) the loop runs without a bias: 8 x 2048 fp16
+  // 128 rows 108 -> 99.5, 256 rows 115 -> 93.5, (2048) 256 rows 127 -> 108; 16 x 700 (300 -) 38.6 -> 35.6, 1 x 8192 (5000) 163 -> 153; bf16
+  // 1 x 16384 (10000) 571 -> 502, 12 x 1000 (500 -) 8 x 128 73 -> 57.
   if constexpr (BIAS) {
-    // (a pass takes 3 us and 0.5 us per tile, a tile in the pipeline 1.6: from eight tiles on)
-    if (end > 0 && (end + 63) / 64 + 8 <= T64) {
+    // (a pass takes 3 us and 0.5 us per tile, a tile in the pipeline 1.6: from eight tiles on, but for the loop without a bias always)
+    const bool cut = end > 0 && end < n && (!WITH || (n >= 1024 && (end + 63) / 64 + 8 <= T64));
+    if (cut) {
       uint32_t* const shared = (uint32_t*)(lds_bias + 256);   // [0] largest |k|, [1] largest |v| (bits), [2] a wavefront refuses
       if (tid < 3) shared[tid] = 0;
-      top_bias = row_max64(top_bias);
       uint32_t kbits = 0, vbits = 0;   // pairs of magnitudes as 16-bit integers (an infinity or a NaN is above all others)
       typedef unsigned short us2 __attribute__((ext_vector_type(2)));
       auto grow = [](uint32_t& m, uint4 x) {
@@ -2941,132 +3062,57 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         }
       if (!__all(nothing)) shared[2] = 1;
       __syncthreads();
-      if (shared[2] == 0) {
+      if (__builtin_amdgcn_readfirstlane(shared[2]) == 0) {
         nk = end;
         T64 = (end + 63) >> 6;
+      } else if (!WITH) {
+        return false;
       }
     }
   }
 
-  const bool rotate_prio = ROTATE && NQB == 1 && T64 >= 64;
-  int wslot = 0;
-  if (rotate_prio) {
-    unsigned hw_id;
-    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw_id));
-    wslot = (int)(hw_id & 15u);  // wave slot within the SIMD
-  }
-
-  // One iteration = the 64 keys of tile t.  Units (key block 2t + u, query block qb) in the order (0,0) .. (0,NQB-1), (1,0) ..:
-  // the vector ALU turns the unit's scores (s_cur) into probabilities while the matrix cores form the NEXT unit's scores
-  // and add the P.V of the same unit of the PREVIOUS tile.  k1, k2: LDS blocks 2t + 1, 2t + 2 of K; v1, v2: 2t - 2, 2t - 1 of V.
-  auto iter = [&](auto FIRSTc, auto LASTc, int t, const uint16_t* k1, const uint16_t* k2, const uint16_t* v1, const uint16_t* v2,
-                  const float* b0, const float* b1, const float* b2) {
-    constexpr bool FIRST = decltype(FIRSTc)::value, LAST = decltype(LASTc)::value;
-    auto unit = [&](auto Uc, auto QBc, typename M::Scores& s_cur, typename M::Scores& s_nxt) {
-      constexpr int U = decltype(Uc)::value, QB = decltype(QBc)::value;
-      constexpr int NQ = (QB + 1) % NQB;
-      constexpr bool NEXT = !(LAST && U == 1 && NQ == 0);     // there is a next unit
-      const float* bnext = NQ != 0 ? (U == 0 ? b0 : b1) : (U == 0 ? b1 : b2);   // bias of the next unit's key block
-      if (NQ == 0 && NEXT) load_ka(U == 0 ? k1 : k2, bnext);
-      if (QB == 0 && !FIRST) {
-#pragma unroll
-        for (int x = 0; x < FR; ++x) va[x] = m.v_frag(U == 0 ? v1 : v2, x);
-      }
-      if (NEXT) score_init(s_nxt, bnext);
-      // score products alternate with output products; Tile32: those whose operands the unit has yet to read from LDS come
-      // a step later (0.5 - 1.2 % of the bf16 calls; Tile16, with twice the steps, lost 0.5 - 1 % by it)
-      constexpr int LATE_S = M::kLateStep && NQ == 0 && NQB == 2 ? 1 : 0, LATE_O = M::kLateStep && !LATE_S ? 1 : 0;
-#pragma unroll
-      for (int i = 0; i <= M::STEPS; ++i) {
-        if (NEXT && !LATE_S && i < M::STEPS) M::score_step(s_nxt, ka, q[NQ], i);
-        if (!FIRST && i >= LATE_O && i - LATE_O < M::STEPS) M::out_step(o[QB], va, p[QB][U], i - LATE_O);
-        if (NEXT && LATE_S && i > 0) M::score_step(s_nxt, ka, q[NQ], i - 1);
-      }
-      if (NEXT) score_end(s_nxt);
-      const uint32_t vis = LAST ? m.visible(2 * t + U, nk) : 0xFFFFu;
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) softmax(s_cur, -mc[QB][qt], QB, U, qt, LAST, vis);
-      // Units moved into each other cost registers (the variants with a bias or a rotation spill), and Tile32 1 % of its time;
-      // Tile16 gains 1 - 2 % by it (8K 12 x 64 179 -> 176 us), 7 x 542 2 %.
-      if (M::COLS == 32 || BIAS || ROPE) __builtin_amdgcn_sched_barrier(0);
-    };
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    if constexpr (NQB == 1) {
-      unit(I0{}, I0{}, sA, sB);
-      unit(I1{}, I0{}, sB, sA);
-    } else {
-      unit(I0{}, I0{}, sA, sB);
-      unit(I0{}, I1{}, sB, sA);
-      unit(I1{}, I0{}, sA, sB);
-      unit(I1{}, I1{}, sB, sA);
-    }
-  };
-  // the tile's operands have landed, in every wavefront's share
-  auto landed = [&](int t) {
-    if (BIAS && wave == 0) lds_bias[(64 * t + 32 + lane) & 255] = bst;
-    wait_direct_loads();
-    __syncthreads();
-    if (ROPE) {
-      if (AHEAD) {
-        if (rot_there(0, TILE_UNITS)) rotate_unit(2 * t + 1, 0, ahead);
-      } else {
-#pragma unroll
-        for (int x = 0; x * THREADS < TILE_UNITS; ++x) {
-          if (!rot_there(x, TILE_UNITS)) continue;
-          Angles now;
-          load_angles(2 * t + 1, x, now);
-          rotate_unit(2 * t + 1, x, now);
+  int t = 0;
+    if (T64 > 1) {
+      if (wave_has_rows) iter(WITHc, Yes{}, No{}, 0, kops(1), kops(2), nullptr, nullptr, bblk(0), bblk(1), bblk(2));
+      auto steady = [&](auto ODDc, int t) {
+        constexpr int ODD = decltype(ODDc)::value;   // t & 1: ring slots are compile-time constants
+        if (rotate_prio) {
+          const int ph = (t + wslot) % 3;
+          if (ph == 0) __builtin_amdgcn_s_setprio(2);
+          else if (ph == 1) __builtin_amdgcn_s_setprio(1);
+          else __builtin_amdgcn_s_setprio(0);
+        }
+        landed(WITHc, t);
+        request(WITHc, t);
+        if (wave_has_rows) {
+          settle(WITHc, t - 1, false);
+          const uint16_t* k1 = kring + 2 * (1 - ODD) * kBlk;   // kops(2 t + 1)
+          iter(WITHc, No{}, No{}, t, k1, k1 + kBlk, vblk(2 * ODD - 2), vblk(2 * ODD - 1), bblk(2 * t), bblk(2 * t + 1), bblk(2 * t + 2));
+        }
+      };
+      t = 1;
+      while (t + 1 < T64) {
+        steady(std::integral_constant<int, 1>{}, t);
+        if (++t + 1 >= T64) break;
+        steady(std::integral_constant<int, 0>{}, t);
+        ++t;
+        if (KN == 8) {
+          m.flip();
+          khalf ^= 4 * kBlk;
         }
       }
-      __syncthreads();
-    }
-  };
-  auto bblk = [&](int b) { return lds_bias + (BIAS ? (b & 7) * 32 : 0); };
-  using No = std::false_type;
-  using Yes = std::true_type;
-  int t = 0;
-  if (T64 > 1) {
-    if (wave_has_rows) iter(Yes{}, No{}, 0, kops(1), kops(2), nullptr, nullptr, bblk(0), bblk(1), bblk(2));
-    auto steady = [&](auto ODDc, int t) {
-      constexpr int ODD = decltype(ODDc)::value;   // t & 1: ring slots are compile-time constants
-      if (rotate_prio) {
-        const int ph = (t + wslot) % 3;
-        if (ph == 0) __builtin_amdgcn_s_setprio(2);
-        else if (ph == 1) __builtin_amdgcn_s_setprio(1);
-        else __builtin_amdgcn_s_setprio(0);
-      }
-      landed(t);
-      request(t);
+      if (rotate_prio) __builtin_amdgcn_s_setprio(0);
+      if (!decltype(WITHc)::value) m.place(lane_now());
+      // t = T64 - 1: the last tile, masked
+      landed(WITHc, t);
+      request(WITHc, t);
       if (wave_has_rows) {
-        settle(t - 1, false);
-        const uint16_t* k1 = kring + 2 * (1 - ODD) * kBlk;   // kops(2 t + 1)
-        iter(No{}, No{}, t, k1, k1 + kBlk, vblk(2 * ODD - 2), vblk(2 * ODD - 1), bblk(2 * t), bblk(2 * t + 1), bblk(2 * t + 2));
+        settle(WITHc, t - 1, false);
+        iter(WITHc, No{}, Yes{}, t, kops(2 * t + 1), nullptr, vblk(2 * t - 2), vblk(2 * t - 1), bblk(2 * t), bblk(2 * t + 1), nullptr);
       }
-    };
-    t = 1;
-    while (t + 1 < T64) {
-      steady(std::integral_constant<int, 1>{}, t);
-      if (++t + 1 >= T64) break;
-      steady(std::integral_constant<int, 0>{}, t);
-      ++t;
-      if (KN == 8) {
-        m.flip();
-        khalf ^= 4 * kBlk;
-      }
+    } else {
+      if (wave_has_rows) iter(WITHc, Yes{}, Yes{}, 0, kops(1), nullptr, nullptr, nullptr, bblk(0), bblk(1), nullptr);
     }
-    if (rotate_prio) __builtin_amdgcn_s_setprio(0);
-    if (!BIAS) m.place(lane_now());
-    // t = T64 - 1: the last tile, masked
-    landed(t);
-    request(t);
-    if (wave_has_rows) {
-      settle(t - 1, false);
-      iter(No{}, Yes{}, t, kops(2 * t + 1), nullptr, vblk(2 * t - 2), vblk(2 * t - 1), bblk(2 * t), bblk(2 * t + 1), nullptr);
-    }
-  } else {
-    if (wave_has_rows) iter(Yes{}, Yes{}, 0, kops(1), nullptr, nullptr, nullptr, bblk(0), bblk(1), nullptr);
-  }
   // ---- drain: V of the last tile; rows at or beyond nk are overwritten with zeros by the lanes that fetched them
   // (0 * whatever is stored in the padding must be 0)
   wait_direct_loads();
@@ -3085,7 +3131,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   }
   __syncthreads();
   if (wave_has_rows) {
-    settle(t, true);
+    settle(WITHc, t, true);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
 #pragma unroll
@@ -3129,6 +3175,25 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       }
     }
   }
+  return true;
+  };
+  if constexpr (PLAIN_LOOP) {
+    if (plain) {
+      if (tiles(No{})) return;
+      // the padding counts after all: from the start
+      wait_direct_loads();
+      __syncthreads();
+      kreq = kp + 3 * k32;
+      vreq = vp;
+      end = n;
+      first_fetch();
+      wait_direct_loads();
+      __syncthreads();
+    }
+    tiles(Yes{});
+  } else {
+    tiles(std::integral_constant<bool, BIAS>{});
+  }
 }
 
 template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false, class M = typename GlobalTile<T, D>::type>
@@ -3137,7 +3202,7 @@ template <class T, int D, int NQB, int NW, bool BIAS = false, bool ROPE = false,
 // three: 8K bf16 272 -> 247, 16 x 700 46.6 -> 43.3, with a bias 59.8 -> 51.2.)
 __global__ __launch_bounds__(NW * 64, NW == 4 ? (D == 64 && NQB == 1 ? 3 : D == 32 ? (NQB == 1 ? 4 : (BIAS ? 2 : 3)) : 2) : 1) void fa_fwd_global_kernel(const FaKernelArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[GlobalLds<D, NW>::kElems];
-  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 260 : 4];  // ring of eight key blocks, bias / |scale|; three words of the pass over padding
+  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? 276 : 4];  // ring of eight key blocks, bias / |scale|; words of the pass over padding and of the search for it
   TileCoord tc;
   if (!locate_tile<NW * 32 * NQB, false, false, true>(a, tc)) return;
   global_body<T, D, NQB, NW, BIAS, true, ROPE, M>(a, tc, lds, lds_bias);

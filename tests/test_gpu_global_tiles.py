@@ -179,3 +179,34 @@ def test_long_excluded_prefixes(head_dim, heads, dtype, tuning):
     o, lse = run_ex(q, k, v, None, dtype, scale, tuning=tuning, key_bias=bias)
     assert (o[-1] == 0).all() and np.isneginf(lse[-1]).all()
     check_against(o[:, -1:], lse[:, -1:], o_ref, lse_ref, None, dtype, relative=True)
+
+
+@pytest.mark.parametrize("kind", ["zeros", "tail", "tail_and_hole", "tail_and_bias", "first_key_biased"])
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256], ids=["128", "256"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+def test_bias_of_zeros_but_for_padding(head_dim, dtype, tuning, kind):
+    """Calls whose bias is zeros and padding run a loop without a bias, others one with; every tile refreshes some rows.  Zeros of
+    either sign give the bits of a call without a bias (head_dim 32 sums other values then)."""
+    n, ends = 1100, [1100, 1099, 700, 641]
+    q, k, v = one_jump_per_row(head_dim, dtype, n, ends, 1)
+    bias = np.zeros((len(ends), n), dtype=np.float32)
+    bias[:, 1::2] = -0.0
+    if kind != "zeros":
+        for b, end in enumerate(ends):
+            bias[b, end:] = -65504.0
+        bias = round_to_storage(bias, dtype)
+    if kind == "tail_and_hole":
+        bias[:, 300:340] = -np.inf
+    if kind == "tail_and_bias":
+        bias[:, 600] = 1.5
+    if kind == "first_key_biased":
+        bias[:, 0] = -2.0
+    scale = 1.0 / np.sqrt(head_dim)
+    o_ref, lse_ref = attention_oracle(q, k, v, None, scale, -1, -1, key_bias=bias)
+    o, lse = run_ex(q, k, v, None, dtype, scale, tuning=tuning, key_bias=bias)
+    check_against(o, lse, o_ref, lse_ref, None, dtype, relative=True)
+    if kind == "zeros" and head_dim != 32:
+        # (head_dim 128 with a bias has 128-row tiles only)
+        o0, lse0 = run_ex(q, k, v, None, dtype, scale, tuning=fa.FA_TUNE_BM_128 if head_dim == 128 else tuning)
+        assert np.array_equal(o, o0) and np.array_equal(lse, lse0)
