@@ -42,6 +42,7 @@
 //   fa_fwd_window_resident_kernel  local layers whose key range per query tile fits in
 //       LDS (the paper's 63/64 window): everything is requested at once, then each
 //       wavefront runs the same pipeline over the blocks its queries can see.
+//   fa_fwd_window_split_kernel  the smallest local layers: 32 query rows per workgroup, a wavefront per key block.
 //   fa_fwd_window_kernel  wider or one-sided windows: ring of 32-key stages.
 //   fa_fwd_split_kernel  global layers with so few query tiles that the kernels above would leave
 //       SIMDs with one wavefront or none (a single request, a few short sequences): NQ query
@@ -2158,6 +2159,189 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
 }
 
 // ======================================================================================
+// Split window kernel: local layers so small that a wavefront per key block fits the chip.  A workgroup is 32 query rows
+// and kTwoPhaseBlocks wavefronts; wavefront g has the g-th of the key blocks that these rows can see (the paper's 63/64 window:
+// five): one block's scores, an ordinary softmax over them, one block's P.V, and the partial results meet in LDS.
+// Bound: latency, the chain launch - arguments - loads - a block - merge - store.  So everything is requested at once by direct
+// loads, the sequence length is looked at after that, and a lane stores its eight bytes of a row as they are: the detour
+// through a patch for whole rows costs a barrier and a trip through LDS.  (A copy of Q per wavefront instead of one behind a
+// barrier is no faster, and its LDS halves the calls that fit a round.)  12 x 64, 487 tokens, us: the resident kernel 6.9, this
+// 4.6 (back to back; the host takes 5.3 for a call).
+// ======================================================================================
+template <class T, int D, bool BIAS>
+__global__ __launch_bounds__(kTwoPhaseBlocks * 64, D == 128 ? 1 : 2) void fa_fwd_window_split_kernel(const FaKernelArgs a) {
+  constexpr int NK = kTwoPhaseBlocks, THREADS = NK * 64, BM = 32;
+  constexpr int KS = D / 16, DB = D / 32, kBlk = 32 * D;
+  constexpr int CH = D / 8, RPL = 64 / CH, LPB = 32 / RPL;   // 16-byte chunks per row, rows per load, loads per block
+  constexpr bool BIAS_LAST = BIAS && D != 64;                // as in the two-phase kernel
+  // the Q block, then per wavefront its K and V block, which become its accumulator, [4 x column block + quad][lane] float4
+  static_assert(2 * kBlk * 2 == 4 * DB * 64 * 16, "an accumulator takes the place of K and V");
+  __shared__ __attribute__((aligned(16))) uint16_t lds[(2 * NK + 1) * kBlk];
+  __shared__ __attribute__((aligned(16))) float lds_state[NK][2][64];   // reference times c, row sum
+  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? NK : 1][32];
+
+  TileCoord tc;
+  if (!locate_tile<BM, false>(a, tc)) return;   // tc.n still as loaded: see below
+  const int N = a.max_len, q0 = tc.q0;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
+
+  const uint16_t* qp = (const uint16_t*)a.q + tc.b * a.qs[0] + tc.h * a.qs[1];
+  const uint16_t* kp = (const uint16_t*)a.k + tc.b * a.ks[0] + tc.h * a.ks[1];
+  const uint16_t* vp = (const uint16_t*)a.v + tc.b * a.vs[0] + tc.h * a.vs[1];
+  uint16_t* op = (uint16_t*)a.o + tc.b * a.os[0] + tc.h * a.os[1];
+  float* lsep = a.lse ? a.lse + ((int64_t)tc.b * a.heads + tc.h) * N : nullptr;
+
+  // a side without a limit reaches past the tensor
+  const int wl = a.wl < 0 ? N : a.wl, wr = a.wr < 0 ? N : a.wr;
+  const int blk = (q0 - wl > 0 ? (q0 - wl) >> 5 : 0) + g, kb0 = 32 * blk;   // the wavefront's key block
+  const bool there = kb0 < N && kb0 <= q0 + BM - 1 + wr;
+  uint16_t *const ql = lds, *const kl = lds + (2 * g + 1) * kBlk, *const vl = kl + kBlk;
+  // 32 rows from `first` on; rows past the tensor are its last one again (masked, zeroed or never stored)
+  auto load_rows = [&](const uint16_t* base, int64_t rs, int first, bool is_v, uint16_t* dst) {
+    const uint16_t* gb = base + (int64_t)first * rs;
+#pragma unroll
+    for (int x = 0; x < LPB; ++x) {
+      const int r = RPL * x + lane / CH, rc = r < N - 1 - first ? r : N - 1 - first;
+      const int swz = is_v ? v_swz_d<D>(r) : k_swz_d<D>(r);
+      load16_to_lds(gb, 2u * ((uint32_t)rc * (uint32_t)rs + (uint32_t)(((lane % CH) ^ swz) * 8)), dst + RPL * x * D);
+    }
+  };
+#pragma unroll
+  for (int x = 0; x < (LPB + NK - 1) / NK; ++x) {
+    const int part = x * NK + g;
+    if (part < LPB) {
+      const int r = RPL * part + lane / CH, rc = r < N - 1 - q0 ? r : N - 1 - q0;
+      load16_to_lds(qp + (int64_t)q0 * a.qs[2], 2u * ((uint32_t)rc * (uint32_t)a.qs[2] + (uint32_t)(((lane % CH) ^ k_swz_d<D>(r)) * 8)), ql + RPL * part * D);
+    }
+  }
+  if (there) {
+    load_rows(kp, a.ks[2], kb0, false, kl);
+    load_rows(vp, a.vs[2], kb0, true, vl);
+  }
+  float bias = 0.f;   // of key kb0 + lane, lanes 0 .. 31
+  if (BIAS && there) {
+    const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
+    bias = bias_over_scale<T, BIAS_LAST>(a, bp[kb0 + l32 < N ? kb0 + l32 : N - 1]);
+  }
+
+  // only now the sequence length
+  const int n = tc.n < 0 ? 0 : (tc.n > N ? N : tc.n);
+  tc.n = n;
+  if (q0 >= n) {
+    wait_direct_loads();  // the loads write this workgroup's LDS: they must land before it ends
+    zero_fill<BM, D, THREADS>(a, tc, op, lsep);
+    return;
+  }
+  const int ig = q0 + l32, q_last = (q0 + BM < n ? q0 + BM : n) - 1;
+  const bool alive = ig < n;
+  const float c = a.c;
+  RowState<1, D> st;
+  init_state(st);
+  if (BIAS) lds_bias[g][l32] = bias;
+  if (there) wait_vmcnt<LPB>();   // Q and K
+  else wait_direct_loads();
+  __syncthreads();
+  if (there && kb0 < n && kb0 <= q_last + wr) {
+    floatx16 s;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const float4 b4 = BIAS && !BIAS_LAST ? *(const float4*)&lds_bias[g][8 * x + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
+      s[4 * x + 0] = b4.x; s[4 * x + 1] = b4.y; s[4 * x + 2] = b4.z; s[4 * x + 3] = b4.w;
+    }
+    const uint32_t flip = a.negate_q ? 0x80008000u : 0u;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint4 u = __builtin_bit_cast(uint4, load_k_frag_swz_d<T, D>(ql, l32, hh, ks));
+      u.x ^= flip; u.y ^= flip; u.z ^= flip; u.w ^= flip;
+      s = T::mfma(load_k_frag_swz_d<T, D>(kl, l32, hh, ks), as_v8<T>(u), s);
+    }
+    if (BIAS_LAST) add_bias(s, lds_bias[g], hh);
+    // softmax of the block: its maximum is the reference
+    const bool interior = kb0 + 32 <= n && kb0 >= q_last - wl && kb0 + 31 <= q0 + wr;
+    const uint32_t vis = interior ? 0xFFFFu : visible_bits(kb0, hh, ig - wl > 0 ? ig - wl : 0, ig + wr < n - 1 ? ig + wr : n - 1);
+    float t0 = -INFINITY;
+    if (interior) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, s[r]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, keep_or_neg_inf(s[r], vis, r));
+    }
+    const float tmax = max_xor32(t0);
+    st.m_ref[0] = tmax;
+    st.mc[0] = tmax == -INFINITY ? 0.f : tmax * c;   // a row without a visible key here: every p is masked to 0
+    uint32_t pk[8];
+    if (interior) prob_block<T, false, BIAS_LAST>(s, c, st.mc[0], vis, pk, st.lsum[0]);
+    else prob_block<T, true, BIAS_LAST>(s, c, st.mc[0], vis, pk, st.lsum[0]);
+    const typename T::v8 p[2] = {as_v8<T>(make_uint4(pk[0], pk[1], pk[2], pk[3])), as_v8<T>(make_uint4(pk[4], pk[5], pk[6], pk[7]))};
+    wait_direct_loads();   // V; its rows at or beyond n are overwritten with zeros (0 * whatever is stored there must be 0)
+    if (kb0 + 32 > n) {
+#pragma unroll
+      for (int x = 0; x < LPB; ++x) {
+        const int r = RPL * x + lane / CH;
+        if (kb0 + r >= n) *(uint4*)&vl[r * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (other lanes' writes: order for the compiler, no instruction)
+#pragma unroll
+    for (int ks2 = 0; ks2 < 2; ++ks2)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        st.oacc[0][db] = T::mfma(load_vt_frag_swz_d<T, D>(vl, lane, ks2, db), p[ks2], st.oacc[0][db]);
+  } else {
+    wait_direct_loads();   // (before its place is taken)
+  }
+
+  // ---- merge: groups of four output columns of a row, dealt round-robin to the wavefronts
+  constexpr int G = 4 * DB;
+  float4* const part = (float4*)kl + lane;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int x = 0; x < G; ++x) {
+    const int r = 4 * (x % 4);
+    part[x * 64] = make_float4(st.oacc[0][x / 4][r], st.oacc[0][x / 4][r + 1], st.oacc[0][x / 4][r + 2], st.oacc[0][x / 4][r + 3]);
+  }
+  // (the reference goes through as the rounded product the probabilities were formed against; -infinity: none)
+  lds_state[g][0][lane] = st.m_ref[0] == -INFINITY ? -INFINITY : st.mc[0];
+  lds_state[g][1][lane] = st.lsum[0];
+  __syncthreads();
+  float mk[NK], fk[NK], mc_new = -INFINITY, ltot = 0.f;
+#pragma unroll
+  for (int x = 0; x < NK; ++x) {
+    mk[x] = lds_state[x][0][lane];
+    mc_new = fmaxf(mc_new, mk[x]);
+  }
+  if (mc_new == -INFINITY) mc_new = 0.f;
+#pragma unroll
+  for (int x = 0; x < NK; ++x) {
+    // a wavefront that saw no key has nothing accumulated: factor 0, kept away from exp2(+inf)
+    fk[x] = mk[x] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk[x] - mc_new);
+    ltot = __builtin_fmaf(fk[x], lds_state[x][1][lane], ltot);
+  }
+  ltot = sum_xor32(ltot);
+  const bool live = alive && ltot > 0.f;
+  const float inv = live ? 1.0f / ltot : 0.f;
+  for (int x = g; x < G; x += NK) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int y = 0; y < NK; ++y) {
+      const float4 u = ((const float4*)(lds + (2 * y + 1) * kBlk))[x * 64 + lane];
+      v.x = __builtin_fmaf(fk[y], u.x, v.x);
+      v.y = __builtin_fmaf(fk[y], u.y, v.y);
+      v.z = __builtin_fmaf(fk[y], u.z, v.z);
+      v.w = __builtin_fmaf(fk[y], u.w, v.w);
+    }
+    if (ig < N)   // columns 8 x + 4 hh .. + 3
+      *(uint2*)(op + ig * a.os[2] + 8 * x + 4 * hh) =
+          live ? make_uint2(T::pack2(v.x * inv, v.y * inv), T::pack2(v.z * inv, v.w * inv)) : make_uint2(0, 0);
+  }
+  if (lsep && g == 0 && hh == 0 && ig < N) lsep[ig] = live ? (mc_new + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
+}
+
+// ======================================================================================
 // Global kernel: a software pipeline over 64-key tiles
 //
 // A workgroup is NW wavefronts (4; 8 and 12 exist for head_dim 64, 8 for 128) that share one pair of rings of 32-key blocks,
@@ -3319,6 +3503,15 @@ Kernel split_kernel(int head_dim, int split) {
 }
 
 template <class T>
+Kernel window_split_kernel(int head_dim, bool bias) {
+  if (bias)
+    return head_dim == 32 ? fa_fwd_window_split_kernel<T, 32, true>
+                          : (head_dim == 64 ? fa_fwd_window_split_kernel<T, 64, true> : fa_fwd_window_split_kernel<T, 128, true>);
+  return head_dim == 32 ? fa_fwd_window_split_kernel<T, 32, false>
+                        : (head_dim == 64 ? fa_fwd_window_split_kernel<T, 64, false> : fa_fwd_window_split_kernel<T, 128, false>);
+}
+
+template <class T>
 int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stream) {
   unsigned grid = (unsigned)a.total_tiles;
   if (a.map_xcd) grid = 8u * (unsigned)a.xcd_per * (unsigned)a.batch;
@@ -3343,7 +3536,11 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
   // against 7.8 us, 4K equal, 8K 17.3 against 14.9 us, 32K 43 against 37 us); it exists for
   // head_dim 64 only.
   const bool latency_bound = a.head_dim == kD && a.total_tiles <= 384;
-  if (a.split) {
+  if (a.win_split) {
+    kern = window_split_kernel<T>(a.head_dim, a.key_bias != nullptr);
+    threads = 64u * kTwoPhaseBlocks;
+    rows = 32;
+  } else if (a.split) {
     // (the host has checked that this shape exists for the head size)
     kern = a.key_bias ? split_kernel<T, true>(a.head_dim, a.split) : split_kernel<T, false>(a.head_dim, a.split);
     threads = 64u * (unsigned)((a.split >> 4) * (a.split & 15));
