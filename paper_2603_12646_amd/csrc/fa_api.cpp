@@ -188,17 +188,29 @@ int choose_split(const fa_params& p) {
   return 0;
 }
 
-// The split window kernel: windows under which 32 rows see at most five key blocks, where its workgroups (five wavefronts
-// for 32 rows) fit one round.  us, fp16, one sequence, the 128-row kernels -> it: 12 x 64 200 tokens 6.7 -> 4.6, 487 6.9 -> 4.6, 690
-// (264 ids) 6.9 -> 5.0, 1300 (492) 7.05 -> 5.6, but 1600 7.1 -> 7.75; 8 x 128 487 8.6 -> 5.9, 1000 (256) 8.7 -> 6.0, but 1300 8.95 -> 10.0;
-// 24 x 32 487 5.5 -> 4.6, 1000 (768) 5.6 -> 5.3, but 1600 6.2 -> 6.6.
-bool window_split_fits(const fa_params& p, bool bias_can_be_divided) {
-  if ((p.window_left < 0 && p.window_right < 0) || p.rope_cos || (p.key_bias && !bias_can_be_divided)) return false;
+// Shape of the small kernel, 16 * wavefronts + key blocks of each, or 0: calls whose 32-row workgroups see at most as many key
+// blocks as the shape holds, and fit one round of as many workgroups per unit as their LDS allows.  It goes before the kernel
+// that the rules above choose.  us, fp16, the kernels before -> it:
+//   local   12 x 64 200 tokens 6.7 -> 4.6, 487 6.9 -> 4.7, 690 (264 ids) 6.9 -> 5.0, 1300 (492) 7.05 -> 5.6, but 1600 7.1 -> 7.75; 8 x 128 487
+//           8.6 -> 5.9, 1000 (256) 8.7 -> 6.0, but 1300 8.95 -> 10.0; 24 x 32 487 5.5 -> 4.6, 1000 (768) 5.6 -> 5.3, but 1600 6.2 -> 6.6.
+//   global  12 x 64 110 tokens 4.8 -> 4.3, 16 x 128 (768) 6.7 -> 6.2, 200 5.4 -> 4.8, 5 x 250 (480) 6.55 -> 5.9, but 6 x 250 7.6 -> 8.4; 512 6.3 -> 5.5,
+//           but 2 x 384 (288) 7.2 -> 8.9; 8 x 128 110 6.5 -> 5.3, 16 x 128 (512) 8.0 -> 7.4, 256 7.1 -> 5.8, but 5 x 250 (320) 8.4 -> 10.8; 24 x 32 110
+//           4.9 -> 3.8, 8 x 110 (768) 5.1 -> 4.9, but 10 x 128 4.96 -> 5.1; 200 6.2 -> 4.2, 4 x 256 (768) 6.0 -> 5.55, but 5 x 250 6.3 -> 6.6; 512 (384)
+//           6.6 -> 6.1, but 2 x 384 (576) 7.0 -> 7.8.
+int choose_small(const fa_params& p, bool bias_can_be_divided) {
+  if (p.rope_cos || (p.key_bias && !bias_can_be_divided)) return 0;
+  const bool windowed = p.window_left >= 0 || p.window_right >= 0;
   const int64_t n = p.max_len, left = p.window_left < 0 || p.window_left > n ? n : p.window_left,
                 right = p.window_right < 0 || p.window_right > n ? n : p.window_right;
-  const int64_t all = (n + 31) / 32, seen = (31 + right) / 32 + (left + 31) / 32 + 1;
-  if ((seen < all ? seen : all) > 5) return false;
-  return (all * p.heads + 7) / 8 * 8 * p.batch <= (p.head_dim == 128 ? 256 : (p.head_dim == 64 ? 512 : 768));
+  const int64_t all = (n + 31) / 32, window = (31 + right) / 32 + (left + 31) / 32 + 1, seen = window < all ? window : all;
+  const int64_t ids = (all * p.heads + 7) / 8 * 8 * p.batch;
+  const int d = p.head_dim == 32 ? 0 : (p.head_dim == 64 ? 1 : 2);
+  // most ids per shape and head size
+  static constexpr int k41[3] = {768, 768, 512}, k42[3] = {768, 512, 256}, k51[3] = {768, 512, 256}, k82[3] = {384, 256, 0};
+  if (windowed) return seen <= 5 && ids <= k51[d] ? 0x51 : 0;
+  if (seen <= 4) return ids <= k41[d] ? 0x41 : 0;
+  if (seen <= 8) return ids <= k42[d] ? 0x42 : 0;
+  return seen <= 16 && ids <= k82[d] ? 0x82 : 0;
 }
 
 }  // namespace
@@ -349,8 +361,8 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
     if (t_bm == FA_TUNE_BM_32 && p->head_dim == 64 && !p->key_bias) split = 0x18;
     if (split) bm = 32 * (split >> 4);
   }
-  const bool win_split = window_split_fits(*p, bias_can_be_divided) && t_bm == FA_TUNE_BM_AUTO && t_v != FA_TUNE_V_SCALAR && (p->tuning & 0xF000u) == 0;
-  if (win_split) bm = 32;
+  int small = 0;
+  if (t_bm == FA_TUNE_BM_AUTO && t_v != FA_TUNE_V_SCALAR && (p->tuning & 0xF000u) == 0) small = choose_small(*p, bias_can_be_divided);
   const int tile_rows = bm == 0 ? 128 : bm;   // (the mixed launch sizes its own grid)
   const int64_t n_qtiles = ((int64_t)p->max_len + tile_rows - 1) / tile_rows;
   const int64_t total = n_qtiles * p->batch * p->heads;
@@ -401,7 +413,7 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   if (8 * per * p->batch > 0x7FFFFFF0LL) return FA_ERR_BAD_SHAPE;
   a.xcd_per = (int32_t)per;
   a.split = split;
-  a.win_split = win_split;
+  a.small = small;
   // (a launch of at most two workgroups per unit has nothing else to hide the read of the sequence length behind)
   a.late_n = total <= 512;
   a.mix_ids_a = bm == 0 ? fa_mix_ids((int)n_qtiles, p->heads) : 0;

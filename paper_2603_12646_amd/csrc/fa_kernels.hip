@@ -42,7 +42,7 @@
 //   fa_fwd_window_resident_kernel  local layers whose key range per query tile fits in
 //       LDS (the paper's 63/64 window): everything is requested at once, then each
 //       wavefront runs the same pipeline over the blocks its queries can see.
-//   fa_fwd_window_split_kernel  the smallest local layers: 32 query rows per workgroup, a wavefront per key block.
+//   fa_fwd_small_kernel  the smallest calls, local and global: 32 query rows per workgroup, whose wavefronts hold all key blocks.
 //   fa_fwd_window_kernel  wider or one-sided windows: ring of 32-key stages.
 //   fa_fwd_split_kernel  global layers with so few query tiles that the kernels above would leave
 //       SIMDs with one wavefront or none (a single request, a few short sequences): NQ query
@@ -2159,26 +2159,29 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
 }
 
 // ======================================================================================
-// Split window kernel: local layers so small that a wavefront per key block fits the chip.  A workgroup is 32 query rows
-// and kTwoPhaseBlocks wavefronts; wavefront g has the g-th of the key blocks that these rows can see (the paper's 63/64 window:
-// five): one block's scores, an ordinary softmax over them, one block's P.V, and the partial results meet in LDS.
-// Bound: latency, the chain launch - arguments - loads - a block - merge - store.  So everything is requested at once by direct
-// loads, the sequence length is looked at after that, and a lane stores its eight bytes of a row as they are: the detour
-// through a patch for whole rows costs a barrier and a trip through LDS.  (A copy of Q per wavefront instead of one behind a
-// barrier is no faster, and its LDS halves the calls that fit a round.)  12 x 64, 487 tokens, us: the resident kernel 6.9, this
-// 4.6 (back to back; the host takes 5.3 for a call).
+// Small kernel: the smallest calls, local and global, where 32-row workgroups whose wavefronts hold all their key blocks at
+// once fit the chip.  Wavefront g of NK has the blocks g, g + NK, .. of those that the workgroup's 32 rows can see, NB at
+// most: their scores, an ordinary softmax over them, their P.V; the partial results meet in LDS.  (The paper's 63/64 window:
+// five wavefronts, one block each.)
+// Bound: latency, the chain launch - arguments - loads - blocks - merge - store.  So everything is requested at once by direct
+// loads, the sequence length is looked at after that, there is no running reference, and a lane stores its eight bytes of a
+// row as they are: the detour through a patch for whole rows costs a barrier and a trip through LDS.  (A copy of Q per
+// wavefront instead of one behind a barrier is no faster, and its LDS halves the calls that fit a round.)  12 x 64, us, back to back
+// (the host takes 5.3 for a call): local 487 tokens 6.9 on the resident kernel -> 4.7, global 512 6.3 on
+// the split kernel -> 5.5 (one block on each of sixteen wavefronts: 6.4, twice the partial results).
 // ======================================================================================
-template <class T, int D, bool BIAS>
-__global__ __launch_bounds__(kTwoPhaseBlocks * 64, D == 128 ? 1 : 2) void fa_fwd_window_split_kernel(const FaKernelArgs a) {
-  constexpr int NK = kTwoPhaseBlocks, THREADS = NK * 64, BM = 32;
+template <class T, int D, int NK, int NB, bool BIAS>
+__global__ __launch_bounds__(NK * 64, 1) void fa_fwd_small_kernel(const FaKernelArgs a) {
+  constexpr int THREADS = NK * 64, BM = 32;
   constexpr int KS = D / 16, DB = D / 32, kBlk = 32 * D;
   constexpr int CH = D / 8, RPL = 64 / CH, LPB = 32 / RPL;   // 16-byte chunks per row, rows per load, loads per block
   constexpr bool BIAS_LAST = BIAS && D != 64;                // as in the two-phase kernel
-  // the Q block, then per wavefront its K and V block, which become its accumulator, [4 x column block + quad][lane] float4
-  static_assert(2 * kBlk * 2 == 4 * DB * 64 * 16, "an accumulator takes the place of K and V");
-  __shared__ __attribute__((aligned(16))) uint16_t lds[(2 * NK + 1) * kBlk];
+  // the Q block, then per wavefront its K and V blocks, which become its accumulator, [4 x column block + quad][lane] float4
+  constexpr int kWave = 2 * NB * kBlk;
+  static_assert(kWave * 2 >= 4 * DB * 64 * 16, "an accumulator takes the place of K and V");
+  __shared__ __attribute__((aligned(16))) uint16_t lds[kBlk + NK * kWave];
   __shared__ __attribute__((aligned(16))) float lds_state[NK][2][64];   // reference times c, row sum
-  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? NK : 1][32];
+  __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? NK * NB : 1][32];
 
   TileCoord tc;
   if (!locate_tile<BM, false>(a, tc)) return;   // tc.n still as loaded: see below
@@ -2196,35 +2199,40 @@ __global__ __launch_bounds__(kTwoPhaseBlocks * 64, D == 128 ? 1 : 2) void fa_fwd
 
   // a side without a limit reaches past the tensor
   const int wl = a.wl < 0 ? N : a.wl, wr = a.wr < 0 ? N : a.wr;
-  const int blk = (q0 - wl > 0 ? (q0 - wl) >> 5 : 0) + g, kb0 = 32 * blk;   // the wavefront's key block
-  const bool there = kb0 < N && kb0 <= q0 + BM - 1 + wr;
-  uint16_t *const ql = lds, *const kl = lds + (2 * g + 1) * kBlk, *const vl = kl + kBlk;
-  // 32 rows from `first` on; rows past the tensor are its last one again (masked, zeroed or never stored)
-  auto load_rows = [&](const uint16_t* base, int64_t rs, int first, bool is_v, uint16_t* dst) {
-    const uint16_t* gb = base + (int64_t)first * rs;
-#pragma unroll
-    for (int x = 0; x < LPB; ++x) {
-      const int r = RPL * x + lane / CH, rc = r < N - 1 - first ? r : N - 1 - first;
-      const int swz = is_v ? v_swz_d<D>(r) : k_swz_d<D>(r);
-      load16_to_lds(gb, 2u * ((uint32_t)rc * (uint32_t)rs + (uint32_t)(((lane % CH) ^ swz) * 8)), dst + RPL * x * D);
-    }
+  const int key0 = 32 * ((q0 - wl > 0 ? (q0 - wl) >> 5 : 0) + g);   // the wavefront's first block; the next NK blocks on
+  auto first_key = [&](int i) { return key0 + 32 * NK * i; };
+  // loads of x = 0 .. LPB - 1 of the 32 rows from `first` on; rows past the tensor are its last one again (masked, zeroed or
+  // never stored)
+  auto load_part = [&](const uint16_t* base, int64_t rs, int first, bool is_v, int x, uint16_t* dst) {
+    const int r = RPL * x + lane / CH, rc = r < N - 1 - first ? r : N - 1 - first;
+    const int swz = is_v ? v_swz_d<D>(r) : k_swz_d<D>(r);
+    load16_to_lds(base + (int64_t)first * rs, 2u * ((uint32_t)rc * (uint32_t)rs + (uint32_t)(((lane % CH) ^ swz) * 8)), dst + RPL * x * D);
   };
+  uint16_t *const kl = lds + kBlk + g * kWave, *const vl = kl + NB * kBlk;
 #pragma unroll
-  for (int x = 0; x < (LPB + NK - 1) / NK; ++x) {
-    const int part = x * NK + g;
-    if (part < LPB) {
-      const int r = RPL * part + lane / CH, rc = r < N - 1 - q0 ? r : N - 1 - q0;
-      load16_to_lds(qp + (int64_t)q0 * a.qs[2], 2u * ((uint32_t)rc * (uint32_t)a.qs[2] + (uint32_t)(((lane % CH) ^ k_swz_d<D>(r)) * 8)), ql + RPL * part * D);
+  for (int x = 0; x < (LPB + NK - 1) / NK; ++x)
+    if (x * NK + g < LPB) load_part(qp, a.qs[2], q0, false, x * NK + g, lds);
+  int there = 0;   // blocks that the tensor has
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    if (first_key(i) < N && first_key(i) <= q0 + BM - 1 + wr) {
+      there = i + 1;
+#pragma unroll
+      for (int x = 0; x < LPB; ++x) load_part(kp, a.ks[2], first_key(i), false, x, kl + i * kBlk);
     }
   }
-  if (there) {
-    load_rows(kp, a.ks[2], kb0, false, kl);
-    load_rows(vp, a.vs[2], kb0, true, vl);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    if (i < there) {
+#pragma unroll
+      for (int x = 0; x < LPB; ++x) load_part(vp, a.vs[2], first_key(i), true, x, vl + i * kBlk);
+    }
   }
-  float bias = 0.f;   // of key kb0 + lane, lanes 0 .. 31
-  if (BIAS && there) {
+  float bias[NB];   // of key first_key(i) + lane, lanes 0 .. 31
+  if (BIAS) {
     const uint16_t* bp = (const uint16_t*)a.key_bias + tc.b * a.kb_stride;
-    bias = bias_over_scale<T, BIAS_LAST>(a, bp[kb0 + l32 < N ? kb0 + l32 : N - 1]);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) bias[i] = bias_over_scale<T, BIAS_LAST>(a, bp[first_key(i) + l32 < N ? first_key(i) + l32 : N - 1]);
   }
 
   // only now the sequence length
@@ -2238,61 +2246,96 @@ __global__ __launch_bounds__(kTwoPhaseBlocks * 64, D == 128 ? 1 : 2) void fa_fwd
   const int ig = q0 + l32, q_last = (q0 + BM < n ? q0 + BM : n) - 1;
   const bool alive = ig < n;
   const float c = a.c;
-  RowState<1, D> st;
-  init_state(st);
-  if (BIAS) lds_bias[g][l32] = bias;
-  if (there) wait_vmcnt<LPB>();   // Q and K
+  if (BIAS) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) lds_bias[g * NB + i][l32] = bias[i];
+  }
+  // Q and K have landed
+  if (NB == 2 && there == 2) wait_vmcnt<2 * LPB>();
+  else if (there == 1) wait_vmcnt<LPB>();
   else wait_direct_loads();
   __syncthreads();
-  if (there && kb0 < n && kb0 <= q_last + wr) {
-    floatx16 s;
+  int cnt = 0;   // blocks with keys that the rows see
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const float4 b4 = BIAS && !BIAS_LAST ? *(const float4*)&lds_bias[g][8 * x + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
-      s[4 * x + 0] = b4.x; s[4 * x + 1] = b4.y; s[4 * x + 2] = b4.z; s[4 * x + 3] = b4.w;
-    }
+  for (int i = 0; i < NB; ++i)
+    if (first_key(i) < n && first_key(i) <= q_last + wr) cnt = i + 1;
+  RowState<1, D> st;
+  init_state(st);
+  if (cnt > 0) {
+    typename T::v8 q[KS];
     const uint32_t flip = a.negate_q ? 0x80008000u : 0u;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      uint4 u = __builtin_bit_cast(uint4, load_k_frag_swz_d<T, D>(ql, l32, hh, ks));
+      uint4 u = __builtin_bit_cast(uint4, load_k_frag_swz_d<T, D>(lds, l32, hh, ks));
       u.x ^= flip; u.y ^= flip; u.z ^= flip; u.w ^= flip;
-      s = T::mfma(load_k_frag_swz_d<T, D>(kl, l32, hh, ks), as_v8<T>(u), s);
+      q[ks] = as_v8<T>(u);
     }
-    if (BIAS_LAST) add_bias(s, lds_bias[g], hh);
-    // softmax of the block: its maximum is the reference
-    const bool interior = kb0 + 32 <= n && kb0 >= q_last - wl && kb0 + 31 <= q0 + wr;
-    const uint32_t vis = interior ? 0xFFFFu : visible_bits(kb0, hh, ig - wl > 0 ? ig - wl : 0, ig + wr < n - 1 ? ig + wr : n - 1);
+    floatx16 s[NB];   // set and used for i < cnt only
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (i >= cnt) continue;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const float4 b4 = BIAS && !BIAS_LAST ? *(const float4*)&lds_bias[g * NB + i][8 * x + 4 * hh] : make_float4(0.f, 0.f, 0.f, 0.f);
+        s[i][4 * x + 0] = b4.x; s[i][4 * x + 1] = b4.y; s[i][4 * x + 2] = b4.z; s[i][4 * x + 3] = b4.w;
+      }
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) s[i] = T::mfma(load_k_frag_swz_d<T, D>(kl + i * kBlk, l32, hh, ks), q[ks], s[i]);
+      if (BIAS_LAST) add_bias(s[i], lds_bias[g * NB + i], hh);
+    }
+    // softmax over the blocks: their maximum is the reference
+    uint32_t vis[NB];
     float t0 = -INFINITY;
-    if (interior) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, s[r]);
-    } else {
+    for (int i = 0; i < NB; ++i) {
+      if (i >= cnt) continue;
+      const int kb0 = first_key(i);
+      if (kb0 + 32 <= n && kb0 >= q_last - wl && kb0 + 31 <= q0 + wr) {   // all rows see all keys
+        vis[i] = 0xFFFFu;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, keep_or_neg_inf(s[r], vis, r));
+        for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, s[i][r]);
+      } else {
+        vis[i] = visible_bits(kb0, hh, ig - wl > 0 ? ig - wl : 0, ig + wr < n - 1 ? ig + wr : n - 1);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t0 = fmaxf(t0, keep_or_neg_inf(s[i][r], vis[i], r));
+      }
     }
     const float tmax = max_xor32(t0);
     st.m_ref[0] = tmax;
     st.mc[0] = tmax == -INFINITY ? 0.f : tmax * c;   // a row without a visible key here: every p is masked to 0
-    uint32_t pk[8];
-    if (interior) prob_block<T, false, BIAS_LAST>(s, c, st.mc[0], vis, pk, st.lsum[0]);
-    else prob_block<T, true, BIAS_LAST>(s, c, st.mc[0], vis, pk, st.lsum[0]);
-    const typename T::v8 p[2] = {as_v8<T>(make_uint4(pk[0], pk[1], pk[2], pk[3])), as_v8<T>(make_uint4(pk[4], pk[5], pk[6], pk[7]))};
-    wait_direct_loads();   // V; its rows at or beyond n are overwritten with zeros (0 * whatever is stored there must be 0)
-    if (kb0 + 32 > n) {
+    typename T::v8 p[NB][2];
 #pragma unroll
-      for (int x = 0; x < LPB; ++x) {
-        const int r = RPL * x + lane / CH;
-        if (kb0 + r >= n) *(uint4*)&vl[r * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
-      }
+    for (int i = 0; i < NB; ++i) {
+      if (i >= cnt) continue;
+      const int kb0 = first_key(i);
+      uint32_t pk[8];
+      float blk;
+      if (kb0 + 32 <= n && kb0 >= q_last - wl && kb0 + 31 <= q0 + wr) prob_block<T, false, BIAS_LAST>(s[i], c, st.mc[0], vis[i], pk, blk);
+      else prob_block<T, true, BIAS_LAST>(s[i], c, st.mc[0], vis[i], pk, blk);
+      st.lsum[0] += blk;
+      p[i][0] = as_v8<T>(make_uint4(pk[0], pk[1], pk[2], pk[3]));
+      p[i][1] = as_v8<T>(make_uint4(pk[4], pk[5], pk[6], pk[7]));
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (other lanes' writes: order for the compiler, no instruction)
+    wait_direct_loads();   // V; its rows at or beyond n are overwritten with zeros (0 * whatever is stored there must be 0)
 #pragma unroll
-    for (int ks2 = 0; ks2 < 2; ++ks2)
+    for (int i = 0; i < NB; ++i) {
+      if (i >= cnt) continue;
+      if (first_key(i) + 32 > n) {
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-        st.oacc[0][db] = T::mfma(load_vt_frag_swz_d<T, D>(vl, lane, ks2, db), p[ks2], st.oacc[0][db]);
+        for (int x = 0; x < LPB; ++x) {
+          const int r = RPL * x + lane / CH;
+          if (first_key(i) + r >= n) *(uint4*)&vl[i * kBlk + r * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (other lanes' writes: order for the compiler, no instruction)
+#pragma unroll
+      for (int ks2 = 0; ks2 < 2; ++ks2)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          st.oacc[0][db] = T::mfma(load_vt_frag_swz_d<T, D>(vl + i * kBlk, lane, ks2, db), p[i][ks2], st.oacc[0][db]);
+    }
   } else {
-    wait_direct_loads();   // (before its place is taken)
+    wait_direct_loads();   // (before their place is taken)
   }
 
   // ---- merge: groups of four output columns of a row, dealt round-robin to the wavefronts
@@ -2328,7 +2371,7 @@ __global__ __launch_bounds__(kTwoPhaseBlocks * 64, D == 128 ? 1 : 2) void fa_fwd
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int y = 0; y < NK; ++y) {
-      const float4 u = ((const float4*)(lds + (2 * y + 1) * kBlk))[x * 64 + lane];
+      const float4 u = ((const float4*)(lds + kBlk + y * kWave))[x * 64 + lane];
       v.x = __builtin_fmaf(fk[y], u.x, v.x);
       v.y = __builtin_fmaf(fk[y], u.y, v.y);
       v.z = __builtin_fmaf(fk[y], u.z, v.z);
@@ -3502,17 +3545,40 @@ Kernel split_kernel(int head_dim, int split) {
   }
 }
 
-template <class T>
-Kernel window_split_kernel(int head_dim, bool bias) {
-  if (bias)
-    return head_dim == 32 ? fa_fwd_window_split_kernel<T, 32, true>
-                          : (head_dim == 64 ? fa_fwd_window_split_kernel<T, 64, true> : fa_fwd_window_split_kernel<T, 128, true>);
-  return head_dim == 32 ? fa_fwd_window_split_kernel<T, 32, false>
-                        : (head_dim == 64 ? fa_fwd_window_split_kernel<T, 64, false> : fa_fwd_window_split_kernel<T, 128, false>);
+// The small kernel's shapes: wavefronts (the key splits) x key blocks of each.
+template <class T, bool BIAS>
+Kernel small_kernel(int head_dim, int shape) {
+  switch (head_dim * 256 + shape) {
+    case 32 * 256 + 0x51: return fa_fwd_small_kernel<T, 32, 5, 1, BIAS>;
+    case 32 * 256 + 0x41: return fa_fwd_small_kernel<T, 32, 4, 1, BIAS>;
+    case 32 * 256 + 0x42: return fa_fwd_small_kernel<T, 32, 4, 2, BIAS>;
+    case 32 * 256 + 0x82: return fa_fwd_small_kernel<T, 32, 8, 2, BIAS>;
+    case 64 * 256 + 0x51: return fa_fwd_small_kernel<T, 64, 5, 1, BIAS>;
+    case 64 * 256 + 0x41: return fa_fwd_small_kernel<T, 64, 4, 1, BIAS>;
+    case 64 * 256 + 0x42: return fa_fwd_small_kernel<T, 64, 4, 2, BIAS>;
+    case 64 * 256 + 0x82: return fa_fwd_small_kernel<T, 64, 8, 2, BIAS>;
+    case 128 * 256 + 0x51: return fa_fwd_small_kernel<T, 128, 5, 1, BIAS>;
+    case 128 * 256 + 0x41: return fa_fwd_small_kernel<T, 128, 4, 1, BIAS>;
+    case 128 * 256 + 0x42: return fa_fwd_small_kernel<T, 128, 4, 2, BIAS>;
+    default: return nullptr;
+  }
 }
 
 template <class T>
 int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stream) {
+  if (a.small) {
+    // 32-row tiles, whatever rows the call was going to have (the host has checked that its blocks fit the shape)
+    FaKernelArgs args = a;
+    args.n_qtiles = (a.max_len + 31) / 32;
+    args.total_tiles = args.n_qtiles * a.heads * a.batch;
+    args.xcd_per = (args.n_qtiles * a.heads + 7) / 8;
+    args.heads_first = args.longest_first = 0;
+    const Kernel kern = a.key_bias ? small_kernel<T, true>(a.head_dim, a.small) : small_kernel<T, false>(a.head_dim, a.small);
+    if (!kern) return (int)hipErrorInvalidValue;
+    void* argv[] = {&args};
+    return (int)hipLaunchKernel((const void*)kern, dim3(a.map_xcd ? 8u * (unsigned)args.xcd_per * (unsigned)a.batch : (unsigned)args.total_tiles),
+                                dim3(64u * (unsigned)(a.small >> 4)), argv, 0, (hipStream_t)stream);
+  }
   unsigned grid = (unsigned)a.total_tiles;
   if (a.map_xcd) grid = 8u * (unsigned)a.xcd_per * (unsigned)a.batch;
   if (bm == 0) grid = a.mix_ids_a + kMixIdsB;
@@ -3536,11 +3602,7 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
   // against 7.8 us, 4K equal, 8K 17.3 against 14.9 us, 32K 43 against 37 us); it exists for
   // head_dim 64 only.
   const bool latency_bound = a.head_dim == kD && a.total_tiles <= 384;
-  if (a.win_split) {
-    kern = window_split_kernel<T>(a.head_dim, a.key_bias != nullptr);
-    threads = 64u * kTwoPhaseBlocks;
-    rows = 32;
-  } else if (a.split) {
+  if (a.split) {
     // (the host has checked that this shape exists for the head size)
     kern = a.key_bias ? split_kernel<T, true>(a.head_dim, a.split) : split_kernel<T, false>(a.head_dim, a.split);
     threads = 64u * (unsigned)((a.split >> 4) * (a.split & 15));

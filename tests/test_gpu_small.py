@@ -1,5 +1,5 @@
-"""GPU parity of the split window kernel (local layers of one round of 32-row workgroups, a wavefront per key block) against the
-fp64 oracle: block edges, windows that reach past the tensor or are open on one side, rows that see no key, padding that
+"""GPU parity of the small kernel (calls of one round of 32-row workgroups whose wavefronts hold all key blocks) against the fp64
+oracle: block edges, windows that reach past the tensor or are open on one side, rows that see no key, padding that
 holds anything, strided output, and the largest calls that take it beside the first that do not."""
 import numpy as np
 import pytest
@@ -36,17 +36,46 @@ def test_windows_and_lengths(D, dtype, left, right, lens, bias):
         for x in (q, k, v):
             x[b, :, n:] = np.nan
     o, lse = run_ex(q, k, v, lens, dtype, scale, left, right, key_bias=kb)
-    check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"window split D{D} {dtype} ({left},{right})")
+    check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"small D{D} {dtype} ({left},{right})")
 
 
-# (workgroups of one round: 512, 256 and 768 ids at head_dim 64, 128 and 32, and one past them)
-@pytest.mark.parametrize("D,H,N", [(64, 16, 1024), (64, 16, 1025), (128, 8, 1024), (128, 8, 1025), (32, 24, 1024), (32, 24, 1025)])
-def test_last_call_of_the_range_and_the_next(D, H, N):
+# Global: four wavefronts with one block each, with two, eight with two; lengths at the edges of blocks and of their number
+GLOBAL = [[128, 97, 96, 1, 0], [20, 3], [129, 128, 31], [256, 255, 160, 33], [257, 129, 0], [512, 480, 289, 31]]
+
+
+@pytest.mark.parametrize("bias", [False, True])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("lens", GLOBAL)
+def test_global_lengths(D, dtype, lens, bias):
+    B, H, N = len(lens), 3, max(lens)
+    _, q, k, v = draw(5300 + D + N, B, H, N, D, dtype, qk_gain=1.7)
+    kb = None
+    if bias:
+        rng = np.random.default_rng(D)
+        kb = round_to_storage(rng.standard_normal((B, N)).astype(np.float32), dtype)
+        kb[rng.random((B, N)) < 0.2] = -np.inf
+        kb[0, :70] = -np.inf           # wavefronts without a key that counts
+        kb[1, :] = -np.inf             # no key at all
+    scale = -(D ** -0.5)
+    o_ref, lse_ref = attention_oracle(q, k, v, lens, scale, key_bias=kb)
+    for b, n in enumerate(lens):
+        for x in (q, k, v):
+            x[b, :, n:] = np.nan
+    o, lse = run_ex(q, k, v, lens, dtype, scale, key_bias=kb)
+    check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"small D{D} {dtype} {lens}")
+
+
+# (workgroups of one round: the most ids of each shape and head size, and one tile past them)
+@pytest.mark.parametrize("D,H,N,left,right", [(64, 16, 1024, 63, 64), (64, 16, 1025, 63, 64), (128, 8, 1024, 63, 64), (128, 8, 1025, 63, 64),
+                                              (32, 24, 1024, 63, 64), (32, 24, 1025, 63, 64), (64, 16, 512, -1, -1), (64, 17, 512, -1, -1),
+                                              (32, 24, 512, -1, -1), (32, 25, 512, -1, -1), (128, 32, 256, -1, -1), (128, 33, 256, -1, -1)])
+def test_last_call_of_the_range_and_the_next(D, H, N, left, right):
     _, q, k, v = draw(5100 + D, 1, H, N, D, "fp16")
-    o, lse = run_ex(q, k, v, None, "fp16", D ** -0.5, 63, 64)
+    o, lse = run_ex(q, k, v, None, "fp16", D ** -0.5, left, right)
     sel = [0, H - 1]
-    o_ref, lse_ref = attention_oracle(q[:, sel], k[:, sel], v[:, sel], None, D ** -0.5, 63, 64)
-    check_against(o[:, sel], lse[:, sel], o_ref, lse_ref, None, "fp16", relative=True, label=f"window split range D{D} N{N}")
+    o_ref, lse_ref = attention_oracle(q[:, sel], k[:, sel], v[:, sel], None, D ** -0.5, left, right)
+    check_against(o[:, sel], lse[:, sel], o_ref, lse_ref, None, "fp16", relative=True, label=f"small range D{D} N{N}")
     assert np.isfinite(o).all() and np.isfinite(lse).all()
 
 
