@@ -2759,7 +2759,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   constexpr int HALF = D / 16, BLOCK_UNITS = 32 * HALF;   // 16-byte chunks per half row; a workgroup has 1, 2 or 4 times a block's
   auto rot_row = [&](int tid) { return (tid % BLOCK_UNITS) / HALF; };
   auto rot_ch = [&](int tid) { return tid % HALF; };
-  const uint32_t rot_lds = rot_row(tid) * D + (rot_ch(tid) ^ M::k_swz(rot_row(tid))) * 8;
+  auto rot_at = [&](int tid) { return (uint32_t)(rot_row(tid) * D + (rot_ch(tid) ^ M::k_swz(rot_row(tid))) * 8); };
+  const uint32_t rot_lds = rot_at(tid);
   struct Angles {
     float c[8], s[8];
   };
@@ -2781,7 +2782,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   };
   auto rotate_unit = [&](int b, int x, const Angles& t) {
     uint16_t* at = kblk(rot_blk(b, x));
-    uint4 *lo_at = (uint4*)&at[rot_lds], *hi_at = (uint4*)&at[rot_lds ^ (8 * HALF)];
+    const uint32_t own = D == 32 && NQB == 2 ? rot_at(wave * 64 + lane_now()) : rot_lds;   // (168 registers for three wavefronts)
+    uint4 *lo_at = (uint4*)&at[own], *hi_at = (uint4*)&at[own ^ (8 * HALF)];
     uint4 lo = *lo_at, hi = *hi_at;
     rotate8<T>(lo, hi, t.c, t.s);
     *lo_at = lo;
@@ -2903,8 +2905,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   // Rows of tile t whose sums ran away from their reference, or that found the first key that counts: the tile's scores are
   // formed again, its maximum is the new reference if it is above the old one, and the probabilities are made anew.  Each
   // row decides on its own lanes' evidence: no dependence on the rows that share its wavefront.
-  auto refresh = [&](auto WITHc, int t, bool masked) {
-    constexpr bool WITH = decltype(WITHc)::value;
+  auto refresh = [&](int t, bool masked) {
     auto vis_of = [&](int u) { return masked ? m.visible(2 * t + u, nk) : 0xFFFFu; };
     auto row_any = [&](bool x) { return M::row_sum(x ? 1.f : 0.f) > 0.f; };
 #pragma unroll
@@ -2939,15 +2940,13 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
           for (int x = 0; x < FR; ++x) kv[x] = as_v8<T>(kk[x]);
         }
         const float* b = lds_bias + (BIAS ? (blk & 7) * 32 : 0);
-        m.template start<BIAS_FIRST && WITH>(s[u], b);
+        m.template start<BIAS_FIRST>(s[u], b);
 #pragma unroll
         for (int i = 0; i < M::STEPS; ++i) M::score_step(s[u], kv, q[qb], i);
         if constexpr (BIAS_LAST) {
-          if (WITH) {
-            typename M::Scores bs;
-            m.template start<true>(bs, b);
-            M::add(s[u], bs);
-          }
+          typename M::Scores bs;
+          m.template start<true>(bs, b);
+          M::add(s[u], bs);
         }
       }
 #pragma unroll
@@ -2974,13 +2973,13 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     }
   };
   // The probabilities of tile t are final after this: one test per tile, of sums formed an iteration ago.
-  auto settle = [&](auto WITHc, int t, bool masked) {
+  auto settle = [&](int t, bool masked) {
     bool trig = false;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) trig = trig || !(z[qb][qt][0] <= kLimit);
-    if (__any(trig)) refresh(WITHc, t, masked);
+    if (__any(trig)) refresh(t, masked);
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
@@ -3182,9 +3181,11 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   auto bblk = [&](int b) { return lds_bias + (BIAS ? (b & 7) * 32 : 0); };
   using No = std::false_type;
   using Yes = std::true_type;
-  // Everything from the first scores on, with the bias (WITHc) or without; false: the padding has a part in the result after
-  // all, nothing has been written.  Two copies, from the first scores to the stores: with anything but the operands' addresses
-  // common to both the variants spill.
+  // Everything from the first scores to the last tile's probabilities, with the bias (WITHc) or without; false: the padding has a
+  // part in the result after all, nothing is lost but time.  (With the first scores common to both loops the variants with a
+  // bias spill; with what follows the loops in here, or a bias that is optional in `refresh`, the kernels without one are
+  // scheduled worse: 32K bf16 1 %.)
+  int t = 0;
   auto tiles = [&](auto WITHc) {
   constexpr bool WITH = decltype(WITHc)::value;
 #pragma unroll
@@ -3298,7 +3299,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     }
   }
 
-  int t = 0;
+    // (a refresh reads the ring of biases: zeros, what the keys that count have)
+    if (BIAS && !WITH && tid < 256) lds_bias[tid] = 0.f;
     if (T64 > 1) {
       if (wave_has_rows) iter(WITHc, Yes{}, No{}, 0, kops(1), kops(2), nullptr, nullptr, bblk(0), bblk(1), bblk(2));
       auto steady = [&](auto ODDc, int t) {
@@ -3312,7 +3314,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         landed(WITHc, t);
         request(WITHc, t);
         if (wave_has_rows) {
-          settle(WITHc, t - 1, false);
+          settle(t - 1, false);
           const uint16_t* k1 = kring + 2 * (1 - ODD) * kBlk;   // kops(2 t + 1)
           iter(WITHc, No{}, No{}, t, k1, k1 + kBlk, vblk(2 * ODD - 2), vblk(2 * ODD - 1), bblk(2 * t), bblk(2 * t + 1), bblk(2 * t + 2));
         }
@@ -3334,12 +3336,34 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
       landed(WITHc, t);
       request(WITHc, t);
       if (wave_has_rows) {
-        settle(WITHc, t - 1, false);
+        settle(t - 1, false);
         iter(WITHc, No{}, Yes{}, t, kops(2 * t + 1), nullptr, vblk(2 * t - 2), vblk(2 * t - 1), bblk(2 * t), bblk(2 * t + 1), nullptr);
       }
     } else {
       if (wave_has_rows) iter(WITHc, Yes{}, Yes{}, 0, kops(1), nullptr, nullptr, nullptr, bblk(0), bblk(1), nullptr);
     }
+  return true;
+  };
+  if constexpr (PLAIN_LOOP) {
+    bool done = false;
+    if (plain) {
+      done = tiles(No{});
+      if (!done) {
+        // the padding counts after all: from the start
+        wait_direct_loads();
+        __syncthreads();
+        kreq = kp + 3 * k32;
+        vreq = vp;
+        end = n;
+        first_fetch();
+        wait_direct_loads();
+        __syncthreads();
+      }
+    }
+    if (!done) tiles(Yes{});
+  } else {
+    tiles(std::integral_constant<bool, BIAS>{});
+  }
   // ---- drain: V of the last tile; rows at or beyond nk are overwritten with zeros by the lanes that fetched them
   // (0 * whatever is stored in the padding must be 0)
   wait_direct_loads();
@@ -3358,7 +3382,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   }
   __syncthreads();
   if (wave_has_rows) {
-    settle(WITHc, t, true);
+    settle(t, true);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
 #pragma unroll
@@ -3401,25 +3425,6 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         if (row < N) *(uint4*)(op + row * a.os[2] + (lane % CH) * 8) = v;
       }
     }
-  }
-  return true;
-  };
-  if constexpr (PLAIN_LOOP) {
-    if (plain) {
-      if (tiles(No{})) return;
-      // the padding counts after all: from the start
-      wait_direct_loads();
-      __syncthreads();
-      kreq = kp + 3 * k32;
-      vreq = vp;
-      end = n;
-      first_fetch();
-      wait_direct_loads();
-      __syncthreads();
-    }
-    tiles(Yes{});
-  } else {
-    tiles(std::integral_constant<bool, BIAS>{});
   }
 }
 
