@@ -188,6 +188,17 @@ int choose_split(const fa_params& p) {
   return 0;
 }
 
+// Tiles per head of the split kernel whose rows follow the length, or 0.  One sequence whose tensor is too long for one round of
+// 96-row workgroups, but not for one of 128-row ones: it goes before the 64-row shape, of which up to two share a unit
+// while others have one.  us, 12 x 64, bf16, fp16, that shape -> it: 1000 of 2048 14.3 -> 11.9, 13.6 -> 11.9; 1340 17.0 -> 13.5, 16.0 -> 13.4;
+// 1400 17.05 -> 15.7, 16.1 -> 15.8; 1900 21.1 -> 18.8, 20.2 -> 19.1; 2040 22.2 -> 22.0, 21.3 -> 22.1; 2300 of 2500 24.9 -> 24.3, 24.2 -> 24.6;
+// 2600 29.2 -> 27.9, 28.5 -> 28.4.  (Shorter tensors: the shapes above need not wait for the length; 1000 of 1024 10.9, here 11.9.)
+int choose_live(const fa_params& p) {
+  if (p.head_dim != 64 || p.key_bias || !p.seq_lens || p.batch != 1 || p.heads > 256) return 0;
+  const int per = 256 / p.heads;
+  return (p.max_len + 127) / 128 <= per && (p.max_len + 95) / 96 > per ? per : 0;
+}
+
 // Shape of the small kernel, 16 * wavefronts + key blocks of each, or 0: calls whose 32-row workgroups see at most as many key
 // blocks as the shape holds, and fit one round of as many workgroups per unit as their LDS allows.  It goes before the kernel
 // that the rules above choose.  us, fp16, the kernels before -> it:
@@ -414,6 +425,7 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   a.xcd_per = (int32_t)per;
   a.split = split;
   a.small = small;
+  a.live_tiles = t_bm == FA_TUNE_BM_AUTO && split && !small ? choose_live(*p) : 0;
   // (a launch of at most two workgroups per unit has nothing else to hide the read of the sequence length behind)
   a.late_n = total <= 512;
   a.mix_ids_a = bm == 0 ? fa_mix_ids((int)n_qtiles, p->heads) : 0;

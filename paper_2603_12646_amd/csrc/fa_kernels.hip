@@ -183,6 +183,15 @@ __device__ __forceinline__ void load16_to_lds(const void* gbase, uint32_t lane_o
                : "s"(l), "v"(lane_off_bytes), "s"(gbase)
                : "memory");
 }
+// The lane index, formed where it is needed: values derived from it outside the main loop then need no register through it.
+// (Only the scalar mask comes out of an asm block: a vector register written in one may still be the destination of a matrix
+// product under way, which the compiler waits for where it sees the write.)
+__device__ __forceinline__ int lane_now() {
+  uint32_t ones;
+  asm volatile("s_mov_b32 %0, -1" : "=s"(ones));
+  return (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0));
+}
+
 // s_waitcnt immediate that waits for vmcnt <= N only (expcnt and lgkmcnt fields at their
 // maxima): vmcnt is bits 3:0 plus bits 15:14 of the immediate.
 template <int N>
@@ -1825,27 +1834,27 @@ struct SplitLds {
   static constexpr int kElems = kRing > kMerge ? kRing : kMerge;
 };
 
-template <class T, int D, int NQ, int NK, int P, int WPS, bool BIAS>
-__global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const FaKernelArgs a) {
+// tc: the workgroup's tile (tc.n as loaded, not clamped; tc.q0 is not used)
+template <class T, int D, int NQ, int NK, int P, bool BIAS, bool KNOWN_N = false>
+__device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, uint16_t* lds) {
   constexpr int NW = NQ * NK, THREADS = NW * 64, BM = 32 * NQ;
   constexpr int KS = D / 16, DB = D / 32;
   typedef SplitLds<D, NQ, NK, P> L;
+  constexpr bool DOUBLES = P == 4 && D != 128;   // two steps between barriers, see below (head_dim 128 has no registers for it)
   constexpr int kBlk = L::kBlk;
   constexpr int CH = D / 8, RPL = 64 / CH, LPB = 32 / RPL;   // 16-byte chunks per row, rows per load, loads per block
   // a block's loads are dealt to NL of the NQ wavefronts that share it, LW each
   constexpr int NL = NQ == 3 ? 2 : NQ, LW = LPB / NL;
   static_assert(LPB % NL == 0 && P >= 2, "whole loads per wavefront");
-  __shared__ __attribute__((aligned(16))) uint16_t lds[L::kElems + (BIAS ? 2 * kSplitBiasKeys : 0)];
   float* const lds_bias = (float*)(lds + L::kElems);
 
-  TileCoord tc;
-  if (!locate_tile<BM, false>(a, tc)) return;   // tc.n still as loaded: see below
+  tc.q0 = tc.qt * BM;
   const int N = a.max_len, q0 = tc.q0;
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
+  int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qb = wave % NQ, g = wave / NQ;
-  const int l32 = lane & 31, hh = lane >> 5;
+  int l32 = lane & 31, hh = lane >> 5;
 
   const uint16_t* qp = (const uint16_t*)a.q + tc.b * a.qs[0] + tc.h * a.qs[1];
   const uint16_t* kp = (const uint16_t*)a.k + tc.b * a.ks[0] + tc.h * a.ks[1];
@@ -1853,7 +1862,7 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   uint16_t* op = (uint16_t*)a.o + tc.b * a.os[0] + tc.h * a.os[1];
   float* lsep = a.lse ? a.lse + ((int64_t)tc.b * a.heads + tc.h) * N : nullptr;
 
-  const bool late_n = a.late_n != 0;
+  const bool late_n = !KNOWN_N && a.late_n != 0;
   if (!late_n) tc.n = tc.n < 0 ? 0 : (tc.n > N ? N : tc.n);
   if (!late_n && q0 >= tc.n) {
     zero_fill<BM, D, THREADS>(a, tc, op, lsep);
@@ -1863,18 +1872,17 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   // A load moves RPL rows of a 32-row block (lane: row lane / CH, chunk position lane % CH).  A block whose rows
   // all exist is addressed by a scalar base and a fixed per-lane offset; where rows would leave the tensor the
   // lane's row is clamped to the last one (such rows are masked, zeroed or never read).
-  int row_of[LW];
-  uint32_t kchunk[LW], vchunk[LW], koff[LW], voff[LW];
+  auto row_of = [&](int x, int lane) { return (qb * LW + x) * RPL + lane / CH; };
+  uint32_t koff[LW], voff[LW], kchunk[LW], vchunk[LW];
 #pragma unroll
   for (int x = 0; x < LW; ++x) {
-    row_of[x] = (qb * LW + x) * RPL + lane / CH;
-    kchunk[x] = 2u * (uint32_t)(((lane % CH) ^ k_swz_d<D>(row_of[x])) * 8);
-    vchunk[x] = 2u * (uint32_t)(((lane % CH) ^ v_swz_d<D>(row_of[x])) * 8);
-    koff[x] = (uint32_t)row_of[x] * 2u * (uint32_t)a.ks[2] + kchunk[x];
-    voff[x] = (uint32_t)row_of[x] * 2u * (uint32_t)a.vs[2] + vchunk[x];
+    const int r = row_of(x, lane);
+    kchunk[x] = 2u * (uint32_t)(((lane % CH) ^ k_swz_d<D>(r)) * 8);
+    vchunk[x] = 2u * (uint32_t)(((lane % CH) ^ v_swz_d<D>(r)) * 8);
+    koff[x] = 2u * ((uint32_t)r * (uint32_t)a.ks[2] + (uint32_t)(((lane % CH) ^ k_swz_d<D>(r)) * 8));
+    voff[x] = 2u * ((uint32_t)r * (uint32_t)a.vs[2] + (uint32_t)(((lane % CH) ^ v_swz_d<D>(r)) * 8));
   }
-  auto load_block = [&](const uint16_t* base, int64_t rs, const uint32_t (&off)[LW], const uint32_t (&chunk)[LW], int j,
-                        uint16_t* dst) {
+  auto load_block = [&](const uint16_t* base, int64_t rs, const uint32_t (&off)[LW], const uint32_t (&chunk)[LW], int j, uint16_t* dst) {
     if (NL < NQ && qb >= NL) return;
     if (32 * j + 32 <= N) {
       const uint16_t* gb = base + (int64_t)(32 * j) * rs;
@@ -1883,10 +1891,13 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
     } else {
       const int first = 32 * j < N ? 32 * j : N - 1;
       const uint16_t* gb = base + (int64_t)first * rs;
+      const int at = DOUBLES ? lane_now() : lane;   // (no register through the loop)
 #pragma unroll
       for (int x = 0; x < LW; ++x) {
-        const int r = row_of[x] < N - 1 - first ? row_of[x] : N - 1 - first;
-        load16_to_lds(gb, (uint32_t)r * 2u * (uint32_t)rs + chunk[x], dst + (qb * LW + x) * RPL * D);
+        const int past = row_of(x, at) - (N - 1 - first);
+        const uint32_t clamped = DOUBLES ? off[x] - 2u * (uint32_t)(past > 0 ? past : 0) * (uint32_t)rs
+                                         : 2u * (uint32_t)(row_of(x, at) - (past > 0 ? past : 0)) * (uint32_t)rs + chunk[x];
+        load16_to_lds(gb, clamped, dst + (qb * LW + x) * RPL * D);
       }
     }
   };
@@ -1936,7 +1947,7 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   const int steps = (nb + NK - 1) / NK;                   // <= steps_req
   const int nfs = n / (32 * NK);                          // steps whose super tile is full: steps or steps - 1
   const bool wave_has_rows = q0 + 32 * qb < n;
-  const int ig = q0 + 32 * qb + l32;
+  int ig = q0 + 32 * qb + l32;
   const bool alive = ig < n;
   const float c = a.c;
 
@@ -1971,10 +1982,11 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   // V rows at or beyond n are overwritten with zeros by the lanes that fetched them, once the partial super tile has
   // landed: 0 * whatever is stored in the padding must be 0
   auto scrub = [&](int i) {
+    const int lane = DOUBLES ? lane_now() : tid & 63;
 #pragma unroll
     for (int x = 0; x < LW; ++x)
-      if ((NL == NQ || qb < NL) && 32 * (i * NK + g) + row_of[x] >= n)
-        *(uint4*)&v_slot(i)[row_of[x] * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
+      if ((NL == NQ || qb < NL) && 32 * (i * NK + g) + row_of(x, lane) >= n)
+        *(uint4*)&v_slot(i)[row_of(x, lane) * D + (lane % CH) * 8] = make_uint4(0, 0, 0, 0);
   };
   if (nfs == 0) {
     request_up_to(0);   // (two slots and a tensor longer than this sequence: V0 has not been requested yet)
@@ -1998,10 +2010,13 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   w.scores(sA, k_slot(0), bias_of_block(0), lane);
   w.prime(sA, nfs > 0 ? 0xFFFFu : visible_bits(32 * g, hh, 0, n - 1), c);
 
-  // Step 0 (if its super tile is full): probabilities of block 0, scores of block 1.
+  // Step 0 (if its super tile is full): probabilities of block 0, scores of block 1.  (Double steps, below, make their own requests.)
+  const bool doubles = DOUBLES && nfs > 5 && pairs == 2;
   if (nfs > 0) {
-    if (steps > P) slots_free();   // K0's slot is refilled
-    request_up_to(P - 2);
+    if (!doubles) {
+      if (steps > P) slots_free();   // K0's slot is refilled
+      request_up_to(P - 2);
+    }
     if (wave_has_rows) {
       const int in = steps > 1 ? 1 : 0;
       w.scores(sB, k_slot(in), bias_of_block(in), lane);
@@ -2011,10 +2026,52 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
   // Step i (a full super tile): probabilities of block i, scores of block i + 1, P.V of block i - 1.
   int i = 1;
   {
-    // The steady part, P steps per turn: ring slots are compile-time constants, the row bases of the requested blocks
-    // just advance, and the wait is one instruction (the pairs under way all hold K and V).  Step i requests pair
-    // i + P - 2, whose K of step i + P lies inside the full super tiles.
-    if ((P == 2 || P == 4) && i + 2 * P - 1 < nfs && pairs == P - 1) {
+    // The steady part, straight-line code: ring slots are compile-time constants, the row bases of the requested blocks just
+    // advance, and the wait is one instruction.
+    if constexpr (DOUBLES) {
+      // Two steps between barriers: steps i and i + 1 request K of steps i + 3, i + 4 and V of i + 1, i + 2, into slots that
+      // the two steps before left, and wait for nothing younger than those before requested.  (The requested K lie inside the full
+      // super tiles.)
+      if (doubles) {
+        const int64_t kstep = (int64_t)(32 * NK) * a.ks[2], vstep = (int64_t)(32 * NK) * a.vs[2];
+        const uint16_t* kg = kp + (int64_t)(32 * g) * a.ks[2] + 4 * kstep;
+        const uint16_t* vg = vp + (int64_t)(32 * g) * a.vs[2] + 2 * vstep;
+        uint16_t* const my_k = ring + g * kBlk;
+        uint16_t* const my_v = ring + (NK + g) * kBlk;
+        auto two = [&](auto Jc, int i) {
+          constexpr int J = decltype(Jc)::value;   // i % 4: 1 or 3
+          wait_vmcnt<0>();
+          slots_free();
+          if (NL == NQ || qb < NL) {
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+#pragma unroll
+              for (int x = 0; x < LW; ++x) load16_to_lds(kg + y * kstep, koff[x], my_k + (J + 3 + y) % 4 * L::kSlot + (qb * LW + x) * RPL * D);
+#pragma unroll
+              for (int x = 0; x < LW; ++x) load16_to_lds(vg + y * vstep, voff[x], my_v + (J + 1 + y) % 4 * L::kSlot + (qb * LW + x) * RPL * D);
+            }
+          }
+          kg += 2 * kstep;
+          vg += 2 * vstep;
+          if (wave_has_rows) {
+            w.step(sB, sA, pA, pB, my_k + (J + 1) % 4 * L::kSlot, my_v + (J + 3) % 4 * L::kSlot, bias_of_block(i + 1), alive, c, lane);
+            __builtin_amdgcn_sched_barrier(0);
+            w.step(sA, sB, pB, pA, my_k + (J + 2) % 4 * L::kSlot, my_v + J * L::kSlot, bias_of_block(i + 2), alive, c, lane);
+          }
+        };
+        for (; i + 6 < nfs; i += 4) {
+          two(std::integral_constant<int, 1>{}, i);
+          two(std::integral_constant<int, 3>{}, i + 2);
+        }
+        if (i + 4 < nfs) {
+          two(std::integral_constant<int, 1>{}, i);
+          i += 2;
+        }
+        pairs = i + 1;
+      }
+    }
+    // P steps per turn, a barrier each.  Step i requests pair i + P - 2, whose K of step i + P lies inside the full super tiles.
+    if ((P == 2 || P == 4) && !DOUBLES && i + 2 * P - 1 < nfs && pairs == P - 1) {
       const int64_t kstep = (int64_t)(32 * NK) * a.ks[2], vstep = (int64_t)(32 * NK) * a.vs[2];
       const uint16_t* kg = kp + (int64_t)(32 * g) * a.ks[2] + (P + 1) * kstep;
       const uint16_t* vg = vp + (int64_t)(32 * g) * a.vs[2] + (P - 1) * vstep;
@@ -2065,6 +2122,12 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
     pA[1] = pB[1];
   } else if (nfs > 0) {
     sA = sB;
+  }
+  // (formed again: no register through the loop)
+  if (DOUBLES) {
+    lane = lane_now();
+    l32 = lane & 31, hh = lane >> 5;
+    ig = q0 + 32 * qb + l32;
   }
   // Now sA holds the scores of the partial super tile (if there is one) and pA the last full block's probabilities.
   if (nfs > 0 || steps > nfs) {
@@ -2156,6 +2219,43 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
     if (row < N) *(uint4*)(op + row * a.os[2] + (lane % CH) * 8) = v;
   }
   if (lsep && g == 0 && hh == 0 && ig < N) lsep[ig] = live ? (mc_new + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
+}
+
+template <class T, int D, int NQ, int NK, int P, int WPS, bool BIAS>
+__global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const FaKernelArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[SplitLds<D, NQ, NK, P>::kElems + (BIAS ? 2 * kSplitBiasKeys : 0)];
+  TileCoord tc;
+  if (!locate_tile<32 * NQ, false>(a, tc)) return;
+  split_body<T, D, NQ, NK, P, BIAS>(a, tc, lds);
+}
+
+// The same for ONE sequence in a tensor that is longer (head_dim 64): the tile's rows and the key split follow the sequence's
+// length, which the host does not know.  A workgroup has twelve wavefronts and a compute unit to itself; every head has
+// a.n_qtiles of them (heads * n_qtiles <= 256), and they are 64, 96 or 128 rows high, as few as hold the sequence.  Rows past what the tiles cover are padding: zeros.
+template <class T>
+__global__ __launch_bounds__(768, 3) void fa_fwd_split_live_kernel(const FaKernelArgs a) {
+  typedef SplitLds<64, 3, 4, 4> L;
+  static_assert(L::kElems >= SplitLds<64, 4, 3, 2>::kElems && L::kElems >= SplitLds<64, 2, 6, 2>::kElems, "one memory for the three shapes");
+  __shared__ __attribute__((aligned(16))) uint16_t lds[L::kElems];
+  TileCoord tc;
+  if (!locate_tile<96>(a, tc)) return;
+  const int per = a.n_qtiles, rows = tc.n <= 64 * per ? 64 : (tc.n <= 96 * per ? 96 : 128);
+  // rows past what the tiles cover: padding, by the workgroups of the last tiles, which often are padding themselves
+  for (tc.q0 = per * rows + 32 * (per - 1 - tc.qt); tc.q0 < a.max_len; tc.q0 += 32 * per)
+    zero_fill<32, 64, 768>(a, tc, (uint16_t*)a.o + tc.h * a.os[1], a.lse ? a.lse + (int64_t)tc.h * a.max_len : nullptr);
+  // (each shape reads the arguments for itself: those of all three together do not fit the scalar registers)
+  auto own_args = [&]() -> const FaKernelArgs& {
+    typedef const __attribute__((address_space(4))) FaKernelArgs Args;
+    Args* p = (Args*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p), "+s"(tc.h), "+s"(tc.qt), "+s"(tc.n));
+    return *(const FaKernelArgs*)p;
+  };
+  tc.h = __builtin_amdgcn_readfirstlane(tc.h);
+  tc.qt = __builtin_amdgcn_readfirstlane(tc.qt);
+  tc.n = __builtin_amdgcn_readfirstlane(tc.n);
+  if (rows == 96) split_body<T, 64, 3, 4, 4, false, true>(own_args(), tc, lds);
+  else if (rows == 128) split_body<T, 64, 4, 3, 2, false, true>(own_args(), tc, lds);
+  else split_body<T, 64, 2, 6, 2, false, true>(own_args(), tc, lds);
 }
 
 // ======================================================================================
@@ -2623,15 +2723,6 @@ __device__ __forceinline__ void load_row(const FaKernelArgs& a, const M& m, cons
       }
     }
   }
-}
-
-// The lane index, formed where it is needed: values derived from it outside the main loop then need no register through it.
-// (Only the scalar mask comes out of an asm block: a vector register written in one may still be the destination of a matrix
-// product under way, which the compiler waits for where it sees the write.)
-__device__ __forceinline__ int lane_now() {
-  uint32_t ones;
-  asm volatile("s_mov_b32 %0, -1" : "=s"(ones));
-  return (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0));
 }
 
 template <int D, int NW>
@@ -3571,6 +3662,17 @@ Kernel small_kernel(int head_dim, int shape) {
 
 template <class T>
 int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stream) {
+  if (a.live_tiles) {
+    // one workgroup per unit, whatever the length turns out to be
+    FaKernelArgs args = a;
+    args.n_qtiles = a.live_tiles;
+    args.total_tiles = a.live_tiles * a.heads;
+    args.xcd_per = (args.total_tiles + 7) / 8;
+    args.late_n = 0;
+    void* argv[] = {&args};
+    return (int)hipLaunchKernel((const void*)fa_fwd_split_live_kernel<T>, dim3(a.map_xcd ? 8u * (unsigned)args.xcd_per : (unsigned)args.total_tiles),
+                                dim3(768), argv, 0, (hipStream_t)stream);
+  }
   if (a.small) {
     // 32-row tiles, whatever rows the call was going to have (the host has checked that its blocks fit the shape)
     FaKernelArgs args = a;
