@@ -1835,9 +1835,9 @@ struct SplitLds {
   static constexpr int kElems = kRing > kMerge ? kRing : kMerge;
 };
 
-// tc: the workgroup's tile (tc.n as loaded, not clamped; tc.q0 is not used)
+// KNOWN_N: tc_in is the workgroup's tile (its q0 is not used) and the length is known; otherwise the body finds its tile.
 template <class T, int D, int NQ, int NK, int P, bool BIAS, bool KNOWN_N = false>
-__device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, uint16_t* lds) {
+__device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc_in, uint16_t* lds) {
   constexpr int NW = NQ * NK, THREADS = NW * 64, BM = 32 * NQ;
   constexpr int KS = D / 16, DB = D / 32;
   typedef SplitLds<D, NQ, NK, P> L;
@@ -1849,13 +1849,15 @@ __device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, 
   static_assert(LPB % NL == 0 && P >= 2, "whole loads per wavefront");
   float* const lds_bias = (float*)(lds + L::kElems);
 
-  tc.q0 = tc.qt * BM;
+  TileCoord tc = tc_in;
+  if (KNOWN_N) tc.q0 = tc.qt * BM;
+  else if (!locate_tile<BM, false>(a, tc)) return;
   const int N = a.max_len, q0 = tc.q0;
   const int tid = threadIdx.x;
-  int lane = tid & 63;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qb = wave % NQ, g = wave / NQ;
-  int l32 = lane & 31, hh = lane >> 5;
+  const int l32 = lane & 31, hh = lane >> 5;
 
   const uint16_t* qp = (const uint16_t*)a.q + tc.b * a.qs[0] + tc.h * a.qs[1];
   const uint16_t* kp = (const uint16_t*)a.k + tc.b * a.ks[0] + tc.h * a.ks[1];
@@ -1873,15 +1875,17 @@ __device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, 
   // A load moves RPL rows of a 32-row block (lane: row lane / CH, chunk position lane % CH).  A block whose rows
   // all exist is addressed by a scalar base and a fixed per-lane offset; where rows would leave the tensor the
   // lane's row is clamped to the last one (such rows are masked, zeroed or never read).
-  auto row_of = [&](int x, int lane) { return (qb * LW + x) * RPL + lane / CH; };
+  int row_at[LW];
+  auto row_of = [&](int x, int lane) { return DOUBLES ? (qb * LW + x) * RPL + lane / CH : row_at[x]; };
   uint32_t koff[LW], voff[LW], kchunk[LW], vchunk[LW];
 #pragma unroll
   for (int x = 0; x < LW; ++x) {
-    const int r = row_of(x, lane);
+    const int r = (qb * LW + x) * RPL + lane / CH;
+    row_at[x] = r;
     kchunk[x] = 2u * (uint32_t)(((lane % CH) ^ k_swz_d<D>(r)) * 8);
     vchunk[x] = 2u * (uint32_t)(((lane % CH) ^ v_swz_d<D>(r)) * 8);
-    koff[x] = 2u * ((uint32_t)r * (uint32_t)a.ks[2] + (uint32_t)(((lane % CH) ^ k_swz_d<D>(r)) * 8));
-    voff[x] = 2u * ((uint32_t)r * (uint32_t)a.vs[2] + (uint32_t)(((lane % CH) ^ v_swz_d<D>(r)) * 8));
+    koff[x] = (uint32_t)r * 2u * (uint32_t)a.ks[2] + kchunk[x];
+    voff[x] = (uint32_t)r * 2u * (uint32_t)a.vs[2] + vchunk[x];
   }
   auto load_block = [&](const uint16_t* base, int64_t rs, const uint32_t (&off)[LW], const uint32_t (&chunk)[LW], int j, uint16_t* dst) {
     if (NL < NQ && qb >= NL) return;
@@ -1895,10 +1899,13 @@ __device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, 
       const int at = DOUBLES ? lane_now() : lane;   // (no register through the loop)
 #pragma unroll
       for (int x = 0; x < LW; ++x) {
-        const int past = row_of(x, at) - (N - 1 - first);
-        const uint32_t clamped = DOUBLES ? off[x] - 2u * (uint32_t)(past > 0 ? past : 0) * (uint32_t)rs
-                                         : 2u * (uint32_t)(row_of(x, at) - (past > 0 ? past : 0)) * (uint32_t)rs + chunk[x];
-        load16_to_lds(gb, clamped, dst + (qb * LW + x) * RPL * D);
+        if (DOUBLES) {
+          const int past = row_of(x, at) - (N - 1 - first);
+          load16_to_lds(gb, off[x] - 2u * (uint32_t)(past > 0 ? past : 0) * (uint32_t)rs, dst + (qb * LW + x) * RPL * D);
+        } else {
+          const int r = row_at[x] < N - 1 - first ? row_at[x] : N - 1 - first;
+          load16_to_lds(gb, (uint32_t)r * 2u * (uint32_t)rs + chunk[x], dst + (qb * LW + x) * RPL * D);
+        }
       }
     }
   };
@@ -1948,7 +1955,7 @@ __device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, 
   const int steps = (nb + NK - 1) / NK;                   // <= steps_req
   const int nfs = n / (32 * NK);                          // steps whose super tile is full: steps or steps - 1
   const bool wave_has_rows = q0 + 32 * qb < n;
-  int ig = q0 + 32 * qb + l32;
+  const int ig = q0 + 32 * qb + l32;
   const bool alive = ig < n;
   const float c = a.c;
 
@@ -2124,12 +2131,8 @@ __device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, 
   } else if (nfs > 0) {
     sA = sB;
   }
-  // (formed again: no register through the loop)
-  if (DOUBLES) {
-    lane = lane_now();
-    l32 = lane & 31, hh = lane >> 5;
-    ig = q0 + 32 * qb + l32;
-  }
+  // (DOUBLES: the lane is formed again, no register through the loop)
+  const int lane_e = DOUBLES ? lane_now() : lane, l32_e = lane_e & 31, hh_e = lane_e >> 5, ig_e = q0 + 32 * qb + l32_e;
   // Now sA holds the scores of the partial super tile (if there is one) and pA the last full block's probabilities.
   if (nfs > 0 || steps > nfs) {
     if (nfs > 0) {
@@ -2145,7 +2148,7 @@ __device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, 
     // (a block that lies past the end as a whole has no part in the result; its row without a reference would only take the
     // detour for one)
     if (32 * (nfs * NK + g) < n) {
-      w.template softmax<true>(sA, pA, visible_bits(32 * (nfs * NK + g), hh, 0, n - 1), alive, c);
+      w.template softmax<true>(sA, pA, visible_bits(32 * (nfs * NK + g), hh_e, 0, n - 1), alive, c);
       w.accumulate(pA, v_slot(nfs));
     }
   }
@@ -2156,11 +2159,11 @@ __device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, 
   // columns of a row; the same lane <-> (row, column) mapping in every wavefront) are dealt to the NK wavefronts,
   // group x to wavefront x % NK, which finishes it
   constexpr int G = 4 * DB;
-  float4* const part = (float4*)lds + (size_t)qb * (NK - 1) * G * 64 + lane;       // [group][contributor][lane]
+  float4* const part = (float4*)lds + (size_t)qb * (NK - 1) * G * 64 + lane_e;       // [group][contributor][lane]
   // [wavefront][reference times c, sum][lane].  The reference goes through as the rounded product the probabilities were
   // formed against (-infinity: none); forming it again here would let the compiler fuse it into the subtraction below,
   // unrounded, and put a wavefront's share off by 2^(half a spacing of it) - 4 % at scores of 10^6
-  float* const state = (float*)(lds + L::kPart) + (size_t)qb * NK * 2 * 64 + lane;
+  float* const state = (float*)(lds + L::kPart) + (size_t)qb * NK * 2 * 64 + lane_e;
   uint16_t* const patch = lds + L::kPart + L::kState + qb * epi_patch(D);
   constexpr int kEpiStride = epi_stride(D);
   state[(2 * g + 0) * 64] = w.st.m_ref[0] == -INFINITY ? -INFINITY : w.st.mc[0];
@@ -2208,26 +2211,24 @@ __device__ __forceinline__ void split_body(const FaKernelArgs& a, TileCoord tc, 
         v.w = __builtin_fmaf(fk[y], u.w, v.w);
       }
       // columns 32 (x / 4) + 8 (x % 4) + 4 hh .. + 3 of the lane's row
-      *(uint2*)&patch[l32 * kEpiStride + 8 * x + 4 * hh] =
+      *(uint2*)&patch[l32_e * kEpiStride + 8 * x + 4 * hh_e] =
           live ? make_uint2(T::pack2(v.x * inv, v.y * inv), T::pack2(v.z * inv, v.w * inv)) : make_uint2(0, 0);
     }
   }
   __syncthreads();
   for (int pass = g; pass < 32 / RPL; pass += NK) {
-    const int r = pass * RPL + lane / CH;
+    const int r = pass * RPL + lane_e / CH;
     const int row = q0 + 32 * qb + r;
-    const uint4 v = *(const uint4*)&patch[r * kEpiStride + (lane % CH) * 8];
-    if (row < N) *(uint4*)(op + row * a.os[2] + (lane % CH) * 8) = v;
+    const uint4 v = *(const uint4*)&patch[r * kEpiStride + (lane_e % CH) * 8];
+    if (row < N) *(uint4*)(op + row * a.os[2] + (lane_e % CH) * 8) = v;
   }
-  if (lsep && g == 0 && hh == 0 && ig < N) lsep[ig] = live ? (mc_new + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
+  if (lsep && g == 0 && hh_e == 0 && ig_e < N) lsep[ig_e] = live ? (mc_new + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
 }
 
 template <class T, int D, int NQ, int NK, int P, int WPS, bool BIAS>
 __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const FaKernelArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[SplitLds<D, NQ, NK, P>::kElems + (BIAS ? 2 * kSplitBiasKeys : 0)];
-  TileCoord tc;
-  if (!locate_tile<32 * NQ, false>(a, tc)) return;
-  split_body<T, D, NQ, NK, P, BIAS>(a, tc, lds);
+  split_body<T, D, NQ, NK, P, BIAS>(a, TileCoord(), lds);
 }
 
 // The same for ONE sequence in a tensor that is longer (head_dim 64): the tile's rows and the key split follow the sequence's
@@ -3196,14 +3197,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     if (cold < 0xFFFF) top_bias = bias_over_scale<T, D == 32>(a, (uint16_t)cold);
   }
   typename M::Scores sA, sB;
-  const bool rotate_prio = ROTATE && NQB == 1 && T64 >= 64;
+  bool rotate_prio = false;
   int wslot = 0;
-  if (rotate_prio) {
-    unsigned hw_id;
-    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw_id));
-    wslot = (int)(hw_id & 15u);  // wave slot within the SIMD
-  }
-
   // One iteration = the 64 keys of tile t.  Units (key block 2t + u, query block qb) in the order (0,0) .. (0,NQB-1), (1,0) ..:
   // the vector ALU turns the unit's scores (s_cur) into probabilities while the matrix cores form the NEXT unit's scores
   // and add the P.V of the same unit of the PREVIOUS tile.  k1, k2: LDS blocks 2t + 1, 2t + 2 of K; v1, v2: 2t - 2, 2t - 1 of V.
@@ -3391,6 +3386,13 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
         return false;
       }
     }
+  }
+
+  rotate_prio = ROTATE && NQB == 1 && T64 >= 64;
+  if (rotate_prio) {
+    unsigned hw_id;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw_id));
+    wslot = (int)(hw_id & 15u);  // wave slot within the SIMD
   }
 
     // (a refresh reads the ring of biases: zeros, what the keys that count have)
