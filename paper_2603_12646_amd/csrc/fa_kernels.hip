@@ -555,6 +555,18 @@ __device__ __forceinline__ void add_bias(floatx16& s, const float* bblk, int hh)
   }
 }
 
+// One word of every 64 bytes of the argument block, all under way at once: left to itself the compiler loads arguments where
+// they are first used, three or four round trips to memory one after the other before a workgroup's first load.  For the kernels
+// that one workgroup's latency bounds, us: small kernel, local 487 tokens 4.7 -> 4.4, global 512 5.5 -> 5.4, resident window kernel, 2K
+// 7.8 -> 7.4; the split kernel, whose first loads need few of them, 7.0 -> 7.2 (3 x 302), calls of several rounds 0.5 - 1 % slower.
+__device__ __forceinline__ void fetch_args() {
+  typedef const __attribute__((address_space(4))) uint32_t Word;
+  Word* const p = (Word*)__builtin_amdgcn_kernarg_segment_ptr();
+  const uint32_t w0 = p[0], w1 = p[16], w2 = p[32], w3 = p[48], w4 = p[64];
+  static_assert(sizeof(FaKernelArgs) > 256 && sizeof(FaKernelArgs) <= 320, "five pieces of 64 bytes");
+  asm volatile("" : : "s"(w0), "s"(w1), "s"(w2), "s"(w3), "s"(w4));
+}
+
 // ---- pieces shared by both kernels ----------------------------------------------------
 struct TileCoord {
   int b, h, qt, n, q0;
@@ -1121,6 +1133,7 @@ __global__ __launch_bounds__(kThreads, 2) void fa_fwd_window_resident_kernel(con
   // operand of each block's first MFMA
   __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? kResBlocks * 32 : 4];
 
+  fetch_args();
   TileCoord tc;
   if (!locate_tile<BM, false>(a, tc)) return;  // tc.n still as loaded: see below
   const int N = a.max_len, q0 = tc.q0;
@@ -2287,6 +2300,7 @@ __global__ __launch_bounds__(NK * 64, 1) void fa_fwd_small_kernel(const FaKernel
   __shared__ __attribute__((aligned(16))) float lds_state[NK][2][64];   // reference times c, row sum
   __shared__ __attribute__((aligned(16))) float lds_bias[BIAS ? NK * NB : 1][32];
 
+  fetch_args();
   TileCoord tc;
   if (!locate_tile<BM, false>(a, tc)) return;   // tc.n still as loaded: see below
   const int N = a.max_len, q0 = tc.q0;
