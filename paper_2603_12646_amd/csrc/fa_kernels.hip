@@ -3303,7 +3303,8 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   if (KN == 4) __syncthreads();   // K block 0 is in registers everywhere: block 4 takes its place
   request(WITHc, 0);
   {
-    const uint32_t vis = m.visible(0, nk);
+    // (without the bias a padded key's score is an ordinary one: the first reference is that of the keys before the padding)
+    const uint32_t vis = m.visible(0, WITH ? nk : end);
 #pragma unroll
     for (int qb = NQB - 1; qb >= 0; --qb) {
       score_init(WITHc, sA, lds_bias);

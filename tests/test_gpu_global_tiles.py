@@ -210,3 +210,35 @@ def test_bias_of_zeros_but_for_padding(head_dim, dtype, tuning, kind):
         # (head_dim 128 with a bias has 128-row tiles only)
         o0, lse0 = run_ex(q, k, v, None, dtype, scale, tuning=fa.FA_TUNE_BM_128 if head_dim == 128 else tuning)
         assert np.array_equal(o, o0) and np.array_equal(lse, lse0)
+
+
+FEW_ENDS = [1, 4, 8, 31, 32, 33, 40]
+
+
+@pytest.mark.parametrize("value", [-65504.0, -np.inf])
+@pytest.mark.parametrize("tuning", [fa.FA_TUNE_BM_128, fa.FA_TUNE_BM_256], ids=["128", "256"])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+def test_few_keys_before_padding_by_bias(head_dim, dtype, tuning, value):
+    """Sequences of a few keys, the padding behind them scoring far higher but for its bias: a row's reference is one of the keys
+    that count, and the bits are the same whatever finite numbers the padding holds."""
+    n = 700
+    _, q, k, v = draw(83, len(FEW_ENDS), 2, n, head_dim, dtype, qk_gain=1.5)
+    bias = np.zeros((len(FEW_ENDS), n), dtype=np.float32)
+    for b, end in enumerate(FEW_ENDS):
+        bias[b, end:] = value
+    bias = round_to_storage(bias, dtype)
+    scale = 1.0 / np.sqrt(head_dim)
+    want = None
+    for k_times, v_times in ((8.0, 1.0), (4.0, 30.0), (1.0, 1.0), (0.0, 0.0)):
+        k2, v2 = k.copy(), v.copy()
+        for b, end in enumerate(FEW_ENDS):
+            k2[b, :, end:] *= k_times
+            v2[b, :, end:] *= v_times
+        k2, v2 = round_to_storage(k2, dtype), round_to_storage(v2, dtype)
+        if want is None:
+            o_ref, lse_ref = attention_oracle(q, k2, v2, None, scale, -1, -1, key_bias=bias)
+        o, lse = run_ex(q, k2, v2, None, dtype, scale, tuning=tuning, key_bias=bias)
+        check_against(o, lse, o_ref, lse_ref, None, dtype, relative=True, label=f"few keys D{head_dim} {dtype} K {k_times}")
+        want = want or (o, lse)
+        assert np.array_equal(o, want[0]) and np.array_equal(lse, want[1]), k_times
