@@ -2,8 +2,9 @@
 // mapping of the public arguments to the kernel argument block, kernel-shape
 // choice.  Nothing here touches device memory; validation failures return before
 // any HIP call.
-#include <cmath>
+#include <algorithm>
 #include <cfloat>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 
@@ -208,12 +209,17 @@ int choose_live(const fa_params& p) {
 //           but 2 x 384 (288) 7.2 -> 8.9; 8 x 128 110 6.5 -> 5.3, 16 x 128 (512) 8.0 -> 7.4, 256 7.1 -> 5.8, but 5 x 250 (320) 8.4 -> 10.8; 24 x 32 110
 //           4.9 -> 3.8, 8 x 110 (768) 5.1 -> 4.9, but 10 x 128 4.96 -> 5.1; 200 6.2 -> 4.2, 4 x 256 (768) 6.0 -> 5.55, but 5 x 250 6.3 -> 6.6; 512 (384)
 //           6.6 -> 6.1, but 2 x 384 (576) 7.0 -> 7.8.
-int choose_small(const fa_params& p, bool bias_can_be_divided) {
+// Windows: those that the resident and two-phase kernels hold (limits on both sides, five blocks for 32 rows), whose sums and
+// biased scores are rounded as here, and those that reach past the tensor on both sides.  Wider and one-sided ones stay with the
+// kernels whose fp16 row sums are those of unrounded probabilities and whose biased scores are rounded once, and so do heads of K or V
+// that 32-bit offsets do not span.
+int choose_small(const fa_params& p, const FaKernelArgs& a, bool bias_can_be_divided) {
   if (p.rope_cos || (p.key_bias && !bias_can_be_divided)) return 0;
   const bool windowed = p.window_left >= 0 || p.window_right >= 0;
-  const int64_t n = p.max_len, left = p.window_left < 0 || p.window_left > n ? n : p.window_left,
-                right = p.window_right < 0 || p.window_right > n ? n : p.window_right;
-  const int64_t all = (n + 31) / 32, window = (31 + right) / 32 + (left + 31) / 32 + 1, seen = window < all ? window : all;
+  const int64_t n = p.max_len, left = p.window_left < 0 || p.window_left >= n ? -1 : p.window_left,
+                right = p.window_right < 0 || p.window_right >= n ? -1 : p.window_right;
+  const int64_t all = (n + 31) / 32, window = (31 + right) / 32 + (left + 31) / 32 + 1, seen = left >= 0 && window < all ? window : all;
+  if ((left < 0) != (right < 0) || (left >= 0 && (window > 5 || (double)n * (double)std::max(a.ks[2], a.vs[2]) * 2.0 >= 4.0e9))) return 0;
   const int64_t ids = (all * p.heads + 7) / 8 * 8 * p.batch;
   const int d = p.head_dim == 32 ? 0 : (p.head_dim == 64 ? 1 : 2);
   // most ids per shape and head size
@@ -373,7 +379,7 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
     if (split) bm = 32 * (split >> 4);
   }
   int small = 0;
-  if (t_bm == FA_TUNE_BM_AUTO && t_v != FA_TUNE_V_SCALAR && (p->tuning & 0xF000u) == 0) small = choose_small(*p, bias_can_be_divided);
+  if (t_bm == FA_TUNE_BM_AUTO && t_v != FA_TUNE_V_SCALAR && (p->tuning & 0xF000u) == 0) small = choose_small(*p, a, bias_can_be_divided);
   const int tile_rows = bm == 0 ? 128 : bm;   // (the mixed launch sizes its own grid)
   const int64_t n_qtiles = ((int64_t)p->max_len + tile_rows - 1) / tile_rows;
   const int64_t total = n_qtiles * p->batch * p->heads;

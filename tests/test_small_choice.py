@@ -1,0 +1,92 @@
+"""The host's choice of the small kernel, walked on the CPU with stub launchers: which local layers take it, and that
+everything its launch counts on holds."""
+import pathlib
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = pathlib.Path(__file__).resolve().parent.parent
+
+HEAD = r"""
+#include <algorithm>
+#include <climits>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <initializer_list>
+#include "fa.h"
+#include "fa_args.h"
+static FaKernelArgs last;
+int fa_launch_f16(const FaKernelArgs& a, int, int, int, void*) { last = a; return 0; }
+int fa_launch_bf16(const FaKernelArgs& a, int, int, int, void*) { last = a; return 0; }
+int fa_launch_rope_rotate(const FaRopeArgs&, int, void*) { return 0; }
+int fa_static_scratch(void**) { return 0; }
+alignas(16) static char buf[64];
+alignas(16) static float table[64];
+static fa_params call(int d, int b, int h, int n) {
+  fa_params p;
+  std::memset(&p, 0, sizeof p);
+  p.struct_size = sizeof p;
+  p.q = p.k = p.v = p.o = buf;
+  p.scale = 0.125f;
+  p.window_left = p.window_right = -1;
+  p.head_dim = d; p.batch = b; p.heads = h; p.max_len = n;
+  return p;
+}
+#define EXPECT(cond) do { if (!(cond)) { printf("FAILED line %d: %s (d %d b %d h %d n %d window %d %d bias %d: small %x)\n", __LINE__, #cond, \
+  p.head_dim, p.batch, p.heads, p.max_len, p.window_left, p.window_right, p.key_bias != nullptr, last.small); return 1; } } while (0)
+"""
+
+WINDOWS = HEAD + r"""
+// The kernels that local layers have otherwise: two-sided windows of at most five blocks for 32 rows (eight for 128) run kernels that
+// sum rounded fp16 probabilities, as the small kernel does; windows past the tensor on both sides run the global kernel, which does too.
+int main() {
+  long small = 0, calls = 0;
+  for (int d : {32, 64, 128})
+    for (int biased = 0; biased < 2; ++biased)
+      for (int n : {1, 20, 31, 32, 40, 63, 64, 65, 96, 100, 128, 129, 160, 161, 300, 487})
+        for (int left : {-1, 0, 7, 31, 50, 63, 64, 96, 127, 128, 129, 200, 1000, INT_MAX})
+          for (int right : {-1, 0, 7, 31, 40, 64, 96, 127, 128, 129, 200, 1000, INT_MAX}) {
+            if (left < 0 && right < 0) continue;
+            fa_params p = call(d, 1, 3, n);
+            p.key_bias = biased ? buf : nullptr;
+            p.window_left = left; p.window_right = right;
+            EXPECT(fa_fwd_ex(&p) == 0);
+            ++calls;
+            const bool l = left >= 0 && left < n, r = right >= 0 && right < n;   // limits inside the tensor
+            const bool held = l && r && (127 + right) / 32 + (left + 31) / 32 + 1 <= 8;
+            EXPECT(!last.small || held || (!l && !r));
+            EXPECT(!held || last.small == 0x51);   // (three heads: these fit one round)
+            small += last.small != 0;
+          }
+  // heads of K or V that 32-bit offsets do not span: the masked kernel
+  for (int which = 0; which < 2; ++which) {
+    fa_params p = call(64, 1, 3, 487);
+    p.window_left = 63; p.window_right = 64;
+    int64_t* st = which ? p.v_strides : p.k_strides;
+    st[0] = st[1] = 64;
+    st[2] = 4000000;
+    EXPECT(fa_fwd_ex(&p) == 0 && last.small == 0x51);
+    st[2] = 5000000;
+    EXPECT(fa_fwd_ex(&p) == 0 && last.small == 0);
+  }
+  printf("ok %ld of %ld\n", small, calls);
+  return 0;
+}
+"""
+
+
+def run(tmp_path, text):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    src, exe, csrc = tmp_path / "driver.cpp", tmp_path / "driver", ROOT / "paper_2603_12646_amd" / "csrc"
+    src.write_text(text)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", str(ROOT / "include"),
+                    "-I", str(csrc), str(src), str(csrc / "fa_api.cpp"), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
+
+
+def test_local_layers_that_take_the_small_kernel(tmp_path):
+    run(tmp_path, WINDOWS)
