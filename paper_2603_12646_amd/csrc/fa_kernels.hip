@@ -2535,6 +2535,19 @@ __device__ __forceinline__ float row_max64(float x) {
   for (int d = 1; d < 64; d *= 2) x = fmaxf(x, __shfl_xor(x, d));
   return x;
 }
+// Any associative op on integers over the wavefront, without trips through LDS: by turns of rows of 16 lanes, then between rows.
+template <class Op>
+__device__ __forceinline__ int reduce64(int x, Op op) {
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x121, 0xF, 0xF, false));   // row_ror:1, 2, 4, 8
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x122, 0xF, 0xF, false));
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x124, 0xF, 0xF, false));
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x128, 0xF, 0xF, false));
+  float a, b;
+  swap_rows16(__builtin_bit_cast(float, x), a, b);
+  x = op(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b));
+  swap_halves(__builtin_bit_cast(float, x), a, b);
+  return op(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b));
+}
 // maximum / sum over the four lanes that hold one query
 __device__ __forceinline__ float max_quad(float x) {
   float a, b;
@@ -3146,43 +3159,59 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   }
   // BIAS: keys end .. n - 1 have biases of -700 or less (-1010 in the log2 domain), none above top_bias (raw units), and plain: the
   // keys before them have zeros.  While the first K blocks are on their way every wavefront looks through a quarter of the
-  // keys, 512 per step from the end, until it has seen a key that counts and then one with a bias.  In short tensors the search
-  // and the pass over the padding cost more than they give (24 x 512 (400 -) bf16 31.9 -> 34.3 us).
+  // keys, 512 per step from the end, two steps under way, until it has seen a key that counts and has a bias.  Bound: latency, a
+  // round trip to memory per two steps and the instructions behind it; one unaligned load per lane and step, steps of zeros
+  // skipped, reductions without LDS.  us, without a search -> with it (eight loads per lane, one step under way): fp16 16 x 700 (350 -) 39.9 ->
+  // 37.7 (38.2), 12 x 1000 (500 -) 51.8 -> 46.1 (46.7), 1 x 8192 (4096) 150.6 -> 134.4 (137.4), but biases that are no padding, keys 100 - 130
+  // excluded, 16 x 700 38.8 -> 40.5 (41.5), 12 x 1000 52.9 -> 54.2 (55.1), 1 x 8192 215.9 -> 215.8 (220.9).  (In short tensors the search
+  // and the pass over the padding cost more than they give: 24 x 512 (400 -) bf16 31.9 -> 34.3.)
   int end = n;
   float top_bias = -INFINITY;
   bool plain = false;
   int* const found = (int*)(lds_bias + 260);   // [wavefront][last key that counts, first with a bias, smallest cold bias's bits, -]
-  if (BIAS && early) {
+  // (head_dim 32: only what the pass over the padding can cut is of use, from 1024 keys on; 12 x 700 42.6 -> 40.7)
+  const bool search = BIAS && early && n >= (PLAIN_LOOP ? 8 : 1024);
+  if (search) {
     constexpr uint32_t kCold = T::kWideRange ? 0xC42Fu : 0xE178u, kInf = T::kWideRange ? 0xFF80u : 0xFC00u;   // -700, -infinity
-    int last = -1, first_biased = INT32_MAX;
+    int last = -1, first_biased = INT32_MAX;   // of the lane's keys
     uint32_t cold = 0xFFFFu;
-    for (int at = (n - 1) / 512 - ((n - 1) / 512 - wave + NW) % NW; at >= 0 && (PLAIN_LOOP ? first_biased > last : last < 0); at -= NW) {
-      uint32_t raw[8];
-      const int first = 512 * at + 8 * lane;   // the lane's eight keys (those past the end: the last one again)
+    bool seen = false;   // a key that counts and has a bias (head_dim 32: that counts)
+    for (int at = (n - 1) / 512 - ((n - 1) / 512 - wave + NW) % NW; at >= 0 && !__any(seen); at -= 2 * NW) {
+      // two steps under way; a lane's eight keys, at whatever alignment, end inside the sequence
+      struct __attribute__((packed, aligned(2))) Eight { uint32_t w[4]; };
+      auto first = [&](int u) {
+        const int f = 512 * (at - u * NW) + 8 * lane;
+        return f < n - 8 ? f : n - 8;
+      };
+      const bool two = at >= NW;
+      Eight x[2];
+      x[0] = *(const Eight*)(bp + first(0));
+      x[1] = *(const Eight*)(bp + first(two ? 1 : 0));
 #pragma unroll
-      for (int i = 0; i < 8; ++i) raw[i] = bp[first + i < n ? first + i : n - 1];
-      uint32_t warm = 0, biased = 0;
+      for (int u = 0; u < 2; ++u) {
+        if (u == 1 && !two) break;
+        if (!__any(((x[u].w[0] | x[u].w[1] | x[u].w[2] | x[u].w[3]) & 0x7FFF7FFFu) != 0)) {
+          last = max(last, first(u) + 7);
+          seen = seen || !PLAIN_LOOP;
+          continue;
+        }
+        uint32_t warm = 0, biased = 0;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const bool is_cold = raw[i] - kCold <= kInf - kCold;   // (as integers: magnitudes rise; a NaN counts)
-        cold = is_cold && raw[i] < cold ? raw[i] : cold;       // (that of some keys before `end` too: above the others at most)
-        warm |= is_cold ? 0u : 1u << i;
-        biased |= (raw[i] & 0x7FFFu) != 0 ? 1u << i : 0u;
-      }
-      const uint64_t warms = __ballot(warm != 0), biases = __ballot(biased != 0);
-      if (last < 0 && warms) {
-        const int l = 63 - __clzll((long long)warms), key = 512 * at + 8 * l + 31 - __clz(__builtin_amdgcn_readlane((int)warm, l));
-        last = key < n ? key : n - 1;
-      }
-      if (biases) {
-        const int l = __ffsll((unsigned long long)biases) - 1;
-        first_biased = 512 * at + 8 * l + __ffs(__builtin_amdgcn_readlane((int)biased, l)) - 1;
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t raw = i & 1 ? x[u].w[i / 2] >> 16 : x[u].w[i / 2] & 0xFFFFu;
+          const bool is_cold = raw - kCold <= kInf - kCold;   // (as integers: magnitudes rise; a NaN counts)
+          cold = is_cold && raw < cold ? raw : cold;          // (that of some keys before `end` too: above the others at most)
+          warm |= is_cold ? 0u : 1u << i;
+          biased |= (raw & 0x7FFFu) != 0 ? 1u << i : 0u;
+        }
+        if (warm) last = max(last, first(u) + 31 - __clz((int)warm));
+        if (biased) first_biased = min(first_biased, first(u) + __ffs((int)biased) - 1);
+        seen = seen || (PLAIN_LOOP ? warm & biased : warm) != 0;
       }
     }
-    if (__any(cold < 0xFFFFu)) {
-#pragma unroll
-      for (int d = 1; d < 64; d *= 2) cold = min(cold, (uint32_t)__shfl_xor((int)cold, d));
-    }
+    last = reduce64(last, [](int x, int y) { return max(x, y); });
+    first_biased = reduce64(first_biased, [](int x, int y) { return min(x, y); });
+    cold = (uint32_t)reduce64((int)cold, [](int x, int y) { return min(x, y); });
     if (lane == 0) *(int4*)&found[4 * wave] = make_int4(last, first_biased, (int)cold, 0);
   }
   wait_direct_loads();
@@ -3197,7 +3226,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
     }
     __syncthreads();
   }
-  if (BIAS && early) {
+  if (search) {
     int last = -1, first_biased = INT32_MAX, cold = 0xFFFF;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
@@ -3327,7 +3356,7 @@ __device__ __forceinline__ void global_body(const FaKernelArgs& a, const TileCoo
   // largest |k| among them, every row's |q|_1, and its first reference (references only rise); and if their V is finite (0
   // times it is 0).  Showing it takes one pass over their K and V without arithmetic on them.
   // Measured, us, without -> with: 8 x 2048 (1024 -) fp16 121.7 -> 112.6, 16 x 1500 (700 -) 140 -> 134, 1 x 8192 (5000) 8 x 128 239 -> 194,
-  // bf16 1 x 16804 (7024) 1075 -> 654; without padding the search costs 0 - 1 %.
+  // bf16 1 x 16804 (7024) 1075 -> 654.
   // Where the keys that are left have zeros for biases (padding is all there is) the loop runs without a bias: 8 x 2048 fp16
   // 128 rows 108 -> 99.5, 256 rows 115 -> 93.5, (2048) 256 rows 127 -> 108; 16 x 700 (300 -) 38.6 -> 35.6, 1 x 8192 (5000) 163 -> 153; bf16
   // 1 x 16384 (10000) 571 -> 502, 12 x 1000 (500 -) 8 x 128 73 -> 57.

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import paper_2603_12646_amd as fa
-from oracle.attention_oracle import attention_oracle
+from oracle.attention_oracle import attention_oracle, attention_oracle_rows
 from workloads import draw, round_to_storage
 
 from tests.gpu_util import check_against, run_ex
@@ -242,3 +242,33 @@ def test_few_keys_before_padding_by_bias(head_dim, dtype, tuning, value):
         check_against(o, lse, o_ref, lse_ref, None, dtype, relative=True, label=f"few keys D{head_dim} {dtype} K {k_times}")
         want = want or (o, lse)
         assert np.array_equal(o, want[0]) and np.array_equal(lse, want[1]), k_times
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+@pytest.mark.parametrize("n", [641, 1023, 2049, 4611])
+def test_padding_is_found_at_any_alignment_and_step(n, head_dim, dtype):
+    """Bias rows of odd length start at odd 16-bit offsets; the padding begins at the edges of every step of the search, alone, with a
+    hole or a single bias somewhere before it, or with a last key behind it that counts."""
+    ends = sorted({e for s in range(0, n, 512) for e in (s + 1, s + 8, s + 505, s + 512) if e <= n} | {n - 1, n})
+    rng = np.random.default_rng(n)
+    _, q, k, v = draw(91, len(ends), 1, n, head_dim, dtype, qk_gain=1.5)
+    scale = 1.0 / np.sqrt(head_dim)
+    rows = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 6)]))
+    for kind in ("padding", "hole", "bias", "last"):
+        bias = np.zeros((len(ends), n), dtype=np.float32)
+        for b, end in enumerate(ends):
+            if kind == "last":
+                bias[b, max(0, end - 40):n - 1] = -65504.0
+            else:
+                bias[b, end:] = -65504.0
+            if kind == "hole":
+                bias[b, rng.integers(0, end) // 2] = -np.inf if end > 1 else 0.0
+            if kind == "bias":
+                bias[b, rng.integers(0, end)] = 2.5
+        bias = round_to_storage(bias, dtype)
+        o, lse = run_ex(q, k, v, None, dtype, scale, tuning=fa.FA_TUNE_BM_128, key_bias=bias)
+        for b in range(len(ends)):
+            o_ref, lse_ref = attention_oracle_rows(q, k, v, b, 0, rows, n, scale, key_bias=bias)
+            check_against(o[b:b + 1, :, rows], lse[b:b + 1, :, rows], o_ref[None, None], lse_ref[None, None], None, dtype, relative=True,
+                          label=f"{kind} D{head_dim} {dtype} end {ends[b]} of {n}")
