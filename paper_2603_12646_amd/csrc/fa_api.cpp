@@ -120,12 +120,12 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
   if (allow_mixed && (w128 <= 768 || w128 > 1024) && mixed_fits(p)) return 0;
   // What a block of 128-row workgroups costs more: plain calls, and head_dim 32, 1.08.  A rotation in the call is done once per
   // query tile (us, 12 x 64, 128 -> 256 rows: 7 x 2048 138 -> 118, 12 x 2048 218 -> 193, but 6 x 2048 in a thin second round
-  // of the larger ones 105 -> 115).  A key bias is padding as a rule, whose kernels make one pass over it per query tile: us,
-  // 12 x 64, 128 -> 256 rows, fp16 8 x 2048 (1024 -) 102 -> 97, 16 x 1024 61.5 -> 58.9, 12 x 3000 297 -> 270, but 12 x 1000 46 -> 49,
-  // 1 x 8192 155 -> 160, 2 x 12000 737 -> 735; bf16 8 x 2048 115 -> 107, 1 x 16K 553 -> 466, 1 x 24000 1131 -> 1000.  (Other
-  // biases lean to the smaller tiles in fp16: keys 100 - 130 excluded, 8 x 2048 110 -> 115, bf16 126 -> 122.)
-  const double rel_bias = p.dtype == FA_DTYPE_F16 ? 1.12 : 1.17;
-  const double rel = p.head_dim == 32 ? 1.08 : (p.rope_cos ? 1.2 : (p.key_bias ? rel_bias : 1.08));
+  // of the larger ones 105 -> 115).  A key bias is padding as a rule, whose kernels make one pass over it per query tile; other
+  // biases, which the host cannot tell from it, gain less by the larger tiles, and the line is where they do not lose: us, 12 x 64,
+  // 128 -> 256 rows, padding from the half on, keys 100 - 130 excluded, fp16: 8 x 2048 105 -> 95, 122 -> 117; 16 x 1024 59.1 -> 55.1,
+  // 67.4 -> 65.7; 20 x 2100 (1.13 here) 272 -> 246, 328 -> 311; 2 x 12000 (1.16) 742 -> 743, 945 -> 966; 12 x 1000 (1.23) 46.7 -> 51.0, 55 -> 64;
+  // bf16: 8 x 2048 99 -> 92, 122 -> 115; 20 x 2100 264 -> 244, 326 -> 312; 2 x 12000 743 -> 729, 956 -> 964; 1 x 16384 521 -> 442, 882 -> 839.
+  const double rel = p.head_dim == 32 ? 1.08 : (p.rope_cos ? 1.2 : (p.key_bias ? 1.15 : 1.08));
   const double c128 = shape_cost(w128, 3, 4, rel), c256 = shape_cost(w256, 2, 8, 1.0),
                c512 = shape_cost(w512, 1, 16, 0.98);
   if (c512 < c256 && c512 < c128 && w512 <= 256) return 512;   // 512 only where one round holds the call

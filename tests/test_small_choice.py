@@ -1,5 +1,4 @@
-"""The host's choice of the small kernel, walked on the CPU with stub launchers: which local layers take it, and that
-everything its launch counts on holds."""
+"""The host's choice of the small kernel and of the tile rows of a key bias, walked on the CPU with stub launchers."""
 import pathlib
 import shutil
 import subprocess
@@ -18,8 +17,9 @@ HEAD = r"""
 #include "fa.h"
 #include "fa_args.h"
 static FaKernelArgs last;
-int fa_launch_f16(const FaKernelArgs& a, int, int, int, void*) { last = a; return 0; }
-int fa_launch_bf16(const FaKernelArgs& a, int, int, int, void*) { last = a; return 0; }
+static int last_bm;
+int fa_launch_f16(const FaKernelArgs& a, int bm, int, int, void*) { last = a; last_bm = bm; return 0; }
+int fa_launch_bf16(const FaKernelArgs& a, int bm, int, int, void*) { last = a; last_bm = bm; return 0; }
 int fa_launch_rope_rotate(const FaRopeArgs&, int, void*) { return 0; }
 int fa_static_scratch(void**) { return 0; }
 alignas(16) static char buf[64];
@@ -76,6 +76,22 @@ int main() {
 }
 """
 
+BIAS_ROWS = HEAD + r"""
+// 12 heads of 64: the larger tiles where no kind of bias loses by them, in both types
+int main() {
+  struct { int b, n, rows; } want[] = {{8, 2048, 256}, {16, 1024, 256}, {20, 2100, 256}, {10, 2048, 256}, {1, 16384, 256}, {4, 2500, 256},
+                                       {2, 12000, 128}, {12, 1000, 128}, {6, 2048, 128}, {1, 8192, 128}, {9, 1200, 128}};
+  for (auto& w : want)
+    for (int dtype : {FA_DTYPE_F16, FA_DTYPE_BF16}) {
+      fa_params p = call(64, w.b, 12, w.n);
+      p.key_bias = buf; p.dtype = dtype;
+      EXPECT(fa_fwd_ex(&p) == 0 && last_bm == w.rows);
+    }
+  printf("ok\n");
+  return 0;
+}
+"""
+
 
 def run(tmp_path, text):
     if shutil.which("g++") is None:
@@ -85,8 +101,12 @@ def run(tmp_path, text):
     subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", str(ROOT / "include"),
                     "-I", str(csrc), str(src), str(csrc / "fa_api.cpp"), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
-    assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
+    assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
 
 
 def test_local_layers_that_take_the_small_kernel(tmp_path):
     run(tmp_path, WINDOWS)
+
+
+def test_tile_rows_of_a_key_bias(tmp_path):
+    run(tmp_path, BIAS_ROWS)
