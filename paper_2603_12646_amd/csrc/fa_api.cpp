@@ -191,11 +191,15 @@ int choose_split(const fa_params& p) {
 
 // Tiles per head of the split kernel whose rows follow the length, or 0.  One sequence whose tensor is too long for one round of
 // 96-row workgroups, but not for one of 128-row ones: it goes before the 64-row shape, of which up to two share a unit
-// while others have one.  us, 12 x 64, bf16, fp16, that shape -> it: 1000 of 2048 14.3 -> 11.9, 13.6 -> 11.9; 1340 17.0 -> 13.5, 16.0 -> 13.4;
-// 1400 17.05 -> 15.7, 16.1 -> 15.8; 1900 21.1 -> 18.8, 20.2 -> 19.1; 2040 22.2 -> 22.0, 21.3 -> 22.1; 2300 of 2500 24.9 -> 24.3, 24.2 -> 24.6;
-// 2600 29.2 -> 27.9, 28.5 -> 28.4.  (Shorter tensors: the shapes above need not wait for the length; 1000 of 1024 10.9, here 11.9.)
+// while others have one.  From 2000 tokens on, as that shape in bf16: below (more than 12 heads) full fp16 sequences lose, and bf16
+// runs the 128-row kernel.  us, that shape -> it, bf16, fp16:
+//   12 heads  1024 of 2048 13.7 -> 11.4, 13.8 -> 11.9; 1331 16.9 -> 12.8, 16.0 -> 13.0; 1638 19.0 -> 16.6, 17.9 -> 16.5; 1904 20.9 -> 18.1, 20.0 -> 18.3; 2048
+//             22.2 -> 21.3, 21.1 -> 21.2; 2048 of 2560 22.3 -> 21.3, 21.2 -> 21.1; 2560 27.5 -> 26.6, 27.1 -> 27.0
+//   8         960 of 3200 9.9 -> 10.3, 10.3 -> 10.4; 1600 13.3 -> 13.6, 13.9 -> 13.7; 2080 22.6 -> 18.4, 21.1 -> 18.2; 3200 31.3 -> 29.2, 30.2 -> 29.4
+//   16        1000 of 2000 14.5 -> 12.0, 13.9 -> 11.9; 1600 18.1 -> 18.6, 17.6 -> 18.5; 2000 23.6 -> 22.6, 23.5 -> 22.9; fp16 1600 of 1600 17.7 -> 18.5
+//   2         7763 of 12321 1.6 times as fast, 1.45; 14336 of 14336 1.04, 0.98
 int choose_live(const fa_params& p) {
-  if (p.head_dim != 64 || p.key_bias || !p.seq_lens || p.batch != 1 || p.heads > 256) return 0;
+  if (p.head_dim != 64 || p.key_bias || !p.seq_lens || p.batch != 1 || p.heads > 256 || p.max_len < 2000) return 0;
   const int per = 256 / p.heads;
   return (p.max_len + 127) / 128 <= per && (p.max_len + 95) / 96 > per ? per : 0;
 }

@@ -1,4 +1,4 @@
-"""The host's choice of the small kernel and of the tile rows of a key bias, walked on the CPU with stub launchers."""
+"""The host's choice of the small kernel, of the split kernel whose rows follow the length and of the tile rows of a key bias, walked on the CPU with stub launchers."""
 import pathlib
 import shutil
 import subprocess
@@ -92,6 +92,38 @@ int main() {
 }
 """
 
+LIVE = HEAD + r"""
+int main() {
+  long taken = 0;
+  for (int h = 1; h <= 300; ++h)
+    for (int n = 1; n < 40000; n += 1 + n / 50)
+      for (int dtype : {FA_DTYPE_F16, FA_DTYPE_BF16}) {
+        fa_params p = call(64, 1, h, n);
+        p.dtype = dtype;
+        p.seq_lens = (const int32_t*)table;
+        EXPECT(fa_fwd_ex(&p) == 0);
+        const int live = last.live_tiles;
+        if (live) {
+          // one round, every row of the tensor in a tile of 128 rows, and tiles of 96 rows would not do
+          EXPECT(live > 0 && live * h <= 256 && (long)live * 128 >= n && (long)live * 96 < n && n >= 2000);
+          ++taken;
+          p.batch = 2; EXPECT(fa_fwd_ex(&p) == 0 && !last.live_tiles); p.batch = 1;
+          p.seq_lens = nullptr; EXPECT(fa_fwd_ex(&p) == 0 && !last.live_tiles); p.seq_lens = (const int32_t*)table;
+          p.key_bias = buf; EXPECT(fa_fwd_ex(&p) == 0 && !last.live_tiles); p.key_bias = nullptr;
+          p.rope_cos = p.rope_sin = table; EXPECT(fa_fwd_ex(&p) == 0 && !last.live_tiles); p.rope_cos = p.rope_sin = nullptr;
+          p.window_left = 63; p.window_right = 64; EXPECT(fa_fwd_ex(&p) == 0 && !last.live_tiles); p.window_left = p.window_right = -1;
+          p.tuning = FA_TUNE_BM_128; EXPECT(fa_fwd_ex(&p) == 0 && !last.live_tiles); p.tuning = 0;
+          p.head_dim = 128; EXPECT(fa_fwd_ex(&p) == 0 && !last.live_tiles); p.head_dim = 64;
+        }
+        // (bf16: the split kernel's own lines have left the call to it)
+        const int per = h <= 256 ? 256 / h : 0;
+        EXPECT((live != 0) == (per && (n + 127) / 128 <= per && (n + 95) / 96 > per && n >= 2000));
+      }
+  printf("ok %ld\n", taken);
+  return 0;
+}
+"""
+
 
 def run(tmp_path, text):
     if shutil.which("g++") is None:
@@ -110,3 +142,7 @@ def test_local_layers_that_take_the_small_kernel(tmp_path):
 
 def test_tile_rows_of_a_key_bias(tmp_path):
     run(tmp_path, BIAS_ROWS)
+
+
+def test_rows_by_the_length(tmp_path):
+    run(tmp_path, LIVE)
