@@ -208,10 +208,11 @@ int choose_live(const fa_params& p) {
 // blocks as the shape holds, and fit one round of as many workgroups per unit as their LDS allows.  It goes before the kernel
 // that the rules above choose.  us, fp16, the kernels before -> it:
 //   local   12 x 64 200 tokens 6.7 -> 4.6, 487 6.9 -> 4.7, 690 (264 ids) 6.9 -> 5.0, 1300 (492) 7.05 -> 5.6, but 1600 7.1 -> 7.75; 8 x 128 487
-//           8.6 -> 5.9, 1000 (256) 8.7 -> 6.0, but 1300 8.95 -> 10.0; 24 x 32 487 5.5 -> 4.6, 1000 (768) 5.6 -> 5.3, but 1600 6.2 -> 6.6.
+//           8.6 -> 5.9, 1000 (256) 8.7 -> 6.0, but 1300 8.95 -> 10.0; 24 x 32 (in a graph, fp16, bf16) 300 5.5 -> 4.0, 5.5 -> 4.05; 700 (528) 5.6 -> 5.3,
+//           5.6 -> 5.3, but 800 (600) 5.2 -> 5.65, 5.1 -> 5.9; 1000 (768) 5.5 -> 5.7, 5.6 -> 6.2.
 //   global  12 x 64 110 tokens 4.8 -> 4.3, 16 x 128 (768) 6.7 -> 6.2, 200 5.4 -> 4.8, 5 x 250 (480) 6.55 -> 5.9, but 6 x 250 7.6 -> 8.4; 512 6.3 -> 5.5,
 //           but 2 x 384 (288) 7.2 -> 8.9; 8 x 128 110 6.5 -> 5.3, 16 x 128 (512) 8.0 -> 7.4, 256 7.1 -> 5.8, but 5 x 250 (320) 8.4 -> 10.8; 24 x 32 110
-//           4.9 -> 3.8, 8 x 110 (768) 5.1 -> 4.9, but 10 x 128 4.96 -> 5.1; 200 6.2 -> 4.2, 4 x 256 (768) 6.0 -> 5.55, but 5 x 250 6.3 -> 6.6; 512 (384)
+//           4.9 -> 3.8, 7 x 110 (672; graph) 4.85 -> 4.7, but bf16 8 x 128 (768) 4.8 -> 4.9; 200 6.2 -> 4.2, 4 x 256 (768) 6.0 -> 5.55, but 5 x 250 6.3 -> 6.6; 512 (384)
 //           6.6 -> 6.1, but 2 x 384 (576) 7.0 -> 7.8.
 // Windows: those that the resident and two-phase kernels hold (limits on both sides, five blocks for 32 rows), whose sums and
 // biased scores are rounded as here, and those that reach past the tensor on both sides.  Wider and one-sided ones stay with the
@@ -227,7 +228,7 @@ int choose_small(const fa_params& p, const FaKernelArgs& a, bool bias_can_be_div
   const int64_t ids = (all * p.heads + 7) / 8 * 8 * p.batch;
   const int d = p.head_dim == 32 ? 0 : (p.head_dim == 64 ? 1 : 2);
   // most ids per shape and head size
-  static constexpr int k41[3] = {768, 768, 512}, k42[3] = {768, 512, 256}, k51[3] = {768, 512, 256}, k82[3] = {384, 256, 0};
+  static constexpr int k41[3] = {672, 768, 512}, k42[3] = {768, 512, 256}, k51[3] = {528, 512, 256}, k82[3] = {384, 256, 0};
   if (windowed) return seen <= 5 && ids <= k51[d] ? 0x51 : 0;
   if (seen <= 4) return ids <= k41[d] ? 0x41 : 0;
   if (seen <= 8) return ids <= k42[d] ? 0x42 : 0;

@@ -92,6 +92,28 @@ int main() {
 }
 """
 
+SIZES = HEAD + r"""
+// The last call of each shape and head size, of a model's 24, 12 and 8 heads, and the first past it
+int main() {
+  struct { int d, b, n, window, small; } want[] = {
+      {32, 1, 704, 1, 0x51}, {32, 1, 705, 1, 0}, {32, 1, 512, 0, 0x82}, {32, 2, 384, 0, 0}, {32, 4, 256, 0, 0x42}, {32, 5, 256, 0, 0},
+      {32, 7, 128, 0, 0x41}, {32, 8, 128, 0, 0}, {64, 1, 1344, 1, 0x51}, {64, 1, 1376, 1, 0}, {64, 1, 512, 0, 0x82}, {64, 1, 513, 0, 0},
+      {64, 5, 256, 0, 0x42}, {64, 6, 256, 0, 0}, {64, 16, 128, 0, 0x41}, {64, 17, 128, 0, 0}, {128, 1, 1024, 1, 0x51}, {128, 1, 1025, 1, 0},
+      {128, 4, 256, 0, 0x42}, {128, 1, 257, 0, 0}, {128, 16, 128, 0, 0x41}, {128, 17, 128, 0, 0}};
+  for (auto& w : want)
+    for (int dtype : {FA_DTYPE_F16, FA_DTYPE_BF16})
+      for (int lengths = 0; lengths < 2; ++lengths) {
+        fa_params p = call(w.d, w.b, 768 / (w.d == 128 ? 96 : w.d), w.n);
+        if (w.window) p.window_left = 63, p.window_right = 64;
+        p.dtype = dtype;
+        p.seq_lens = lengths ? (const int32_t*)table : nullptr;
+        EXPECT(fa_fwd_ex(&p) == 0 && last.small == w.small);
+      }
+  printf("ok\n");
+  return 0;
+}
+"""
+
 LIVE = HEAD + r"""
 int main() {
   long taken = 0;
@@ -138,6 +160,10 @@ def run(tmp_path, text):
 
 def test_local_layers_that_take_the_small_kernel(tmp_path):
     run(tmp_path, WINDOWS)
+
+
+def test_last_calls_of_the_small_kernel(tmp_path):
+    run(tmp_path, SIZES)
 
 
 def test_tile_rows_of_a_key_bias(tmp_path):
