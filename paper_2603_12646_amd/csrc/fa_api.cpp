@@ -136,16 +136,15 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
 // NK wavefronts that split the keys), or 0 where the other kernels are faster.  A shape is taken only where the call's
 // workgroups fit the 256 units in one round - a second, thin round costs as much as the first.  What has to fit are the
 // IDS: every XCD takes an eighth of each batch element's tiles, rounded up, so 3 x 12 heads x 197 tokens are 252 tiles of 32
-// rows but 264 ids (7.7 us in 128 rows, 11.0 in 32).  The host knows max_len only, not the lengths.  All lines below are
+// rows but 264 ids.  The host knows max_len only, not the lengths.  (The small kernel has taken the smallest calls by then: of head
+// size 64 those of up to 512 tokens and 256 ids of 32 rows, or 256 tokens and 512.)  All lines below are
 // from a sweep of 1 - 16 sequences x 4 - 32 heads x 65 - 4096 tokens, full and at 0.7 and 0.45 of max_len, in both types;
 // us per call, the 128 / 256-row kernels -> the shape:
-//   head_dim 64   32 rows on four wavefronts (two workgroups per unit): 12 heads x 110 tokens 6.0 -> 4.8, 200 6.7 -> 5.3,
-//                 380 8.3 -> 6.0, 230 of 512 5.4 (on eight 6.1); on eight from 640, 4 heads x 1024 13.8 -> 8.0, and without
-//                 lengths, where every row is there, from 385: 512 9.0 -> 6.3 (on four 6.3 - 6.4), 540 6.9 (7.2), but 384
-//                 6.2 (5.8).  At 64 tokens there is nothing to split.
+//   head_dim 64   32 rows on eight wavefronts, 4 heads x 1024 13.8 -> 8.0; on four (two workgroups per unit) below 640 tokens where
+//                 lengths are given: 540 7.2 (on eight, where every row is there, 6.9).
 //                 64 rows: on four wavefronts, three workgroups per unit, 850 12.5 -> 10.4, 1024 13.6 -> 10.9, 1250
-//                 16.1 -> 12.4; on eight where the workgroups are short, 3 x 230 7.3 -> 6.5 (four: 6.8), or nearly alone, 4
-//                 heads x 3500 36.4 -> 23.0 (26.3).
+//                 16.1 -> 12.4; on eight where the workgroups are short, 2 x 400 7.9 (four: 8.1), 30
+//                 heads x 330 7.3 (7.6), or nearly alone, 4 heads x 3500 36.4 -> 23.0 (26.3).
 //                 96 rows (bf16): 1440 19.0 -> 17.4, 1750 21.7 -> 18.8, 2 x 880 13.5 -> 13.1; one sequence of 1000 tokens
 //                 in a tensor of 2000 loses (12.3 -> 13.0), and of 400 in 880 more (8.9 -> 10.0), where a batch does not.
 //                 64 rows, three per unit, beyond 256: where the 128-row kernel fits one round as well it pays for long
@@ -155,9 +154,9 @@ int choose_bm(const fa_params& p, bool allow_mixed) {
 //                 2900 49 -> 42; 6 x 400 12.0 -> 12.7).
 //                 With a key bias, whose pipelined kernel is slower: 64 rows 600 12.6 -> 9.4, 96 rows 4 x 460 11.7 -> 10.7,
 //                 128 rows 2400 43 -> 30, but 4 x 512 10.9 -> 11.5.
-//   head_dim 128  32 rows: 512 13.6 -> 8.4, 105 8.1 -> 6.4;  64 rows: 2048 37 -> 24;  128 rows: 4 x 640
+//   head_dim 128  32 rows: 512 13.6 -> 8.4;  64 rows: 2048 37 -> 24;  128 rows: 4 x 640
 //                 16.8 -> 15.5, 4096 75 -> 65, but 8 x 512 15.6 -> 15.8.  With a bias 16 x 256 13.5 -> 12.3.
-//   head_dim 32   32 rows (two workgroups per unit; with a bias one): 24 heads x 512 7.8 -> 7.0, 1024 11.8 -> 9.4 at 12 heads;
+//   head_dim 32   32 rows (two workgroups per unit; with a bias one): 12 heads x 1024 11.8 -> 9.4;
 //                 64 rows, three per unit, where the 128-row kernel has its thin second round: 1500 22.5 -> 20.7, 2048
 //                 29.3 -> 26.7, but 2 x 700 11.9 -> 12.7.  With a bias 12 heads x 600 11.0 -> 7.2 in 32 rows, 1024
 //                 15.6 -> 11.9 in 64; 2 x 24 heads x 470 9.7 -> 10.4.
@@ -167,12 +166,12 @@ int choose_split(const fa_params& p) {
   const bool bias = p.key_bias != nullptr, fp16 = p.dtype == FA_DTYPE_F16, one = p.batch == 1;
   if (n <= 64) return 0;
   if (p.head_dim == 64 && bias) {
-    if (ids(64) <= 256) return ids(32) <= 256 && n > 128 ? 0x18 : 0x24;
+    if (ids(64) <= 256) return ids(32) <= 256 ? 0x18 : 0x24;
     if (ids(96) <= 256 && n >= 448) return 0x34;
     if (ids(128) <= 256 && n >= 560) return 0x42;
   } else if (p.head_dim == 64) {
-    if (ids(32) <= 256) return n < (p.seq_lens ? 640 : 385) ? 0x14 : 0x18;
-    if (ids(64) <= 256) return n >= 1600 || (n >= 200 && n < 560) ? 0x24 : 0x22;
+    if (ids(32) <= 256) return p.seq_lens && n < 640 ? 0x14 : 0x18;
+    if (ids(64) <= 256) return n >= 1600 || n < 560 ? 0x24 : 0x22;
     if (ids(96) <= 256 && n >= (one ? 1200 : 860)) return 0x34;
     if (ids(128) <= 256) return n >= (fp16 ? (one ? 1000 : 700) : (one ? 2000 : 1100)) ? 0x22 : 0;
     if (ids(64) <= 768 && n >= 480) return 0x22;
@@ -374,17 +373,19 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
     if (t_bm == FA_TUNE_BM_128) bm = 128;
     if (t_bm == FA_TUNE_BM_256) bm = 256;
   }
-  // Split kernel (a workgroup's wavefronts split the keys as well as the rows): global layers too small for the shapes
-  // above to give every SIMD two wavefronts.  Its key bias sits in LDS.
-  int split = 0;
-  if (!windowed && !p->rope_cos && t_v != FA_TUNE_V_SCALAR && !bias_on_masked_kernel &&
+  // The kernels of the smallest calls, at most one of them.  Split kernel (a workgroup's wavefronts split the keys as well as the
+  // rows): global layers too small for the shapes above to give every SIMD two wavefronts.  Its key bias sits in LDS.
+  int small = 0, live = 0, split = 0;
+  if (t_bm == FA_TUNE_BM_AUTO && t_v != FA_TUNE_V_SCALAR && (!windowed || (p->tuning & 0xF000u) == 0)) small = choose_small(*p, a, bias_can_be_divided);
+  if (small) bm = 32;
+  if (!small && !windowed && !p->rope_cos && t_v != FA_TUNE_V_SCALAR && !bias_on_masked_kernel &&
       (!p->key_bias || p->max_len <= kSplitBiasKeys)) {
     if (t_bm == FA_TUNE_BM_AUTO) split = choose_split(*p);
     if (t_bm == FA_TUNE_BM_32 && p->head_dim == 64 && !p->key_bias) split = 0x18;
+    if (t_bm == FA_TUNE_BM_AUTO && split) live = choose_live(*p);
+    if (live) split = 0;
     if (split) bm = 32 * (split >> 4);
   }
-  int small = 0;
-  if (t_bm == FA_TUNE_BM_AUTO && t_v != FA_TUNE_V_SCALAR && (p->tuning & 0xF000u) == 0) small = choose_small(*p, a, bias_can_be_divided);
   const int tile_rows = bm == 0 ? 128 : bm;   // (the mixed launch sizes its own grid)
   const int64_t n_qtiles = ((int64_t)p->max_len + tile_rows - 1) / tile_rows;
   const int64_t total = n_qtiles * p->batch * p->heads;
@@ -423,7 +424,7 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   // 10.0 -> 9.3, 8K 17.1 -> 16.3 - and heads of 32 side by side in a row, two of which share a 128-byte line: 32K packed 67 -> 53,
   // 2K 7.1 -> 6.8, 32 x 1024 (8 tiles) 51.8 -> 53.1.  (Other calls: 8K head_dim 64 12.7 -> 12.9, 32K 41.9 -> 48.1; a rotation at
   // head_dim 32 on dense tensors with padding, where the padding tiles then all come last: 16000 of 32768 48.5 -> 50.3.)
-  a.heads_first = a.map_xcd && windowed &&
+  a.heads_first = a.map_xcd && windowed && !small &&
                   ((p->rope_cos && n_qtiles >= (p->head_dim == 128 ? 11 : 16) && (p->head_dim != 32 || !p->seq_lens)) || (p->head_dim == 32 && n_qtiles >= 16 && a.ks[1] == 32 && a.ks[2] >= 64));
   // Ragged batches on the pipelined kernel: long sequences first, so that the short tiles fill the last round.  Finding the
   // r-th sequence takes a workgroup 1 us before its first load, which short tiles do not earn back: us, 12 x 64, as they
@@ -436,7 +437,7 @@ int fwd_ex_impl(const fa_params* p_in, void* scratch, size_t scratch_bytes, bool
   a.xcd_per = (int32_t)per;
   a.split = split;
   a.small = small;
-  a.live_tiles = t_bm == FA_TUNE_BM_AUTO && split && !small ? choose_live(*p) : 0;
+  a.live_tiles = live;
   // (a launch of at most two workgroups per unit has nothing else to hide the read of the sequence length behind)
   a.late_n = total <= 512;
   a.mix_ids_a = bm == 0 ? fa_mix_ids((int)n_qtiles, p->heads) : 0;

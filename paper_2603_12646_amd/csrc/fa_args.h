@@ -36,8 +36,8 @@ struct FaKernelArgs {
   int32_t late_n;   // split kernel: loads are issued before the sequence length is looked at
   int32_t mix_ids_a; // mixed-shape kernel: workgroup ids reserved for 256-row workgroups (fa_mix_map.h)
   // (for the launcher alone, behind what the kernels read)
-  int32_t small;    // small kernel: 16 * wavefronts + key blocks of each (32 query rows per workgroup); goes before the kernel and rows chosen otherwise
-  int32_t live_tiles; // split kernel whose tile rows follow the sequence's length: tiles per head; goes before the kernel chosen otherwise
+  int32_t small;    // small kernel: 16 * wavefronts + key blocks of each (32 query rows per workgroup), 0 = another kernel
+  int32_t live_tiles; // split kernel whose tile rows follow the sequence's length: tiles per head, 0 = another kernel
 };
 
 // Rotation of q and k ahead of a global layer (rows of both tensors rotated by position and

@@ -1708,19 +1708,21 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 4) void fa_fwd_window_twop
 // wavefront per SIMD, 0.245 at two; the bare instruction mix takes 0.22 - 0.24).  Hence
 //   * everything is fetched by direct loads in an order the waits can count on (Q, K0, K1, then
 //     pairs (K of step t + 2, V of step t)), so the first product waits for Q and K0 only, and
-//     loads run P - 2 steps ahead of their use; a call with at most P steps requests everything
-//     up front;
+//     loads run P - 2 steps ahead of their use (double steps, below, wait for all that the two before
+//     requested); a call with at most P steps requests everything up front;
 //   * the requests are issued before the sequence length is looked at (late_n), where the launch
 //     is so small that no other workgroup hides that read;
 //   * the steady part of the loop is unrolled over the ring and free of branches (0.30 us per unit at one
 //     wavefront per SIMD against 0.52 for the general step, whose ~100 scalar instructions a lone wavefront pays); with four
-//     ring slots two steps share a barrier (twelve wavefronts, us: 1500 tokens 15.7 -> 15.1, 2 x 950 13.5 -> 13.2, 1900 18.9 -> 18.5);
+//     ring slots two steps share a barrier, but at head_dim 128, which has no registers for it (twelve wavefronts, us: 1500 tokens
+//     15.7 -> 15.1, 2 x 950 13.5 -> 13.2, 1900 18.9 -> 18.5);
 //   * the ragged last block is a masked step like any other: nothing is staged a second time;
 //   * the NK partial (reference, sum, accumulator) states are merged through LDS with the
 //     split / merge identity of the online softmax, every wavefront finishing 1/NK of the output
 //     columns.
-// Measured, fp16, 12 x 64, us per call against the 128-row kernel (512: against four wavefronts without a shared Q):
-// 512 tokens 7.6 -> 6.3, 1024 14.7 -> 10.9, 2000 25.0 -> 21.0, 3072 48.3 -> 43.7; 8 x 128, 2048 tokens 39 -> 24.
+// Measured, fp16, 12 x 64, us per call against the 128-row kernel: 1024 tokens 14.7 -> 10.9, 2000 25.0 -> 21.0, 3072 48.3 -> 43.7; 8 x 128,
+// 2048 tokens 39 -> 24.  (As a function of its own, which the kernel below shares, the body of a shape is scheduled otherwise: 64 rows on
+// four wavefronts, 1000 tokens, as a kernel -> so, bf16 10.9 -> 11.2, fp16 11.3 -> 11.1.)
 // ======================================================================================
 template <class T, int D, bool BIAS>
 struct SplitWave {
@@ -2247,7 +2249,7 @@ __global__ __launch_bounds__(NQ * NK * 64, WPS) void fa_fwd_split_kernel(const F
 // The same for ONE sequence in a tensor that is longer (head_dim 64): the tile's rows and the key split follow the sequence's
 // length, which the host does not know.  A workgroup has twelve wavefronts and a compute unit to itself; every head has
 // a.n_qtiles of them (heads * n_qtiles <= 256), and they are 64, 96 or 128 rows high, as few as hold the sequence.  (The host has
-// to lay out tiles for the whole tensor, whose dead ones delay live ones: 1900 of 2048 tokens, 12 heads, 21.1 -> 18.8 us.)
+// to lay out tiles for the whole tensor, whose dead ones delay live ones: 1904 of 2048 tokens, 12 heads, bf16 20.9 -> 18.1 us.)
 // Rows past what the tiles cover are padding: zeros.
 template <class T>
 __global__ __launch_bounds__(768, 3) void fa_fwd_split_live_kernel(const FaKernelArgs a) {
@@ -2291,8 +2293,8 @@ __global__ __launch_bounds__(768, 3) void fa_fwd_split_live_kernel(const FaKerne
 // Bound: latency, the chain launch - arguments - loads - blocks - merge - store.  So everything is requested at once by direct
 // loads, the sequence length is looked at after that, there is no running reference, and a lane stores its eight bytes of a
 // row as they are: the detour through a patch for whole rows costs a barrier and a trip through LDS.  (A copy of Q per
-// wavefront instead of one behind a barrier is no faster, and its LDS halves the calls that fit a round.)  12 x 64, us, back to back
-// (the host takes 5.3 for a call): local 487 tokens 6.9 on the resident kernel -> 4.7, global 512 6.3 on
+// wavefront instead of one behind a barrier is no faster, and its LDS halves the calls that fit a round.)  12 x 64, us on the GPU alone
+// (in a graph; the host takes 5 for a call): local 487 tokens 6.6 on the resident kernel -> 4.5, global 512 6.3 on
 // the split kernel -> 5.5 (one block on each of sixteen wavefronts: 6.4, twice the partial results).
 // ======================================================================================
 template <class T, int D, int NK, int NB, bool BIAS>
@@ -3719,6 +3721,7 @@ Kernel small_kernel(int head_dim, int shape) {
 
 template <class T>
 int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stream) {
+  // (a grid of its own, whatever rows the host has laid out)
   if (a.live_tiles) {
     // one workgroup per unit, whatever the length turns out to be
     FaKernelArgs args = a;
@@ -3729,19 +3732,6 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
     void* argv[] = {&args};
     return (int)hipLaunchKernel((const void*)fa_fwd_split_live_kernel<T>, dim3(a.map_xcd ? 8u * (unsigned)args.xcd_per : (unsigned)args.total_tiles),
                                 dim3(768), argv, 0, (hipStream_t)stream);
-  }
-  if (a.small) {
-    // 32-row tiles, whatever rows the call was going to have (the host has checked that its blocks fit the shape)
-    FaKernelArgs args = a;
-    args.n_qtiles = (a.max_len + 31) / 32;
-    args.total_tiles = args.n_qtiles * a.heads * a.batch;
-    args.xcd_per = (args.n_qtiles * a.heads + 7) / 8;
-    args.heads_first = args.longest_first = 0;
-    const Kernel kern = a.key_bias ? small_kernel<T, true>(a.head_dim, a.small) : small_kernel<T, false>(a.head_dim, a.small);
-    if (!kern) return (int)hipErrorInvalidValue;
-    void* argv[] = {&args};
-    return (int)hipLaunchKernel((const void*)kern, dim3(a.map_xcd ? 8u * (unsigned)args.xcd_per * (unsigned)a.batch : (unsigned)args.total_tiles),
-                                dim3(64u * (unsigned)(a.small >> 4)), argv, 0, (hipStream_t)stream);
   }
   unsigned grid = (unsigned)a.total_tiles;
   if (a.map_xcd) grid = 8u * (unsigned)a.xcd_per * (unsigned)a.batch;
@@ -3766,7 +3756,13 @@ int launch(const FaKernelArgs& a, int bm, int v_path, int win_kernel, void* stre
   // against 7.8 us, 4K equal, 8K 17.3 against 14.9 us, 32K 43 against 37 us); it exists for
   // head_dim 64 only.
   const bool latency_bound = a.head_dim == kD && a.total_tiles <= 384;
-  if (a.split) {
+  if (a.small) {
+    // (the host has checked that the blocks fit the shape, and that it exists for the head size)
+    kern = a.key_bias ? small_kernel<T, true>(a.head_dim, a.small) : small_kernel<T, false>(a.head_dim, a.small);
+    threads = 64u * (unsigned)(a.small >> 4);
+    rows = 32;
+    if (!kern) return (int)hipErrorInvalidValue;
+  } else if (a.split) {
     // (the host has checked that this shape exists for the head size)
     kern = a.key_bias ? split_kernel<T, true>(a.head_dim, a.split) : split_kernel<T, false>(a.head_dim, a.split);
     threads = 64u * (unsigned)((a.split >> 4) * (a.split & 15));

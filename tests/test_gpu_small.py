@@ -1,5 +1,5 @@
-"""GPU parity of the small kernel (calls of one round of 32-row workgroups whose wavefronts hold all key blocks) against the fp64
-oracle: block edges, windows that reach past the tensor or are open on one side, rows that see no key, padding that
+"""GPU parity of the small kernel (calls of one round of 32-row workgroups whose wavefronts hold all key blocks) and, where its range
+ends, of the kernels beside it, against the fp64 oracle; which call runs which is checked on the CPU: block edges, windows that reach past the tensor or are open on one side, rows that see no key, padding that
 holds anything, strided output, and the largest calls that take it beside the first that do not."""
 import numpy as np
 import pytest
@@ -13,6 +13,7 @@ from tests.gpu_util import FA_DT, check_against, poison, run_ex, to_dev
 
 pytestmark = pytest.mark.gpu
 
+# (windows that are open on one side or wider than five blocks for 32 rows run other kernels)
 WINDOWS = [(63, 64, [450, 449, 64, 33, 1, 0]), (0, 0, [97, 96, 31]), (128, 0, [300, 129]), (0, 128, [300, 129]), (7, 100, [160, 128, 5]),
            (50, -1, [160, 159, 32]), (-1, 40, [131, 1]), (63, 64, [32]), (63, 64, [20])]
 
@@ -39,7 +40,8 @@ def test_windows_and_lengths(D, dtype, left, right, lens, bias):
     check_against(o, lse, o_ref, lse_ref, lens, dtype, relative=True, label=f"small D{D} {dtype} ({left},{right})")
 
 
-# Global: four wavefronts with one block each, with two, eight with two; lengths at the edges of blocks and of their number
+# Global: four wavefronts with one block each, with two, eight with two (head_dim 128 has no such shape: 257 and 512 run the split kernel);
+# lengths at the edges of blocks and of their number
 GLOBAL = [[128, 97, 96, 1, 0], [20, 3], [129, 128, 31], [256, 255, 160, 33], [257, 129, 0], [512, 480, 289, 31]]
 
 
@@ -67,9 +69,12 @@ def test_global_lengths(D, dtype, lens, bias):
 
 
 # (workgroups of one round: the most ids of each shape and head size, and one tile past them)
-@pytest.mark.parametrize("D,H,N,left,right", [(64, 16, 1024, 63, 64), (64, 16, 1025, 63, 64), (128, 8, 1024, 63, 64), (128, 8, 1025, 63, 64),
-                                              (32, 24, 1024, 63, 64), (32, 24, 1025, 63, 64), (64, 16, 512, -1, -1), (64, 17, 512, -1, -1),
-                                              (32, 24, 512, -1, -1), (32, 25, 512, -1, -1), (128, 32, 256, -1, -1), (128, 33, 256, -1, -1)])
+RANGE = [(64, 16, 1024, 63, 64), (64, 16, 1025, 63, 64), (128, 8, 1024, 63, 64), (128, 8, 1025, 63, 64), (32, 24, 704, 63, 64), (32, 24, 705, 63, 64),
+         (32, 24, 1024, 63, 64), (32, 24, 1025, 63, 64), (64, 16, 512, -1, -1), (64, 17, 512, -1, -1), (32, 24, 512, -1, -1), (32, 25, 512, -1, -1),
+         (128, 32, 256, -1, -1), (128, 33, 256, -1, -1)]
+
+
+@pytest.mark.parametrize("D,H,N,left,right", RANGE)
 def test_last_call_of_the_range_and_the_next(D, H, N, left, right):
     _, q, k, v = draw(5100 + D, 1, H, N, D, "fp16")
     o, lse = run_ex(q, k, v, None, "fp16", D ** -0.5, left, right)

@@ -17,19 +17,19 @@ pytestmark = pytest.mark.gpu
 # (head_dim, heads, max_len, lengths, key bias, 16 * NQ + NK): the shape is what the library chooses for the call in either
 # type (checked on the CPU).  "long": more steps than two turns of the ring, so that the unrolled part of the loop runs.
 CASES = {
-    "d64_1x4": (64, 2, 300, [300, 129, 128, 0], False, 0x14),
+    "d64_1x4": (64, 2, 600, [600, 129, 128, 0], False, 0x14),
     "d64_1x4_longest": (64, 4, 639, [639, 512, 513], False, 0x14),
     "d64_1x8": (64, 2, 700, [700, 256, 255, 0], False, 0x18),
     "d64_1x8_long": (64, 1, 1300, [1300, 1024, 513, 31], False, 0x18),
-    "d64_2x4": (64, 30, 200, [200, 128], False, 0x24),
+    "d64_2x4": (64, 12, 400, [400, 128], False, 0x24),
     "d64_2x4_long": (64, 4, 2100, [2090], False, 0x24),
     "d64_3x4": (64, 12, 900, [900, 865], False, 0x34),
     "d64_3x4_long": (64, 12, 1500, [1497], False, 0x34),
     "d64_3x4_other": (64, 16, 1290, [97], False, 0x34),
-    "d64_2x2_short": (64, 30, 150, [150, 65], False, 0x22),
+    "d64_2x2_short": (64, 8, 700, [150, 65], False, 0x22),
     "d64_2x2": (64, 35, 500, [500, 333], False, 0x22),
-    "d64_2x2_padded": (64, 12, 2048, [1900], False, 0x22),
-    "d64_2x2_long": (64, 12, 2210, [2177], False, 0x22),
+    "d64_2x2_padded": (64, 12, 1200, [1100, 700], False, 0x22),
+    "d64_2x2_long": (64, 6, 2210, [2177, 2000], False, 0x22),
     "d128_1x4": (128, 2, 300, [300, 129, 128, 1], False, 0x14),
     "d128_1x4_long": (128, 2, 700, [700, 641], False, 0x14),
     "d128_2x4": (128, 30, 200, [200, 63], False, 0x24),
@@ -38,9 +38,9 @@ CASES = {
     "d32_1x4": (32, 20, 300, [300, 161], False, 0x14),
     "d32_1x4_long": (32, 4, 1400, [1390], False, 0x14),
     "d32_2x2_long": (32, 20, 1010, [1010, 64], False, 0x22),
-    "d64_1x8_bias": (64, 2, 500, [500, 256, 255, 1], True, 0x18),
+    "d64_1x8_bias": (64, 2, 600, [600, 256, 255, 1], True, 0x18),
     "d64_1x8_bias_long": (64, 1, 1400, [1400], True, 0x18),
-    "d64_2x4_bias": (64, 30, 200, [200, 128], True, 0x24),
+    "d64_2x4_bias": (64, 12, 400, [400, 128], True, 0x24),
     "d64_2x4_bias_long": (64, 4, 1300, [1300, 1200], True, 0x24),
     "d64_3x4_bias": (64, 15, 700, [700, 641], True, 0x34),
     "d64_4x2_bias_long": (64, 24, 600, [600, 577], True, 0x42),
@@ -49,7 +49,7 @@ CASES = {
     "d128_2x4_bias": (128, 30, 200, [200, 63], True, 0x24),
     "d128_2x4_bias_long": (128, 8, 1400, [1300], True, 0x24),
     "d128_4x2_bias_long": (128, 15, 700, [700, 577], True, 0x42),
-    "d32_1x4_bias": (32, 4, 300, [300, 161], True, 0x14),
+    "d32_1x4_bias": (32, 4, 600, [600, 161], True, 0x14),
     "d32_1x4_bias_long": (32, 2, 1400, [1390], True, 0x14),
     "d32_2x2_bias": (32, 20, 300, [300, 161], True, 0x22),
     "d32_2x2_bias_long": (32, 12, 1200, [1190], True, 0x22),
@@ -119,8 +119,9 @@ def test_key_bias_pipelined_kernel_head_dim_32(N, dtype, tuning):
 
 
 # (head_dim, heads, max_len, 16 * NQ + NK): one call per shape the library picks without a key bias, more than one block per
-# wavefront
-SHAPES = {"d64_1x4": (64, 2, 380, 0x14), "d64_1x8_short": (64, 2, 450, 0x18), "d64_1x8": (64, 1, 700, 0x18),
+# wavefront; LENGTHS: those that have the shape only where a length is given (the whole tensor here)
+LENGTHS = {"d64_1x4"}
+SHAPES = {"d64_1x4": (64, 2, 600, 0x14), "d64_1x8_short": (64, 2, 530, 0x18), "d64_1x8": (64, 1, 700, 0x18),
           "d64_2x4": (64, 4, 2100, 0x24), "d64_3x4": (64, 12, 1500, 0x34), "d64_2x2": (64, 12, 2500, 0x22),
           "d128_1x4": (128, 2, 600, 0x14), "d128_2x4": (128, 8, 1500, 0x24), "d128_4x2": (128, 8, 2600, 0x42),
           "d32_1x4": (32, 24, 600, 0x14), "d32_2x2": (32, 24, 1500, 0x22)}
@@ -141,7 +142,7 @@ def test_split_kernel_first_block_without_a_finite_score(name, dtype):
         q2[..., 1], k2[..., 1] = 40.0, shift          # every score moved by 40 * shift * scale
         k2[..., 32 * g: 32 * g + 32, 0] = -np.inf
         o_ref, lse_ref = attention_oracle(q2, k2, v, None, D ** -0.5)
-        o, lse = run_ex(rep(q2), rep(k2), rep(v), None, dtype, D ** -0.5)
+        o, lse = run_ex(rep(q2), rep(k2), rep(v), [N] if name in LENGTHS else None, dtype, D ** -0.5)
         check_against(o[:, :1], lse[:, :1], o_ref, lse_ref, None, dtype, label=f"{name} block {g} shift {shift}")
         assert (o == o[:, :1]).all() and (lse == lse[:, :1]).all()
 
@@ -163,7 +164,7 @@ def test_split_kernel_merge_of_large_references(name, dtype):
     v[...] = np.where(g % 2 == 0, 1.0, -1.0)[:, None]
     w = np.exp(g / 8.0)
     want = (w * np.where(g % 2 == 0, 1.0, -1.0)).sum() / w.sum()
-    o, lse = run_ex(q, k, v, None, dtype, 1.0)
+    o, lse = run_ex(q, k, v, [N] if name in LENGTHS else None, dtype, 1.0)
     # a probability is rounded to 2^-12 (fp16) or 2^-9 (bf16) of itself, o likewise
     assert np.abs(o - want).max() <= (2.0 ** -11 if dtype == "fp16" else 2.0 ** -8), np.abs(o - want).max()
     assert np.abs(lse - (1024000.0 + np.log(w.sum()))).max() <= 0.5   # eight fp32 spacings there

@@ -14,10 +14,13 @@ from tests.gpu_util import LSE_TOL, TOL, run_ex
 pytestmark = pytest.mark.gpu
 
 
-# 12 heads: 21 tiles each, so up to 1344, 2016 and 2688 rows; 30 heads: 8 tiles, up to 512, 768, 1024
+# (heads, max_len, lengths); that these calls run this kernel in either type is checked on the CPU.  12 heads: 21 tiles each, so up
+# to 1344, 2016 and 2688 rows; 15 heads: 17 tiles, up to 1088, 1632, 2176
+CASES = [(12, 2049, [2049, 2048, 2017, 2016, 1900, 1345, 1344, 700, 31, 1, 0, -5, 4000]), (15, 2160, [2160, 1633, 1632, 1089, 1088, 300])]
+
+
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
-@pytest.mark.parametrize("H,N,lens", [(12, 2049, [2049, 2048, 2017, 2016, 1900, 1345, 1344, 700, 31, 1, 0, -5, 4000]),
-                                      (30, 1000, [1000, 769, 768, 513, 512, 300])])
+@pytest.mark.parametrize("H,N,lens", CASES)
 def test_rows_follow_the_length(H, N, lens, dtype):
     _, q, k, v = draw(8200 + N, 1, H, N, 64, dtype, qk_gain=1.5)
     for n in lens:
@@ -33,7 +36,9 @@ def test_rows_follow_the_length(H, N, lens, dtype):
                                          np.random.default_rng(n).integers(0, live, 64)]))
         for h in (0, H - 1):
             o_ref, lse_ref = attention_oracle_rows(q, k, v, 0, h, rows, live, 0.125)
-            assert np.abs(o[0, h, rows] - o_ref).max() <= TOL[dtype]["max_abs"], (n, h)
+            # (rows with a peaked softmax have outputs of 2 and more, which as bf16 numbers are by themselves up to 7.8e-3 off: against
+            # their magnitude, as in the other tests)
+            assert (np.abs(o[0, h, rows] - o_ref) / np.maximum(1.0, np.abs(o_ref))).max() <= TOL[dtype]["max_abs"], (n, h)
             assert np.abs(lse[0, h, rows] - lse_ref).max() <= LSE_TOL, (n, h)
         assert np.isfinite(o).all() and np.isfinite(lse[:, :, :live]).all()
 

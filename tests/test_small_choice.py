@@ -92,6 +92,43 @@ int main() {
 }
 """
 
+SHAPES = HEAD + r"""
+// What a launch of the small kernel counts on: the shape exists for the head size, no 32-row tile sees more key blocks than it holds
+// (counted row by row), the grid is made of 32-row tiles, and the workgroups of one round fit the LDS of 256 units.
+int main() {
+  long taken = 0;
+  for (int d : {32, 64, 128})
+    for (int b : {1, 2, 3, 5, 8, 16})
+      for (int h : {1, 3, 8, 12, 24, 31})
+        for (int n = 1; n < 1500; n += 1 + n / 11)
+          for (int w = 0; w < 7; ++w) {
+            const int sides[7][2] = {{-1, -1}, {63, 64}, {0, 0}, {128, 0}, {0, 128}, {31, 33}, {5000, 600}};
+            fa_params p = call(d, b, h, n);
+            p.window_left = sides[w][0]; p.window_right = sides[w][1];
+            p.key_bias = w & 1 ? buf : nullptr;
+            EXPECT(fa_fwd_ex(&p) == 0);
+            if (!last.small) continue;
+            ++taken;
+            const int s = last.small, nk = s >> 4, nb = s & 15;
+            EXPECT(s == 0x51 || s == 0x41 || s == 0x42 || (s == 0x82 && d != 128));
+            for (int q0 = 0; q0 < n; q0 += 32) {
+              int lo = n, hi = -1;   // keys that a row of the tile sees
+              for (int i = q0; i < q0 + 32 && i < n; ++i) {
+                lo = std::min(lo, p.window_left < 0 ? 0 : std::max(0, i - p.window_left));
+                hi = std::max(hi, p.window_right < 0 ? n - 1 : (int)std::min<long>(n - 1, (long)i + p.window_right));
+              }
+              EXPECT(hi / 32 - lo / 32 + 1 <= nk * nb);
+            }
+            EXPECT(last_bm == 32 && last.n_qtiles == (n + 31) / 32 && last.total_tiles == last.n_qtiles * h * b && last.map_xcd);
+            EXPECT(!last.heads_first && !last.longest_first && !last.split && !last.live_tiles);
+            const long ids = 8L * last.xcd_per * b, block = 32 * d * 2, lds = block + nk * 2 * nb * block + nk * 2 * 64 * 4 + nk * nb * 128;
+            EXPECT(ids >= last.total_tiles && ids <= 256 * (160 * 1024 / lds));
+          }
+  printf("ok %ld\n", taken);
+  return taken < 3000;
+}
+"""
+
 SIZES = HEAD + r"""
 // The last call of each shape and head size, of a model's 24, 12 and 8 heads, and the first past it
 int main() {
@@ -160,6 +197,10 @@ def run(tmp_path, text):
 
 def test_local_layers_that_take_the_small_kernel(tmp_path):
     run(tmp_path, WINDOWS)
+
+
+def test_what_a_launch_of_the_small_kernel_counts_on(tmp_path):
+    run(tmp_path, SHAPES)
 
 
 def test_last_calls_of_the_small_kernel(tmp_path):

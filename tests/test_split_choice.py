@@ -1,6 +1,7 @@
 """The host's choice of a split-kernel shape, walked on the CPU with stub launchers: a shape is one the kernels exist in,
 its grid matches its rows per workgroup and its ids fit the 256 compute units in one round, and calls that the kernel does not
-cover (windows, a rotation in the call, a long key bias, forced shapes) never get one."""
+cover (windows, a rotation in the call, a long key bias, forced shapes) never get one.  And the GPU tests of the kernels of small
+calls: each of their calls launches the kernel that it is there for."""
 import pathlib
 import shutil
 import subprocess
@@ -33,14 +34,19 @@ int main(int argc, char** argv) {
   p.q = p.k = p.v = p.o = buf;
   p.scale = 0.125f;
   p.window_left = p.window_right = -1;
-  if (argc > 1) {   // the shapes of the calls given as: head_dim batch heads max_len biased bf16 lengths
-    for (int i = 1; i + 6 < argc; i += 7) {
+  if (argc > 1) {   // the kernels of the calls given as: head_dim batch heads max_len biased bf16 lengths window_left window_right
+    for (int i = 1; i + 8 < argc; i += 9) {
       p.head_dim = std::atoi(argv[i]); p.batch = std::atoi(argv[i + 1]); p.heads = std::atoi(argv[i + 2]);
       p.max_len = std::atoi(argv[i + 3]); p.key_bias = std::atoi(argv[i + 4]) ? buf : nullptr;
       p.dtype = std::atoi(argv[i + 5]) ? FA_DTYPE_BF16 : FA_DTYPE_F16;
       p.seq_lens = std::atoi(argv[i + 6]) ? (const int32_t*)table : nullptr;
+      p.window_left = std::atoi(argv[i + 7]); p.window_right = std::atoi(argv[i + 8]);
       if (fa_fwd_ex(&p) != 0) return 1;
-      printf("%x\n", last.split);
+      if ((last.small != 0) + (last.live_tiles != 0) + (last.split != 0) > 1) return 2;
+      if (last.small) printf("small-%x\n", last.small);
+      else if (last.live_tiles) printf("live\n");
+      else if (last.split) printf("split-%x\n", last.split);
+      else printf("other\n");
     }
     return 0;
   }
@@ -78,7 +84,8 @@ int main(int argc, char** argv) {
             p.tuning = 0; p.scale = 0.0f;
             EXPECT(fa_fwd_ex(&p) == 0 && (!biased || last.split == 0));
           }
-  // no shape is there for one size: of one sequence of 1 - 48 heads each is taken for many head counts, and at many lengths
+  // no shape is there for one size: of one sequence of 1 - 48 heads each is taken for many head counts, and at many lengths (the
+  // narrowest, head_dim 64 on four wavefronts of 32 rows, at 513 - 639 tokens where lengths are given: half of them here)
   p.scale = 0.125f; p.batch = 1; p.tuning = 0;
   for (int d : {32, 64, 128})
     for (int biased = 0; biased < 2; ++biased) {
@@ -98,7 +105,7 @@ int main(int argc, char** argv) {
         for (int s = 0; s < 256; ++s) head_counts[s] += here[s];
       }
       for (int s = 1; s < 256; ++s)
-        if (lengths[s] && (head_counts[s] < 12 || lengths[s] < 100 * head_counts[s])) {
+        if (lengths[s] && (head_counts[s] < 12 || lengths[s] < 50 * head_counts[s])) {
           printf("FAILED head_dim %d bias %d shape %x: %d head counts, %d lengths\n", d, biased, s, head_counts[s], lengths[s]);
           return 1;
         }
@@ -129,22 +136,52 @@ def test_split_shapes_chosen_by_the_host(driver):
     assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
 
 
-def test_gpu_cases_run_the_shapes_they_are_named_after(driver):
-    """The calls of the GPU tests get the shape written beside them, and every shape that any call gets is among them."""
-    from tests.test_gpu_split import CASES, SHAPES
-    calls = [(name, D, len(lens), H, N, int(biased), 1, s) for name, (D, H, N, lens, biased, s) in CASES.items()]
-    calls += [("shape " + name, D, 1, H, N, 0, 0, s) for name, (D, H, N, s) in SHAPES.items()]
-    for bf16 in (0, 1):
-        args = [str(x) for (_, D, B, H, N, biased, lengths, _) in calls
-                for x in (D, B, H, N, biased, bf16, lengths)]
-        r = subprocess.run([driver, *args], capture_output=True, text=True, check=True)
-        got = [int(x, 16) for x in r.stdout.split()]
-        assert len(got) == len(calls)
-        assert [(c[0], hex(g)) for c, g in zip(calls, got)] == [(c[0], hex(c[-1])) for c in calls]
-    assert {(D, b, s) for (_, D, _, _, _, b, _, s) in calls} == {
+def kernels(driver, calls):
+    """The kernel of each call (head_dim, batch, heads, max_len, biased, bf16, lengths, window_left, window_right)."""
+    r = subprocess.run([driver, *[str(int(x)) for c in calls for x in c]], capture_output=True, text=True, check=True)
+    got = r.stdout.split()
+    assert len(got) == len(calls)
+    return got
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_gpu_cases_run_the_shapes_they_are_named_after(driver, bf16):
+    """The calls of the GPU tests of the split kernel launch the shape written beside them, and every shape that any call gets is among
+    them."""
+    from tests.test_gpu_split import CASES, LENGTHS, SHAPES
+    cases = [(name, D, len(lens), H, N, biased, 1, s) for name, (D, H, N, lens, biased, s) in CASES.items()]
+    cases += [("shape " + name, D, 1, H, N, False, name in LENGTHS, s) for name, (D, H, N, s) in SHAPES.items()]
+    got = kernels(driver, [(D, B, H, N, biased, bf16, lengths, -1, -1) for _, D, B, H, N, biased, lengths, _ in cases])
+    assert list(zip([c[0] for c in cases], got)) == [(c[0], f"split-{c[-1]:x}") for c in cases]
+    assert {(D, biased, s) for _, D, _, _, _, biased, _, s in cases} == {
         (64, 0, 0x14), (64, 0, 0x18), (64, 0, 0x24), (64, 0, 0x34), (64, 0, 0x22), (128, 0, 0x14), (128, 0, 0x24), (128, 0, 0x42),
         (32, 0, 0x14), (32, 0, 0x22), (64, 1, 0x18), (64, 1, 0x24), (64, 1, 0x34), (64, 1, 0x42), (128, 1, 0x14), (128, 1, 0x24),
         (128, 1, 0x42), (32, 1, 0x14), (32, 1, 0x22)}
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_gpu_cases_of_the_kernel_whose_rows_follow_the_length(driver, bf16):
+    from tests.test_gpu_split_live import CASES
+    calls = [(64, 1, H, N, 0, bf16, 1, -1, -1) for H, N, _ in CASES] + [(64, 1, 12, 2048, 0, 1, 1, -1, -1)]
+    assert kernels(driver, calls) == ["live"] * len(calls)
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_gpu_cases_of_the_small_kernel(driver, bf16):
+    from tests.test_gpu_small import GLOBAL, RANGE, WINDOWS
+    for D in (32, 64, 128):
+        for biased in (0, 1):
+            got = kernels(driver, [(D, len(lens), 3, max(lens), biased, bf16, 1, left, right) for left, right, lens in WINDOWS])
+            # (open on one side, or more than five blocks for 32 rows: the kernels of such windows; six sequences of head_dim 128 are
+            # more than one round)
+            assert got == ["other" if (left, right) in {(7, 100), (50, -1), (-1, 40)} or (D == 128 and len(lens) == 6) else "small-51"
+                           for left, right, lens in WINDOWS]
+            got = kernels(driver, [(D, len(lens), 3, max(lens), biased, bf16, 1, -1, -1) for lens in GLOBAL])
+            assert got == ["small-41", "small-41", "small-42", "small-42"] + (["split-14"] * 2 if D == 128 else ["small-82"] * 2)
+    got = kernels(driver, [(D, 1, H, N, 0, bf16, 0, left, right) for D, H, N, left, right in RANGE])
+    for (D, H, N, left, right), kernel in zip(RANGE, got):
+        inside = (D, H, N, left) in {(64, 16, 1024, 63), (128, 8, 1024, 63), (32, 24, 704, 63), (64, 16, 512, -1), (32, 24, 512, -1), (128, 32, 256, -1)}
+        assert kernel.startswith("small") == inside, (D, H, N, left, kernel)
 
 
 HEADS_FIRST_DRIVER = r"""
