@@ -147,9 +147,11 @@ typedef struct fa_params {
      multiplied by scale); -infinity excludes key j, so any key mask can be expressed,
      and the paper's -65504 on padded keys works as written.  It applies on top of
      seq_lens and the window.  2-byte alignment.  Global layers and
-     narrow two-sided windows (the local layers' 63 / 64) keep their pipelines (the bias enters through
-     the score product's accumulator input); wider or one-sided windows and scale == 0 take the
-     general (masked) kernel. */
+     narrow two-sided windows (the local layers' 63 / 64) keep their kernels; wider or one-sided
+     windows, a rotation in the call and scales too small to divide a bias by (0 among them) take
+     the general (masked) kernel.  Padding (-65504 or -infinity from some key on, zeros before it)
+     is what a global layer of 640 tokens and more is fastest with: it leaves the call where it
+     can be shown to count for nothing, with the same result. */
   const void* key_bias;
   int64_t key_bias_stride; /* elements between batch rows; 0 = max_len; >= max_len */
   /* Rotary position embedding of q and k inside the call (the paper's classifier uses rotary
@@ -189,7 +191,11 @@ typedef struct fa_params {
                                 picks this or another shape that splits the keys by itself for
                                 small global calls of more than 64 tokens: up to one workgroup
                                 per compute unit, or two or three where the shape allows them,
-                                by lines that depend on head size, type, key bias and length. */
+                                by lines that depend on head size, type, key bias and length.
+                                The smallest calls, global and with narrow windows, have a kernel
+                                of their own whose wavefronts hold all keys of 32 query rows; one
+                                sequence with a length in a tensor of 2000 tokens and more may get
+                                64, 96 or 128 rows by its length.  A forced shape has neither. */
 #define FA_TUNE_BM_384 0x4u  /* 12 wavefronts x 32 query rows sharing one K/V stage (global layers of
                                 head_dim 64 without a key bias; ignored otherwise) */
 #define FA_TUNE_BM_512 0x5u  /* 8 wavefronts x 64 query rows sharing one K/V stage (same restriction) */
